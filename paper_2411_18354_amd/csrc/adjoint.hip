@@ -254,7 +254,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     const int nslots = (int)(gen.size() / 8);
     a->nslots = nslots;
     const int m_cap = std::max(1, tuning().tile_log2[dtype == SV_C128 ? 0 : 1] - 1);
-    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, &a->rc));
+    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, false, &a->rc));
     sv_circuit *rc = a->rc;
 
     // per pass: single passes need pair plans, fused ones per-descriptor slots

@@ -21,7 +21,8 @@
 namespace sv {
 
 __global__ void k_param_mats(const ParamJob *__restrict__ jobs, int njobs, const double *__restrict__ params,
-                             double *__restrict__ mats, TileGate *__restrict__ tiles, SweepMember *__restrict__ mems) {
+                             double *__restrict__ mats, TileGate *__restrict__ tiles, SweepMember *__restrict__ mems,
+                             RtOp *__restrict__ ops, int ops_f32) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= njobs)
         return;
@@ -41,6 +42,14 @@ __global__ void k_param_mats(const ParamJob *__restrict__ jobs, int njobs, const
                     mems[t.mem[s]].theta = t.ph[s];
         }
     }
+    for (int s = 0; s < 2; ++s)
+        if (j.op[s] >= 0)
+            for (int k = 0; k < 8; ++k) {
+                if (ops_f32)
+                    ops[j.op[s]].f[k] = (float)m[k];
+                else
+                    ops[j.op[s]].m[k] = m[k];
+            }
 }
 
 // Gates a and b commute when every qubit they share is, in each of them,
@@ -225,6 +234,7 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
         a = std::min(std::max(a, kQBlockBits), m);
     const int min_run = std::max(1, tuning().fuse_min_gates);
     std::vector<int> tile_slot(G, -1);
+    std::vector<std::pair<int, int>> op_slot(G, {-1, -1});
     std::vector<char> diag(G, 0);
     for (int i = 0; i < G; ++i)
         diag[i] = gate_is_diagonal(c->gates[i], &mats[(size_t)8 * i]);
@@ -445,10 +455,27 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 }
                 mark_diag_sweeps(&tiles[p.first], p.count, from_param.data(), phase_min);
                 build_sweep_patterns(&tiles[p.first], p.count, (int)p.tm.m, from_param.data(), pats, mems);
-                if (tuning().fuse_pairs)
-                    mark_coset_pairs(&tiles[p.first], p.count);
-                if (tuning().fuse_perm)  // checked first by the tile loops
-                    mark_permutation_runs(&tiles[p.first], p.count);
+                // Register tiles wherever a tile has 64 to 512 lanes: below
+                // that a wavefront would be partly idle (k_tile stays), and
+                // wider tiles do not exist.
+                if (c->want_rt && rt_tile_ok(tdt, m)) {
+                    std::vector<RtGateInfo> info;
+                    for (int k = p.first; k < p.first + p.count; ++k) {
+                        const int gi = tiles[k].src_gate;
+                        const sv_gate_t &g = c->gates[gi];
+                        info.push_back(rt_gate_info(g.kind, g.param >= 0, &mats[(size_t)8 * gi], diag[gi]));
+                    }
+                    p.rt = true;
+                    p.rp = build_rt_pass(p.tm, fmask, tdt, &tiles[p.first], p.count, info.data(), pats,
+                                         tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->prog);
+                    for (int k = 0; k < p.count; ++k)
+                        op_slot[tiles[p.first + k].src_gate] = {info[k].op, info[k].op2};
+                } else {
+                    if (tuning().fuse_pairs)
+                        mark_coset_pairs(&tiles[p.first], p.count);
+                    if (tuning().fuse_perm)  // checked first by the tile loops
+                        mark_permutation_runs(&tiles[p.first], p.count);
+                }
                 c->passes.push_back(p);
                 c->fused_gates += (int64_t)run.size();
                 c->fused_runs++;
@@ -511,14 +538,15 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
     for (int i = 0; i < G; ++i) {
         const sv_gate_t &g = c->gates[i];
         if (g.param >= 0)
-            jobs.push_back(ParamJob{g.kind, g.param, i, tile_slot[i]});
+            jobs.push_back(ParamJob{g.kind, g.param, i, tile_slot[i], {op_slot[i].first, op_slot[i].second}});
     }
     c->njobs = (int)jobs.size();
     return SV_OK;
 }
 
 static void free_buffers(sv_circuit *c, hipStream_t st) {
-    void *bufs[7] = {c->d_mats, c->d_tiles, c->d_jobs, c->d_dense, c->d_rmat, c->d_pats, c->d_mems};
+    void *bufs[9] = {c->d_mats, c->d_tiles, c->d_jobs, c->d_dense, c->d_rmat, c->d_pats, c->d_mems, c->rt.ops,
+                     c->rt.pats};
     for (void *b : bufs)
         if (b) {
             if (c->async_buffers)
@@ -533,6 +561,7 @@ static void free_buffers(sv_circuit *c, hipStream_t st) {
     c->d_rmat = nullptr;
     c->d_pats = nullptr;
     c->d_mems = nullptr;
+    c->rt = RtDevice{nullptr, nullptr};
 }
 
 template <typename T> static int upload(T **dst, const std::vector<T> &src, bool async, hipStream_t st) {
@@ -576,7 +605,7 @@ static int launch_tile_pass(cplx_t<R> *psi, const TileMap &tm_in, const DeviceGa
 }
 
 int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int flags, bool async,
-                   hipStream_t st, int m_cap, sv_circuit **out) {
+                   hipStream_t st, int m_cap, bool rt, sv_circuit **out) {
     *out = nullptr;
     if (!known_dtype(dtype))
         return fail(SV_EINVAL, "unknown dtype %d", dtype);
@@ -600,6 +629,7 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
     c->nparams = nparams;
     c->async_buffers = async;
     c->m_cap = m_cap;
+    c->want_rt = rt;
     // a one-shot plan (stream-ordered buffers, run once) keeps planning cheap:
     // the two-step lookahead pays for itself only over repeated runs
     c->max_lookahead = async ? 1 : 2;
@@ -620,6 +650,10 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
         r = upload(&c->d_pats, pats, async, st);
     if (r == SV_OK)
         r = upload(&c->d_mems, mems, async, st);
+    if (r == SV_OK)
+        r = upload(&c->rt.ops, c->prog.ops, async, st);
+    if (r == SV_OK)
+        r = upload(&c->rt.pats, c->prog.pats, async, st);
     if (r == SV_OK)
         r = upload(&c->d_tiles, tiles, async, st);
     if (r == SV_OK)
@@ -654,7 +688,8 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
 int circuit_param_mats(sv_circuit *c, const double *params, hipStream_t st) {
     if (c->njobs > 0) {
         hipLaunchKernelGGL(k_param_mats, dim3((c->njobs + 127) / 128), dim3(128), 0, st, c->d_jobs, c->njobs,
-                           params, c->d_mats, c->d_tiles, c->d_mems);
+                           params, c->d_mats, c->d_tiles, c->d_mems, c->rt.ops,
+                           tile_dtype(c->dtype) == SV_C64 ? 1 : 0);
         SV_LAUNCH_CHECK();
     }
     return SV_OK;
@@ -681,7 +716,10 @@ template <typename R> static int enqueue(sv_circuit *c, cplx_t<R> *psi, const do
             SV_TRY(launch_dense(c->dtype, psi, c->n, c->dense_k, rm, st));
         } else if (p.fused) {
             DeviceGates dg{c->d_tiles + p.first, p.count, c->d_pats, c->d_mems};
-            SV_TRY(launch_tile_pass<R>(psi, p.tm, dg, lds, st));
+            if (p.rt)
+                SV_TRY(launch_rt_pass(c->dtype, psi, p.tm, p.rp, c->rt, dg, st));
+            else
+                SV_TRY(launch_tile_pass<R>(psi, p.tm, dg, lds, st));
         } else {
             SV_TRY(launch_plan<R>(psi, p.plan, MatPtr<R>{c->d_mats + (size_t)8 * p.gate}, st));
         }
@@ -911,7 +949,7 @@ int sv_circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int 
     clear_error();
     if (!out)
         return fail(SV_EINVAL, "out is NULL");
-    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, out);
+    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, !is_fixed(dtype), out);
 }
 
 int sv_circuit_run(sv_circuit_t *c, const sv_state_t *s, const double *params_dev, sv_stream_t st) {
@@ -968,7 +1006,8 @@ int sv_apply_circuit(const sv_state_t *s, const sv_gate_t *gates, int ngates, co
     clear_error();
     SV_TRY(validate_state(s, true));
     sv_circuit *c = nullptr;
-    SV_TRY(circuit_create(s->n, s->dtype, gates, ngates, nparams, flags & ~SV_GRAPH, true, (hipStream_t)st, 64, &c));
+    SV_TRY(circuit_create(s->n, s->dtype, gates, ngates, nparams, flags & ~SV_GRAPH, true, (hipStream_t)st, 64, !is_fixed(s->dtype),
+                          &c));
     int r = check_run_args(c, s, params_dev);
     if (r == SV_OK)
         r = enqueue_any(c, s, params_dev, (hipStream_t)st);

@@ -1,6 +1,7 @@
 // Internal circuit plan shared by the circuit driver and the adjoint sweep.
 #pragma once
 
+#include "rtile_plan.hpp"
 #include "tile.hpp"
 
 namespace sv {
@@ -10,6 +11,7 @@ struct ParamJob {
     int32_t param;
     int32_t mat_slot;   // gate index: matrix at mats + 8 * mat_slot
     int32_t tile_slot;  // fused-run descriptor index or -1
+    int32_t op[2];      // register-tile operations holding the matrix, or -1
 };
 
 // The complex type a fused tile holds: fixed-point states decode 16-bit
@@ -30,6 +32,8 @@ struct Pass {
     GatePlan plan;   // single
     FixedPlan fx;    // single, fixed-point state
     TileMap tm;      // fused: which qubits a tile spans
+    bool rt = false; // fused: register tile pass
+    RtPass rp;
 };
 
 } // namespace sv
@@ -39,6 +43,9 @@ struct sv_circuit {
     int n = 0, dtype = 0, flags = 0, nparams = 0, device = 0, m = 0;
     int m_cap = 64;  // upper bound on the tile width (callers with a fixed LDS budget)
     int max_lookahead = 2;  // cap on the planner's lookahead depth (one-shot plans and batches: 1)
+    bool want_rt = false;  // plan fused runs for register tiles where their width allows
+    sv::RtProgram prog;             // their operations
+    sv::RtDevice rt{nullptr, nullptr};
     std::vector<sv_gate_t> gates;   // after the SV_REMAP relabelling, if any
     std::vector<int32_t> remap;      // SV_REMAP: qubit swaps a0 b0 a1 b1 ... (empty: none)
     std::vector<sv::Pass> passes;
@@ -83,8 +90,10 @@ int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int
                        std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, int *m_used,
                        std::vector<SweepPat> *pats = nullptr, std::vector<SweepMember> *mems = nullptr);
 
+// rt: fused runs on register tiles where their width allows (the caller runs
+// Pass::rt passes with launch_rt_pass).
 int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int flags, bool async,
-                   hipStream_t st, int m_cap, sv_circuit **out);
+                   hipStream_t st, int m_cap, bool rt, sv_circuit **out);
 // Release device buffers (stream-ordered on st for async plans) and the plan.
 void circuit_free(sv_circuit *c, hipStream_t st);
 // Compute the matrices of parameterised gates from params (device) into the

@@ -1,0 +1,513 @@
+// Register-resident tile pass (rtile.hpp): the host scheduler of a fused run
+// and the kernel for complex128 and complex64 states.
+#include <algorithm>
+#include <cstring>
+
+#include "gates.hpp"
+#include "rtile.hpp"
+
+namespace sv {
+
+// ---------------------------------------------------------------------------
+// host: layouts and scheduling
+// ---------------------------------------------------------------------------
+
+namespace {
+
+// Where each tile-local bit sits: reg[k] is the tile-local bit of register
+// bit k, thr[i] that of thread bit i.
+struct Layout {
+    std::vector<int> reg, thr;
+    int reg_of[kTileMaxLog], thr_of[kTileMaxLog];
+    bool operator==(const Layout &o) const { return reg == o.reg && thr == o.thr; }
+};
+
+// The lowest five lane bits take tile-local bits of different residues
+// modulo 5 where the register bits leave them: rt_slot then puts 32
+// consecutive lanes on 32 different slots modulo 32.  Of equal residues the
+// lowest bit comes first, so a load or store layout keeps the state's lowest
+// index bits on lane bits.
+Layout make_layout(int m, uint32_t rmask, bool block) {
+    Layout L;
+    std::vector<int> rest;
+    for (int q = 0; q < m; ++q)
+        if ((rmask >> q) & 1u)
+            L.reg.push_back(q);
+        else
+            rest.push_back(q);
+    if (block) {
+        L.thr = rest;  // 2..5 first: a 64-amplitude block is 16 lanes of 4 registers
+    } else {
+        uint32_t seen = 0;
+        std::vector<int> later;
+        for (int q : rest) {
+            if ((int)L.thr.size() < 5 && !((seen >> (q % 5)) & 1u)) {
+                seen |= 1u << (q % 5);
+                L.thr.push_back(q);
+            } else {
+                later.push_back(q);
+            }
+        }
+        L.thr.insert(L.thr.end(), later.begin(), later.end());
+    }
+    for (int q = 0; q < kTileMaxLog; ++q)
+        L.reg_of[q] = L.thr_of[q] = -1;
+    for (size_t k = 0; k < L.reg.size(); ++k)
+        L.reg_of[L.reg[k]] = (int)k;
+    for (size_t i = 0; i < L.thr.size(); ++i)
+        L.thr_of[L.thr[i]] = (int)i;
+    return L;
+}
+
+// A tile-local condition split into its register and thread parts.
+struct Cond {
+    uint32_t rm = 0, rv = 0, tm = 0, tv = 0;
+};
+Cond split_cond(const Layout &L, uint32_t lm, uint32_t lv) {
+    Cond c;
+    for (int q = 0; q < kTileMaxLog; ++q) {
+        if (!((lm >> q) & 1u))
+            continue;
+        const uint32_t v = (lv >> q) & 1u;
+        if (L.reg_of[q] >= 0) {
+            c.rm |= 1u << L.reg_of[q];
+            c.rv |= v << L.reg_of[q];
+        } else {
+            c.tm |= 1u << L.thr_of[q];
+            c.tv |= v << L.thr_of[q];
+        }
+    }
+    return c;
+}
+
+uint32_t regs_where(int nb, uint32_t rm, uint32_t rv) {
+    uint32_t s = 0;
+    for (uint32_t r = 0; r < (1u << nb); ++r)
+        if ((r & rm) == rv)
+            s |= 1u << r;
+    return s;
+}
+
+// One schedulable operation: a pair gate, a diagonal gate, or a block of
+// diagonal gates.  nd: tile-local bits it mixes, dg: bits it only reads.
+struct Unit {
+    int first, count;
+    bool phase, diag;
+    int bit;
+    uint32_t nd, dg;
+};
+
+struct Deferred {
+    uint32_t nd = 0, dg = 0;
+    bool free(const Unit &u) const { return !(u.nd & (nd | dg)) && !(u.dg & nd); }
+    void add(const Unit &u) {
+        nd |= u.nd;
+        dg |= u.dg;
+    }
+};
+
+// Pair gates a segment with the register bits of rmask would take.
+int taken(const std::vector<Unit> &units, uint32_t rmask) {
+    Deferred d;
+    int n = 0;
+    for (const Unit &u : units) {
+        if (d.free(u) && (u.diag || ((rmask >> u.bit) & 1u)))
+            n += u.diag ? 0 : 1;
+        else
+            d.add(u);
+    }
+    return n;
+}
+
+// The register bits of the next segment, one at a time: the bit that lets
+// the segment take the most pair gates.  allowed: bits it may choose from;
+// fixed bits are kept.  Bits left over go to the highest allowed positions,
+// so a layout kept for the store leaves the low bits to the lanes.
+uint32_t choose_regs(const std::vector<Unit> &units, int m, int nb, uint32_t fixed, uint32_t allowed) {
+    uint32_t r = fixed;
+    int cur = taken(units, r);
+    while (__builtin_popcount(r) < nb) {
+        int best = -1, best_n = cur;
+        for (int q = 0; q < m; ++q) {
+            if (!((allowed >> q) & 1u) || ((r >> q) & 1u))
+                continue;
+            const int n = taken(units, r | (1u << q));
+            if (n > best_n) {
+                best_n = n;
+                best = q;
+            }
+        }
+        if (best < 0)
+            break;
+        r |= 1u << best;
+        cur = best_n;
+    }
+    for (int q = m - 1; q >= 0 && __builtin_popcount(r) < nb; --q)
+        if ((allowed >> q) & 1u)
+            r |= 1u << q;
+    return r;
+}
+
+RtIO make_io(const TileMap &tm, const Layout &L, uint32_t comp) {
+    RtIO io;
+    memset(&io, 0, sizeof(io));
+    auto global = [&](int q) { return (uint8_t)(q < (int)tm.a ? q : (int)tm.hpos[q - (int)tm.a]); };
+    for (size_t i = 0; i < L.thr.size(); ++i) {
+        io.tq[i] = global(L.thr[i]);
+        io.slot[i] = rt_slot(1u << L.thr[i]) * comp;
+    }
+    for (size_t k = 0; k < L.reg.size(); ++k)
+        io.rq[k] = global(L.reg[k]);
+    return io;
+}
+
+// comp: bytes of a component
+RtOp exchange_op(const Layout &from, const Layout &to, uint32_t comp) {
+    RtOp o;
+    memset(&o, 0, sizeof(o));
+    o.w[0] = kRtExch * 8;
+    o.w[5] = rt_jump(kRtEntryExch);
+    static const int at[kRtMaxNB] = {2, 3, 4, 6, 7};
+    for (size_t i = 0; i < to.thr.size(); ++i)
+        o.t[i] = rt_slot(1u << to.thr[i]) * comp;
+    for (size_t k = 0; k < to.reg.size(); ++k) {
+        o.w[at[k]] = rt_slot(1u << from.reg[k]) * comp;
+        o.w[8 + k] = rt_slot(1u << to.reg[k]) * comp;
+    }
+    return o;
+}
+
+void set_matrix(RtOp &o, int tile_dt, const double *m) {
+    for (int k = 0; k < 8; ++k)
+        if (tile_dt == SV_C128)
+            o.m[k] = m[k];
+        else
+            o.f[k] = (float)m[k];
+}
+
+} // namespace
+
+RtGateInfo rt_gate_info(int kind, bool from_param, const double *m, bool diag) {
+    RtGateInfo g;
+    const int k = kind & ~SV_G_ADJOINT;
+    g.kind = kRtGen;
+    g.unit_a = 0;
+    g.pad[0] = g.pad[1] = 0;
+    if (diag) {
+        g.kind = kRtDiag;
+        g.unit_a = k == SV_G_P || k == SV_G_Z || (!from_param && m[0] == 1.0 && m[1] == 0.0);
+    } else if (from_param) {
+        g.kind = k == SV_G_RX ? kRtCross : kRtReal;  // RY is real; the other kinds are diagonal
+    } else {
+        const bool real = m[1] == 0.0 && m[3] == 0.0 && m[5] == 0.0 && m[7] == 0.0;
+        if (real && m[0] == 0.0 && m[2] == 1.0 && m[4] == 1.0 && m[6] == 0.0)
+            g.kind = kRtSwap;
+        else if (real)
+            g.kind = kRtReal;
+        else if (m[1] == 0.0 && m[7] == 0.0 && m[2] == 0.0 && m[4] == 0.0)
+            g.kind = kRtCross;
+    }
+    return g;
+}
+
+RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *t, int count,
+                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, RtProgram &prog) {
+    const int m = (int)tm.m, nb = rt_nb_of(tile_dt);
+    RtPass pass;
+    memset(&pass, 0, sizeof(pass));
+    pass.first = (uint32_t)prog.ops.size();
+    auto outer_mask = [&](int k) { return t[k].diag ? t[k].o_mask : t[k].hi_mask; };
+    auto outer_vals = [&](int k) { return t[k].diag ? t[k].o_vals : t[k].hi_vals; };
+    for (int k = 0; k < count; ++k)
+        if (!(outer_mask(k) & ~fixed_mask))
+            pass.always = 1;
+    std::vector<Unit> units;
+    for (int k = 0; k < count;) {
+        Unit u;
+        u.first = k;
+        u.count = 1;
+        u.phase = t[k].diag && t[k].sweep_phase;
+        if (u.phase)
+            u.count = std::max(1, (int)t[k].sweep_len);
+        u.diag = info[k].kind == kRtDiag;
+        u.bit = t[k].l_target;
+        u.nd = u.dg = 0;
+        for (int q = k; q < k + u.count; ++q) {
+            u.dg |= t[q].l_mask;
+            if (t[q].l_target >= 0)
+                (u.diag ? u.dg : u.nd) |= 1u << t[q].l_target;
+        }
+        units.push_back(u);
+        k += u.count;
+    }
+    const uint32_t comp = tile_dt == SV_C128 ? 8 : 4;
+    size_t lds = 16;
+
+    // phase patterns as a preparation and the multiplications by its factors
+    struct Part {
+        Cond c;
+        RtPat p;
+    };
+    auto emit_phases = [&](const Part *parts, size_t np) {
+        std::vector<Part> ts, rs, xs;
+        for (size_t i = 0; i < np; ++i) {
+            const Part &a = parts[i];
+            (!a.c.rm ? ts : !a.c.tm ? rs : xs).push_back(a);
+        }
+        for (Part &a : rs) {
+            a.p.cm = a.c.rm;
+            a.p.cv = a.c.rv;
+        }
+        std::stable_sort(xs.begin(), xs.end(), [](const Part &a, const Part &b) {
+            return a.c.rm != b.c.rm ? a.c.rm < b.c.rm : a.c.rv < b.c.rv;
+        });
+        RtOp o;
+        memset(&o, 0, sizeof(o));
+        o.w[0] = kRtPrep * 8;
+        o.w[1] = (uint32_t)np;
+        o.w[2] = (uint32_t)prog.pats.size();
+        o.w[3] = (uint32_t)ts.size();
+        o.w[4] = (uint32_t)rs.size();
+        prog.ops.push_back(o);
+        for (const std::vector<Part> *v : {&ts, &rs, &xs})
+            for (const Part &a : *v)
+                prog.pats.push_back(a.p);
+        auto factor = [&](uint32_t regs, size_t first, size_t cnt) {
+            RtOp f;
+            memset(&f, 0, sizeof(f));
+            f.w[0] = kRtFactor * 8;
+            f.w[1] = regs;
+            f.w[5] = rt_jump(kRtEntryMul);
+            f.w[12] = (uint32_t)first;
+            f.w[13] = (uint32_t)cnt;
+            prog.ops.push_back(f);
+        };
+        if (!ts.empty())
+            factor(regs_where(nb, 0, 0), 0, ts.size());
+        if (!rs.empty()) {
+            RtOp f;
+            memset(&f, 0, sizeof(f));
+            f.w[0] = kRtTable * 8;
+            f.w[5] = rt_jump(kRtEntryTab);
+            prog.ops.push_back(f);
+        }
+        for (size_t i = 0; i < xs.size();) {
+            size_t e = i;
+            while (e < xs.size() && xs[e].c.rm == xs[i].c.rm && xs[e].c.rv == xs[i].c.rv)
+                ++e;
+            factor(regs_where(nb, xs[i].c.rm, xs[i].c.rv), ts.size() + rs.size() + i, e - i);
+            i = e;
+        }
+        lds = std::max(lds, np * sizeof(RtPat) + ((size_t)16 << nb));
+    };
+
+    auto emit = [&](const Unit &u, const Layout &L) {
+        RtOp o;
+        memset(&o, 0, sizeof(o));
+        const int k = u.first;
+        if (u.phase) {
+            const TileGate &h = t[k];
+            const uint32_t np = h.sweep_cls[3 + (m - 6)];
+            std::vector<Part> parts;
+            for (uint32_t i = 0; i < np; ++i) {
+                const SweepPat &sp = pats[h.pat0 + i];
+                Part a;
+                a.c = split_cond(L, sp.lmask, sp.lvals);
+                for (uint32_t f = 0; f < sp.count; f += kRtPatMembers) {
+                    a.p = RtPat{a.c.tm, a.c.tv, sp.first + f, std::min(kRtPatMembers, sp.count - f)};
+                    parts.push_back(a);
+                }
+            }
+            for (size_t p0 = 0; p0 < parts.size(); p0 += kRtMaxPats)
+                emit_phases(&parts[p0], std::min<size_t>(kRtMaxPats, parts.size() - p0));
+            for (int q = k; q < k + u.count; ++q)
+                info[q].op = info[q].op2 = -1;
+            return;
+        }
+        const Cond c = split_cond(L, t[k].l_mask, t[k].l_vals);
+        uint64_t om = outer_mask(k), ov = outer_vals(k), ob = 0;
+        o.w[2] = c.tm;
+        o.w[3] = c.tv;
+        set_matrix(o, tile_dt, t[k].m);
+        info[k].op2 = -1;
+        auto put = [&]() {
+            o.w[6] = (uint32_t)om;
+            o.w[7] = (uint32_t)(om >> 32);
+            o.w[8] = (uint32_t)ov;
+            o.w[9] = (uint32_t)(ov >> 32);
+            o.w[10] = (uint32_t)ob;
+            o.w[11] = (uint32_t)(ob >> 32);
+            prog.ops.push_back(o);
+            return (int32_t)prog.ops.size() - 1;
+        };
+        if (u.diag) {
+            o.w[0] = kRtDiag * 8;
+            o.w[5] = rt_jump(kRtEntryMul);
+            o.w[1] = regs_where(nb, c.rm, c.rv);
+            const bool unit_a = info[k].unit_a != 0;
+            const int lt = t[k].l_target;
+            if (lt >= 0 && L.reg_of[lt] >= 0) {
+                const uint32_t one = regs_where(nb, 1u << L.reg_of[lt], 1u << L.reg_of[lt]), regs = o.w[1];
+                if (!unit_a) {  // the registers with the bit clear, as an operation of its own
+                    o.w[1] = regs & ~one;
+                    info[k].op2 = put();
+                }
+                o.w[0] = kRtDiag * 8 + 1;
+                o.w[1] = regs & one;
+            } else if (lt >= 0) {
+                const uint32_t b = 1u << L.thr_of[lt];
+                if (unit_a) {  // only the lanes with the bit set
+                    o.w[2] |= b;
+                    o.w[3] |= b;
+                    o.w[0] = kRtDiag * 8 + 1;
+                } else {
+                    o.w[4] = b;
+                }
+            } else {  // target outside the tile
+                const uint64_t b = 1ull << t[k].target;
+                if (unit_a) {
+                    om |= b;
+                    ov |= b;
+                    o.w[0] = kRtDiag * 8 + 1;
+                } else {
+                    ob = b;
+                }
+            }
+        } else {
+            const int b = L.reg_of[u.bit];
+            o.w[0] = (uint32_t)info[k].kind * 8 + (uint32_t)b;
+            for (uint32_t p = 0; p < (1u << (nb - 1)); ++p) {
+                const uint32_t i = ((p >> b) << (b + 1)) | (p & ((1u << b) - 1u));
+                if ((i & c.rm) == c.rv)
+                    o.w[1] |= 1u << p;
+            }
+            o.w[5] = rt_jump(o.w[0] + (c.rm ? 0u : kRtEntryFull));
+        }
+        info[k].op = put();
+    };
+
+    const uint32_t all = (1u << m) - 1u;
+    // load and store layouts: the low bits on lanes (complex states), or
+    // bits 0 and 1 in registers and 2..5 on lanes (fixed-point blocks)
+    const uint32_t io_fixed = block ? 3u : 0u;
+    const uint32_t io_allowed = all & ~(block ? 63u : (1u << std::min(coal, m - nb)) - 1u);
+    auto io_ok = [&](uint32_t r) { return (r & io_fixed) == io_fixed && !(r & ~(io_allowed | io_fixed)); };
+    uint32_t r = choose_regs(units, m, nb, io_fixed, io_allowed);
+    Layout cur = make_layout(m, r, block);
+    pass.in = make_io(tm, cur, comp);
+    bool exch = false;
+    while (true) {
+        Deferred d;
+        std::vector<Unit> rest;
+        for (const Unit &u : units) {
+            if (d.free(u) && (u.diag || ((r >> u.bit) & 1u))) {
+                emit(u, cur);
+            } else {
+                d.add(u);
+                rest.push_back(u);
+            }
+        }
+        units.swap(rest);
+        if (units.empty())
+            break;
+        // when what is left fits register bits a store layout may have, take them
+        const uint32_t rs = choose_regs(units, m, nb, io_fixed, io_allowed);
+        r = choose_regs(units, m, nb, 0u, all);
+        const int npair = (int)std::count_if(units.begin(), units.end(), [](const Unit &u) { return !u.diag; });
+        const bool last = taken(units, rs) == npair;
+        if (last)
+            r = rs;
+        const Layout next = make_layout(m, r, last && block);
+        prog.ops.push_back(exchange_op(cur, next, comp));
+        exch = true;
+        cur = next;
+    }
+    if (!io_ok(r) || (block && !(cur == make_layout(m, r, true)))) {
+        uint32_t keep = 0;
+        if (!block)
+            keep = r & io_allowed;
+        const Layout next = make_layout(m, choose_regs({}, m, nb, io_fixed | keep, io_allowed), block);
+        prog.ops.push_back(exchange_op(cur, next, comp));
+        exch = true;
+        cur = next;
+    }
+    pass.out = make_io(tm, cur, comp);
+    pass.count = (uint32_t)prog.ops.size() - pass.first;
+    if (exch)
+        lds = std::max(lds, ((size_t)1 << m) * comp);
+    pass.lds = (uint32_t)lds;
+    return pass;
+}
+
+// ---------------------------------------------------------------------------
+// device
+// ---------------------------------------------------------------------------
+
+// One workgroup of 2^(m - NB) lanes per tile.  128 registers per lane keep
+// four wavefronts per SIMD: four complex128 tiles of 2^12 (or complex64 tiles
+// of 2^13) amplitudes per CU, so one tile's exchanges and copies overlap the
+// others' arithmetic.
+//
+// Measured against the LDS tiles of k_tile on one MI355X (complex128 unless
+// noted): 28-qubit layered circuit of 315 gates 40.1 -> 27.8 ms (16 passes of
+// 1.64 ms; a read and write of the 4 GiB state takes 1.28 ms), 24-qubit
+// ansatz forward 8.2 -> 3.7 ms, 29-qubit QFT in complex64 25.8 -> 9.1 ms, 200
+// gates on one 12-qubit tile 194 -> 128 us.  A real gate on a resident tile
+// costs about 375 cycles per tile and CU (256 of them FP64 instructions), a
+// general one 630 (512), X 296; complex64 tiles 615, 1140 and 370 for twice
+// the amplitudes.  Tiles of 2^13 complex128 amplitudes (512 lanes) save one
+// pass of 17 on the layered circuit but run 4% slower in all, 2^11 ones 25%
+// slower.
+template <typename R>
+__global__ __launch_bounds__(kRtMaxThreads, 4) void k_rtile(cplx_t<R> *__restrict__ psi, TileMap tm, RtPass p,
+                                                            const RtOp *__restrict__ ops,
+                                                            const RtPat *__restrict__ pats,
+                                                            const SweepMember *__restrict__ mems,
+                                                            DeviceGates gates) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int NB = rt_nb<R>();
+    const uint64_t base = expand_index<uint64_t>(tm.outer, tm.tile0 + blockIdx.x);
+    if (!p.always && !tile_touched(base, gates))
+        return;
+    const int tb = (int)tm.m - NB;
+    RtRegs<R, NB> v;
+    const cplx_t<R> *src = psi + (base | rt_thread_offset(p.in, threadIdx.x, tb));
+    SV_RT_FOR(1 << NB, r) {
+        const cplx_t<R> a = ld_stream<R>(src + rt_reg_offset<NB>(p.in, r));
+        v.x[r] = rt_own(a.x);
+        v.y[r] = rt_own(a.y);
+    });
+    const uint32_t slot = rt_xor_terms(threadIdx.x, p.in.slot);
+    rt_run<R, NB>(v, lds, slot, base, ops + p.first, p.count, pats, mems);
+    cplx_t<R> *dst = psi + (base | rt_thread_offset(p.out, rt_fresh(threadIdx.x), tb));
+    SV_RT_FOR(1 << NB, r) {
+        cplx_t<R> a;
+        a.x = rt_own(v.x[r]);
+        a.y = rt_own(v.y[r]);
+        st_stream<R>(dst + rt_reg_offset<NB>(p.out, r), a);
+    });
+}
+
+template <typename R>
+static int launch_rt(void *psi, const TileMap &tm_in, const RtPass &p, const RtDevice &d, const DeviceGates &gates,
+                     hipStream_t st) {
+    TileMap tm = tm_in;
+    const unsigned lanes = 1u << ((int)tm.m - rt_nb<R>());
+    for (uint64_t t0 = 0; t0 < tm.ntiles; t0 += kMaxGridBlocks) {
+        tm.tile0 = t0;
+        const dim3 grid((unsigned)std::min(kMaxGridBlocks, tm_in.ntiles - t0));
+        hipLaunchKernelGGL(k_rtile<R>, grid, dim3(lanes), p.lds, st, reinterpret_cast<cplx_t<R> *>(psi), tm, p, d.ops,
+                           d.pats, gates.mm, gates);
+        SV_LAUNCH_CHECK();
+    }
+    return SV_OK;
+}
+
+int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,
+                   const DeviceGates &gates, hipStream_t st) {
+    if (!rt_tile_ok(dtype, (int)tm.m))
+        return fail(SV_EINVAL, "register tiles of 2^%u amplitudes", tm.m);
+    return dtype == SV_C128 ? launch_rt<double>(psi, tm, p, d, gates, st) : launch_rt<float>(psi, tm, p, d, gates, st);
+}
+
+} // namespace sv

@@ -1,0 +1,262 @@
+// Register-resident tile pass: a fused run applied to tiles whose amplitudes
+// live in registers, 2^NB per lane (16 complex128 or 32 complex64: 64 vector
+// registers), for the whole run.
+//
+// What bounds a long run is the work inside the tile.  With the tile in LDS
+// (k_tile) every operation reads and writes all of it there: 64 KiB each way
+// for a complex128 tile of 2^12 amplitudes, at least 1024 cycles at 128 B per
+// clock, plus a barrier, against 512 cycles for a general FP64 pair update
+// and 256 for a real or axis rotation.  Here a gate whose target is one of the
+// NB "register bits" of the current layout touches registers only.  Gates on
+// other targets wait until an exchange through LDS has given their targets
+// register positions; the host schedules a run as segments, each with the NB
+// register bits that serve most of the gates that may come next (gates pass
+// each other only where they commute).
+//
+// A layout places every tile-local index bit: NB of them number a lane's
+// registers, the rest are bits of the thread index (6 lane bits, then
+// wavefront bits).  A control on a thread bit is a lane predicate, one on a
+// register bit selects registers (a mask formed on the host), one outside the
+// tile is a predicate on the tile's base index.  The exchange writes one
+// component of every amplitude, meets at a barrier and reads it back in the
+// new layout, so it needs only half the tile's bytes of LDS; the slot of
+// amplitude j is j with its upper bits folded onto the lowest five (rt_slot),
+// which keeps a wavefront's accesses on different banks for the lane-bit
+// choices of RtLayout.
+#pragma once
+
+#include <utility>
+
+#include "reduce.hpp"
+#include "rtile_ops.hpp"
+#include "rtile_plan.hpp"
+
+namespace sv {
+
+// Slot of amplitude j in the exchange buffer; linear over xor.
+__host__ __device__ constexpr uint32_t rt_slot(uint32_t j) { return j ^ ((j >> 5) & 31u) ^ ((j >> 10) & 31u); }
+
+#ifdef __HIPCC__
+
+// f(integral constant) for 0 .. N - 1: register arrays are only ever indexed
+// by constants of the source.
+template <typename F, int... I>
+__device__ __forceinline__ void rt_unrolled(const F &f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void rt_for(const F &f) {
+    rt_unrolled(f, std::make_integer_sequence<int, N>());
+}
+#define SV_RT_FOR(N, i) rt_for<(N)>([&](auto i) __attribute__((always_inline))
+
+template <typename R> __device__ __forceinline__ Mat2<R> rt_mat(const RtOp &o) {
+    if constexpr (sizeof(R) == 8)
+        return Mat2<R>{o.m[0], o.m[1], o.m[2], o.m[3], o.m[4], o.m[5], o.m[6], o.m[7]};
+    else
+        return Mat2<R>{o.f[0], o.f[1], o.f[2], o.f[3], o.f[4], o.f[5], o.f[6], o.f[7]};
+}
+
+// A value the compiler may not take as known: keeps what depends on it where
+// it is written instead of hoisted out of the operation loop, where it would
+// occupy registers beside the tile's for the whole run.
+__device__ __forceinline__ uint32_t rt_fresh(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Coefficients of phase_factor's polynomials (tile.hpp): 2/pi, pi/2 in two
+// parts, the sine series from 1/17! down to 1, the cosine series from 1/16!
+// down to 1.  Read from memory as uniform operands, for the reason above.
+static __device__ const double kRtSeries[21] = {
+    0.63661977236758134, 1.5707963267948966, 6.123233995736766e-17,
+    1.0 / 355687428096000.0, 1.0 / 1307674368000.0, 1.0 / 6227020800.0, 1.0 / 39916800.0, 1.0 / 362880.0,
+    1.0 / 5040.0, 1.0 / 120.0, 1.0 / 6.0, 1.0,
+    1.0 / 20922789888000.0, 1.0 / 87178291200.0, 1.0 / 479001600.0, 1.0 / 3628800.0, 1.0 / 40320.0, 1.0 / 720.0,
+    1.0 / 24.0, 1.0 / 2.0, 1.0};
+static __device__ const float kRtSeriesF[10] = {
+    1.0f / 362880.0f, 1.0f / 5040.0f, 1.0f / 120.0f, 1.0f / 6.0f, 1.0f,
+    1.0f / 40320.0f, 1.0f / 720.0f, 1.0f / 24.0f, 1.0f / 2.0f, 1.0f};
+
+// exp(i th) as phase_factor evaluates it.
+template <typename R> __device__ __forceinline__ void rt_phase_factor(double th, R *fr, R *fi) {
+    const double *c = kRtSeries;
+    asm volatile("" : "+s"(c));
+    const double k = rint(th * c[0]);
+    double rd = fma(-k, c[1], th);
+    rd = fma(-k, c[2], rd);
+    R s, co;
+    if constexpr (sizeof(R) == 8) {
+        const double r2 = rd * rd;
+        double ps = c[3], pc = c[12];
+#pragma unroll
+        for (int i = 4; i < 12; ++i)
+            ps = fma(ps, -r2, c[i]);
+#pragma unroll
+        for (int i = 13; i < 21; ++i)
+            pc = fma(pc, -r2, c[i]);
+        s = rd * ps;
+        co = pc;
+    } else {
+        const float *f = kRtSeriesF;
+        asm volatile("" : "+s"(f));
+        const float r = (float)rd, r2 = r * r;
+        float ps = f[0], pc = f[5];
+#pragma unroll
+        for (int i = 1; i < 5; ++i)
+            ps = fmaf(ps, -r2, f[i]);
+#pragma unroll
+        for (int i = 6; i < 10; ++i)
+            pc = fmaf(pc, -r2, f[i]);
+        s = r * ps;
+        co = pc;
+    }
+    const int q = (int)((int64_t)k & 3);
+    *fi = q == 0 ? s : q == 1 ? co : q == 2 ? -s : -co;
+    *fr = q == 0 ? co : q == 1 ? -s : q == 2 ? -co : s;
+}
+
+// One phase pattern of the current tile, kept in LDS.
+struct RtPhase {
+    uint32_t cm, cv;
+    double th;
+};
+
+// Sum of the phases of patterns [first, first + count) that index idx
+// selects.
+__device__ __forceinline__ double rt_phase_sum(const RtPhase *ph, uint32_t first, uint32_t count, uint32_t idx) {
+    double t = 0.0;
+#pragma unroll 4
+    for (uint32_t p = first; p < first + count; ++p) {
+        const RtPhase q = ph[p];
+        t += (idx & q.cm) == q.cv ? q.th : 0.0;
+    }
+    return t;
+}
+
+// A block of diagonal gates multiplies every amplitude by exp(i theta), theta
+// the sum of the block's phases its index selects.  The phases split by the
+// register condition they carry: those without one (T patterns) sum to one
+// phase per lane, those without a thread condition (R patterns) to one per
+// register number, shared by all lanes, and the rest to one phase per lane
+// for each distinct register condition; so an amplitude costs a few complex
+// products and a lane a few sines and cosines, however many gates the block
+// has.  This operation sums every pattern's members for the tile and forms
+// the R patterns' table of factors; kRtFactor and kRtTable operations follow.
+template <typename R, int NB>
+__device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const uint32_t (&w)[16],
+                                        const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems) {
+    const uint32_t tid = rt_fresh(threadIdx.x), np = w[1];
+    cplx_t<R> *fr = reinterpret_cast<cplx_t<R> *>(lds);
+    RtPhase *ph = reinterpret_cast<RtPhase *>(fr + (1 << NB));
+    __syncthreads();  // the buffer's last readers are done
+    for (uint32_t p = tid; p < np; p += blockDim.x) {
+        const RtPat q = pats[w[2] + p];
+        double th = 0.0;
+#pragma unroll 1
+        for (uint32_t k = 0; k < q.count; ++k) {
+            const SweepMember mm = mems[q.first + k];
+            th += (base & mm.om) == mm.ov ? mm.theta : 0.0;
+        }
+        RtPhase a;
+        a.cm = q.cm;
+        a.cv = q.cv;
+        a.th = th;
+        ph[p] = a;
+    }
+    __syncthreads();
+    if (w[4]) {  // uniform
+        if (tid < (1u << NB)) {
+            cplx_t<R> f;
+            rt_phase_factor<R>(rt_phase_sum(ph, w[3], w[4], tid), &f.x, &f.y);
+            fr[tid] = f;
+        }
+        __syncthreads();
+    }
+}
+
+// xor of the terms of a thread index's set bits
+__device__ __forceinline__ uint32_t rt_xor_terms(uint32_t tid, const uint32_t *t) {
+    uint32_t a = 0;
+#pragma unroll
+    for (int i = 0; i < kRtMaxThreadBits; ++i)
+        a ^= ((tid >> i) & 1u) ? t[i] : 0u;
+    return a;
+}
+
+// A run's operations on the tile in registers.  slot: the lane's byte offset
+// in the exchange buffer in the current layout.
+template <typename R, int NB>
+__device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uint32_t slot, uint64_t base,
+                                       const RtOp *__restrict__ ops, uint32_t count,
+                                       const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems) {
+    const uint32_t tid = threadIdx.x;
+    // LDS byte address of the buffer
+    const uint32_t buf = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    const RtPhase *ph = reinterpret_cast<const RtPhase *>(reinterpret_cast<cplx_t<R> *>(lds) + (1 << NB));
+    for (uint32_t i = 0; i < count; ++i) {
+        const RtOp &o = ops[i];
+        uint32_t w[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            w[k] = o.w[k];
+        const uint32_t kind = w[0] >> 3;
+        const Mat2<R> m = rt_mat<R>(o);
+        R fr = (R)0, fi = (R)0;
+        uint64_t lanes = ~0ull;
+        uint32_t next = slot;
+        if (kind <= kRtDiag) {
+            const uint64_t om = (uint64_t)w[7] << 32 | w[6], ov = (uint64_t)w[9] << 32 | w[8];
+            const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
+            lanes = (base & om) == ov ? __ballot((tid & w[2]) == w[3]) : 0ull;
+            const bool one = (tid & w[4]) != 0 || (base & ob) != 0 || (w[0] & 7u) != 0;
+            fr = one ? m.dr : m.ar;
+            fi = one ? m.di : m.ai;
+        } else if (kind == kRtFactor) {
+            rt_phase_factor<R>(rt_phase_sum(ph, w[12], w[13], tid), &fr, &fi);
+        } else if (kind == kRtExch) {
+            next = rt_xor_terms(rt_fresh(tid), o.t);
+        } else if (kind == kRtPrep) {
+            rt_prep<R, NB>(lds, base, w, pats, mems);
+            lanes = 0;
+        }
+        uint32_t sa = buf + slot, na = buf + next;
+        rt_apply(v, w, m, fr, fi, lanes, buf, sa, na);
+        slot = next;
+    }
+}
+
+// A component in registers of its own.  Amplitudes are loaded and stored as
+// whole 16- or 8-byte values; without these moves the compiler keeps each one
+// in adjacent registers through the run, and the aligned groups no longer fit.
+__device__ __forceinline__ double rt_own(double v) {
+    double o;
+    asm("v_mov_b64 %0, %1" : "=v"(o) : "v"(v));
+    return o;
+}
+__device__ __forceinline__ float rt_own(float v) {
+    float o;
+    asm("v_mov_b32 %0, %1" : "=v"(o) : "v"(v));
+    return o;
+}
+
+// The lane's part of a global amplitude index, and one register's.
+__device__ __forceinline__ uint64_t rt_thread_offset(const RtIO &io, uint32_t tid, int bits) {
+    uint64_t a = 0;
+#pragma unroll
+    for (int i = 0; i < kRtMaxThreadBits; ++i)
+        if (i < bits)  // uniform
+            a |= (uint64_t)((tid >> i) & 1u) << io.tq[i];
+    return a;
+}
+template <int NB> __device__ __forceinline__ uint64_t rt_reg_offset(const RtIO &io, int r) {
+    uint64_t a = 0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+        if ((r >> k) & 1)
+            a |= 1ull << io.rq[k];
+    return a;
+}
+
+#endif  // __HIPCC__
+
+} // namespace sv

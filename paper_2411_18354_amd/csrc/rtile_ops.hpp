@@ -1,0 +1,305 @@
+// The gate operations of the register tile pass (rtile.hpp) on a lane's
+// amplitudes, as one block of instructions per call.
+//
+// Written as instructions because the amplitudes have to stay where they are:
+// 64 registers live through every branch of an interpreter loop leave the
+// compiler's allocator copying and spilling at each operation (measured: 130
+// to 800 spilled registers of 128), while operands tied to the block cannot
+// move.  The block jumps by operation code to one of its variants (a kind and
+// a register bit), which updates the pairs, or registers, of its mask under
+// the lanes' condition.
+//
+// The rounding of each update is that of apply_pair (gate_math.hpp), products
+// with an entry known to be zero left out.
+#pragma once
+
+#include "gate_math.hpp"
+
+namespace sv {
+
+// One step of a pair (x, y): operands are named x<i>, y<i> (real and
+// imaginary part of register i); t0 .. t3 are scratch; ar .. di the matrix.
+#define RT_N(c, i) "%[" #c #i "]"
+#define RT_STEP_REAL(SZ, i, j)                                                                                     \
+    "v_mul_" SZ " %[t0], %[br], " RT_N(x, j) "\n"                                                                  \
+    "v_mul_" SZ " %[t1], %[br], " RT_N(y, j) "\n"                                                                  \
+    "v_mul_" SZ " " RT_N(x, j) ", %[dr], " RT_N(x, j) "\n"                                                         \
+    "v_mul_" SZ " " RT_N(y, j) ", %[dr], " RT_N(y, j) "\n"                                                         \
+    "v_fma_" SZ " " RT_N(x, j) ", %[cr], " RT_N(x, i) ", " RT_N(x, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(y, j) ", %[cr], " RT_N(y, i) ", " RT_N(y, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(x, i) ", %[ar], " RT_N(x, i) ", %[t0]\n"                                                  \
+    "v_fma_" SZ " " RT_N(y, i) ", %[ar], " RT_N(y, i) ", %[t1]\n"
+#define RT_STEP_CROSS(SZ, i, j)                                                                                    \
+    "v_mul_" SZ " %[t0], %[bi], " RT_N(y, j) "\n"                                                                  \
+    "v_mul_" SZ " %[t1], %[bi], " RT_N(x, j) "\n"                                                                  \
+    "v_mul_" SZ " " RT_N(x, j) ", %[dr], " RT_N(x, j) "\n"                                                         \
+    "v_mul_" SZ " " RT_N(y, j) ", %[dr], " RT_N(y, j) "\n"                                                         \
+    "v_fma_" SZ " " RT_N(x, j) ", -%[ci], " RT_N(y, i) ", " RT_N(x, j) "\n"                                        \
+    "v_fma_" SZ " " RT_N(y, j) ", %[ci], " RT_N(x, i) ", " RT_N(y, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(x, i) ", %[ar], " RT_N(x, i) ", -%[t0]\n"                                                 \
+    "v_fma_" SZ " " RT_N(y, i) ", %[ar], " RT_N(y, i) ", %[t1]\n"
+#define RT_STEP_GEN(SZ, i, j)                                                                                      \
+    "v_mul_" SZ " %[t0], %[bi], " RT_N(y, j) "\n"                                                                  \
+    "v_mul_" SZ " %[t1], %[bi], " RT_N(x, j) "\n"                                                                  \
+    "v_mul_" SZ " %[t2], %[di], " RT_N(y, j) "\n"                                                                  \
+    "v_mul_" SZ " %[t3], %[di], " RT_N(x, j) "\n"                                                                  \
+    "v_fma_" SZ " %[t0], %[br], " RT_N(x, j) ", -%[t0]\n"                                                          \
+    "v_fma_" SZ " %[t1], %[br], " RT_N(y, j) ", %[t1]\n"                                                           \
+    "v_fma_" SZ " " RT_N(x, j) ", %[dr], " RT_N(x, j) ", -%[t2]\n"                                                 \
+    "v_fma_" SZ " " RT_N(y, j) ", %[dr], " RT_N(y, j) ", %[t3]\n"                                                  \
+    "v_fma_" SZ " %[t0], -%[ai], " RT_N(y, i) ", %[t0]\n"                                                          \
+    "v_fma_" SZ " %[t1], %[ai], " RT_N(x, i) ", %[t1]\n"                                                           \
+    "v_fma_" SZ " " RT_N(x, j) ", -%[ci], " RT_N(y, i) ", " RT_N(x, j) "\n"                                        \
+    "v_fma_" SZ " " RT_N(y, j) ", %[ci], " RT_N(x, i) ", " RT_N(y, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(x, j) ", %[cr], " RT_N(x, i) ", " RT_N(x, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(y, j) ", %[cr], " RT_N(y, i) ", " RT_N(y, j) "\n"                                         \
+    "v_fma_" SZ " " RT_N(x, i) ", %[ar], " RT_N(x, i) ", %[t0]\n"                                                  \
+    "v_fma_" SZ " " RT_N(y, i) ", %[ar], " RT_N(y, i) ", %[t1]\n"
+#define RT_STEP_SWAP_f64(i, j)                                                                                     \
+    "v_mov_b64 %[t0], " RT_N(x, i) "\n"                                                                            \
+    "v_mov_b64 %[t1], " RT_N(y, i) "\n"                                                                            \
+    "v_mov_b64 " RT_N(x, i) ", " RT_N(x, j) "\n"                                                                   \
+    "v_mov_b64 " RT_N(y, i) ", " RT_N(y, j) "\n"                                                                   \
+    "v_mov_b64 " RT_N(x, j) ", %[t0]\n"                                                                            \
+    "v_mov_b64 " RT_N(y, j) ", %[t1]\n"
+#define RT_STEP_SWAP_f32(i, j)                                                                                     \
+    "v_swap_b32 " RT_N(x, i) ", " RT_N(x, j) "\n"                                                                  \
+    "v_swap_b32 " RT_N(y, i) ", " RT_N(y, j) "\n"
+// one register times the lane's factor
+#define RT_STEP_MUL(SZ, i)                                                                                         \
+    "v_mul_" SZ " %[t0], %[fi], " RT_N(y, i) "\n"                                                                  \
+    "v_mul_" SZ " %[t1], %[fi], " RT_N(x, i) "\n"                                                                  \
+    "v_fma_" SZ " " RT_N(x, i) ", %[fr], " RT_N(x, i) ", -%[t0]\n"                                                 \
+    "v_fma_" SZ " " RT_N(y, i) ", %[fr], " RT_N(y, i) ", %[t1]\n"
+
+// one register times its own factor, read from the table at byte address ta
+// (two components of SB bytes each)
+#define RT_STEP_TAB(SZ, RD, i, off0, off1)                                                                         \
+    RD " %[t2], %[ta] offset:" #off0 "\n" RD " %[t3], %[ta] offset:" #off1 "\n"                                    \
+    "s_waitcnt lgkmcnt(0)\n"                                                                                       \
+    "v_mul_" SZ " %[t0], %[t3], " RT_N(y, i) "\n"                                                                  \
+    "v_mul_" SZ " %[t1], %[t3], " RT_N(x, i) "\n"                                                                  \
+    "v_fma_" SZ " " RT_N(x, i) ", %[t2], " RT_N(x, i) ", -%[t0]\n"                                                 \
+    "v_fma_" SZ " " RT_N(y, i) ", %[t2], " RT_N(y, i) ", %[t1]\n"
+
+#define RT_REAL_f64(i, j) RT_STEP_REAL("f64", i, j)
+#define RT_REAL_f32(i, j) RT_STEP_REAL("f32", i, j)
+#define RT_CROSS_f64(i, j) RT_STEP_CROSS("f64", i, j)
+#define RT_CROSS_f32(i, j) RT_STEP_CROSS("f32", i, j)
+#define RT_GEN_f64(i, j) RT_STEP_GEN("f64", i, j)
+#define RT_GEN_f32(i, j) RT_STEP_GEN("f32", i, j)
+#define RT_SWAP_f64(i, j) RT_STEP_SWAP_f64(i, j)
+#define RT_SWAP_f32(i, j) RT_STEP_SWAP_f32(i, j)
+#define RT_MUL_f64(i) RT_STEP_MUL("f64", i)
+#define RT_MUL_f32(i) RT_STEP_MUL("f32", i)
+
+// Step of pair p = (i, j), skipped where the mask's bit is clear.
+#define RT_PAIR(OP, V, p, i, j)                                                                                    \
+    "s_bitcmp1_b32 %[pm], " #p "\n"                                                                                \
+    "s_cbranch_scc0 .Lrt_" V "_" #p "_%=\n" OP(i, j) ".Lrt_" V "_" #p "_%=:\n"
+// the same where every pair is meant: no test per pair (a test and branch
+// cost a wavefront about 30 cycles beside the 32 of a real pair's update)
+#define RT_FULL(OP, V, p, i, j) OP(i, j)
+#define RT_REG(OP, i)                                                                                              \
+    "s_bitcmp1_b32 %[pm], " #i "\n"                                                                                \
+    "s_cbranch_scc0 .Lrt_mul_" #i "_%=\n" OP(i) ".Lrt_mul_" #i "_%=:\n"
+
+// The pairs of register bit T among 16 registers, in pair order.
+#define RT_PAIRS4_0(P, F, V)                                                                                          \
+    P(F, V, 0, 0, 1) P(F, V, 1, 2, 3) P(F, V, 2, 4, 5) P(F, V, 3, 6, 7)                    \
+    P(F, V, 4, 8, 9) P(F, V, 5, 10, 11) P(F, V, 6, 12, 13) P(F, V, 7, 14, 15)
+#define RT_PAIRS4_1(P, F, V)                                                                                          \
+    P(F, V, 0, 0, 2) P(F, V, 1, 1, 3) P(F, V, 2, 4, 6) P(F, V, 3, 5, 7)                    \
+    P(F, V, 4, 8, 10) P(F, V, 5, 9, 11) P(F, V, 6, 12, 14) P(F, V, 7, 13, 15)
+#define RT_PAIRS4_2(P, F, V)                                                                                          \
+    P(F, V, 0, 0, 4) P(F, V, 1, 1, 5) P(F, V, 2, 2, 6) P(F, V, 3, 3, 7)                    \
+    P(F, V, 4, 8, 12) P(F, V, 5, 9, 13) P(F, V, 6, 10, 14) P(F, V, 7, 11, 15)
+#define RT_PAIRS4_3(P, F, V)                                                                                          \
+    P(F, V, 0, 0, 8) P(F, V, 1, 1, 9) P(F, V, 2, 2, 10) P(F, V, 3, 3, 11)                  \
+    P(F, V, 4, 4, 12) P(F, V, 5, 5, 13) P(F, V, 6, 6, 14) P(F, V, 7, 7, 15)
+// and among 32
+#define RT_PAIRS5_0(P, F, V)                                                                                          \
+    RT_PAIRS4_0(P, F, V)                                                                                              \
+    P(F, V, 8, 16, 17) P(F, V, 9, 18, 19) P(F, V, 10, 20, 21) P(F, V, 11, 22, 23)          \
+    P(F, V, 12, 24, 25) P(F, V, 13, 26, 27) P(F, V, 14, 28, 29) P(F, V, 15, 30, 31)
+#define RT_PAIRS5_1(P, F, V)                                                                                          \
+    RT_PAIRS4_1(P, F, V)                                                                                              \
+    P(F, V, 8, 16, 18) P(F, V, 9, 17, 19) P(F, V, 10, 20, 22) P(F, V, 11, 21, 23)          \
+    P(F, V, 12, 24, 26) P(F, V, 13, 25, 27) P(F, V, 14, 28, 30) P(F, V, 15, 29, 31)
+#define RT_PAIRS5_2(P, F, V)                                                                                          \
+    RT_PAIRS4_2(P, F, V)                                                                                              \
+    P(F, V, 8, 16, 20) P(F, V, 9, 17, 21) P(F, V, 10, 18, 22) P(F, V, 11, 19, 23)          \
+    P(F, V, 12, 24, 28) P(F, V, 13, 25, 29) P(F, V, 14, 26, 30) P(F, V, 15, 27, 31)
+#define RT_PAIRS5_3(P, F, V)                                                                                          \
+    RT_PAIRS4_3(P, F, V)                                                                                              \
+    P(F, V, 8, 16, 24) P(F, V, 9, 17, 25) P(F, V, 10, 18, 26) P(F, V, 11, 19, 27)          \
+    P(F, V, 12, 20, 28) P(F, V, 13, 21, 29) P(F, V, 14, 22, 30) P(F, V, 15, 23, 31)
+#define RT_PAIRS5_4(P, F, V)                                                                                          \
+    P(F, V, 0, 0, 16) P(F, V, 1, 1, 17) P(F, V, 2, 2, 18) P(F, V, 3, 3, 19)                \
+    P(F, V, 4, 4, 20) P(F, V, 5, 5, 21) P(F, V, 6, 6, 22) P(F, V, 7, 7, 23)                \
+    P(F, V, 8, 8, 24) P(F, V, 9, 9, 25) P(F, V, 10, 10, 26) P(F, V, 11, 11, 27)            \
+    P(F, V, 12, 12, 28) P(F, V, 13, 13, 29) P(F, V, 14, 14, 30) P(F, V, 15, 15, 31)
+#define RT_REGS4(F)                                                                                                \
+    RT_REG(F, 0) RT_REG(F, 1) RT_REG(F, 2) RT_REG(F, 3) RT_REG(F, 4) RT_REG(F, 5) RT_REG(F, 6) RT_REG(F, 7)        \
+    RT_REG(F, 8) RT_REG(F, 9) RT_REG(F, 10) RT_REG(F, 11) RT_REG(F, 12) RT_REG(F, 13) RT_REG(F, 14) RT_REG(F, 15)
+#define RT_REGS5(F)                                                                                                \
+    RT_REGS4(F)                                                                                                    \
+    RT_REG(F, 16) RT_REG(F, 17) RT_REG(F, 18) RT_REG(F, 19) RT_REG(F, 20) RT_REG(F, 21) RT_REG(F, 22)              \
+    RT_REG(F, 23) RT_REG(F, 24) RT_REG(F, 25) RT_REG(F, 26) RT_REG(F, 27) RT_REG(F, 28) RT_REG(F, 29)              \
+    RT_REG(F, 30) RT_REG(F, 31)
+
+// The registers in Gray-code order, S a step and F(b) the flip of register bit
+// b between two; R: the same order backwards.
+#define RT_GRAY4(S, F)                                                                                             \
+    S(0) F(0) S(1) F(1) S(3) F(0) S(2) F(2) S(6) F(0) S(7) F(1) S(5) F(0) S(4) F(3)                                \
+    S(12) F(0) S(13) F(1) S(15) F(0) S(14) F(2) S(10) F(0) S(11) F(1) S(9) F(0) S(8)
+#define RT_GRAY4R(S, F)                                                                                            \
+    S(8) F(0) S(9) F(1) S(11) F(0) S(10) F(2) S(14) F(0) S(15) F(1) S(13) F(0) S(12) F(3)                          \
+    S(4) F(0) S(5) F(1) S(7) F(0) S(6) F(2) S(2) F(0) S(3) F(1) S(1) F(0) S(0)
+#define RT_GRAY5(S, F)                                                                                             \
+    RT_GRAY4(S, F) F(4)                                                                                            \
+    S(24) F(0) S(25) F(1) S(27) F(0) S(26) F(2) S(30) F(0) S(31) F(1) S(29) F(0) S(28) F(3)                        \
+    S(20) F(0) S(21) F(1) S(23) F(0) S(22) F(2) S(18) F(0) S(19) F(1) S(17) F(0) S(16)
+#define RT_GRAY5R(S, F)                                                                                            \
+    S(16) F(0) S(17) F(1) S(19) F(0) S(18) F(2) S(22) F(0) S(23) F(1) S(21) F(0) S(20) F(3)                        \
+    S(28) F(0) S(29) F(1) S(31) F(0) S(30) F(2) S(26) F(0) S(27) F(1) S(25) F(0) S(24) F(4)                        \
+    RT_GRAY4R(S, F)
+// Exchange: one component written in the old layout, read in the new one, the
+// lane's slot stepping through the registers by xor; the second component
+// walks back, so both slots end where they began.
+#define RT_FW(b) "v_xor_b32 %[sa], %[w" #b "], %[sa]\n"
+#define RT_FD(b) "v_xor_b32 %[na], %[d" #b "], %[na]\n"
+#define RT_WX_f64(i) "ds_write_b64 %[sa], " RT_N(x, i) "\n"
+#define RT_WY_f64(i) "ds_write_b64 %[sa], " RT_N(y, i) "\n"
+#define RT_RX_f64(i) "ds_read_b64 " RT_N(x, i) ", %[na]\n"
+#define RT_RY_f64(i) "ds_read_b64 " RT_N(y, i) ", %[na]\n"
+#define RT_WX_f32(i) "ds_write_b32 %[sa], " RT_N(x, i) "\n"
+#define RT_WY_f32(i) "ds_write_b32 %[sa], " RT_N(y, i) "\n"
+#define RT_RX_f32(i) "ds_read_b32 " RT_N(x, i) ", %[na]\n"
+#define RT_RY_f32(i) "ds_read_b32 " RT_N(y, i) ", %[na]\n"
+#define RT_MEET "s_waitcnt lgkmcnt(0)\ns_barrier\n"
+#define RT_EXCH(G, GR, SZ)                                                                                         \
+    RT_MEET G(RT_WX_##SZ, RT_FW) RT_MEET G(RT_RX_##SZ, RT_FD) RT_MEET GR(RT_WY_##SZ, RT_FW)                        \
+    RT_MEET GR(RT_RY_##SZ, RT_FD) "s_waitcnt lgkmcnt(0)\n"
+
+#define RT_TAB_f64(i, o0, o1) RT_STEP_TAB("f64", "ds_read_b64", i, o0, o1)
+#define RT_TAB_f32(i, o0, o1) RT_STEP_TAB("f32", "ds_read_b32", i, o0, o1)
+#define RT_TABLE_f64                                                                                               \
+    RT_TAB_f64(0, 0, 8) RT_TAB_f64(1, 16, 24) RT_TAB_f64(2, 32, 40) RT_TAB_f64(3, 48, 56)                          \
+    RT_TAB_f64(4, 64, 72) RT_TAB_f64(5, 80, 88) RT_TAB_f64(6, 96, 104) RT_TAB_f64(7, 112, 120)                     \
+    RT_TAB_f64(8, 128, 136) RT_TAB_f64(9, 144, 152) RT_TAB_f64(10, 160, 168) RT_TAB_f64(11, 176, 184)              \
+    RT_TAB_f64(12, 192, 200) RT_TAB_f64(13, 208, 216) RT_TAB_f64(14, 224, 232) RT_TAB_f64(15, 240, 248)
+#define RT_TABLE_f32                                                                                               \
+    RT_TAB_f32(0, 0, 4) RT_TAB_f32(1, 8, 12) RT_TAB_f32(2, 16, 20) RT_TAB_f32(3, 24, 28)                           \
+    RT_TAB_f32(4, 32, 36) RT_TAB_f32(5, 40, 44) RT_TAB_f32(6, 48, 52) RT_TAB_f32(7, 56, 60)                        \
+    RT_TAB_f32(8, 64, 68) RT_TAB_f32(9, 72, 76) RT_TAB_f32(10, 80, 84) RT_TAB_f32(11, 88, 92)                      \
+    RT_TAB_f32(12, 96, 100) RT_TAB_f32(13, 104, 108) RT_TAB_f32(14, 112, 116) RT_TAB_f32(15, 120, 124)             \
+    RT_TAB_f32(16, 128, 132) RT_TAB_f32(17, 136, 140) RT_TAB_f32(18, 144, 148) RT_TAB_f32(19, 152, 156)            \
+    RT_TAB_f32(20, 160, 164) RT_TAB_f32(21, 168, 172) RT_TAB_f32(22, 176, 180) RT_TAB_f32(23, 184, 188)            \
+    RT_TAB_f32(24, 192, 196) RT_TAB_f32(25, 200, 204) RT_TAB_f32(26, 208, 212) RT_TAB_f32(27, 216, 220)            \
+    RT_TAB_f32(28, 224, 228) RT_TAB_f32(29, 232, 236) RT_TAB_f32(30, 240, 244) RT_TAB_f32(31, 248, 252)
+
+// The lanes' condition, then a jump into the branch table that follows, whose
+// entry k (4 k bytes into it) is the branch to a variant; %[jo] = rt_jump(k)
+// counts from behind s_getpc, past the three instructions before the table.
+#define RT_DISPATCH                                                                                                \
+    "s_mov_b64 %[sv], exec\n"                                                                                      \
+    "s_and_b64 exec, exec, %[lm]\n"                                                                                \
+    "s_cbranch_execz .Lrt_end_%=\n"                                                                                \
+    "s_getpc_b64 vcc\n"                                                                                            \
+    "s_add_u32 vcc_lo, vcc_lo, %[jo]\n"                                                                            \
+    "s_addc_u32 vcc_hi, vcc_hi, 0\n"                                                                               \
+    "s_setpc_b64 vcc\n"
+#define RT_GO(V) "s_branch .Lrt_" V "_%=\n"
+#define RT_AT(V) ".Lrt_" V "_%=:\n"
+#define RT_END "s_branch .Lrt_end_%=\n"
+#define RT_NONE "s_branch .Lrt_end_%=\n"
+// entries of one kind: register bits 0 .. 7 (those there are)
+#define RT_TABLE4(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_NONE RT_NONE RT_NONE RT_NONE
+#define RT_TABLE5(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_GO(K "4") RT_NONE RT_NONE RT_NONE
+#define RT_KIND4(P, OP, K)                                                                                         \
+    RT_AT(K "0") RT_PAIRS4_0(P, OP, K "0") RT_END RT_AT(K "1") RT_PAIRS4_1(P, OP, K "1") RT_END                    \
+    RT_AT(K "2") RT_PAIRS4_2(P, OP, K "2") RT_END RT_AT(K "3") RT_PAIRS4_3(P, OP, K "3") RT_END
+#define RT_KIND5(P, OP, K)                                                                                         \
+    RT_AT(K "0") RT_PAIRS5_0(P, OP, K "0") RT_END RT_AT(K "1") RT_PAIRS5_1(P, OP, K "1") RT_END                    \
+    RT_AT(K "2") RT_PAIRS5_2(P, OP, K "2") RT_END RT_AT(K "3") RT_PAIRS5_3(P, OP, K "3") RT_END                    \
+    RT_AT(K "4") RT_PAIRS5_4(P, OP, K "4") RT_END
+// every variant: entry kind * 8 + register bit of the pair kinds, again with
+// every pair from kRtEntryFull on, then the rest
+#define RT_BLOCK_f64                                                                                               \
+    RT_DISPATCH RT_TABLE4("r") RT_TABLE4("c") RT_TABLE4("g") RT_TABLE4("s") RT_TABLE4("rf") RT_TABLE4("cf") RT_TABLE4("gf") RT_TABLE4("sf")\
+    RT_GO("mul") RT_GO("tab") RT_GO("ex")                                                                          \
+    RT_KIND4(RT_PAIR, RT_REAL_f64, "r")                                                                            \
+    RT_KIND4(RT_PAIR, RT_CROSS_f64, "c")                                                                           \
+    RT_KIND4(RT_PAIR, RT_GEN_f64, "g")                                                                             \
+    RT_KIND4(RT_PAIR, RT_SWAP_f64, "s")                                                                            \
+    RT_KIND4(RT_FULL, RT_REAL_f64, "rf")                                                                           \
+    RT_KIND4(RT_FULL, RT_CROSS_f64, "cf")                                                                          \
+    RT_KIND4(RT_FULL, RT_GEN_f64, "gf")                                                                            \
+    RT_KIND4(RT_FULL, RT_SWAP_f64, "sf")                                                                           \
+    RT_AT("tab") RT_TABLE_f64 RT_END RT_AT("ex") RT_EXCH(RT_GRAY4, RT_GRAY4R, f64) RT_END                          \
+    RT_AT("mul") RT_REGS4(RT_MUL_f64) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
+#define RT_BLOCK_f32                                                                                               \
+    RT_DISPATCH RT_TABLE5("r") RT_TABLE5("c") RT_TABLE5("g") RT_TABLE5("s") RT_TABLE5("rf") RT_TABLE5("cf") RT_TABLE5("gf") RT_TABLE5("sf")\
+    RT_GO("mul") RT_GO("tab") RT_GO("ex")                                                                          \
+    RT_KIND5(RT_PAIR, RT_REAL_f32, "r")                                                                            \
+    RT_KIND5(RT_PAIR, RT_CROSS_f32, "c")                                                                           \
+    RT_KIND5(RT_PAIR, RT_GEN_f32, "g")                                                                             \
+    RT_KIND5(RT_PAIR, RT_SWAP_f32, "s")                                                                            \
+    RT_KIND5(RT_FULL, RT_REAL_f32, "rf")                                                                           \
+    RT_KIND5(RT_FULL, RT_CROSS_f32, "cf")                                                                          \
+    RT_KIND5(RT_FULL, RT_GEN_f32, "gf")                                                                            \
+    RT_KIND5(RT_FULL, RT_SWAP_f32, "sf")                                                                           \
+    RT_AT("tab") RT_TABLE_f32 RT_END RT_AT("ex") RT_EXCH(RT_GRAY5, RT_GRAY5R, f32) RT_END                          \
+    RT_AT("mul") RT_REGS5(RT_MUL_f32) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
+
+#define RT_AMP(i) [x##i] "+v"(v.x[i]), [y##i] "+v"(v.y[i])
+#define RT_AMPS16                                                                                                  \
+    RT_AMP(0), RT_AMP(1), RT_AMP(2), RT_AMP(3), RT_AMP(4), RT_AMP(5), RT_AMP(6), RT_AMP(7), RT_AMP(8), RT_AMP(9),  \
+        RT_AMP(10), RT_AMP(11), RT_AMP(12), RT_AMP(13), RT_AMP(14), RT_AMP(15)
+#define RT_AMPS32                                                                                                  \
+    RT_AMPS16, RT_AMP(16), RT_AMP(17), RT_AMP(18), RT_AMP(19), RT_AMP(20), RT_AMP(21), RT_AMP(22), RT_AMP(23),     \
+        RT_AMP(24), RT_AMP(25), RT_AMP(26), RT_AMP(27), RT_AMP(28), RT_AMP(29), RT_AMP(30), RT_AMP(31)
+
+#define RT_OPERANDS                                                                                                \
+    [ar] "s"(m.ar), [ai] "s"(m.ai), [br] "s"(m.br), [bi] "s"(m.bi), [cr] "s"(m.cr), [ci] "s"(m.ci), [dr] "s"(m.dr), \
+        [di] "s"(m.di), [fr] "v"(fr), [fi] "v"(fi), [pm] "s"(w[1]), [lm] "s"(lanes), [jo] "s"(w[5]),               \
+        [ta] "v"(table), [w0] "s"(w[2]), [w1] "s"(w[3]), [w2] "s"(w[4]), [w3] "s"(w[6]), [d0] "s"(w[8]),           \
+        [d1] "s"(w[9]), [d2] "s"(w[10]), [d3] "s"(w[11])
+#define RT_SCRATCH                                                                                                 \
+    [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [sv] "=&s"(save), [sa] "+v"(slot),             \
+        [na] "+v"(next)
+
+// A lane's amplitudes, components apart.
+template <typename R, int NB> struct RtRegs {
+    R x[1 << NB], y[1 << NB];
+};
+
+constexpr uint32_t kRtEntryFull = 32, kRtEntryMul = 64, kRtEntryTab = 65, kRtEntryExch = 66;
+constexpr uint32_t rt_jump(uint32_t entry) { return 4 * entry + 12; }
+
+// One operation in the lanes of `lanes` (uniform).  w: the operation's first
+// 16 words: w[1] the pairs or registers, w[5] rt_jump(entry); an exchange has
+// the register terms of the old layout in w[2], w[3], w[4], w[6], w[7] and of
+// the new one in w[8] .. w[12].  m: the matrix; fr, fi: the lane's factor
+// (entry kRtEntryMul); table: byte address in LDS (kRtEntryTab); slot, next:
+// the lane's byte address in the exchange buffer in the old and new layout.
+// All lanes of the workgroup call together, with every load of LDS done.
+__device__ __forceinline__ void rt_apply(RtRegs<double, 4> &v, const uint32_t (&w)[16], const Mat2<double> &m,
+                                         double fr, double fi, uint64_t lanes, uint32_t table, uint32_t &slot,
+                                         uint32_t &next) {
+    double t0, t1, t2, t3;
+    uint64_t save;
+    asm volatile(RT_BLOCK_f64 : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+}
+__device__ __forceinline__ void rt_apply(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m, float fr,
+                                         float fi, uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next) {
+    float t0, t1, t2, t3;
+    uint64_t save;
+    asm volatile(RT_BLOCK_f32
+                 : RT_AMPS32, RT_SCRATCH
+                 : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12])
+                 : "scc", "vcc", "memory");
+}
+
+} // namespace sv

@@ -1,0 +1,109 @@
+// Descriptors of the register tile pass (rtile.hpp), shared by the planner,
+// the circuit driver and the kernels.
+#pragma once
+
+#include "tile.hpp"
+
+namespace sv {
+
+constexpr int kRtMaxThreadBits = 9;  // workgroups of up to 512 lanes
+constexpr int kRtMaxThreads = 1 << kRtMaxThreadBits;
+constexpr int kRtMaxNB = 5;
+template <typename R> constexpr int rt_nb() { return sizeof(R) == 8 ? 4 : 5; }
+inline int rt_nb_of(int tile_dt) { return tile_dt == SV_C128 ? 4 : 5; }
+// Tiles of 64 to 512 lanes; narrower ones stay with k_tile.
+inline bool rt_tile_ok(int tile_dt, int m) {
+    const int t = m - rt_nb_of(tile_dt);
+    return t >= 6 && t <= kRtMaxThreadBits;
+}
+
+// Operation kinds (RtOp::w[0] = kind * 8 + a small number).
+constexpr uint32_t kRtReal = 0;    // pair gate, real entries (number: the register bit)
+constexpr uint32_t kRtCross = 1;   // pair gate, real diagonal, imaginary off-diagonal
+constexpr uint32_t kRtGen = 2;     // pair gate, any entries
+constexpr uint32_t kRtSwap = 3;    // X
+constexpr uint32_t kRtDiag = 4;    // registers times entry a of a diagonal gate, or entry d where the lane's
+                                   // or the tile's target bit is 1 (number 1: d everywhere)
+constexpr uint32_t kRtFactor = 5;  // registers times a factor per lane, exp(i sum of phases)
+constexpr uint32_t kRtTable = 6;   // registers times the prepared table's factors
+constexpr uint32_t kRtExch = 7;    // to another layout
+constexpr uint32_t kRtPrep = 8;    // phases of a block of diagonal gates in this tile
+
+struct RtOp {
+    uint32_t w[16];
+    //  w[0] kind and number, w[1] pairs or registers, w[5] rt_jump
+    //  gates: w[2] w[3] condition on the thread index (mask, value), w[4] thread bit of a diagonal
+    //    gate's target, w[6] w[7] and w[8] w[9] condition on the tile's base index (low and high
+    //    words), w[10] w[11] base-index bit of a diagonal gate's target
+    //  kRtFactor: w[12] first and w[13] number of its patterns
+    //  kRtPrep: w[1] patterns, w[2] first pattern, w[3] first and w[4] number of the R patterns
+    //  kRtExch: register terms as rt_apply takes them
+    union {
+        double m[8];    // matrix, complex128 tiles
+        float f[8];     // matrix, complex64 tiles
+        uint32_t t[16]; // exchange: slot terms of the new thread bits (bytes)
+    };
+};
+static_assert(sizeof(RtOp) == 128, "descriptor layout");
+
+// A phase pattern in a layout: the sum of its members' phases (those whose
+// outer predicate holds) is added where (index & cm) == cv, the index being
+// the register number for R patterns and the thread index otherwise.  A
+// pattern with more than kRtPatMembers members is split, so that the lanes
+// share the members of a long one; one preparation holds at most kRtMaxPats.
+constexpr uint32_t kRtPatMembers = 4, kRtMaxPats = 1024;
+struct RtPat {
+    uint32_t cm, cv, first, count;
+};
+
+// Where a layout's amplitudes live in global memory: the qubits of its
+// thread and register bits, and the slot terms (bytes) of its thread bits.
+struct RtIO {
+    uint8_t tq[kRtMaxThreadBits], rq[kRtMaxNB];
+    uint32_t slot[kRtMaxThreadBits];
+};
+
+struct RtPass {
+    RtIO in, out;
+    uint32_t first, count;  // operations
+    uint32_t always;        // every launched tile is touched
+    uint32_t lds;           // bytes of dynamic LDS
+};
+
+// Host-side program of a circuit's fused passes.
+struct RtProgram {
+    std::vector<RtOp> ops;
+    std::vector<RtPat> pats;
+};
+
+// Device copies.
+struct RtDevice {
+    RtOp *ops;
+    RtPat *pats;
+};
+
+// Structure of a gate's matrix, known on the host for every angle.
+struct RtGateInfo {
+    uint8_t kind;     // kRtReal .. kRtDiag
+    uint8_t unit_a;   // diagonal: entry a is exactly 1
+    uint8_t pad[2];
+    int32_t op = -1, op2 = -1;  // out: its operations (matrix slots); -1 inside a phase block
+};
+RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag);
+
+// Schedule one fused run (descriptors tiles[0 .. count), with the marks of
+// mark_diag_sweeps and the patterns of build_sweep_patterns) over the tile
+// map tm and append its operations.  coal: the state's lowest index bits
+// that stay thread bits where tiles are loaded and stored (whole 128-byte
+// lines); block: fixed-point tiles, loaded and stored with tile-local bits 0
+// and 1 in registers and 2..5 on the lowest lane bits instead.
+// fixed_mask: outer index bits every launched tile has with the required
+// values.
+RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *tiles, int count,
+                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, RtProgram &prog);
+
+// One pass over a complex128 or complex64 state.
+int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,
+                   const DeviceGates &gates, hipStream_t st);
+
+} // namespace sv

@@ -1,0 +1,116 @@
+"""Register tile passes (csrc/rtile.hpp) against the oracle at every tile width
+they take: each kind of matrix with its target on register, lane, wavefront
+and outer bits in turn, controls of both values in every position, blocks of
+diagonal gates short and long, angles from the device, and tiles that no gate
+touches.  Tolerances are the library's: 1e-12 (complex128) and 1e-5
+(complex64) of the largest amplitude."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+TOL = {"c128": 1e-12, "c64": 1e-5}
+# tiles of 64, 128, 256 and 512 lanes (16 complex128 or 32 complex64 per lane)
+WIDTHS = [("c128", m) for m in (10, 11, 12, 13)] + [("c64", m) for m in (11, 12, 13, 14)]
+
+
+def _matrix(rng, shape):
+    a, b, c = rng.uniform(0, 2 * np.pi, 3)
+    if shape == "general":
+        return W.haar_unitary_2x2(int(rng.integers(1 << 30)))
+    if shape == "cross":     # real diagonal, imaginary off-diagonal
+        return (np.cos(a), 0.0, 0.0, -np.sin(a), 0.0, -np.sin(a), np.cos(a), 0.0)
+    if shape == "diagonal":  # not of unit modulus
+        return (0.9 * np.cos(a), 0.9 * np.sin(a), 0.0, 0.0, 0.0, 0.0, 1.1 * np.cos(b), 1.1 * np.sin(b))
+    return (np.cos(a), 0.0, -np.sin(a), 0.0, np.sin(a), 0.0, np.cos(a), 0.0)
+
+
+def _random_circuit(n, count, seed, params=0):
+    rng = np.random.default_rng(seed)
+    kinds = ["X", "Y", "Z", "H", "RX", "RY", "RZ", "P", "U", "~RX", "~RZ", "~P", "~U"]
+    gates = []
+    for _ in range(count):
+        kind = kinds[int(rng.integers(len(kinds)))]
+        t = int(rng.integers(n))
+        nc = int(rng.integers(0, 4))
+        ctrls = tuple(int(q) for q in rng.choice([q for q in range(n) if q != t], size=nc, replace=False))
+        vals = tuple(int(v) for v in rng.integers(0, 2, size=nc))
+        mat = _matrix(rng, ("general", "cross", "diagonal", "real")[int(rng.integers(4))]) if kind[-1] == "U" else None
+        p = int(rng.integers(params)) if params and kind in ("RX", "RY", "RZ", "P") and rng.random() < 0.7 else -1
+        gates.append(W.Gate(kind, t, ctrls, vals, float(rng.uniform(0, 6.28)) if p < 0 else 0.0, p, mat))
+    return W.Circuit(n, gates, rng.uniform(0, 6.28, params) if params else None)
+
+
+def _diagonal_circuit(n, count, seed):
+    """Blocks of diagonal gates between two layers of H: up to `count` phases
+    in a row, many sharing a condition."""
+    rng = np.random.default_rng(seed)
+    gates = [W.Gate("H", q) for q in range(n)]
+    for _ in range(count):
+        t = int(rng.integers(n))
+        nc = int(rng.integers(0, 4))
+        ctrls = tuple(int(q) for q in rng.choice([q for q in range(n) if q != t], size=nc, replace=False))
+        gates.append(W.Gate(("P", "RZ", "Z")[int(rng.integers(3))], t, ctrls,
+                            tuple(int(v) for v in rng.integers(0, 2, size=nc)), float(rng.uniform(0, 6.28))))
+    return W.Circuit(n, gates + [W.Gate("H", q) for q in range(n)])
+
+
+def _check(gpu, circ, dtype, params=None, seed=3, slack=0.0):
+    psi0 = W.random_state(circ.n, seed)
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    psi = torch.tensor(psi0, device="cuda").to(tdt)
+    plan = gpu.Circuit(circ.n, circ, dtype=gpu.SV_C128 if dtype == "c128" else gpu.SV_C64, nparams=circ.nparams)
+    for p in ([None] if params is None else params):
+        start = psi.cpu().numpy().astype(np.complex128)
+        plan.run(psi, None if p is None else torch.tensor(p, device="cuda"))
+        ref = oracle.run_circuit(circ, params=p, psi0=start)
+        got = psi.cpu().numpy().astype(np.complex128)
+        assert np.abs(got - ref).max() <= (TOL[dtype] + slack) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype,m", WIDTHS)
+@pytest.mark.parametrize("extra", [0, 2])
+def test_all_kinds(gpu, dtype, m, extra):
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    _check(gpu, _random_circuit(m + extra, 160, 100 * m + extra), dtype)
+
+
+@pytest.mark.parametrize("dtype,m", WIDTHS)
+def test_narrow_low_block_and_angles(gpu, dtype, m):
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    gpu.sv_tune_set("tile_low_bits_" + dtype, 1 + m // 13 * 3)
+    c = _random_circuit(m + 2, 120, 7 * m, params=24)
+    rng = np.random.default_rng(m)
+    _check(gpu, c, dtype, params=[c.params, rng.uniform(0, 6.28, 24)])
+
+
+@pytest.mark.parametrize("dtype,m", [("c128", 10), ("c128", 12), ("c64", 11), ("c64", 14)])
+@pytest.mark.parametrize("count", [5, 60, 3000])
+def test_diagonal_blocks(gpu, dtype, m, count):
+    """A block adds phases: up to `count` additions, each rounding a sum of
+    at most 2 pi count to 53 bits (beside the library's tolerance)."""
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    _check(gpu, _diagonal_circuit(m + 1, count, count + m), dtype, slack=2 * np.pi * count ** 2 * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_untouched_tiles_keep_their_bytes(gpu, dtype):
+    """Every gate needs one of two outer controls: tiles with both clear stay
+    as they are, bit for bit (and the rest follow the oracle)."""
+    n = 15
+    rng = np.random.default_rng(5)
+    gates = [W.Gate("RY", int(rng.integers(0, 8)), (13 if i % 2 else 14,), (1,), float(rng.uniform(0, 6)))
+             for i in range(24)]
+    c = W.Circuit(n, gates)
+    gpu.sv_tune_set("tile_log2_" + dtype, 11)
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    psi = torch.tensor(W.random_state(n, 8), device="cuda").to(tdt)
+    before = psi.clone()
+    gpu.Circuit(n, c, dtype=gpu.SV_C128 if dtype == "c128" else gpu.SV_C64).run(psi)
+    k = 1 << 13
+    assert torch.equal(psi[:k], before[:k])
+    ref = oracle.run_circuit(c, psi0=before.cpu().numpy().astype(np.complex128))
+    assert np.abs(psi.cpu().numpy() - ref).max() <= TOL[dtype] * np.abs(ref).max()
