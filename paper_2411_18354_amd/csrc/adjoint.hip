@@ -254,7 +254,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     const int nslots = (int)(gen.size() / 8);
     a->nslots = nslots;
     const int m_cap = std::max(1, tuning().tile_log2[dtype == SV_C128 ? 0 : 1] - 1);
-    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, false, &a->rc));
+    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, true, true, &a->rc));
     sv_circuit *rc = a->rc;
 
     // per pass: single passes need pair plans, fused ones per-descriptor slots
@@ -323,7 +323,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     // dynamic LDS: the two tiles, then 8 accumulators per parameterised gate
     // of the pass (sized for the largest pass)
     a->pass_lds.assign(rc->passes.size(), 0);
-    size_t lds = 0;
+    size_t lds = 0, lds_rt = 0;
     for (size_t pi = 0; pi < rc->passes.size(); ++pi) {
         const Pass &p = rc->passes[pi];
         if (!p.fused)
@@ -331,12 +331,19 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
         size_t npg = 0;
         for (int j = 0; j < p.count; ++j)
             npg += dslot[p.first + j] >= 0 ? 1 : 0;
+        if (p.rt) {
+            a->pass_lds[pi] = rt_adjoint_lds(dtype, p.tm, p.rp);
+            lds_rt = std::max(lds_rt, a->pass_lds[pi]);
+            continue;
+        }
         a->pass_lds[pi] = ((size_t)2 << rc->m) * amp_bytes(dtype) + npg * (kAdjTileThreads / 64) * sizeof(double);
         lds = std::max(lds, a->pass_lds[pi]);
     }
     constexpr size_t kLdsPerWorkgroup = 160 * 1024;  // gfx950, with the opt-in limit raised
-    if (lds > kLdsPerWorkgroup)
-        return fail(SV_ENOTSUP, "adjoint pass needs %zu bytes of LDS", lds);
+    if (std::max(lds, lds_rt) > kLdsPerWorkgroup)
+        return fail(SV_ENOTSUP, "adjoint pass needs %zu bytes of LDS", std::max(lds, lds_rt));
+    if (lds_rt > 65536)
+        SV_TRY(rt_adjoint_lds_limit(dtype, lds_rt));
     if (lds > 65536) {
         const hipError_t e = dtype == SV_C128 ? hipFuncSetAttribute((const void *)k_adj_tile<double>,
                                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -367,7 +374,12 @@ static int adjoint_enqueue(AdjointPlan *a, const sv_state_t *psi, const sv_state
         const Pass &p = rc->passes[pi];
         if (p.fused) {
             const unsigned grid = (unsigned)std::min<uint64_t>(p.tm.ntiles, kMaxPartials);
-            const DeviceGates dg{rc->d_tiles + p.first, p.count};
+            const DeviceGates dg{rc->d_tiles + p.first, p.count, rc->d_pats, rc->d_mems};
+            if (p.rt) {
+                SV_TRY(launch_rt_adjoint(dtype, psi->data, lam->data, p.tm, p.rp, rc->rt, dg, grid, a->d_partials,
+                                         kMaxPartials, st));
+                continue;
+            }
             if (dtype == SV_C128)
                 hipLaunchKernelGGL(k_adj_tile<double>, dim3(grid), dim3(kAdjTileThreads), a->pass_lds[pi], st,
                                    (double2 *)psi->data, (double2 *)lam->data, p.tm, dg, a->d_dslot + p.first,

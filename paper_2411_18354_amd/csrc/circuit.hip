@@ -235,6 +235,10 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
     const int min_run = std::max(1, tuning().fuse_min_gates);
     std::vector<int> tile_slot(G, -1);
     std::vector<std::pair<int, int>> op_slot(G, {-1, -1});
+    std::vector<int> grad_slot(G, -1);
+    for (int i = 0, k = 0; i < G; ++i)
+        if (c->gates[i].param >= 0)
+            grad_slot[i] = k++;
     std::vector<char> diag(G, 0);
     for (int i = 0; i < G; ++i)
         diag[i] = gate_is_diagonal(c->gates[i], &mats[(size_t)8 * i]);
@@ -458,16 +462,27 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 // Register tiles wherever a tile has 64 to 512 lanes: below
                 // that a wavefront would be partly idle (k_tile stays), and
                 // wider tiles do not exist.
-                if (c->want_rt && rt_tile_ok(tdt, m)) {
+                if (c->want_rt && rt_tile_ok(tdt, m, c->dual)) {
                     std::vector<RtGateInfo> info;
                     for (int k = p.first; k < p.first + p.count; ++k) {
                         const int gi = tiles[k].src_gate;
                         const sv_gate_t &g = c->gates[gi];
                         info.push_back(rt_gate_info(g.kind, g.param >= 0, &mats[(size_t)8 * gi], diag[gi]));
+                        if (c->dual && g.param >= 0) {
+                            const int kd = g.kind & ~SV_G_ADJOINT;
+                            RtGateInfo &r = info.back();
+                            r.grad = kd == SV_G_RY   ? kRtGradRY
+                                     : kd == SV_G_RX ? kRtGradRX
+                                     : kd == SV_G_RZ ? kRtGradRZ
+                                                     : kRtGradP;
+                            // the sweep holds the gates' inverses
+                            r.sign = (g.kind & SV_G_ADJOINT) ? 1 : -1;
+                            r.slot = grad_slot[gi];
+                        }
                     }
                     p.rt = true;
                     p.rp = build_rt_pass(p.tm, fmask, tdt, &tiles[p.first], p.count, info.data(), pats,
-                                         tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->prog);
+                                         tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->dual, c->prog);
                     for (int k = 0; k < p.count; ++k)
                         op_slot[tiles[p.first + k].src_gate] = {info[k].op, info[k].op2};
                 } else {
@@ -545,8 +560,8 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
 }
 
 static void free_buffers(sv_circuit *c, hipStream_t st) {
-    void *bufs[9] = {c->d_mats, c->d_tiles, c->d_jobs, c->d_dense, c->d_rmat, c->d_pats, c->d_mems, c->rt.ops,
-                     c->rt.pats};
+    void *bufs[10] = {c->d_mats, c->d_tiles, c->d_jobs, c->d_dense, c->d_rmat, c->d_pats, c->d_mems, c->rt.ops,
+                     c->rt.pats, c->rt.acc};
     for (void *b : bufs)
         if (b) {
             if (c->async_buffers)
@@ -561,7 +576,7 @@ static void free_buffers(sv_circuit *c, hipStream_t st) {
     c->d_rmat = nullptr;
     c->d_pats = nullptr;
     c->d_mems = nullptr;
-    c->rt = RtDevice{nullptr, nullptr};
+    c->rt = RtDevice{nullptr, nullptr, nullptr};
 }
 
 template <typename T> static int upload(T **dst, const std::vector<T> &src, bool async, hipStream_t st) {
@@ -605,7 +620,7 @@ static int launch_tile_pass(cplx_t<R> *psi, const TileMap &tm_in, const DeviceGa
 }
 
 int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int flags, bool async,
-                   hipStream_t st, int m_cap, bool rt, sv_circuit **out) {
+                   hipStream_t st, int m_cap, bool rt, bool dual, sv_circuit **out) {
     *out = nullptr;
     if (!known_dtype(dtype))
         return fail(SV_EINVAL, "unknown dtype %d", dtype);
@@ -630,6 +645,7 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
     c->async_buffers = async;
     c->m_cap = m_cap;
     c->want_rt = rt;
+    c->dual = dual;
     // a one-shot plan (stream-ordered buffers, run once) keeps planning cheap:
     // the two-step lookahead pays for itself only over repeated runs
     c->max_lookahead = async ? 1 : 2;
@@ -654,6 +670,8 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
         r = upload(&c->rt.ops, c->prog.ops, async, st);
     if (r == SV_OK)
         r = upload(&c->rt.pats, c->prog.pats, async, st);
+    if (r == SV_OK)
+        r = upload(&c->rt.acc, c->prog.acc, async, st);
     if (r == SV_OK)
         r = upload(&c->d_tiles, tiles, async, st);
     if (r == SV_OK)
@@ -949,7 +967,8 @@ int sv_circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int 
     clear_error();
     if (!out)
         return fail(SV_EINVAL, "out is NULL");
-    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, !is_fixed(dtype), out);
+    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, !is_fixed(dtype), false,
+                          out);
 }
 
 int sv_circuit_run(sv_circuit_t *c, const sv_state_t *s, const double *params_dev, sv_stream_t st) {
@@ -1007,7 +1026,7 @@ int sv_apply_circuit(const sv_state_t *s, const sv_gate_t *gates, int ngates, co
     SV_TRY(validate_state(s, true));
     sv_circuit *c = nullptr;
     SV_TRY(circuit_create(s->n, s->dtype, gates, ngates, nparams, flags & ~SV_GRAPH, true, (hipStream_t)st, 64, !is_fixed(s->dtype),
-                          &c));
+                          false, &c));
     int r = check_run_args(c, s, params_dev);
     if (r == SV_OK)
         r = enqueue_any(c, s, params_dev, (hipStream_t)st);

@@ -44,8 +44,9 @@ struct sv_circuit {
     int m_cap = 64;  // upper bound on the tile width (callers with a fixed LDS budget)
     int max_lookahead = 2;  // cap on the planner's lookahead depth (one-shot plans and batches: 1)
     bool want_rt = false;  // plan fused runs for register tiles where their width allows
+    bool dual = false;     // a reverse sweep: tiles of psi and lambda together
     sv::RtProgram prog;             // their operations
-    sv::RtDevice rt{nullptr, nullptr};
+    sv::RtDevice rt{nullptr, nullptr, nullptr};
     std::vector<sv_gate_t> gates;   // after the SV_REMAP relabelling, if any
     std::vector<int32_t> remap;      // SV_REMAP: qubit swaps a0 b0 a1 b1 ... (empty: none)
     std::vector<sv::Pass> passes;
@@ -91,9 +92,11 @@ int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int
                        std::vector<SweepPat> *pats = nullptr, std::vector<SweepMember> *mems = nullptr);
 
 // rt: fused runs on register tiles where their width allows (the caller runs
-// Pass::rt passes with launch_rt_pass).
+// Pass::rt passes with launch_rt_pass).  dual: a reverse sweep; the gradient
+// slot of a parameterised gate is its rank among them (passes run with
+// launch_rt_adjoint).
 int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int flags, bool async,
-                   hipStream_t st, int m_cap, bool rt, sv_circuit **out);
+                   hipStream_t st, int m_cap, bool rt, bool dual, sv_circuit **out);
 // Release device buffers (stream-ordered on st for async plans) and the plan.
 void circuit_free(sv_circuit *c, hipStream_t st);
 // Compute the matrices of parameterised gates from params (device) into the

@@ -184,11 +184,14 @@ __device__ __forceinline__ uint32_t rt_xor_terms(uint32_t tid, const uint32_t *t
 }
 
 // A run's operations on the tile in registers.  slot: the lane's byte offset
-// in the exchange buffer in the current layout.
-template <typename R, int NB>
+// in the exchange buffer in the current layout.  GRAD: the reverse sweep; accl
+// holds one accumulator per parameterised gate and wavefront (accl[k * nw +
+// wavefront]).
+template <typename R, int NB, bool GRAD = false>
 __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uint32_t slot, uint64_t base,
                                        const RtOp *__restrict__ ops, uint32_t count,
-                                       const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems) {
+                                       const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems,
+                                       double *accl = nullptr) {
     const uint32_t tid = threadIdx.x;
     // LDS byte address of the buffer
     const uint32_t buf = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
@@ -204,7 +207,9 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
         R fr = (R)0, fi = (R)0;
         uint64_t lanes = ~0ull;
         uint32_t next = slot;
-        if (kind <= kRtDiag) {
+        // every path meets at rt_apply (lanes 0: nothing to do): paths of
+        // their own around it would split the amplitudes' live ranges
+        if (kind <= kRtDiag || (GRAD && kind == kRtGrad)) {
             const uint64_t om = (uint64_t)w[7] << 32 | w[6], ov = (uint64_t)w[9] << 32 | w[8];
             const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
             lanes = (base & om) == ov ? __ballot((tid & w[2]) == w[3]) : 0ull;
@@ -220,7 +225,19 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
             lanes = 0;
         }
         uint32_t sa = buf + slot, na = buf + next;
-        rt_apply(v, w, m, fr, fi, lanes, buf, sa, na);
+        if constexpr (GRAD) {
+            double g[4] = {0.0, 0.0, 0.0, 0.0};
+            rt_apply_grad(v, w, m, fr, fi, lanes, buf, sa, na, g);
+            if (kind == kRtGrad && lanes) {  // uniform in the wavefront
+                const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
+                const bool one = (tid & w[4]) != 0 || (base & ob) != 0;
+                const double s = wave_sum((one ? o.m[1] : o.m[0]) * ((g[0] + g[1]) - (g[2] + g[3])));
+                if ((tid & 63u) == 0)
+                    accl[w[13] * (blockDim.x >> 6) + (tid >> 6)] += s;
+            }
+        } else {
+            rt_apply(v, w, m, fr, fi, lanes, buf, sa, na);
+        }
         slot = next;
     }
 }

@@ -82,6 +82,26 @@ namespace sv {
     "v_fma_" SZ " " RT_N(x, i) ", %[t2], " RT_N(x, i) ", -%[t0]\n"                                                 \
     "v_fma_" SZ " " RT_N(y, i) ", %[t2], " RT_N(y, i) ", %[t1]\n"
 
+// Gradient terms of a reverse sweep, where registers i, j are psi and I, J the
+// same amplitudes of lambda: sums over pairs (or registers) into a0 .. a3, in
+// double precision for either type; the term is (a0 + a1) - (a2 + a3).
+#define RT_DOT_f64(a, p, q) "v_fma_f64 %[" #a "], " p ", " q ", %[" #a "]\n"
+#define RT_DOT_f32(a, p, q)                                                                                        \
+    "v_cvt_f64_f32 %[e0], " p "\n"                                                                                 \
+    "v_cvt_f64_f32 %[e1], " q "\n"                                                                                 \
+    "v_fma_f64 %[" #a "], %[e0], %[e1], %[" #a "]\n"
+// Re(conj(lambda_1) psi_0) - Re(conj(lambda_0) psi_1)
+#define RT_STEP_GY(D, i, j, I, J)                                                                                  \
+    D(a0, RT_N(x, J), RT_N(x, i)) D(a1, RT_N(y, J), RT_N(y, i)) D(a2, RT_N(x, I), RT_N(x, j))                      \
+    D(a3, RT_N(y, I), RT_N(y, j))
+// Im(conj(lambda_0) psi_1) + Im(conj(lambda_1) psi_0)
+#define RT_STEP_GX(D, i, j, I, J)                                                                                  \
+    D(a0, RT_N(x, I), RT_N(y, j)) D(a1, RT_N(x, J), RT_N(y, i)) D(a2, RT_N(y, I), RT_N(x, j))                      \
+    D(a3, RT_N(y, J), RT_N(x, i))
+// Im(conj(lambda) psi), added for the registers of pm, subtracted for pm2
+#define RT_STEP_GD(D, i, I) D(a0, RT_N(x, I), RT_N(y, i)) D(a2, RT_N(y, I), RT_N(x, i))
+#define RT_STEP_GE(D, i, I) D(a3, RT_N(x, I), RT_N(y, i)) D(a1, RT_N(y, I), RT_N(x, i))
+
 #define RT_REAL_f64(i, j) RT_STEP_REAL("f64", i, j)
 #define RT_REAL_f32(i, j) RT_STEP_REAL("f32", i, j)
 #define RT_CROSS_f64(i, j) RT_STEP_CROSS("f64", i, j)
@@ -147,6 +167,49 @@ namespace sv {
     RT_REG(F, 16) RT_REG(F, 17) RT_REG(F, 18) RT_REG(F, 19) RT_REG(F, 20) RT_REG(F, 21) RT_REG(F, 22)              \
     RT_REG(F, 23) RT_REG(F, 24) RT_REG(F, 25) RT_REG(F, 26) RT_REG(F, 27) RT_REG(F, 28) RT_REG(F, 29)              \
     RT_REG(F, 30) RT_REG(F, 31)
+
+#define RT_QUAD(S, D, V, p, i, j, I, J)                                                                            \
+    "s_bitcmp1_b32 %[pm], " #p "\n"                                                                                \
+    "s_cbranch_scc0 .Lrt_" V "_" #p "_%=\n" S(D, i, j, I, J) ".Lrt_" V "_" #p "_%=:\n"
+#define RT_BOTH(D, i, I)                                                                                           \
+    "s_bitcmp1_b32 %[pm], " #i "\n"                                                                                \
+    "s_cbranch_scc0 .Lrt_gd_" #i "_%=\n" RT_STEP_GD(D, i, I) ".Lrt_gd_" #i "_%=:\n"                                \
+    "s_bitcmp1_b32 %[pm2], " #i "\n"                                                                               \
+    "s_cbranch_scc0 .Lrt_ge_" #i "_%=\n" RT_STEP_GE(D, i, I) ".Lrt_ge_" #i "_%=:\n"
+// the pairs of register bit T among 8 registers of each state
+#define RT_QUADS4_0(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 1, 8, 9) RT_QUAD(S, D, V, 1, 2, 3, 10, 11) RT_QUAD(S, D, V, 2, 4, 5, 12, 13)            \
+    RT_QUAD(S, D, V, 3, 6, 7, 14, 15)
+#define RT_QUADS4_1(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 2, 8, 10) RT_QUAD(S, D, V, 1, 1, 3, 9, 11) RT_QUAD(S, D, V, 2, 4, 6, 12, 14)            \
+    RT_QUAD(S, D, V, 3, 5, 7, 13, 15)
+#define RT_QUADS4_2(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 4, 8, 12) RT_QUAD(S, D, V, 1, 1, 5, 9, 13) RT_QUAD(S, D, V, 2, 2, 6, 10, 14)            \
+    RT_QUAD(S, D, V, 3, 3, 7, 11, 15)
+#define RT_BOTHS4(D)                                                                                               \
+    RT_BOTH(D, 0, 8) RT_BOTH(D, 1, 9) RT_BOTH(D, 2, 10) RT_BOTH(D, 3, 11) RT_BOTH(D, 4, 12) RT_BOTH(D, 5, 13)      \
+    RT_BOTH(D, 6, 14) RT_BOTH(D, 7, 15)
+// and among 16
+#define RT_QUADS5_0(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 1, 16, 17) RT_QUAD(S, D, V, 1, 2, 3, 18, 19) RT_QUAD(S, D, V, 2, 4, 5, 20, 21)          \
+    RT_QUAD(S, D, V, 3, 6, 7, 22, 23) RT_QUAD(S, D, V, 4, 8, 9, 24, 25) RT_QUAD(S, D, V, 5, 10, 11, 26, 27)        \
+    RT_QUAD(S, D, V, 6, 12, 13, 28, 29) RT_QUAD(S, D, V, 7, 14, 15, 30, 31)
+#define RT_QUADS5_1(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 2, 16, 18) RT_QUAD(S, D, V, 1, 1, 3, 17, 19) RT_QUAD(S, D, V, 2, 4, 6, 20, 22)          \
+    RT_QUAD(S, D, V, 3, 5, 7, 21, 23) RT_QUAD(S, D, V, 4, 8, 10, 24, 26) RT_QUAD(S, D, V, 5, 9, 11, 25, 27)        \
+    RT_QUAD(S, D, V, 6, 12, 14, 28, 30) RT_QUAD(S, D, V, 7, 13, 15, 29, 31)
+#define RT_QUADS5_2(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 4, 16, 20) RT_QUAD(S, D, V, 1, 1, 5, 17, 21) RT_QUAD(S, D, V, 2, 2, 6, 18, 22)          \
+    RT_QUAD(S, D, V, 3, 3, 7, 19, 23) RT_QUAD(S, D, V, 4, 8, 12, 24, 28) RT_QUAD(S, D, V, 5, 9, 13, 25, 29)        \
+    RT_QUAD(S, D, V, 6, 10, 14, 26, 30) RT_QUAD(S, D, V, 7, 11, 15, 27, 31)
+#define RT_QUADS5_3(S, D, V)                                                                                       \
+    RT_QUAD(S, D, V, 0, 0, 8, 16, 24) RT_QUAD(S, D, V, 1, 1, 9, 17, 25) RT_QUAD(S, D, V, 2, 2, 10, 18, 26)         \
+    RT_QUAD(S, D, V, 3, 3, 11, 19, 27) RT_QUAD(S, D, V, 4, 4, 12, 20, 28) RT_QUAD(S, D, V, 5, 5, 13, 21, 29)       \
+    RT_QUAD(S, D, V, 6, 6, 14, 22, 30) RT_QUAD(S, D, V, 7, 7, 15, 23, 31)
+#define RT_BOTHS5(D)                                                                                               \
+    RT_BOTH(D, 0, 16) RT_BOTH(D, 1, 17) RT_BOTH(D, 2, 18) RT_BOTH(D, 3, 19) RT_BOTH(D, 4, 20) RT_BOTH(D, 5, 21)    \
+    RT_BOTH(D, 6, 22) RT_BOTH(D, 7, 23) RT_BOTH(D, 8, 24) RT_BOTH(D, 9, 25) RT_BOTH(D, 10, 26)                     \
+    RT_BOTH(D, 11, 27) RT_BOTH(D, 12, 28) RT_BOTH(D, 13, 29) RT_BOTH(D, 14, 30) RT_BOTH(D, 15, 31)
 
 // The registers in Gray-code order, S a step and F(b) the flip of register bit
 // b between two; R: the same order backwards.
@@ -226,9 +289,10 @@ namespace sv {
     RT_AT(K "4") RT_PAIRS5_4(P, OP, K "4") RT_END
 // every variant: entry kind * 8 + register bit of the pair kinds, again with
 // every pair from kRtEntryFull on, then the rest
-#define RT_BLOCK_f64                                                                                               \
+#define RT_HEAD_f64                                                                                                \
     RT_DISPATCH RT_TABLE4("r") RT_TABLE4("c") RT_TABLE4("g") RT_TABLE4("s") RT_TABLE4("rf") RT_TABLE4("cf") RT_TABLE4("gf") RT_TABLE4("sf")\
-    RT_GO("mul") RT_GO("tab") RT_GO("ex")                                                                          \
+    RT_GO("mul") RT_GO("tab") RT_GO("ex")
+#define RT_BODY_f64                                                                                                \
     RT_KIND4(RT_PAIR, RT_REAL_f64, "r")                                                                            \
     RT_KIND4(RT_PAIR, RT_CROSS_f64, "c")                                                                           \
     RT_KIND4(RT_PAIR, RT_GEN_f64, "g")                                                                             \
@@ -237,11 +301,27 @@ namespace sv {
     RT_KIND4(RT_FULL, RT_CROSS_f64, "cf")                                                                          \
     RT_KIND4(RT_FULL, RT_GEN_f64, "gf")                                                                            \
     RT_KIND4(RT_FULL, RT_SWAP_f64, "sf")                                                                           \
-    RT_AT("tab") RT_TABLE_f64 RT_END RT_AT("ex") RT_EXCH(RT_GRAY4, RT_GRAY4R, f64) RT_END                          \
+    RT_AT("tab") RT_TABLE_f64 RT_END RT_AT("ex") RT_EXCH(RT_GRAY4, RT_GRAY4R, f64) RT_END
+#define RT_TAIL_f64                                                                                                \
     RT_AT("mul") RT_REGS4(RT_MUL_f64) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
-#define RT_BLOCK_f32                                                                                               \
+#define RT_BLOCK_f64 RT_HEAD_f64 RT_BODY_f64 RT_TAIL_f64
+// the same with the gradient terms
+#define RT_BLOCK_GRAD_f64                                                                                          \
+    RT_HEAD_f64 RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                        \
+    RT_GO("gy0") RT_GO("gy1") RT_GO("gy2") RT_NONE RT_NONE RT_NONE RT_NONE RT_NONE                                 \
+    RT_GO("gx0") RT_GO("gx1") RT_GO("gx2") RT_NONE RT_NONE RT_NONE RT_NONE RT_NONE                                 \
+    RT_BODY_f64                                                                                                    \
+    RT_AT("gy0") RT_QUADS4_0(RT_STEP_GY, RT_DOT_f64, "gy0") RT_END                                                 \
+    RT_AT("gy1") RT_QUADS4_1(RT_STEP_GY, RT_DOT_f64, "gy1") RT_END                                                 \
+    RT_AT("gy2") RT_QUADS4_2(RT_STEP_GY, RT_DOT_f64, "gy2") RT_END                                                 \
+    RT_AT("gx0") RT_QUADS4_0(RT_STEP_GX, RT_DOT_f64, "gx0") RT_END                                                 \
+    RT_AT("gx1") RT_QUADS4_1(RT_STEP_GX, RT_DOT_f64, "gx1") RT_END                                                 \
+    RT_AT("gx2") RT_QUADS4_2(RT_STEP_GX, RT_DOT_f64, "gx2") RT_END                                                 \
+    RT_AT("gd") RT_BOTHS4(RT_DOT_f64) RT_END RT_TAIL_f64
+#define RT_HEAD_f32                                                                                                \
     RT_DISPATCH RT_TABLE5("r") RT_TABLE5("c") RT_TABLE5("g") RT_TABLE5("s") RT_TABLE5("rf") RT_TABLE5("cf") RT_TABLE5("gf") RT_TABLE5("sf")\
-    RT_GO("mul") RT_GO("tab") RT_GO("ex")                                                                          \
+    RT_GO("mul") RT_GO("tab") RT_GO("ex")
+#define RT_BODY_f32                                                                                                \
     RT_KIND5(RT_PAIR, RT_REAL_f32, "r")                                                                            \
     RT_KIND5(RT_PAIR, RT_CROSS_f32, "c")                                                                           \
     RT_KIND5(RT_PAIR, RT_GEN_f32, "g")                                                                             \
@@ -250,8 +330,25 @@ namespace sv {
     RT_KIND5(RT_FULL, RT_CROSS_f32, "cf")                                                                          \
     RT_KIND5(RT_FULL, RT_GEN_f32, "gf")                                                                            \
     RT_KIND5(RT_FULL, RT_SWAP_f32, "sf")                                                                           \
-    RT_AT("tab") RT_TABLE_f32 RT_END RT_AT("ex") RT_EXCH(RT_GRAY5, RT_GRAY5R, f32) RT_END                          \
+    RT_AT("tab") RT_TABLE_f32 RT_END RT_AT("ex") RT_EXCH(RT_GRAY5, RT_GRAY5R, f32) RT_END
+#define RT_TAIL_f32                                                                                                \
     RT_AT("mul") RT_REGS5(RT_MUL_f32) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
+#define RT_BLOCK_f32 RT_HEAD_f32 RT_BODY_f32 RT_TAIL_f32
+// the same with the gradient terms
+#define RT_BLOCK_GRAD_f32                                                                                          \
+    RT_HEAD_f32 RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                        \
+    RT_GO("gy0") RT_GO("gy1") RT_GO("gy2") RT_GO("gy3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
+    RT_GO("gx0") RT_GO("gx1") RT_GO("gx2") RT_GO("gx3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
+    RT_BODY_f32                                                                                                    \
+    RT_AT("gy0") RT_QUADS5_0(RT_STEP_GY, RT_DOT_f32, "gy0") RT_END                                                 \
+    RT_AT("gy1") RT_QUADS5_1(RT_STEP_GY, RT_DOT_f32, "gy1") RT_END                                                 \
+    RT_AT("gy2") RT_QUADS5_2(RT_STEP_GY, RT_DOT_f32, "gy2") RT_END                                                 \
+    RT_AT("gy3") RT_QUADS5_3(RT_STEP_GY, RT_DOT_f32, "gy3") RT_END                                                 \
+    RT_AT("gx0") RT_QUADS5_0(RT_STEP_GX, RT_DOT_f32, "gx0") RT_END                                                 \
+    RT_AT("gx1") RT_QUADS5_1(RT_STEP_GX, RT_DOT_f32, "gx1") RT_END                                                 \
+    RT_AT("gx2") RT_QUADS5_2(RT_STEP_GX, RT_DOT_f32, "gx2") RT_END                                                 \
+    RT_AT("gx3") RT_QUADS5_3(RT_STEP_GX, RT_DOT_f32, "gx3") RT_END                                                 \
+    RT_AT("gd") RT_BOTHS5(RT_DOT_f32) RT_END RT_TAIL_f32
 
 #define RT_AMP(i) [x##i] "+v"(v.x[i]), [y##i] "+v"(v.y[i])
 #define RT_AMPS16                                                                                                  \
@@ -275,7 +372,8 @@ template <typename R, int NB> struct RtRegs {
     R x[1 << NB], y[1 << NB];
 };
 
-constexpr uint32_t kRtEntryFull = 32, kRtEntryMul = 64, kRtEntryTab = 65, kRtEntryExch = 66;
+constexpr uint32_t kRtEntryFull = 32, kRtEntryMul = 64, kRtEntryTab = 65, kRtEntryExch = 66,
+                   kRtEntryGradD = 67, kRtEntryGradY = 72, kRtEntryGradX = 80;
 constexpr uint32_t rt_jump(uint32_t entry) { return 4 * entry + 12; }
 
 // One operation in the lanes of `lanes` (uniform).  w: the operation's first
@@ -299,6 +397,34 @@ __device__ __forceinline__ void rt_apply(RtRegs<float, 5> &v, const uint32_t (&w
     asm volatile(RT_BLOCK_f32
                  : RT_AMPS32, RT_SCRATCH
                  : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12])
+                 : "scc", "vcc", "memory");
+}
+
+// The same on a lane's amplitudes of psi (registers with the top bit 0) and
+// lambda (1), with the gradient entries: g accumulates a0 .. a3.  w[12]: the
+// registers kRtEntryGradD subtracts.
+#define RT_GRAD_OUT [a0] "+v"(g[0]), [a1] "+v"(g[1]), [a2] "+v"(g[2]), [a3] "+v"(g[3])
+__device__ __forceinline__ void rt_apply_grad(RtRegs<double, 4> &v, const uint32_t (&w)[16], const Mat2<double> &m,
+                                              double fr, double fi, uint64_t lanes, uint32_t table, uint32_t &slot,
+                                              uint32_t &next, double (&g)[4]) {
+    double t0, t1, t2, t3;
+    uint64_t save;
+    asm volatile(RT_BLOCK_GRAD_f64
+                 : RT_AMPS16, RT_SCRATCH, RT_GRAD_OUT
+                 : RT_OPERANDS, [pm2] "s"(w[12])
+                 : "scc", "vcc", "memory");
+}
+__device__ __forceinline__ void rt_apply_grad(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m,
+                                              float fr, float fi, uint64_t lanes, uint32_t table, uint32_t &slot,
+                                              uint32_t &next, double (&g)[4]) {
+    float t0, t1, t2, t3;
+    double e0, e1;
+    uint64_t save;
+    // an exchange's fifth new register term and a gradient's second mask
+    // share w[12]
+    asm volatile(RT_BLOCK_GRAD_f32
+                 : RT_AMPS32, RT_SCRATCH, RT_GRAD_OUT, [e0] "=&v"(e0), [e1] "=&v"(e1)
+                 : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12]), [pm2] "s"(w[12])
                  : "scc", "vcc", "memory");
 }
 

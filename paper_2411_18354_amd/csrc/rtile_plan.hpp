@@ -11,9 +11,11 @@ constexpr int kRtMaxThreads = 1 << kRtMaxThreadBits;
 constexpr int kRtMaxNB = 5;
 template <typename R> constexpr int rt_nb() { return sizeof(R) == 8 ? 4 : 5; }
 inline int rt_nb_of(int tile_dt) { return tile_dt == SV_C128 ? 4 : 5; }
-// Tiles of 64 to 512 lanes; narrower ones stay with k_tile.
-inline bool rt_tile_ok(int tile_dt, int m) {
-    const int t = m - rt_nb_of(tile_dt);
+// Tiles of 64 to 512 lanes; narrower ones stay with the LDS tiles.  dual: the
+// reverse sweep, whose lanes hold psi and lambda together (the top register
+// bit tells them apart, so a layout has one register bit less).
+inline bool rt_tile_ok(int tile_dt, int m, bool dual) {
+    const int t = m - rt_nb_of(tile_dt) + (dual ? 1 : 0);
     return t >= 6 && t <= kRtMaxThreadBits;
 }
 
@@ -28,6 +30,7 @@ constexpr uint32_t kRtFactor = 5;  // registers times a factor per lane, exp(i s
 constexpr uint32_t kRtTable = 6;   // registers times the prepared table's factors
 constexpr uint32_t kRtExch = 7;    // to another layout
 constexpr uint32_t kRtPrep = 8;    // phases of a block of diagonal gates in this tile
+constexpr uint32_t kRtGrad = 9;    // gradient term of a parameterised gate (reverse sweep)
 
 struct RtOp {
     uint32_t w[16];
@@ -38,6 +41,9 @@ struct RtOp {
     //  kRtFactor: w[12] first and w[13] number of its patterns
     //  kRtPrep: w[1] patterns, w[2] first pattern, w[3] first and w[4] number of the R patterns
     //  kRtExch: register terms as rt_apply takes them
+    //  kRtGrad: as a gate; w[12] the registers subtracted (diagonal gates), w[13] its accumulator;
+    //    m[0] the term's factor, or m[1] where the lane's or the tile's target bit is 1 (both
+    //    precisions: double)
     union {
         double m[8];    // matrix, complex128 tiles
         float f[8];     // matrix, complex64 tiles
@@ -67,26 +73,35 @@ struct RtPass {
     RtIO in, out;
     uint32_t first, count;  // operations
     uint32_t always;        // every launched tile is touched
-    uint32_t lds;           // bytes of dynamic LDS
+    uint32_t lds;           // bytes of dynamic LDS (dual: accumulators not included)
+    uint32_t acc_first, acc_count;  // dual: gradient accumulators (RtProgram::acc)
 };
 
 // Host-side program of a circuit's fused passes.
 struct RtProgram {
     std::vector<RtOp> ops;
     std::vector<RtPat> pats;
+    std::vector<int32_t> acc;  // gradient slot of every accumulator
 };
 
 // Device copies.
 struct RtDevice {
     RtOp *ops;
     RtPat *pats;
+    int32_t *acc;
 };
+
+// Gradient terms 2 Re <lambda|A|psi> by generator A: -i/2 Y, -i/2 X, -i/2 Z and
+// diag(0, i).
+constexpr uint8_t kRtNoGrad = 0, kRtGradRY = 1, kRtGradRX = 2, kRtGradRZ = 3, kRtGradP = 4;
 
 // Structure of a gate's matrix, known on the host for every angle.
 struct RtGateInfo {
     uint8_t kind;     // kRtReal .. kRtDiag
     uint8_t unit_a;   // diagonal: entry a is exactly 1
-    uint8_t pad[2];
+    uint8_t grad;     // gradient term to take: kRtNoGrad ..
+    int8_t sign;      // its sign (-1: the gate was given with the adjoint flag)
+    int32_t slot;     // its gradient slot
     int32_t op = -1, op2 = -1;  // out: its operations (matrix slots); -1 inside a phase block
 };
 RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag);
@@ -97,13 +112,24 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag)
 // that stay thread bits where tiles are loaded and stored (whole 128-byte
 // lines); block: fixed-point tiles, loaded and stored with tile-local bits 0
 // and 1 in registers and 2..5 on the lowest lane bits instead.
+// dual: the reverse sweep's passes.
 // fixed_mask: outer index bits every launched tile has with the required
 // values.
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *tiles, int count,
-                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, RtProgram &prog);
+                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, bool dual,
+                     RtProgram &prog);
 
 // One pass over a complex128 or complex64 state.
 int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,
                    const DeviceGates &gates, hipStream_t st);
+
+// One pass of the reverse sweep over psi and lambda (dual program): partials
+// [slot * stride + workgroup] receive every accumulator's sum per workgroup of
+// the grid.
+int launch_rt_adjoint(int dtype, void *psi, void *lam, const TileMap &tm, const RtPass &p, const RtDevice &d,
+                      const DeviceGates &gates, unsigned grid, double *partials, int stride, hipStream_t st);
+// Dynamic LDS of such a pass, and the per-kernel limit raised to lds bytes.
+size_t rt_adjoint_lds(int dtype, const TileMap &tm, const RtPass &p);
+int rt_adjoint_lds_limit(int dtype, size_t lds);
 
 } // namespace sv

@@ -114,3 +114,42 @@ def test_untouched_tiles_keep_their_bytes(gpu, dtype):
     assert torch.equal(psi[:k], before[:k])
     ref = oracle.run_circuit(c, psi0=before.cpu().numpy().astype(np.complex128))
     assert np.abs(psi.cpu().numpy() - ref).max() <= TOL[dtype] * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype,m", WIDTHS)
+@pytest.mark.parametrize("diagonals", [False, True])
+def test_reverse_sweep(gpu, dtype, m, diagonals):
+    """Gradients of every parameterised kind (and their adjoints) under 0-2
+    controls of either value, blocks of diagonal gates among them, against the
+    oracle's shift rules at 1e-8 (complex128).  complex64 states: every
+    amplitude error of the library's 1e-5 enters a term 2 Re <lambda|A|psi>,
+    |lambda| <= sum|coef|, once from each state and for each of a parameter's
+    gates."""
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    n, P = m + 1 if m < 13 else m, 10
+    rng = np.random.default_rng(50 * m + diagonals)
+    kinds = ("RZ", "P", "~RZ", "~P", "RZ", "Z") if diagonals else ("RX", "RY", "RZ", "P", "~RX", "~RY", "H", "X", "U")
+    gates = [W.Gate("RY", q, theta=float(rng.uniform(0, 6))) for q in range(n)]
+    for i in range(40):
+        kind = "H" if diagonals and i % 14 == 13 else kinds[i % len(kinds)]
+        t = int(rng.integers(n))
+        nc = int(rng.integers(0, 3))
+        ctrls = tuple(int(q) for q in rng.choice([q for q in range(n) if q != t], size=nc, replace=False))
+        p = int(rng.integers(P)) if kind[-1] in "XYZP" and len(kind.strip("~")) == (1 if kind[-1] == "P" else 2) else -1
+        gates.append(W.Gate(kind, t, ctrls, tuple(int(v) for v in rng.integers(0, 2, size=nc)),
+                            float(rng.uniform(0, 6)), p, _matrix(rng, "general") if kind == "U" else None))
+    c = W.Circuit(n, gates, rng.uniform(0, 6.28, P))
+    terms = W.zz_x_hamiltonian(n, 3)
+    ref = oracle.grad_param_shift(c, c.params, terms)
+    code, tdt = (gpu.SV_C128, torch.complex128) if dtype == "c128" else (gpu.SV_C64, torch.complex64)
+    params = torch.tensor(c.params, device="cuda")
+    psi = torch.zeros(1 << n, dtype=tdt, device="cuda")
+    psi[0] = 1
+    gpu.Circuit(n, c, dtype=code, nparams=P).run(psi, params)
+    grad, _ = gpu.AdjointPlan(n, c, terms, P, dtype=code).run(psi, torch.empty_like(psi), params)
+    l1 = sum(abs(t.coef) for t in terms)
+    uses = max(sum(g.param == j for g in gates) for j in range(P))
+    tol = 1e-8 * max(1.0, np.abs(ref).max()) if dtype == "c128" else 2e-5 * l1 * uses
+    assert np.abs(grad.cpu().numpy() - ref).max() <= tol
+    psi[0] -= 1  # the sweep un-applies every gate
+    assert psi.abs().max().item() <= TOL[dtype]
