@@ -460,9 +460,23 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 mark_diag_sweeps(&tiles[p.first], p.count, from_param.data(), phase_min);
                 build_sweep_patterns(&tiles[p.first], p.count, (int)p.tm.m, from_param.data(), pats, mems);
                 // Register tiles wherever a tile has 64 to 512 lanes: below
-                // that a wavefront would be partly idle (k_tile stays), and
-                // wider tiles do not exist.
-                if (c->want_rt && rt_tile_ok(tdt, m, c->dual)) {
+                // that a wavefront would be partly idle (the LDS tiles stay),
+                // and wider tiles do not exist.  A run that is one permutation
+                // is a single gather through an LDS tile; register tiles pay
+                // for each of its gates and lose on complex128 (streaming
+                // circuit, n = 12: 12.4 against 10.8 us, n = 26: 447 against
+                // 431 us; n = 16 to 22 even or faster) and where complex64
+                // has a few tiles only (n = 13: 15.2 against 13.4 us, n = 14:
+                // 17.8 against 15.5; n = 16: 21.2 against 21.9, n = 26: 232
+                // against 255).
+                bool gather = tuning().fuse_perm && !c->dual && !is_fixed(c->dtype) &&
+                              (tdt == SV_C128 || p.tm.ntiles <= 4) &&
+                              (1u << m) <= 512u * (tdt == SV_C128 ? perm_per_lane<double>() : perm_per_lane<float>());
+                if (gather) {
+                    mark_permutation_runs(&tiles[p.first], p.count);
+                    gather = (int)tiles[p.first].perm_len == p.count;
+                }
+                if (c->want_rt && !gather && rt_tile_ok(tdt, m, c->dual)) {
                     std::vector<RtGateInfo> info;
                     for (int k = p.first; k < p.first + p.count; ++k) {
                         const int gi = tiles[k].src_gate;
@@ -560,15 +574,13 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
 }
 
 static void free_buffers(sv_circuit *c, hipStream_t st) {
-    void *bufs[10] = {c->d_mats, c->d_tiles, c->d_jobs, c->d_dense, c->d_rmat, c->d_pats, c->d_mems, c->rt.ops,
-                     c->rt.pats, c->rt.acc};
-    for (void *b : bufs)
-        if (b) {
-            if (c->async_buffers)
-                (void)hipFreeAsync(b, st);
-            else
-                (void)hipFree(b);
-        }
+    if (c->d_block) {
+        if (c->async_buffers)
+            (void)hipFreeAsync(c->d_block, st);
+        else
+            (void)hipFree(c->d_block);
+    }
+    c->d_block = nullptr;
     c->d_mats = nullptr;
     c->d_tiles = nullptr;
     c->d_jobs = nullptr;
@@ -579,23 +591,40 @@ static void free_buffers(sv_circuit *c, hipStream_t st) {
     c->rt = RtDevice{nullptr, nullptr, nullptr};
 }
 
-template <typename T> static int upload(T **dst, const std::vector<T> &src, bool async, hipStream_t st) {
-    *dst = nullptr;
-    if (src.empty())
-        return SV_OK;
-    const size_t bytes = src.size() * sizeof(T);
-    hipError_t e = async ? hipMallocAsync((void **)dst, bytes, st) : hipMalloc((void **)dst, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
+// A plan's device tables, packed into one allocation and one copy (ten of
+// each cost a small plan more than its planning did).
+struct TableBlock {
+    std::vector<char> host;
+    std::vector<std::pair<void **, size_t>> at;  // device pointer, offset
+    template <typename T> void add(T **dst, const std::vector<T> &src) {
         *dst = nullptr;
-        return fail(SV_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+        if (src.empty())
+            return;
+        const size_t off = (host.size() + 255) / 256 * 256;
+        host.resize(off + src.size() * sizeof(T));
+        memcpy(host.data() + off, src.data(), src.size() * sizeof(T));
+        at.push_back({(void **)dst, off});
     }
-    if (async)
-        SV_HIP_TRY(hipMemcpyAsync(*dst, src.data(), bytes, hipMemcpyHostToDevice, st));
-    else
-        SV_HIP_TRY(hipMemcpy(*dst, src.data(), bytes, hipMemcpyHostToDevice));
-    return SV_OK;
-}
+    int upload(void **block, bool async, hipStream_t st) {
+        *block = nullptr;
+        if (host.empty())
+            return SV_OK;
+        const size_t bytes = host.size();
+        const hipError_t e = async ? hipMallocAsync(block, bytes, st) : hipMalloc(block, bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            *block = nullptr;
+            return fail(SV_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+        }
+        for (auto &p : at)
+            *p.first = (char *)*block + p.second;
+        if (async)
+            SV_HIP_TRY(hipMemcpyAsync(*block, host.data(), bytes, hipMemcpyHostToDevice, st));
+        else
+            SV_HIP_TRY(hipMemcpy(*block, host.data(), bytes, hipMemcpyHostToDevice));
+        return SV_OK;
+    }
+};
 
 // Dynamic LDS of a fused pass: the tile (in the arithmetic type), then the
 // diagonal-sweep tables.
@@ -661,28 +690,23 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
     std::vector<SweepMember> mems;
     int dense_runs = 0;
     SV_TRY(plan_circuit(c.get(), tiles, jobs, mats, dense_list, dense_runs, pats, mems));
-    int r = upload(&c->d_mats, mats, async, st);
-    if (r == SV_OK)
-        r = upload(&c->d_pats, pats, async, st);
-    if (r == SV_OK)
-        r = upload(&c->d_mems, mems, async, st);
-    if (r == SV_OK)
-        r = upload(&c->rt.ops, c->prog.ops, async, st);
-    if (r == SV_OK)
-        r = upload(&c->rt.pats, c->prog.pats, async, st);
-    if (r == SV_OK)
-        r = upload(&c->rt.acc, c->prog.acc, async, st);
-    if (r == SV_OK)
-        r = upload(&c->d_tiles, tiles, async, st);
-    if (r == SV_OK)
-        r = upload(&c->d_jobs, jobs, async, st);
-    if (r == SV_OK)
-        r = upload((DenseGate **)&c->d_dense, dense_list, async, st);
-    if (r == SV_OK && dense_runs > 0) {
+    TableBlock tb;
+    tb.add(&c->d_mats, mats);
+    tb.add(&c->d_pats, pats);
+    tb.add(&c->d_mems, mems);
+    tb.add(&c->rt.ops, c->prog.ops);
+    tb.add(&c->rt.pats, c->prog.pats);
+    tb.add(&c->rt.acc, c->prog.acc);
+    tb.add(&c->d_tiles, tiles);
+    tb.add(&c->d_jobs, jobs);
+    tb.add((DenseGate **)&c->d_dense, dense_list);
+    std::vector<double> rmat;
+    if (dense_runs > 0) {
         const size_t D = (size_t)2 << c->dense_k;
-        std::vector<double> zeros(D * D * (size_t)dense_runs, 0.0);  // room for either precision
-        r = upload((double **)&c->d_rmat, zeros, async, st);
+        rmat.assign(D * D * (size_t)dense_runs, 0.0);  // room for either precision
     }
+    tb.add((double **)&c->d_rmat, rmat);
+    const int r = tb.upload(&c->d_block, async, st);
     if (r != SV_OK) {
         free_buffers(c.get(), st);
         return r;

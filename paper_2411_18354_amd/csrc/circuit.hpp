@@ -56,6 +56,7 @@ struct sv_circuit {
     void *d_rmat = nullptr;         // one real embedding per dense pass
     int njobs = 0;
     int64_t fused_gates = 0, fused_runs = 0;
+    void *d_block = nullptr;             // the device tables below, one allocation
     double *d_mats = nullptr;
     sv::TileGate *d_tiles = nullptr;
     sv::ParamJob *d_jobs = nullptr;

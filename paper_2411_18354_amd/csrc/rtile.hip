@@ -219,9 +219,10 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
                      RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, bool dual,
                      RtProgram &prog) {
     // nr: register bits of the layouts; nb: with the bit telling psi and lambda apart
-    const int m = (int)tm.m, nb = rt_nb_of(tile_dt), nr = nb - (dual ? 1 : 0);
+    const int m = (int)tm.m, nb = rt_pass_nb(tile_dt, m, dual, tm.ntiles), nr = nb - (dual ? 1 : 0);
     RtPass pass;
     memset(&pass, 0, sizeof(pass));
+    pass.nb = (uint32_t)nb;
     pass.first = (uint32_t)prog.ops.size();
     pass.acc_first = (uint32_t)prog.acc.size();
     auto outer_mask = [&](int k) { return t[k].diag ? t[k].o_mask : t[k].hi_mask; };
@@ -475,13 +476,16 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
         units.swap(rest);
         if (units.empty())
             break;
-        // when what is left fits register bits a store layout may have, take them
-        const uint32_t rs = choose_regs(units, m, nr, io_fixed, io_allowed);
         r = choose_regs(units, m, nr, 0u, all);
+        // a last segment takes register bits a store layout may have, if they do
         const int npair = (int)std::count_if(units.begin(), units.end(), [](const Unit &u) { return !u.diag; });
-        const bool last = taken(units, rs) == npair;
-        if (last)
-            r = rs;
+        bool last = taken(units, r) == npair;
+        if (last) {
+            const uint32_t rs = choose_regs(units, m, nr, io_fixed, io_allowed);
+            last = taken(units, rs) == npair;
+            if (last)
+                r = rs;
+        }
         const Layout next = make_layout(m, r, last && block);
         prog.ops.push_back(exchange_op(cur, next, comp, dual ? m : -1));
         exch = true;
@@ -524,14 +528,13 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
 // the amplitudes.  Tiles of 2^13 complex128 amplitudes (512 lanes) save one
 // pass of 17 on the layered circuit but run 4% slower in all, 2^11 ones 25%
 // slower.
-template <typename R>
+template <typename R, int NB>
 __global__ __launch_bounds__(kRtMaxThreads, 4) void k_rtile(cplx_t<R> *__restrict__ psi, TileMap tm, RtPass p,
                                                             const RtOp *__restrict__ ops,
                                                             const RtPat *__restrict__ pats,
                                                             const SweepMember *__restrict__ mems,
                                                             DeviceGates gates) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    constexpr int NB = rt_nb<R>();
     const uint64_t base = expand_index<uint64_t>(tm.outer, tm.tile0 + blockIdx.x);
     if (!p.always && !tile_touched(base, gates))
         return;
@@ -554,15 +557,15 @@ __global__ __launch_bounds__(kRtMaxThreads, 4) void k_rtile(cplx_t<R> *__restric
     });
 }
 
-template <typename R>
+template <typename R, int NB>
 static int launch_rt(void *psi, const TileMap &tm_in, const RtPass &p, const RtDevice &d, const DeviceGates &gates,
                      hipStream_t st) {
     TileMap tm = tm_in;
-    const unsigned lanes = 1u << ((int)tm.m - rt_nb<R>());
+    const unsigned lanes = 1u << ((int)tm.m - NB);
     for (uint64_t t0 = 0; t0 < tm.ntiles; t0 += kMaxGridBlocks) {
         tm.tile0 = t0;
         const dim3 grid((unsigned)std::min(kMaxGridBlocks, tm_in.ntiles - t0));
-        hipLaunchKernelGGL(k_rtile<R>, grid, dim3(lanes), p.lds, st, reinterpret_cast<cplx_t<R> *>(psi), tm, p, d.ops,
+        hipLaunchKernelGGL((k_rtile<R, NB>), grid, dim3(lanes), p.lds, st, reinterpret_cast<cplx_t<R> *>(psi), tm, p, d.ops,
                            d.pats, gates.mm, gates);
         SV_LAUNCH_CHECK();
     }
@@ -573,7 +576,10 @@ int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, con
                    const DeviceGates &gates, hipStream_t st) {
     if (!rt_tile_ok(dtype, (int)tm.m, false))
         return fail(SV_EINVAL, "register tiles of 2^%u amplitudes", tm.m);
-    return dtype == SV_C128 ? launch_rt<double>(psi, tm, p, d, gates, st) : launch_rt<float>(psi, tm, p, d, gates, st);
+    if (dtype == SV_C128)
+        return p.nb == 4 ? launch_rt<double, 4>(psi, tm, p, d, gates, st)
+                         : launch_rt<double, 3>(psi, tm, p, d, gates, st);
+    return p.nb == 5 ? launch_rt<float, 5>(psi, tm, p, d, gates, st) : launch_rt<float, 4>(psi, tm, p, d, gates, st);
 }
 
 // The reverse sweep on register tiles: a lane holds the same amplitudes of psi

@@ -209,20 +209,27 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
         uint32_t next = slot;
         // every path meets at rt_apply (lanes 0: nothing to do): paths of
         // their own around it would split the amplitudes' live ranges
-        if (kind <= kRtDiag || (GRAD && kind == kRtGrad)) {
+        const bool gate = kind <= kRtDiag || (GRAD && kind == kRtGrad);
+        if (gate) {
             const uint64_t om = (uint64_t)w[7] << 32 | w[6], ov = (uint64_t)w[9] << 32 | w[8];
+            lanes = __ballot((tid & w[2]) == w[3]);
+            if ((base & om) != ov)
+                lanes = 0;
+        }
+        if (kind == kRtDiag) {
             const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
-            lanes = (base & om) == ov ? __ballot((tid & w[2]) == w[3]) : 0ull;
             const bool one = (tid & w[4]) != 0 || (base & ob) != 0 || (w[0] & 7u) != 0;
             fr = one ? m.dr : m.ar;
             fi = one ? m.di : m.ai;
-        } else if (kind == kRtFactor) {
-            rt_phase_factor<R>(rt_phase_sum(ph, w[12], w[13], tid), &fr, &fi);
-        } else if (kind == kRtExch) {
-            next = rt_xor_terms(rt_fresh(tid), o.t);
-        } else if (kind == kRtPrep) {
-            rt_prep<R, NB>(lds, base, w, pats, mems);
-            lanes = 0;
+        } else if (!gate) {
+            if (kind == kRtFactor) {
+                rt_phase_factor<R>(rt_phase_sum(ph, w[12], w[13], tid), &fr, &fi);
+            } else if (kind == kRtExch) {
+                next = rt_xor_terms(rt_fresh(tid), o.t);
+            } else if (kind == kRtPrep) {
+                rt_prep<R, NB>(lds, base, w, pats, mems);
+                lanes = 0;
+            }
         }
         uint32_t sa = buf + slot, na = buf + next;
         if constexpr (GRAD) {

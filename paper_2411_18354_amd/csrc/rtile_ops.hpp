@@ -124,7 +124,11 @@ namespace sv {
     "s_bitcmp1_b32 %[pm], " #i "\n"                                                                                \
     "s_cbranch_scc0 .Lrt_mul_" #i "_%=\n" OP(i) ".Lrt_mul_" #i "_%=:\n"
 
-// The pairs of register bit T among 16 registers, in pair order.
+// The pairs of register bit T among 8 registers, in pair order.
+#define RT_PAIRS3_0(P, F, V) P(F, V, 0, 0, 1) P(F, V, 1, 2, 3) P(F, V, 2, 4, 5) P(F, V, 3, 6, 7)
+#define RT_PAIRS3_1(P, F, V) P(F, V, 0, 0, 2) P(F, V, 1, 1, 3) P(F, V, 2, 4, 6) P(F, V, 3, 5, 7)
+#define RT_PAIRS3_2(P, F, V) P(F, V, 0, 0, 4) P(F, V, 1, 1, 5) P(F, V, 2, 2, 6) P(F, V, 3, 3, 7)
+// among 16
 #define RT_PAIRS4_0(P, F, V)                                                                                          \
     P(F, V, 0, 0, 1) P(F, V, 1, 2, 3) P(F, V, 2, 4, 5) P(F, V, 3, 6, 7)                    \
     P(F, V, 4, 8, 9) P(F, V, 5, 10, 11) P(F, V, 6, 12, 13) P(F, V, 7, 14, 15)
@@ -159,8 +163,10 @@ namespace sv {
     P(F, V, 4, 4, 20) P(F, V, 5, 5, 21) P(F, V, 6, 6, 22) P(F, V, 7, 7, 23)                \
     P(F, V, 8, 8, 24) P(F, V, 9, 9, 25) P(F, V, 10, 10, 26) P(F, V, 11, 11, 27)            \
     P(F, V, 12, 12, 28) P(F, V, 13, 13, 29) P(F, V, 14, 14, 30) P(F, V, 15, 15, 31)
+#define RT_REGS3(F)                                                                                                \
+    RT_REG(F, 0) RT_REG(F, 1) RT_REG(F, 2) RT_REG(F, 3) RT_REG(F, 4) RT_REG(F, 5) RT_REG(F, 6) RT_REG(F, 7)
 #define RT_REGS4(F)                                                                                                \
-    RT_REG(F, 0) RT_REG(F, 1) RT_REG(F, 2) RT_REG(F, 3) RT_REG(F, 4) RT_REG(F, 5) RT_REG(F, 6) RT_REG(F, 7)        \
+    RT_REGS3(F)                                                                                                    \
     RT_REG(F, 8) RT_REG(F, 9) RT_REG(F, 10) RT_REG(F, 11) RT_REG(F, 12) RT_REG(F, 13) RT_REG(F, 14) RT_REG(F, 15)
 #define RT_REGS5(F)                                                                                                \
     RT_REGS4(F)                                                                                                    \
@@ -213,6 +219,8 @@ namespace sv {
 
 // The registers in Gray-code order, S a step and F(b) the flip of register bit
 // b between two; R: the same order backwards.
+#define RT_GRAY3(S, F) S(0) F(0) S(1) F(1) S(3) F(0) S(2) F(2) S(6) F(0) S(7) F(1) S(5) F(0) S(4)
+#define RT_GRAY3R(S, F) S(4) F(0) S(5) F(1) S(7) F(0) S(6) F(2) S(2) F(0) S(3) F(1) S(1) F(0) S(0)
 #define RT_GRAY4(S, F)                                                                                             \
     S(0) F(0) S(1) F(1) S(3) F(0) S(2) F(2) S(6) F(0) S(7) F(1) S(5) F(0) S(4) F(3)                                \
     S(12) F(0) S(13) F(1) S(15) F(0) S(14) F(2) S(10) F(0) S(11) F(1) S(9) F(0) S(8)
@@ -247,16 +255,20 @@ namespace sv {
 
 #define RT_TAB_f64(i, o0, o1) RT_STEP_TAB("f64", "ds_read_b64", i, o0, o1)
 #define RT_TAB_f32(i, o0, o1) RT_STEP_TAB("f32", "ds_read_b32", i, o0, o1)
-#define RT_TABLE_f64                                                                                               \
+#define RT_TABLE3_f64                                                                                              \
     RT_TAB_f64(0, 0, 8) RT_TAB_f64(1, 16, 24) RT_TAB_f64(2, 32, 40) RT_TAB_f64(3, 48, 56)                          \
-    RT_TAB_f64(4, 64, 72) RT_TAB_f64(5, 80, 88) RT_TAB_f64(6, 96, 104) RT_TAB_f64(7, 112, 120)                     \
+    RT_TAB_f64(4, 64, 72) RT_TAB_f64(5, 80, 88) RT_TAB_f64(6, 96, 104) RT_TAB_f64(7, 112, 120)
+#define RT_TABLE4_f64                                                                                              \
+    RT_TABLE3_f64                                                                                                  \
     RT_TAB_f64(8, 128, 136) RT_TAB_f64(9, 144, 152) RT_TAB_f64(10, 160, 168) RT_TAB_f64(11, 176, 184)              \
     RT_TAB_f64(12, 192, 200) RT_TAB_f64(13, 208, 216) RT_TAB_f64(14, 224, 232) RT_TAB_f64(15, 240, 248)
-#define RT_TABLE_f32                                                                                               \
+#define RT_TABLE4_f32                                                                                              \
     RT_TAB_f32(0, 0, 4) RT_TAB_f32(1, 8, 12) RT_TAB_f32(2, 16, 20) RT_TAB_f32(3, 24, 28)                           \
     RT_TAB_f32(4, 32, 36) RT_TAB_f32(5, 40, 44) RT_TAB_f32(6, 48, 52) RT_TAB_f32(7, 56, 60)                        \
     RT_TAB_f32(8, 64, 68) RT_TAB_f32(9, 72, 76) RT_TAB_f32(10, 80, 84) RT_TAB_f32(11, 88, 92)                      \
-    RT_TAB_f32(12, 96, 100) RT_TAB_f32(13, 104, 108) RT_TAB_f32(14, 112, 116) RT_TAB_f32(15, 120, 124)             \
+    RT_TAB_f32(12, 96, 100) RT_TAB_f32(13, 104, 108) RT_TAB_f32(14, 112, 116) RT_TAB_f32(15, 120, 124)
+#define RT_TABLE5_f32                                                                                              \
+    RT_TABLE4_f32                                                                                                  \
     RT_TAB_f32(16, 128, 132) RT_TAB_f32(17, 136, 140) RT_TAB_f32(18, 144, 148) RT_TAB_f32(19, 152, 156)            \
     RT_TAB_f32(20, 160, 164) RT_TAB_f32(21, 168, 172) RT_TAB_f32(22, 176, 180) RT_TAB_f32(23, 184, 188)            \
     RT_TAB_f32(24, 192, 196) RT_TAB_f32(25, 200, 204) RT_TAB_f32(26, 208, 212) RT_TAB_f32(27, 216, 220)            \
@@ -278,8 +290,12 @@ namespace sv {
 #define RT_END "s_branch .Lrt_end_%=\n"
 #define RT_NONE "s_branch .Lrt_end_%=\n"
 // entries of one kind: register bits 0 .. 7 (those there are)
-#define RT_TABLE4(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_NONE RT_NONE RT_NONE RT_NONE
-#define RT_TABLE5(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_GO(K "4") RT_NONE RT_NONE RT_NONE
+#define RT_ENTRIES3(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_NONE RT_NONE RT_NONE RT_NONE RT_NONE
+#define RT_ENTRIES4(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_NONE RT_NONE RT_NONE RT_NONE
+#define RT_ENTRIES5(K) RT_GO(K "0") RT_GO(K "1") RT_GO(K "2") RT_GO(K "3") RT_GO(K "4") RT_NONE RT_NONE RT_NONE
+#define RT_KIND3(P, OP, K)                                                                                         \
+    RT_AT(K "0") RT_PAIRS3_0(P, OP, K "0") RT_END RT_AT(K "1") RT_PAIRS3_1(P, OP, K "1") RT_END                    \
+    RT_AT(K "2") RT_PAIRS3_2(P, OP, K "2") RT_END
 #define RT_KIND4(P, OP, K)                                                                                         \
     RT_AT(K "0") RT_PAIRS4_0(P, OP, K "0") RT_END RT_AT(K "1") RT_PAIRS4_1(P, OP, K "1") RT_END                    \
     RT_AT(K "2") RT_PAIRS4_2(P, OP, K "2") RT_END RT_AT(K "3") RT_PAIRS4_3(P, OP, K "3") RT_END
@@ -289,57 +305,40 @@ namespace sv {
     RT_AT(K "4") RT_PAIRS5_4(P, OP, K "4") RT_END
 // every variant: entry kind * 8 + register bit of the pair kinds, again with
 // every pair from kRtEntryFull on, then the rest
-#define RT_HEAD_f64                                                                                                \
-    RT_DISPATCH RT_TABLE4("r") RT_TABLE4("c") RT_TABLE4("g") RT_TABLE4("s") RT_TABLE4("rf") RT_TABLE4("cf") RT_TABLE4("gf") RT_TABLE4("sf")\
-    RT_GO("mul") RT_GO("tab") RT_GO("ex")
-#define RT_BODY_f64                                                                                                \
-    RT_KIND4(RT_PAIR, RT_REAL_f64, "r")                                                                            \
-    RT_KIND4(RT_PAIR, RT_CROSS_f64, "c")                                                                           \
-    RT_KIND4(RT_PAIR, RT_GEN_f64, "g")                                                                             \
-    RT_KIND4(RT_PAIR, RT_SWAP_f64, "s")                                                                            \
-    RT_KIND4(RT_FULL, RT_REAL_f64, "rf")                                                                           \
-    RT_KIND4(RT_FULL, RT_CROSS_f64, "cf")                                                                          \
-    RT_KIND4(RT_FULL, RT_GEN_f64, "gf")                                                                            \
-    RT_KIND4(RT_FULL, RT_SWAP_f64, "sf")                                                                           \
-    RT_AT("tab") RT_TABLE_f64 RT_END RT_AT("ex") RT_EXCH(RT_GRAY4, RT_GRAY4R, f64) RT_END
-#define RT_TAIL_f64                                                                                                \
-    RT_AT("mul") RT_REGS4(RT_MUL_f64) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
-#define RT_BLOCK_f64 RT_HEAD_f64 RT_BODY_f64 RT_TAIL_f64
+#define RT_HEAD(B)                                                                                                 \
+    RT_DISPATCH RT_ENTRIES##B("r") RT_ENTRIES##B("c") RT_ENTRIES##B("g") RT_ENTRIES##B("s")                        \
+    RT_ENTRIES##B("rf") RT_ENTRIES##B("cf") RT_ENTRIES##B("gf") RT_ENTRIES##B("sf") RT_GO("mul") RT_GO("tab") RT_GO("ex")
+#define RT_BODY(B, SZ)                                                                                             \
+    RT_KIND##B(RT_PAIR, RT_REAL_##SZ, "r")                                                                         \
+    RT_KIND##B(RT_PAIR, RT_CROSS_##SZ, "c")                                                                        \
+    RT_KIND##B(RT_PAIR, RT_GEN_##SZ, "g")                                                                          \
+    RT_KIND##B(RT_PAIR, RT_SWAP_##SZ, "s")                                                                         \
+    RT_KIND##B(RT_FULL, RT_REAL_##SZ, "rf")                                                                        \
+    RT_KIND##B(RT_FULL, RT_CROSS_##SZ, "cf")                                                                       \
+    RT_KIND##B(RT_FULL, RT_GEN_##SZ, "gf")                                                                         \
+    RT_KIND##B(RT_FULL, RT_SWAP_##SZ, "sf")                                                                        \
+    RT_AT("tab") RT_TABLE##B##_##SZ RT_END RT_AT("ex") RT_EXCH(RT_GRAY##B, RT_GRAY##B##R, SZ) RT_END
+#define RT_TAIL(B, SZ)                                                                                             \
+    RT_AT("mul") RT_REGS##B(RT_MUL_##SZ) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
+#define RT_BLOCK(B, SZ) RT_HEAD(B) RT_BODY(B, SZ) RT_TAIL(B, SZ)
 // the same with the gradient terms
 #define RT_BLOCK_GRAD_f64                                                                                          \
-    RT_HEAD_f64 RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                        \
+    RT_HEAD(4) RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                         \
     RT_GO("gy0") RT_GO("gy1") RT_GO("gy2") RT_NONE RT_NONE RT_NONE RT_NONE RT_NONE                                 \
     RT_GO("gx0") RT_GO("gx1") RT_GO("gx2") RT_NONE RT_NONE RT_NONE RT_NONE RT_NONE                                 \
-    RT_BODY_f64                                                                                                    \
+    RT_BODY(4, f64)                                                                                                \
     RT_AT("gy0") RT_QUADS4_0(RT_STEP_GY, RT_DOT_f64, "gy0") RT_END                                                 \
     RT_AT("gy1") RT_QUADS4_1(RT_STEP_GY, RT_DOT_f64, "gy1") RT_END                                                 \
     RT_AT("gy2") RT_QUADS4_2(RT_STEP_GY, RT_DOT_f64, "gy2") RT_END                                                 \
     RT_AT("gx0") RT_QUADS4_0(RT_STEP_GX, RT_DOT_f64, "gx0") RT_END                                                 \
     RT_AT("gx1") RT_QUADS4_1(RT_STEP_GX, RT_DOT_f64, "gx1") RT_END                                                 \
     RT_AT("gx2") RT_QUADS4_2(RT_STEP_GX, RT_DOT_f64, "gx2") RT_END                                                 \
-    RT_AT("gd") RT_BOTHS4(RT_DOT_f64) RT_END RT_TAIL_f64
-#define RT_HEAD_f32                                                                                                \
-    RT_DISPATCH RT_TABLE5("r") RT_TABLE5("c") RT_TABLE5("g") RT_TABLE5("s") RT_TABLE5("rf") RT_TABLE5("cf") RT_TABLE5("gf") RT_TABLE5("sf")\
-    RT_GO("mul") RT_GO("tab") RT_GO("ex")
-#define RT_BODY_f32                                                                                                \
-    RT_KIND5(RT_PAIR, RT_REAL_f32, "r")                                                                            \
-    RT_KIND5(RT_PAIR, RT_CROSS_f32, "c")                                                                           \
-    RT_KIND5(RT_PAIR, RT_GEN_f32, "g")                                                                             \
-    RT_KIND5(RT_PAIR, RT_SWAP_f32, "s")                                                                            \
-    RT_KIND5(RT_FULL, RT_REAL_f32, "rf")                                                                           \
-    RT_KIND5(RT_FULL, RT_CROSS_f32, "cf")                                                                          \
-    RT_KIND5(RT_FULL, RT_GEN_f32, "gf")                                                                            \
-    RT_KIND5(RT_FULL, RT_SWAP_f32, "sf")                                                                           \
-    RT_AT("tab") RT_TABLE_f32 RT_END RT_AT("ex") RT_EXCH(RT_GRAY5, RT_GRAY5R, f32) RT_END
-#define RT_TAIL_f32                                                                                                \
-    RT_AT("mul") RT_REGS5(RT_MUL_f32) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
-#define RT_BLOCK_f32 RT_HEAD_f32 RT_BODY_f32 RT_TAIL_f32
-// the same with the gradient terms
+    RT_AT("gd") RT_BOTHS4(RT_DOT_f64) RT_END RT_TAIL(4, f64)
 #define RT_BLOCK_GRAD_f32                                                                                          \
-    RT_HEAD_f32 RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                        \
+    RT_HEAD(5) RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                         \
     RT_GO("gy0") RT_GO("gy1") RT_GO("gy2") RT_GO("gy3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
     RT_GO("gx0") RT_GO("gx1") RT_GO("gx2") RT_GO("gx3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
-    RT_BODY_f32                                                                                                    \
+    RT_BODY(5, f32)                                                                                                \
     RT_AT("gy0") RT_QUADS5_0(RT_STEP_GY, RT_DOT_f32, "gy0") RT_END                                                 \
     RT_AT("gy1") RT_QUADS5_1(RT_STEP_GY, RT_DOT_f32, "gy1") RT_END                                                 \
     RT_AT("gy2") RT_QUADS5_2(RT_STEP_GY, RT_DOT_f32, "gy2") RT_END                                                 \
@@ -348,9 +347,11 @@ namespace sv {
     RT_AT("gx1") RT_QUADS5_1(RT_STEP_GX, RT_DOT_f32, "gx1") RT_END                                                 \
     RT_AT("gx2") RT_QUADS5_2(RT_STEP_GX, RT_DOT_f32, "gx2") RT_END                                                 \
     RT_AT("gx3") RT_QUADS5_3(RT_STEP_GX, RT_DOT_f32, "gx3") RT_END                                                 \
-    RT_AT("gd") RT_BOTHS5(RT_DOT_f32) RT_END RT_TAIL_f32
+    RT_AT("gd") RT_BOTHS5(RT_DOT_f32) RT_END RT_TAIL(5, f32)
 
 #define RT_AMP(i) [x##i] "+v"(v.x[i]), [y##i] "+v"(v.y[i])
+#define RT_AMPS8                                                                                                   \
+    RT_AMP(0), RT_AMP(1), RT_AMP(2), RT_AMP(3), RT_AMP(4), RT_AMP(5), RT_AMP(6), RT_AMP(7)
 #define RT_AMPS16                                                                                                  \
     RT_AMP(0), RT_AMP(1), RT_AMP(2), RT_AMP(3), RT_AMP(4), RT_AMP(5), RT_AMP(6), RT_AMP(7), RT_AMP(8), RT_AMP(9),  \
         RT_AMP(10), RT_AMP(11), RT_AMP(12), RT_AMP(13), RT_AMP(14), RT_AMP(15)
@@ -388,16 +389,31 @@ __device__ __forceinline__ void rt_apply(RtRegs<double, 4> &v, const uint32_t (&
                                          uint32_t &next) {
     double t0, t1, t2, t3;
     uint64_t save;
-    asm volatile(RT_BLOCK_f64 : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+    asm volatile(RT_BLOCK(4, f64) : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
 }
 __device__ __forceinline__ void rt_apply(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m, float fr,
                                          float fi, uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next) {
     float t0, t1, t2, t3;
     uint64_t save;
-    asm volatile(RT_BLOCK_f32
+    asm volatile(RT_BLOCK(5, f32)
                  : RT_AMPS32, RT_SCRATCH
                  : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12])
                  : "scc", "vcc", "memory");
+}
+
+// with half as many amplitudes per lane
+__device__ __forceinline__ void rt_apply(RtRegs<double, 3> &v, const uint32_t (&w)[16], const Mat2<double> &m,
+                                         double fr, double fi, uint64_t lanes, uint32_t table, uint32_t &slot,
+                                         uint32_t &next) {
+    double t0, t1, t2, t3;
+    uint64_t save;
+    asm volatile(RT_BLOCK(3, f64) : RT_AMPS8, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+}
+__device__ __forceinline__ void rt_apply(RtRegs<float, 4> &v, const uint32_t (&w)[16], const Mat2<float> &m, float fr,
+                                         float fi, uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next) {
+    float t0, t1, t2, t3;
+    uint64_t save;
+    asm volatile(RT_BLOCK(4, f32) : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
 }
 
 // The same on a lane's amplitudes of psi (registers with the top bit 0) and

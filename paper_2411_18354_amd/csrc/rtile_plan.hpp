@@ -9,14 +9,24 @@ namespace sv {
 constexpr int kRtMaxThreadBits = 9;  // workgroups of up to 512 lanes
 constexpr int kRtMaxThreads = 1 << kRtMaxThreadBits;
 constexpr int kRtMaxNB = 5;
+// Register bits: 16 complex128 or 32 complex64 amplitudes per lane; half as
+// many where a pass has no more tiles than the chip has CUs.  Such a pass is
+// bound by the latency of each operation, which twice the wavefronts with
+// half the work each hide better (complex64 QFT n=12 45.0 -> 34.5 us, n=20
+// 88.1 -> 78.7; complex128 n=10 28.4 -> 24.3 us, even from n=12 on).
 template <typename R> constexpr int rt_nb() { return sizeof(R) == 8 ? 4 : 5; }
 inline int rt_nb_of(int tile_dt) { return tile_dt == SV_C128 ? 4 : 5; }
+constexpr uint64_t kRtFewTiles = 256;
 // Tiles of 64 to 512 lanes; narrower ones stay with the LDS tiles.  dual: the
 // reverse sweep, whose lanes hold psi and lambda together (the top register
 // bit tells them apart, so a layout has one register bit less).
 inline bool rt_tile_ok(int tile_dt, int m, bool dual) {
     const int t = m - rt_nb_of(tile_dt) + (dual ? 1 : 0);
     return t >= 6 && t <= kRtMaxThreadBits;
+}
+inline int rt_pass_nb(int tile_dt, int m, bool dual, uint64_t ntiles) {
+    const int nb = rt_nb_of(tile_dt);
+    return !dual && ntiles <= kRtFewTiles && m - nb < kRtMaxThreadBits ? nb - 1 : nb;
 }
 
 // Operation kinds (RtOp::w[0] = kind * 8 + a small number).
@@ -73,6 +83,7 @@ struct RtPass {
     RtIO in, out;
     uint32_t first, count;  // operations
     uint32_t always;        // every launched tile is touched
+    uint32_t nb;            // register bits
     uint32_t lds;           // bytes of dynamic LDS (dual: accumulators not included)
     uint32_t acc_first, acc_count;  // dual: gradient accumulators (RtProgram::acc)
 };

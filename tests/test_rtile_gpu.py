@@ -72,10 +72,14 @@ def _check(gpu, circ, dtype, params=None, seed=3, slack=0.0):
 
 
 @pytest.mark.parametrize("dtype,m", WIDTHS)
-@pytest.mark.parametrize("extra", [0, 2])
+@pytest.mark.parametrize("extra", [0, 2, 9])
 def test_all_kinds(gpu, dtype, m, extra):
+    """One tile, a few, and more than there are CUs (up to 256 tiles a lane
+    holds half as many amplitudes)."""
+    if extra == 9 and m > 12:
+        pytest.skip("tiles of 512 lanes hold the same amplitudes per lane at every count")
     gpu.sv_tune_set("tile_log2_" + dtype, m)
-    _check(gpu, _random_circuit(m + extra, 160, 100 * m + extra), dtype)
+    _check(gpu, _random_circuit(m + extra, 160 if extra < 9 else 60, 100 * m + extra), dtype)
 
 
 @pytest.mark.parametrize("dtype,m", WIDTHS)
@@ -88,12 +92,12 @@ def test_narrow_low_block_and_angles(gpu, dtype, m):
 
 
 @pytest.mark.parametrize("dtype,m", [("c128", 10), ("c128", 12), ("c64", 11), ("c64", 14)])
-@pytest.mark.parametrize("count", [5, 60, 3000])
-def test_diagonal_blocks(gpu, dtype, m, count):
+@pytest.mark.parametrize("count,extra", [(5, 1), (60, 1), (3000, 1), (40, 9)])
+def test_diagonal_blocks(gpu, dtype, m, count, extra):
     """A block adds phases: up to `count` additions, each rounding a sum of
     at most 2 pi count to 53 bits (beside the library's tolerance)."""
     gpu.sv_tune_set("tile_log2_" + dtype, m)
-    _check(gpu, _diagonal_circuit(m + 1, count, count + m), dtype, slack=2 * np.pi * count ** 2 * 2.0 ** -53)
+    _check(gpu, _diagonal_circuit(m + extra, count, count + m), dtype, slack=2 * np.pi * count ** 2 * 2.0 ** -53)
 
 
 @pytest.mark.parametrize("dtype", ["c128", "c64"])
@@ -153,3 +157,21 @@ def test_reverse_sweep(gpu, dtype, m, diagonals):
     assert np.abs(grad.cpu().numpy() - ref).max() <= tol
     psi[0] -= 1  # the sweep un-applies every gate
     assert psi.abs().max().item() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,n", [("c128", 12), ("c128", 14), ("c64", 13), ("c64", 15), ("c64", 17)])
+def test_runs_of_x_only(gpu, dtype, n):
+    """Runs that only permute (a gather through LDS tiles, or register tiles):
+    amplitudes move exactly."""
+    rng = np.random.default_rng(n)
+    gates = []
+    for _ in range(40):
+        t, nc = int(rng.integers(n)), int(rng.integers(0, 5))
+        ctrls = tuple(int(q) for q in rng.choice([q for q in range(n) if q != t], size=nc, replace=False))
+        gates.append(W.Gate("X", t, ctrls, tuple(int(v) for v in rng.integers(0, 2, size=nc))))
+    for c in (W.Circuit(n, gates), W.stream(n)):
+        tdt = torch.complex128 if dtype == "c128" else torch.complex64
+        psi = torch.tensor(W.random_state(n, 4), device="cuda").to(tdt)
+        ref = oracle.run_circuit(c, psi0=psi.cpu().numpy().astype(np.complex128))
+        gpu.Circuit(n, c, dtype=gpu.SV_C128 if dtype == "c128" else gpu.SV_C64).run(psi)
+        assert np.array_equal(psi.cpu().numpy().astype(np.complex128), ref)
