@@ -465,12 +465,12 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 // is a single gather through an LDS tile; register tiles pay
                 // for each of its gates and lose on complex128 (streaming
                 // circuit, n = 12: 12.4 against 10.8 us, n = 26: 447 against
-                // 431 us; n = 16 to 22 even or faster) and where complex64
-                // has a few tiles only (n = 13: 15.2 against 13.4 us, n = 14:
-                // 17.8 against 15.5; n = 16: 21.2 against 21.9, n = 26: 232
-                // against 255).
-                bool gather = tuning().fuse_perm && !c->dual && !is_fixed(c->dtype) &&
-                              (tdt == SV_C128 || p.tm.ntiles <= 4) &&
+                // 431 us; n = 16 to 22 even or faster) and where the other
+                // dtypes have a few tiles only (complex64 n = 13: 15.2 against
+                // 13.4 us, n = 14: 17.8 against 15.5; n = 16: 21.2 against
+                // 21.9, n = 26: 232 against 255; 32-bit codes n = 13: 16.2
+                // against 14.7, n = 27: 476 against 574).
+                bool gather = tuning().fuse_perm && !c->dual && (c->dtype == SV_C128 || p.tm.ntiles <= 4) &&
                               (1u << m) <= 512u * (tdt == SV_C128 ? perm_per_lane<double>() : perm_per_lane<float>());
                 if (gather) {
                     mark_permutation_runs(&tiles[p.first], p.count);
@@ -780,7 +780,10 @@ static int enqueue_fixed(sv_circuit *c, void *state, const double *params, hipSt
     for (const Pass &p : c->passes) {
         if (p.fused) {
             DeviceGates dg{c->d_tiles + p.first, p.count, c->d_pats, c->d_mems};
-            SV_TRY(launch_fixed_tile_pass(state, c->n, c->dtype, p.tm, dg, lds, st));
+            if (p.rt)
+                SV_TRY(launch_fixed_rt_pass(state, c->n, c->dtype, p.tm, p.rp, c->rt, dg, st));
+            else
+                SV_TRY(launch_fixed_tile_pass(state, c->n, c->dtype, p.tm, dg, lds, st));
         } else {
             SV_TRY(launch_fixed_gate(state, p.fx, nullptr, c->d_mats + (size_t)8 * p.gate, st));
         }
@@ -991,8 +994,7 @@ int sv_circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int 
     clear_error();
     if (!out)
         return fail(SV_EINVAL, "out is NULL");
-    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, !is_fixed(dtype), false,
-                          out);
+    return circuit_create(n, dtype, gates, ngates, nparams, flags, false, nullptr, 64, dtype != SV_CQ16, false, out);
 }
 
 int sv_circuit_run(sv_circuit_t *c, const sv_state_t *s, const double *params_dev, sv_stream_t st) {
@@ -1049,8 +1051,8 @@ int sv_apply_circuit(const sv_state_t *s, const sv_gate_t *gates, int ngates, co
     clear_error();
     SV_TRY(validate_state(s, true));
     sv_circuit *c = nullptr;
-    SV_TRY(circuit_create(s->n, s->dtype, gates, ngates, nparams, flags & ~SV_GRAPH, true, (hipStream_t)st, 64, !is_fixed(s->dtype),
-                          false, &c));
+    SV_TRY(circuit_create(s->n, s->dtype, gates, ngates, nparams, flags & ~SV_GRAPH, true, (hipStream_t)st, 64,
+                          s->dtype != SV_CQ16, false, &c));
     int r = check_run_args(c, s, params_dev);
     if (r == SV_OK)
         r = enqueue_any(c, s, params_dev, (hipStream_t)st);

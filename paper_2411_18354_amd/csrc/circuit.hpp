@@ -23,6 +23,9 @@ inline int tile_dtype(int dtype) { return dtype == SV_CQ32 ? SV_C128 : dtype == 
 int launch_fixed_tile_pass(void *state, int n, int dtype, const TileMap &tm, const DeviceGates &dg, size_t lds,
                            hipStream_t st);
 int fixed_tile_lds_limit(int dtype, size_t lds);
+// The same on register tiles (SV_CQ32).
+int launch_fixed_rt_pass(void *state, int n, int dtype, const TileMap &tm, const RtPass &p, const RtDevice &d,
+                         const DeviceGates &dg, hipStream_t st);
 
 struct Pass {
     bool fused;

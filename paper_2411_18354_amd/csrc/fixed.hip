@@ -28,6 +28,7 @@
 #include <cstring>
 
 #include "circuit.hpp"
+#include "rtile.hpp"
 
 namespace sv {
 
@@ -522,6 +523,62 @@ __global__ __launch_bounds__(512, 4) void k_fix_tile(char *__restrict__ codes, i
     }
 }
 
+// The same on register tiles (rtile.hpp): the tile is loaded and stored in a
+// layout whose register bits 0 and 1 are the tile's lowest two bits and whose
+// lowest four lane bits the next four, so 16 lanes hold a block, 4 amplitudes
+// each, as above; the run's exchanges end in that layout again.  Measured
+// against k_fix_tile (MI355X, 32-bit codes, n = 27): QFT 9.20 -> 4.16 ms, a
+// layer of H, RY, CNOT and MCX gates 4.35 -> 2.38 ms; a pass reads and writes
+// 2.2 GB, 0.33 ms, so the arithmetic inside the tile is the bound.
+// 16-bit codes keep k_fix_tile: a register tile applies commuting gates in
+// another order, which moves a value by a float rounding and about one code in
+// a thousand by one, and each later pass re-encodes and multiplies such
+// differences, to as much as the format's own error (6e-5 at n = 27) after
+// three.  (Their QFT would take 2.1 instead of 5.6 ms.)  With 31 bits the
+// same differences stay near 1e-9.
+template <typename Q, int NB>
+__global__ __launch_bounds__(kRtMaxThreads, 4) void k_fix_rtile(char *__restrict__ codes,
+                                                                int8_t *__restrict__ scales, TileMap tm, RtPass p,
+                                                                const RtOp *__restrict__ ops,
+                                                                const RtPat *__restrict__ pats,
+                                                                const SweepMember *__restrict__ mems,
+                                                                DeviceGates gates) {
+    using R = typename Q::R;
+    constexpr size_t kBlockBytes = 64 * Q::kAmpBytes;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    const uint64_t base = expand_index<uint64_t>(tm.outer, tm.tile0 + blockIdx.x);
+    if (!p.always && !tile_touched(base, gates))
+        return;  // no operation of the run touches it: its blocks stay as they are
+    const int tb = (int)tm.m - NB, j = threadIdx.x & 15;
+    RtRegs<R, NB> v;
+    const uint64_t src = base | rt_thread_offset(p.in, threadIdx.x & ~15u, tb);
+    SV_RT_FOR(1 << (NB - 2), g) {
+        const uint64_t b = (src + rt_reg_offset<NB>(p.in, 4 * g)) >> kQBlockBits;
+        const typename Q::Lane w = Q::ld(codes + b * kBlockBytes, j);
+        R re[4], im[4];
+        Q::decode(w, scales[b], re, im);
+        SV_RT_FOR(4, i) {
+            v.x[4 * g + i] = re[i];
+            v.y[4 * g + i] = im[i];
+        });
+    });
+    const uint32_t slot = rt_xor_terms(threadIdx.x, p.in.slot);
+    rt_run<R, NB>(v, lds_raw, slot, base, ops + p.first, p.count, pats, mems);
+    const uint64_t dst = base | rt_thread_offset(p.out, rt_fresh(threadIdx.x) & ~15u, tb);
+    SV_RT_FOR(1 << (NB - 2), g) {
+        const uint64_t b = (dst + rt_reg_offset<NB>(p.out, 4 * g)) >> kQBlockBits;
+        R re[4], im[4];
+        SV_RT_FOR(4, i) {
+            re[i] = v.x[4 * g + i];
+            im[i] = v.y[4 * g + i];
+        });
+        const int s = Q::scale(group16_max<R>(absmax4<R>(re, im)));
+        Q::st(codes + b * kBlockBytes, j, Q::encode(re, im, s));
+        if (j == 0)
+            scales[b] = (int8_t)s;
+    });
+}
+
 // ---------------------------------------------------------------- host side
 
 static int8_t *fixed_scales(void *state, int n, int dtype) {
@@ -690,6 +747,30 @@ int launch_fixed_tile_pass(void *state, int n, int dtype, const TileMap &tm_in, 
         SV_LAUNCH_CHECK();
     }
     return SV_OK;
+}
+
+template <typename Q, int NB>
+static int launch_fix_rt(char *codes, int8_t *sc, const TileMap &tm_in, const RtPass &p, const RtDevice &d,
+                         const DeviceGates &dg, hipStream_t st) {
+    TileMap tm = tm_in;
+    for (uint64_t t0 = 0; t0 < tm.ntiles; t0 += kMaxGridBlocks) {
+        tm.tile0 = t0;
+        const dim3 grid((unsigned)std::min(kMaxGridBlocks, tm_in.ntiles - t0));
+        hipLaunchKernelGGL((k_fix_rtile<Q, NB>), grid, dim3(1u << ((int)tm.m - NB)), p.lds, st, codes, sc, tm, p, d.ops,
+                           d.pats, dg.mm, dg);
+        SV_LAUNCH_CHECK();
+    }
+    return SV_OK;
+}
+
+int launch_fixed_rt_pass(void *state, int n, int dtype, const TileMap &tm, const RtPass &p, const RtDevice &d,
+                         const DeviceGates &dg, hipStream_t st) {
+    if (dtype != SV_CQ32 || tm.a < (uint32_t)kQBlockBits || !rt_tile_ok(SV_C128, (int)tm.m, false))
+        return fail(SV_EINVAL, "fixed-point register tile (m=%u, contiguous %u)", tm.m, tm.a);
+    char *codes = (char *)state;
+    int8_t *sc = fixed_scales(state, n, dtype);
+    return p.nb == 4 ? launch_fix_rt<Q32, 4>(codes, sc, tm, p, d, dg, st)
+                     : launch_fix_rt<Q32, 3>(codes, sc, tm, p, d, dg, st);
 }
 
 template <typename Q, typename RD> static int decode_to(const sv_state_t *dst, const sv_state_t *src, hipStream_t st) {
