@@ -843,7 +843,7 @@ def measure_extras(sv, W, torch, np, stream, with_layered, psi_host=None, cases=
         torch.cuda.synchronize()
         batch.set_timing(None)
         occ = batch_occupancy(np, stamps.cpu().numpy(), ns_tick, ns,
-                              min(len(items), 2 * torch.cuda.get_device_properties(0).multi_processor_count),
+                              min(len(items), 4 * torch.cuda.get_device_properties(0).multi_processor_count),
                               items)
         ngates = sum(len(c.gates) for c in circs)
         alg = sum(len(c.gates) * (1 << c.n) * 2 * (16 if dt == "c128" else 8) for c in circs)

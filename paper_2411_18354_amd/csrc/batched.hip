@@ -5,16 +5,15 @@
 // (an atomic counter; circuits ordered by decreasing cost so the longest ones
 // start first) and runs it alone, so no barrier ever spans workgroups and
 // every workgroup leaves the loop once the queue is empty.
-//  - A state that fits the workgroup's LDS (2^n amplitudes <= kBatchLds
-//    bytes) is read once, all gates are applied in LDS, and it is written
-//    back once.
-//  - A larger state is processed pass by pass from global memory with the
-//    circuit's fused plan (the same planner and tile code as single
-//    circuits): a fused run visits the state tile by tile, a tile being the
-//    2^m amplitudes that share the index bits outside the run's qubit set S,
-//    held in LDS while the run's operations act on it (pair gates, and
-//    diagonal sweeps through the phase tables); other gates are pair loops
-//    over the state.  A workgroup barrier separates passes.
+//  - A circuit follows its fused plan (the same planner and register tiles as
+//    single circuits, rtile.hpp): a fused run visits the state tile by tile,
+//    a tile being the 2^m amplitudes that share the index bits outside the
+//    run's qubit set S, held in the workgroup's registers while the run's
+//    operations act on it; other gates are pair loops over the state.  A
+//    workgroup barrier separates passes.  A state of at most one tile is read
+//    and written once per pass, mostly once in all.
+//  - The smallest states (below one wavefront of register tiles) are read
+//    into LDS, all gates are applied there, and written back.
 // Each gate visits only the amplitude pairs whose controls hold: the pair
 // index is built by inserting the target bit (0) and the control bits (their
 // values) into the iteration counter, lowest position first (Sec. III-B).
@@ -28,6 +27,7 @@
 #include "circuit.hpp"
 #include "gates.hpp"
 #include "pauli.hpp"
+#include "rtile.hpp"
 #include "tile_adj.hpp"
 
 namespace sv {
@@ -35,17 +35,25 @@ namespace sv {
 int validate_circuit_gate(int n, int nparams, const sv_gate_t &g, int index);
 int validate_unitary_gate(const sv_gate_t &g, int index);
 
+// Forward: workgroups of 256 lanes, four per CU (128 registers per lane),
+// with the exchange buffer of the widest tile (2^12 complex128 or 2^13
+// complex64 amplitudes; one component of each) before the work-item slot.
+// Bound by the tiles' arithmetic once every workgroup has work; with LDS
+// tiles (two workgroups of 512 lanes per CU, two barriers per operation) the
+// LDS bound it.  512 circuits of widths 10-20, 100-400 gates, complex128:
+// 21.9 ms with LDS tiles, 11.5 ms; 300 of widths 10-18, complex64: 1.89 ms,
+// 1.23 ms; 400 of widths 8-12: 0.49 ms, 0.42 ms.
+constexpr int kFwdThreads = 256, kFwdThreadBits = 8;
+constexpr unsigned kFwdPerCu = 4;
+constexpr size_t kBatchSlot = 64;
+constexpr size_t kFwdLds = kBatchSlot + 32768;
+// Adjoint: 512 lanes, or 1024 where the batch has at most one circuit per CU.
 constexpr int kBatchThreads = 512;
-constexpr int kBatchAdjMaxThreads = 1024;  // the batched adjoint's wider shape
+constexpr int kBatchAdjMaxThreads = 1024;
 // amplitudes per lane in flight when the batched adjoint writes a tile pair
 // back (the batched kernels have fewer registers to spare than the
-// single-circuit ones: they load tiles by direct HBM-to-LDS copies and the
-// forward one writes one amplitude at a time)
+// single-circuit ones: they load tiles by direct HBM-to-LDS copies)
 constexpr int kBatchCopy = 2;
-constexpr size_t kBatchLds = 65536;  // the tile (or a whole resident state)
-// dynamic LDS: the work-item slot, the tile, then the diagonal-sweep tables
-constexpr size_t kBatchSlot = 64;
-constexpr size_t kBatchDynLds = kBatchSlot + kBatchLds + sizeof(double) * diag_table_doubles(13);  // tile widths up to 13
 
 struct BGate {
     double m[8];      // matrix of a fixed gate
@@ -58,7 +66,8 @@ struct BGate {
 
 // One pass of a circuit's fused plan.
 struct BPass {
-    TileMap tm;       // fused: the tiles' qubit set (tm.tab set: tables reserved)
+    TileMap tm;       // fused: the tiles' qubit set
+    RtPass rt;        // fused, forward: the register tiles' operations
     int32_t fused;    // 1: tile descriptors [first, first + count); 0: gate `gate`
     int32_t gate;     // single: index among the circuit's gates
     int32_t first, count;
@@ -72,7 +81,8 @@ struct BPass {
 // A parameterised gate inside a fused run: its descriptor's matrix (and
 // phases) is recomputed from the angle before each batched run.
 struct BTileJob {
-    int32_t kind, param, tile, pad;
+    int32_t kind, param, tile;
+    int32_t op[2];    // forward: the operations holding its matrix, or -1
 };
 
 struct BCirc {
@@ -122,7 +132,7 @@ constexpr int kBatchPairUnroll = 4;  // pairs per lane per step of a pair loop
 // Apply one gate (target, controls) to amplitudes held at base[0 .. 2^nbits)
 // (LDS or global), controls below nbits enumerated, controls at or above
 // nbits already known to hold: the iteration indices [lo, min(hi, pairs)).
-template <typename R, typename I>
+template <typename R, typename I, int THREADS>
 __device__ __forceinline__ void gate_on_block_i(cplx_t<R> *base, int nbits, int target, uint64_t cmask,
                                                 uint64_t cvals, const Mat2<R> &mm, uint64_t lo, uint64_t hi) {
     const uint64_t lowm = (nbits >= 64) ? ~0ull : ((1ull << nbits) - 1);
@@ -133,12 +143,12 @@ __device__ __forceinline__ void gate_on_block_i(cplx_t<R> *base, int nbits, int 
     const I st = (I)1 << target;
     const I cv = (I)(cvals & cm);
     constexpr int U = kBatchPairUnroll;  // 2U loads in flight
-    for (I i0 = (I)lo + threadIdx.x; i0 < npairs; i0 += (I)U * kBatchThreads) {
+    for (I i0 = (I)lo + threadIdx.x; i0 < npairs; i0 += (I)U * THREADS) {
         cplx_t<R> x[U], y[U];
         I p1[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const I i = i0 + (I)u * kBatchThreads;
+            const I i = i0 + (I)u * THREADS;
             p1[u] = insert_bits<I>(i, pos, cv);
             if (i < npairs) {
                 x[u] = base[p1[u]];
@@ -147,7 +157,7 @@ __device__ __forceinline__ void gate_on_block_i(cplx_t<R> *base, int nbits, int 
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (i0 + (I)u * kBatchThreads < npairs) {
+            if (i0 + (I)u * THREADS < npairs) {
                 apply_pair<R>(mm, x[u], y[u]);
                 base[p1[u]] = x[u];
                 base[p1[u] | st] = y[u];
@@ -160,62 +170,80 @@ __device__ __forceinline__ void gate_on_block_i(cplx_t<R> *base, int nbits, int 
 // tiles; for global memory up to n = 32).
 template <typename R>
 __device__ __forceinline__ void gate_on_block(cplx_t<R> *base, int nbits, int target, uint64_t cmask, uint64_t cvals,
-                                              const Mat2<R> &mm, uint64_t lo = 0, uint64_t hi = ~0ull) {
+                                              const Mat2<R> &mm, uint64_t lo, uint64_t hi) {
     if (nbits <= 32)
-        gate_on_block_i<R, uint32_t>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint32_t, kFwdThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
     else
-        gate_on_block_i<R, uint64_t>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint64_t, kFwdThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
 }
+
+// Device tables of the forward run.
+struct FwdTables {
+    const BGate *gates;
+    const BPass *passes;
+    const TileGate *tiles;
+    const RtOp *ops;
+    const RtPat *pats;
+    const SweepMember *mems;
+    const double *params;
+};
 
 // Tiles [lo, hi) of a fused pass over the state in global memory.
 template <typename R>
-__device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, const TileGate *__restrict__ tiles,
-                                            const SweepPat *__restrict__ pats, const SweepMember *__restrict__ mems,
-                                            cplx_t<R> *lds, uint64_t lo, uint64_t hi) {
-    const DeviceGates dg{tiles + p.first, p.count, pats, mems};
-    const uint32_t T = 1u << p.tm.m;
+__device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, const FwdTables &d, unsigned char *lds,
+                                            uint64_t lo, uint64_t hi) {
+    constexpr int NB = rt_nb<R>();
+    const DeviceGates dg{d.tiles + p.first, p.count};
+    const int tb = (int)p.tm.m - NB;
     for (uint64_t tt = lo; tt < hi; ++tt) {
         const uint64_t base = expand_index<uint64_t>(p.tm.outer, tt);
-        if (!tile_touched(base, dg))
+        if (!p.rt.always && !tile_touched(base, dg))
             continue;  // uniform
-        tile_load_dma<R, kBatchThreads>(lds, psi, base, p.tm, T);
-        __syncthreads();
-        tile_run<R, kBatchThreads, false>(lds, base, p.tm, dg);  // at its register limit
-        tile_store<R, kBatchThreads, false, 1>(psi, lds, base, p.tm, T);
-        __syncthreads();
+        RtRegs<R, NB> v;
+        const uint32_t tid = rt_fresh(threadIdx.x);
+        const bool in = (tid >> tb) == 0;
+        const cplx_t<R> *src = psi + (base | rt_thread_offset(p.rt.in, in ? tid : 0u, tb));
+        SV_RT_FOR(1 << NB, r) {
+            const cplx_t<R> a = src[rt_reg_offset<NB>(p.rt.in, r)];
+            v.x[r] = rt_own(a.x);
+            v.y[r] = rt_own(a.y);
+        });
+        rt_run<R, NB, false, true>(v, lds, rt_xor_terms(tid, p.rt.in.slot), base, d.ops + p.rt.first, p.rt.count,
+                                   d.pats, d.mems, nullptr, tb);
+        const uint32_t tod = rt_fresh(threadIdx.x);
+        if ((tod >> tb) == 0) {
+            cplx_t<R> *dst = psi + (base | rt_thread_offset(p.rt.out, tod, tb));
+            SV_RT_FOR(1 << NB, r) {
+                cplx_t<R> a;
+                a.x = rt_own(v.x[r]);
+                a.y = rt_own(v.y[r]);
+                dst[rt_reg_offset<NB>(p.rt.out, r)] = a;
+            });
+        }
     }
 }
 
+// States held in LDS for the whole circuit, gate by gate: those whose
+// register tile would leave a wavefront's lanes without amplitudes.  (400
+// circuits of widths 8-9: 0.41 ms, as before the wider ones moved to
+// register tiles.)
+__host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 10 : 11; }
+
 template <typename R>
-__device__ void run_circuit_block(const BCirc &c, const BGate *__restrict__ gates, const BPass *__restrict__ passes,
-                                  const TileGate *__restrict__ tiles, const SweepPat *__restrict__ pats,
-                                  const SweepMember *__restrict__ mems, const double *__restrict__ params,
-                                  cplx_t<R> *lds) {
+__device__ void run_circuit_resident(const BCirc &c, const FwdTables &d, unsigned char *buf) {
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     const uint64_t N = 1ull << c.n;
-    if (N * sizeof(cplx_t<R>) <= kBatchLds) {
-        for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
-            lds[k] = psi[k];
+    cplx_t<R> *lds = reinterpret_cast<cplx_t<R> *>(buf);
+    for (uint64_t k = threadIdx.x; k < N; k += kFwdThreads)
+        lds[k] = psi[k];
+    __syncthreads();
+    for (int i = 0; i < c.ngates; ++i) {
+        const BGate &g = d.gates[c.first_gate + i];
+        gate_on_block<R>(lds, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), 0, ~0ull);
         __syncthreads();
-        for (int i = 0; i < c.ngates; ++i) {
-            const BGate &g = gates[c.first_gate + i];
-            gate_on_block<R>(lds, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, params, false));
-            __syncthreads();
-        }
-        for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
-            psi[k] = lds[k];
-        return;
     }
-    for (int pi = 0; pi < c.npasses; ++pi) {
-        const BPass &p = passes[c.first_pass + pi];
-        if (p.fused) {  // uniform
-            fused_tiles<R>(psi, p, tiles, pats, mems, lds, 0, p.tm.ntiles);
-        } else {
-            const BGate &g = gates[c.first_gate + p.gate];
-            gate_on_block<R>(psi, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, params, false));
-            __syncthreads();
-        }
-    }
+    for (uint64_t k = threadIdx.x; k < N; k += kFwdThreads)
+        psi[k] = lds[k];
 }
 
 // Wait (lane 0 polling, the workgroup held at a barrier) until *ctr >= target,
@@ -240,7 +268,9 @@ __device__ __forceinline__ void wait_count(unsigned int *ctr, unsigned int targe
     __syncthreads();
 }
 
-// A circuit split over several workgroups.  Every workgroup that joins it
+// A circuit's passes.  Alone (group < 0) a workgroup runs them in order, a
+// barrier between.
+// A circuit split over several workgroups: every workgroup that joins it
 // takes chunk tickets from the circuit's counter: the chunks of all passes
 // are numbered in program order, and a chunk of pass p starts once the
 // circuit's completion count has reached the first ticket of p.  Chunks of
@@ -250,57 +280,66 @@ __device__ __forceinline__ void wait_count(unsigned int *ctr, unsigned int targe
 // workgroups that have joined (one is enough); a workgroup that finds the
 // tickets used up goes back to the work queue.  Each tile or pair is
 // computed exactly as by one workgroup, so results do not depend on the
-// split.
+// split.  (One loop for both: the tile code is in the kernel once.)
 template <typename R>
-__device__ void run_circuit_split(const BCirc &c, const BGate *__restrict__ gates, const BPass *__restrict__ passes,
-                                  const TileGate *__restrict__ tiles, const SweepPat *__restrict__ pats,
-                                  const SweepMember *__restrict__ mems, const double *__restrict__ params,
-                                  unsigned int *gstate, uint64_t limit, unsigned int *err, cplx_t<R> *lds,
-                                  int *slot) {
+__device__ void run_circuit(const BCirc &c, const FwdTables &d, unsigned int *gstate, uint64_t limit,
+                            unsigned int *err, unsigned char *buf, int *slot) {
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
+    const BPass *passes = d.passes + c.first_pass;
+    const bool split = c.group >= 0;  // uniform
     unsigned int *next = gstate + 2 * c.group, *done = next + 1;
     int pi = 0, ready = -1;
     for (;;) {
-        if (threadIdx.x == 0)
-            *slot = (int)__hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int k = *slot;
-        __syncthreads();
-        if (k >= c.nchunks)
+        uint64_t lo = 0, hi = ~0ull;
+        if (split) {
+            if (threadIdx.x == 0)
+                *slot = (int)__hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int k = __builtin_amdgcn_readfirstlane(*slot);
+            __syncthreads();
+            if (k >= c.nchunks)
+                break;
+            while (k >= passes[pi].chunk0 + passes[pi].nchunks)
+                ++pi;  // tickets only grow
+            if (ready != pi) {
+                wait_count(done, (unsigned int)passes[pi].chunk0, limit, err);
+                ready = pi;
+            }
+            lo = (uint64_t)(k - passes[pi].chunk0) * passes[pi].chunk_len;
+            hi = lo + passes[pi].chunk_len;
+        } else if (pi >= c.npasses) {
             break;
-        while (k >= passes[c.first_pass + pi].chunk0 + passes[c.first_pass + pi].nchunks)
-            ++pi;  // tickets only grow
-        const BPass &p = passes[c.first_pass + pi];
-        if (ready != pi) {
-            wait_count(done, (unsigned int)p.chunk0, limit, err);
-            ready = pi;
         }
-        const uint64_t lo = (uint64_t)(k - p.chunk0) * p.chunk_len;
+        const BPass &p = passes[pi];
         if (p.fused) {  // uniform
-            const uint64_t hi = lo + p.chunk_len < p.tm.ntiles ? lo + p.chunk_len : p.tm.ntiles;
-            fused_tiles<R>(psi, p, tiles, pats, mems, lds, lo, hi);
+            fused_tiles<R>(psi, p, d, buf, lo, hi < p.tm.ntiles ? hi : p.tm.ntiles);
         } else {
-            const BGate &g = gates[c.first_gate + p.gate];
-            gate_on_block<R>(psi, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, params, false), lo,
-                             lo + p.chunk_len);
+            const BGate &g = d.gates[c.first_gate + p.gate];
+            gate_on_block<R>(psi, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), lo, hi);
         }
-        // Publish the chunk: every wavefront waits until its own stores have
-        // reached the L2 (a workgroup barrier alone does not wait for them),
-        // then lane 0's device-scope release writes the L2 back once and
-        // counts the chunk.  (A release in every wavefront writes the L2 back
-        // eight times: a 256-circuit batch of width 16 ran 2.95 ms against
-        // 2.15 ms this way.)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (split) {
+            // Publish the chunk: every wavefront waits until its own stores
+            // have reached the L2 (a workgroup barrier alone does not wait
+            // for them), then lane 0's device-scope release writes the L2
+            // back once and counts the chunk.  (A release in every wavefront
+            // writes the L2 back once for each: a 256-circuit batch of width
+            // 16 ran 2.95 ms against 2.15 ms this way.)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (threadIdx.x == 0)
+                __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            __syncthreads();
+            ++pi;
+        }
     }
 }
 
 // Angles of the parameterised gates inside fused runs, into their tile
-// descriptors (matrix, and phases of diagonal ones).
+// descriptors (matrix, and phases of diagonal ones) and register operations.
 __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs, const double *__restrict__ params,
-                                    TileGate *__restrict__ tiles, SweepMember *__restrict__ mems) {
+                                    TileGate *__restrict__ tiles, SweepMember *__restrict__ mems,
+                                    RtOp *__restrict__ ops, int ops_f32) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= njobs)
         return;
@@ -316,40 +355,47 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
             if (mems && t.mem[s] >= 0)
                 mems[t.mem[s]].theta = t.ph[s];
     }
+    if (ops)
+        for (int s = 0; s < 2; ++s)
+            if (j.op[s] >= 0)
+                rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
 }
 
 // Work items: items[i] is a circuit; a circuit split over workgroups appears
 // once per workgroup that may join it.
 template <typename R>
-__global__ __launch_bounds__(kBatchThreads, 4) void k_batched(const BCirc *__restrict__ circs,
-                                                           const int32_t *__restrict__ items, int nitems,
-                                                           const BGate *__restrict__ gates,
-                                                           const BPass *__restrict__ passes,
-                                                           const TileGate *__restrict__ tiles,
-                                                           const SweepPat *__restrict__ pats,
-                                                           const SweepMember *__restrict__ mems,
-                                                           const double *__restrict__ params,
-                                                           unsigned int *__restrict__ queue,
-                                                           unsigned int *gstate, uint64_t limit,
-                                                           unsigned int *err, uint64_t *__restrict__ stamps) {
-    extern __shared__ unsigned char lds_raw[];
-    int *item = reinterpret_cast<int *>(lds_raw);
+__global__ __launch_bounds__(kFwdThreads, 4) void k_batched(const BCirc *__restrict__ circs,
+                                                         const int32_t *__restrict__ items, int nitems,
+                                                         const BGate *__restrict__ gates,
+                                                         const BPass *__restrict__ passes,
+                                                         const TileGate *__restrict__ tiles,
+                                                         const RtOp *__restrict__ ops,
+                                                         const RtPat *__restrict__ pats,
+                                                         const SweepMember *__restrict__ mems,
+                                                         const double *__restrict__ params,
+                                                         unsigned int *__restrict__ queue, unsigned int *gstate,
+                                                         uint64_t limit, unsigned int *err,
+                                                         uint64_t *__restrict__ stamps) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    // the exchange buffer first: its addresses step by xor
+    unsigned char *buf = lds_raw;
+    int *item = reinterpret_cast<int *>(lds_raw + (kFwdLds - kBatchSlot));
     int *ticket = item + 1;
-    cplx_t<R> *lds = reinterpret_cast<cplx_t<R> *>(lds_raw + kBatchSlot);
+    const FwdTables d{gates, passes, tiles, ops, pats, mems, params};
     for (;;) {
         if (threadIdx.x == 0)
             *item = (int)atomicAdd(queue, 1u);
         __syncthreads();
-        const int it = *item;
+        const int it = __builtin_amdgcn_readfirstlane(*item);  // uniform: descriptors are scalar loads
         __syncthreads();
         if (it >= nitems)
             break;
         const uint64_t t0 = stamps ? wall_clock64() : 0;
         const BCirc &c = circs[items[it]];
-        if (c.group >= 0)  // uniform
-            run_circuit_split<R>(c, gates, passes, tiles, pats, mems, params, gstate, limit, err, lds, ticket);
+        if (c.n < resident_below(sizeof(R) == 8))  // uniform
+            run_circuit_resident<R>(c, d, buf);
         else
-            run_circuit_block<R>(c, gates, passes, tiles, pats, mems, params, lds);
+            run_circuit<R>(c, d, gstate, limit, err, buf, ticket);
         __syncthreads();
         if (stamps && threadIdx.x == 0) {
             stamps[2 * it] = t0;
@@ -525,9 +571,9 @@ struct CircBuild {
     std::vector<BGate> gates;
     std::vector<BPass> passes;     // forward plan (circuit-local indices)
     std::vector<TileGate> tiles;
-    std::vector<SweepPat> pats;    // phase patterns of the table sweeps (circuit-local)
-    std::vector<SweepMember> mems;
-    std::vector<BTileJob> jobs;    // tile indices circuit-local
+    PlanRt rt;                     // register tile operations (circuit-local)
+    std::vector<SweepMember> mems; // members of their phase patterns
+    std::vector<BTileJob> jobs;    // tile and operation indices circuit-local
     // adjoint: the reverse sweep's fused plan, each descriptor's generator
     // slot (circuit-local, -1 none), each slot's parameter (batch-global)
     std::vector<BPass> apasses;
@@ -567,7 +613,7 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
     bc.lam = adjoint ? A.lams[c].data : nullptr;
     bc.n = s.n;
     // the fused tiles must fit the workgroup's LDS buffer
-    const int m_cap = dtype == SV_C128 ? 12 : 13;  // 2^m amplitudes <= kBatchLds bytes
+    const int m_cap = rt_nb_of(dtype) + kFwdThreadBits;  // one workgroup's registers
     const int tl = tuning().tile_log2[dtype == SV_C128 ? 0 : 1];
     bc.m = std::min(std::min(tl, s.n), m_cap);
     bc.ngates = (int32_t)(g1 - g0);
@@ -579,12 +625,13 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
             if (adjoint)
                 SV_TRY(validate_unitary_gate(A.gates[i], (int)(i - g0)));
         }
-        const bool resident = ((size_t)1 << s.n) * amp_bytes(dtype) <= kBatchLds;
+        const bool resident = s.n < resident_below(dtype == SV_C128);
         if (!adjoint && !resident) {
             std::vector<PlanPass> pp;
             int m_used = 0;
+            std::vector<SweepPat> pats;
             SV_TRY(circuit_plan_tiles(s.n, dtype, A.gates + g0, bc.ngates, (int)(p1 - p0), m_cap, &pp, &out->tiles,
-                                      &m_used, &out->pats, &out->mems));
+                                      &m_used, &pats, &out->mems, &out->rt));
             if (m_used != bc.m)
                 return fail(SV_EINVAL, "planner tile width %d != %d", m_used, bc.m);
             for (const PlanPass &q : pp) {
@@ -597,16 +644,16 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
                 if (q.fused) {
                     if (q.tm.m > (uint32_t)m_cap)
                         return fail(SV_EINVAL, "tile width %u beyond the batch limit", q.tm.m);
+                    if (!q.rt || q.rp.lds > kFwdLds - kBatchSlot)
+                        return fail(SV_EINVAL, "fused pass beyond the batch's register tiles");
                     b.tm = q.tm;
-                    b.tm.tab = 1;  // the launch reserves the tables
+                    b.rt = q.rp;
                 }
                 out->passes.push_back(b);
             }
-            for (size_t t = 0; t < out->tiles.size(); ++t) {
-                const sv_gate_t &g = A.gates[g0 + out->tiles[t].src_gate];
-                if (g.param >= 0)
-                    out->jobs.push_back(BTileJob{g.kind, (int32_t)(p0 + g.param), (int32_t)t, 0});
-            }
+            for (const ParamJob &j : out->rt.jobs)
+                if (j.tile_slot >= 0)
+                    out->jobs.push_back(BTileJob{j.kind, (int32_t)p0 + j.param, j.tile_slot, {j.op[0], j.op[1]}});
         }
     }
     bc.npasses = (int32_t)out->passes.size();
@@ -682,7 +729,7 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
             out->atslot.push_back(out->gen_of[f]);
             const sv_gate_t &g = A.gates[g0 + f];
             if (g.param >= 0)
-                out->ajobs.push_back(BTileJob{g.kind ^ SV_G_ADJOINT, (int32_t)(p0 + g.param), (int32_t)t, 0});
+                out->ajobs.push_back(BTileJob{g.kind ^ SV_G_ADJOINT, (int32_t)(p0 + g.param), (int32_t)t, {-1, -1}});
         }
         bc.napasses = (int32_t)out->apasses.size();
     }
@@ -713,7 +760,7 @@ struct BatchHost {
     std::vector<BGate> gates;
     std::vector<BPass> passes;
     std::vector<TileGate> tiles;
-    std::vector<SweepPat> pats;
+    RtProgram prog;
     std::vector<SweepMember> mems;
     std::vector<BTileJob> jobs;
     std::vector<BPass> apasses;
@@ -744,12 +791,12 @@ constexpr uint64_t kWaitLimitSeconds = 10;
 // slower, and so were 8 or 16 chunks per workgroup.
 constexpr int kChunksPerWorker = 4;
 
-static void split_circuits(BatchHost *h, const std::vector<double> &cost, std::vector<int32_t> *workers) {
+static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &cost, std::vector<int32_t> *workers) {
     const int gmax = tuning().batch_split;
     if (gmax <= 1)
         return;
     DeviceInfo di;
-    const double P = device_info(&di) == SV_OK ? 2.0 * di.num_cus : 512.0;  // persistent workgroups
+    const double P = (double)kFwdPerCu * (device_info(&di) == SV_OK ? di.num_cus : 256);  // persistent workgroups
     double W = 0.0;
     for (double c : cost)
         W += c;
@@ -757,8 +804,8 @@ static void split_circuits(BatchHost *h, const std::vector<double> &cost, std::v
     const int kc = kChunksPerWorker;
     for (size_t c = 0; c < h->circs.size(); ++c) {
         BCirc &bc = h->circs[c];
-        if (bc.npasses == 0 || !(cost[c] > load))
-            continue;  // LDS-resident, empty, or short enough
+        if (bc.npasses == 0 || bc.n <= rt_nb_of(dtype) + kFwdThreadBits || !(cost[c] > load))
+            continue;  // LDS-resident, empty, one workgroup's registers, or short enough
         const int g = (int)std::min<double>(gmax, std::ceil(cost[c] / load));
         if (g < 2 || (int64_t)bc.npasses * g * kc > (1 << 30))
             continue;
@@ -772,7 +819,7 @@ static void split_circuits(BatchHost *h, const std::vector<double> &cost, std::v
             } else {
                 const BGate &gt = h->gates[bc.first_gate + p.gate];
                 total = 1ull << (bc.n - 1 - popcount64(gt.cmask));
-                unit = (uint64_t)kBatchPairUnroll * kBatchThreads;
+                unit = (uint64_t)kBatchPairUnroll * kFwdThreads;
             }
             const uint64_t steps = (total + unit - 1) / unit;
             const uint64_t want = std::max<uint64_t>(1, std::min<uint64_t>(steps, (uint64_t)g * kc));
@@ -869,30 +916,37 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         b.bc.first_gate = (int32_t)h->gates.size();
         b.bc.first_term = (int32_t)h->terms.size();
         b.bc.first_pass = (int32_t)h->passes.size();
-        const int32_t tbase = (int32_t)h->tiles.size();
+        const int32_t tbase = (int32_t)h->tiles.size(), obase = (int32_t)h->prog.ops.size();
+        const uint32_t pbase = (uint32_t)h->prog.pats.size(), mbase = (uint32_t)h->mems.size();
         for (BPass p : b.passes) {
-            if (p.fused)
+            if (p.fused) {
                 p.first += tbase;
+                p.rt.first += (uint32_t)obase;
+            }
             h->passes.push_back(p);
         }
         for (BTileJob j : b.jobs) {
             j.tile += tbase;
+            for (int s = 0; s < 2; ++s)
+                if (j.op[s] >= 0)
+                    j.op[s] += obase;
             h->jobs.push_back(j);
         }
-        // phase patterns: rebase the descriptors' and patterns' indices
-        const uint32_t pbase = (uint32_t)h->pats.size(), mbase = (uint32_t)h->mems.size();
+        for (RtOp o : b.rt.prog.ops) {
+            if (o.w[0] >> 3 == kRtPrep)
+                o.w[2] += pbase;
+            h->prog.ops.push_back(o);
+        }
+        for (RtPat p : b.rt.prog.pats) {
+            p.first += mbase;
+            h->prog.pats.push_back(p);
+        }
         for (TileGate t : b.tiles) {
-            if (t.diag) {
-                t.pat0 += pbase;
+            if (t.diag)
                 for (int s = 0; s < 2; ++s)
                     if (t.mem[s] >= 0)
                         t.mem[s] += (int32_t)mbase;
-            }
             h->tiles.push_back(t);
-        }
-        for (SweepPat p : b.pats) {
-            p.first += mbase;
-            h->pats.push_back(p);
         }
         h->mems.insert(h->mems.end(), b.mems.begin(), b.mems.end());
         const int32_t gbase = (int32_t)(h->gens.size() / 8);  // generator slots before this circuit's
@@ -922,7 +976,7 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
     }
     std::vector<int32_t> workers(A.ncirc, 1);
     if (!adjoint)
-        split_circuits(h, cost, &workers);
+        split_circuits(h, *dtype, cost, &workers);
     std::vector<int32_t> circ(A.ncirc);
     std::iota(circ.begin(), circ.end(), 0);
     std::stable_sort(circ.begin(), circ.end(),
@@ -937,7 +991,8 @@ struct BatchDevice {
     BGate *gates = nullptr;
     BPass *passes = nullptr;
     TileGate *tiles = nullptr;
-    SweepPat *pats = nullptr;
+    RtOp *ops = nullptr;
+    RtPat *pats = nullptr;
     SweepMember *mems = nullptr;
     BTileJob *jobs = nullptr;
     int njobs = 0;
@@ -962,7 +1017,7 @@ struct BatchDevice {
 // Stream-ordered release when async (after the kernels enqueued on st),
 // otherwise an immediate free.
 static void batch_release(BatchDevice *d, bool async, hipStream_t st) {
-    void *ps[] = {d->circs,  d->gates,  d->passes, d->tiles,  d->pats, d->mems, d->jobs,  d->apasses,
+    void *ps[] = {d->circs,  d->gates,  d->passes, d->tiles,  d->ops, d->pats, d->mems, d->jobs,  d->apasses,
                   d->atiles, d->ajobs,  d->atslot, d->slot_param, d->order, d->gen_of, d->gens,    d->terms,
                   d->queue, d->gstate};
     for (void *p : ps)
@@ -1001,7 +1056,9 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     if (r == SV_OK)
         r = dev_copy(&d->tiles, h.tiles, async, st, 1);
     if (r == SV_OK)
-        r = dev_copy(&d->pats, h.pats, async, st, 1);
+        r = dev_copy(&d->ops, h.prog.ops, async, st, 1);
+    if (r == SV_OK)
+        r = dev_copy(&d->pats, h.prog.pats, async, st, 1);
     if (r == SV_OK)
         r = dev_copy(&d->mems, h.mems, async, st, 1);
     if (r == SV_OK)
@@ -1063,42 +1120,34 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     return r;
 }
 
-static unsigned persistent_grid(int ncirc) {
+// Workgroups of a persistent launch, `per_cu` resident per CU.
+static unsigned persistent_grid(int ncirc, unsigned per_cu) {
     DeviceInfo di;
     if (device_info(&di) != SV_OK)
         return 256;
-    const unsigned g = (unsigned)di.num_cus * 2;  // two 512-lane workgroups per CU
-    return std::min<unsigned>(g, (unsigned)ncirc);
+    return std::min<unsigned>((unsigned)di.num_cus * per_cu, (unsigned)ncirc);
 }
 
 static int launch_forward(int dtype, const BatchDevice &d, int ncirc, const double *params, hipStream_t s,
                           uint64_t *stamps = nullptr) {
-    hipError_t a = dtype == SV_C128 ? hipFuncSetAttribute((const void *)k_batched<double>,
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                          (int)kBatchDynLds)
-                                    : hipFuncSetAttribute((const void *)k_batched<float>,
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                          (int)kBatchDynLds);
-    if (a != hipSuccess)
-        return fail(SV_EHIP, "LDS limit: %s", hipGetErrorString(a));
     (void)ncirc;
-    const unsigned grid = persistent_grid(d.nitems);
+    const unsigned grid = persistent_grid(d.nitems, kFwdPerCu);
     if (d.njobs > 0)
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.njobs + 255) / 256), dim3(256), 0, s, d.jobs, d.njobs, params,
-                           d.tiles, d.mems);
+                           d.tiles, d.mems, d.ops, dtype == SV_C64 ? 1 : 0);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
     if (d.ngroups > 0)  // the ticket counters, not the timeout count after them
         hipLaunchKernelGGL(k_zero_words, dim3((2 * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,
                            2 * d.ngroups);
     unsigned int *err = d.gstate ? d.gstate + 2 * d.ngroups : nullptr;
     if (dtype == SV_C128)
-        hipLaunchKernelGGL(k_batched<double>, dim3(grid), dim3(kBatchThreads), kBatchDynLds, s, d.circs, d.order,
-                           d.nitems, d.gates, d.passes, d.tiles, d.pats, d.mems, params, d.queue, d.gstate,
-                           d.wait_limit, err, stamps);
+        hipLaunchKernelGGL(k_batched<double>, dim3(grid), dim3(kFwdThreads), kFwdLds, s, d.circs, d.order, d.nitems,
+                           d.gates, d.passes, d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
+                           err, stamps);
     else
-        hipLaunchKernelGGL(k_batched<float>, dim3(grid), dim3(kBatchThreads), kBatchDynLds, s, d.circs, d.order,
-                           d.nitems, d.gates, d.passes, d.tiles, d.pats, d.mems, params, d.queue, d.gstate,
-                           d.wait_limit, err, stamps);
+        hipLaunchKernelGGL(k_batched<float>, dim3(grid), dim3(kFwdThreads), kFwdLds, s, d.circs, d.order, d.nitems,
+                           d.gates, d.passes, d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
+                           err, stamps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail(SV_EHIP, "batched launch failed: %s", hipGetErrorString(e));
@@ -1133,10 +1182,10 @@ static int launch_adjoint(int dtype, const BatchDevice &d, int ncirc, const doub
     DeviceInfo di;
     const int cus = device_info(&di) == SV_OK ? di.num_cus : 256;
     const bool wide = ncirc <= cus;
-    const unsigned grid = wide ? (unsigned)std::max(1, ncirc) : persistent_grid(ncirc);
+    const unsigned grid = wide ? (unsigned)std::max(1, ncirc) : persistent_grid(ncirc, 2);
     if (d.najobs > 0)
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.najobs + 255) / 256), dim3(256), 0, s, d.ajobs, d.najobs,
-                           params, d.atiles, nullptr);
+                           params, d.atiles, nullptr, nullptr, 0);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
     if (dtype == SV_C128)
         return wide ? go_adjoint<double, kBatchAdjMaxThreads>(d, ncirc, grid, lds, params, grad, loss, s, stamps)

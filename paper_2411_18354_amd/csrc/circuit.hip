@@ -17,6 +17,7 @@
 
 #include "circuit.hpp"
 #include "gates.hpp"
+#include "rtile.hpp"
 
 namespace sv {
 
@@ -44,12 +45,7 @@ __global__ void k_param_mats(const ParamJob *__restrict__ jobs, int njobs, const
     }
     for (int s = 0; s < 2; ++s)
         if (j.op[s] >= 0)
-            for (int k = 0; k < 8; ++k) {
-                if (ops_f32)
-                    ops[j.op[s]].f[k] = (float)m[k];
-                else
-                    ops[j.op[s]].m[k] = m[k];
-            }
+            rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
 }
 
 // Gates a and b commute when every qubit they share is, in each of them,
@@ -470,13 +466,13 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 // 13.4 us, n = 14: 17.8 against 15.5; n = 16: 21.2 against
                 // 21.9, n = 26: 232 against 255; 32-bit codes n = 13: 16.2
                 // against 14.7, n = 27: 476 against 574).
-                bool gather = tuning().fuse_perm && !c->dual && (c->dtype == SV_C128 || p.tm.ntiles <= 4) &&
+                bool gather = tuning().fuse_perm && !c->dual && !c->rt_nb && (c->dtype == SV_C128 || p.tm.ntiles <= 4) &&
                               (1u << m) <= 512u * (tdt == SV_C128 ? perm_per_lane<double>() : perm_per_lane<float>());
                 if (gather) {
                     mark_permutation_runs(&tiles[p.first], p.count);
                     gather = (int)tiles[p.first].perm_len == p.count;
                 }
-                if (c->want_rt && !gather && rt_tile_ok(tdt, m, c->dual)) {
+                if (c->want_rt && !gather && (c->rt_nb || rt_tile_ok(tdt, m, c->dual))) {
                     std::vector<RtGateInfo> info;
                     for (int k = p.first; k < p.first + p.count; ++k) {
                         const int gi = tiles[k].src_gate;
@@ -496,6 +492,7 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                     }
                     p.rt = true;
                     p.rp = build_rt_pass(p.tm, fmask, tdt, &tiles[p.first], p.count, info.data(), pats,
+                                         c->rt_nb ? c->rt_nb : rt_pass_nb(tdt, m, c->dual, p.tm.ntiles),
                                          tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->dual, c->prog);
                     for (int k = 0; k < p.count; ++k)
                         op_slot[tiles[p.first + k].src_gate] = {info[k].op, info[k].op2};
@@ -878,7 +875,7 @@ namespace sv {
 
 int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int m_cap,
                        std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, int *m_used,
-                       std::vector<SweepPat> *pats, std::vector<SweepMember> *mems) {
+                       std::vector<SweepPat> *pats, std::vector<SweepMember> *mems, PlanRt *rt) {
     if (dtype != SV_C128 && dtype != SV_C64)
         return fail(SV_EINVAL, "unknown dtype %d", dtype);
     if (n < 1 || n > max_qubits(dtype))
@@ -894,6 +891,9 @@ int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int
     c.nparams = nparams;
     c.m_cap = m_cap;
     c.max_lookahead = 1;  // thousands of circuits: the one-step lookahead keeps planning cheap
+    c.want_rt = rt != nullptr;
+    c.dual = rt && rt->dual;
+    c.rt_nb = rt ? rt_nb_of(dtype) : 0;
     c.gates.assign(gates, gates + ngates);
     std::vector<ParamJob> jobs;
     std::vector<double> mats;
@@ -917,7 +917,14 @@ int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int
         q.count = p.fused ? p.count : 1;
         if (p.fused)
             q.tm = p.tm;
+        q.rt = p.rt ? 1 : 0;
+        if (p.rt)
+            q.rp = p.rp;
         passes->push_back(q);
+    }
+    if (rt) {
+        rt->prog = std::move(c.prog);
+        rt->jobs = std::move(jobs);
     }
     if (m_used)
         *m_used = c.m;

@@ -48,6 +48,7 @@ struct sv_circuit {
     int max_lookahead = 2;  // cap on the planner's lookahead depth (one-shot plans and batches: 1)
     bool want_rt = false;  // plan fused runs for register tiles where their width allows
     bool dual = false;     // a reverse sweep: tiles of psi and lambda together
+    int rt_nb = 0;         // register bits of every register tile (0: chosen per pass)
     sv::RtProgram prog;             // their operations
     sv::RtDevice rt{nullptr, nullptr, nullptr};
     std::vector<sv_gate_t> gates;   // after the SV_REMAP relabelling, if any
@@ -88,12 +89,22 @@ namespace sv {
 struct PlanPass {
     TileMap tm;
     int32_t fused, gate, first, count;
+    int32_t rt;  // register tiles (when asked for): pass rp
+    RtPass rp;
+};
+// Register tiles for such executors: workgroups of 2^8 lanes with rt_nb_of
+// register bits run tiles of every width they take (dual: a reverse sweep).
+struct PlanRt {
+    bool dual = false;
+    RtProgram prog;
+    std::vector<ParamJob> jobs;
 };
 // pats/mems (optional): the phase patterns of the table sweeps, indexed
 // from 0 (pat0 and mem[] of the descriptors refer to them).
 int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int m_cap,
                        std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, int *m_used,
-                       std::vector<SweepPat> *pats = nullptr, std::vector<SweepMember> *mems = nullptr);
+                       std::vector<SweepPat> *pats = nullptr, std::vector<SweepMember> *mems = nullptr,
+                       PlanRt *rt = nullptr);
 
 // rt: fused runs on register tiles where their width allows (the caller runs
 // Pass::rt passes with launch_rt_pass).  dual: a reverse sweep; the gradient

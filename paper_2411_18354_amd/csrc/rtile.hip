@@ -148,35 +148,41 @@ uint32_t choose_regs(const std::vector<Unit> &units, int m, int nb, uint32_t fix
     return r;
 }
 
-RtIO make_io(const TileMap &tm, const Layout &L, uint32_t comp) {
+// Slot terms of a layout's thread bits; a thread bit beyond the tile's leads
+// past the tile's slots (2^top of them).
+void thread_terms(uint32_t *t, const Layout &L, uint32_t comp, int top) {
+    const int tb = (int)L.thr.size();
+    for (int i = 0; i < kRtMaxThreadBits; ++i)
+        t[i] = (i < tb ? rt_slot(1u << L.thr[i]) : 1u << (top + i - tb)) * comp;
+}
+
+RtIO make_io(const TileMap &tm, const Layout &L, uint32_t comp, int top) {
     RtIO io;
     memset(&io, 0, sizeof(io));
     auto global = [&](int q) { return (uint8_t)(q < (int)tm.a ? q : (int)tm.hpos[q - (int)tm.a]); };
-    for (size_t i = 0; i < L.thr.size(); ++i) {
+    for (size_t i = 0; i < L.thr.size(); ++i)
         io.tq[i] = global(L.thr[i]);
-        io.slot[i] = rt_slot(1u << L.thr[i]) * comp;
-    }
+    thread_terms(io.slot, L, comp, top);
     for (size_t k = 0; k < L.reg.size(); ++k)
         io.rq[k] = global(L.reg[k]);
     return io;
 }
 
-// comp: bytes of a component; top: slot bit of the register bit that tells psi
-// and lambda apart (-1: none)
-RtOp exchange_op(const Layout &from, const Layout &to, uint32_t comp, int top) {
+// comp: bytes of a component; dual: a further register bit tells psi and
+// lambda apart
+RtOp exchange_op(const Layout &from, const Layout &to, uint32_t comp, int m, bool dual) {
     RtOp o;
     memset(&o, 0, sizeof(o));
     o.w[0] = kRtExch * 8;
     o.w[5] = rt_jump(kRtEntryExch);
     static const int at[kRtMaxNB] = {2, 3, 4, 6, 7};
-    for (size_t i = 0; i < to.thr.size(); ++i)
-        o.t[i] = rt_slot(1u << to.thr[i]) * comp;
+    thread_terms(o.t, to, comp, dual ? m + 1 : m);
     for (size_t k = 0; k < to.reg.size(); ++k) {
         o.w[at[k]] = rt_slot(1u << from.reg[k]) * comp;
         o.w[8 + k] = rt_slot(1u << to.reg[k]) * comp;
     }
-    if (top >= 0)
-        o.w[at[to.reg.size()]] = o.w[8 + to.reg.size()] = (1u << top) * comp;
+    if (dual)
+        o.w[at[to.reg.size()]] = o.w[8 + to.reg.size()] = (1u << m) * comp;
     return o;
 }
 
@@ -216,10 +222,10 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *m, bool diag) {
 }
 
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *t, int count,
-                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, bool dual,
+                     RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
                      RtProgram &prog) {
     // nr: register bits of the layouts; nb: with the bit telling psi and lambda apart
-    const int m = (int)tm.m, nb = rt_pass_nb(tile_dt, m, dual, tm.ntiles), nr = nb - (dual ? 1 : 0);
+    const int m = (int)tm.m, nr = nb - (dual ? 1 : 0);
     RtPass pass;
     memset(&pass, 0, sizeof(pass));
     pass.nb = (uint32_t)nb;
@@ -235,7 +241,7 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
         Unit u;
         u.first = k;
         u.count = 1;
-        u.phase = t[k].diag && t[k].sweep_phase;
+        u.phase = t[k].diag && t[k].sweep_phase && m >= 7;  // narrower runs have no phase patterns
         if (u.phase)
             u.count = std::max(1, (int)t[k].sweep_len);
         u.diag = info[k].kind == kRtDiag;
@@ -460,7 +466,7 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
     auto io_ok = [&](uint32_t r) { return (r & io_fixed) == io_fixed && !(r & ~(io_allowed | io_fixed)); };
     uint32_t r = choose_regs(units, m, nr, io_fixed, io_allowed);
     Layout cur = make_layout(m, r, block);
-    pass.in = make_io(tm, cur, comp);
+    pass.in = make_io(tm, cur, comp, dual ? m + 1 : m);
     bool exch = false;
     while (true) {
         Deferred d;
@@ -487,7 +493,7 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
                 r = rs;
         }
         const Layout next = make_layout(m, r, last && block);
-        prog.ops.push_back(exchange_op(cur, next, comp, dual ? m : -1));
+        prog.ops.push_back(exchange_op(cur, next, comp, m, dual));
         exch = true;
         cur = next;
     }
@@ -496,11 +502,11 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
         if (!block)
             keep = r & io_allowed;
         const Layout next = make_layout(m, choose_regs({}, m, nr, io_fixed | keep, io_allowed), block);
-        prog.ops.push_back(exchange_op(cur, next, comp, dual ? m : -1));
+        prog.ops.push_back(exchange_op(cur, next, comp, m, dual));
         exch = true;
         cur = next;
     }
-    pass.out = make_io(tm, cur, comp);
+    pass.out = make_io(tm, cur, comp, dual ? m + 1 : m);
     pass.count = (uint32_t)prog.ops.size() - pass.first;
     if (exch)
         lds = std::max(lds, ((size_t)(dual ? 2 : 1) << m) * comp);

@@ -49,6 +49,16 @@ template <int N, typename F> __device__ __forceinline__ void rt_for(const F &f) 
 }
 #define SV_RT_FOR(N, i) rt_for<(N)>([&](auto i) __attribute__((always_inline))
 
+// A matrix formed on the device into an operation.
+__device__ __forceinline__ void rt_set_matrix(RtOp &o, bool f32, const double *m) {
+    for (int k = 0; k < 8; ++k) {
+        if (f32)
+            o.f[k] = (float)m[k];
+        else
+            o.m[k] = m[k];
+    }
+}
+
 template <typename R> __device__ __forceinline__ Mat2<R> rt_mat(const RtOp &o) {
     if constexpr (sizeof(R) == 8)
         return Mat2<R>{o.m[0], o.m[1], o.m[2], o.m[3], o.m[4], o.m[5], o.m[6], o.m[7]};
@@ -186,12 +196,13 @@ __device__ __forceinline__ uint32_t rt_xor_terms(uint32_t tid, const uint32_t *t
 // A run's operations on the tile in registers.  slot: the lane's byte offset
 // in the exchange buffer in the current layout.  GRAD: the reverse sweep; accl
 // holds one accumulator per parameterised gate and wavefront (accl[k * nw +
-// wavefront]).
-template <typename R, int NB, bool GRAD = false>
+// wavefront]).  tb: thread bits of the tile; in a wider workgroup (PART) the
+// lanes beyond them only take part in the exchanges, on slots of their own.
+template <typename R, int NB, bool GRAD = false, bool PART = false>
 __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uint32_t slot, uint64_t base,
                                        const RtOp *__restrict__ ops, uint32_t count,
                                        const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems,
-                                       double *accl = nullptr) {
+                                       double *accl = nullptr, int tb = kRtMaxThreadBits) {
     const uint32_t tid = threadIdx.x;
     // LDS byte address of the buffer
     const uint32_t buf = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
@@ -232,6 +243,8 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
             }
         }
         uint32_t sa = buf + slot, na = buf + next;
+        if (PART && kind != kRtExch)
+            lanes &= __ballot((tid >> tb) == 0);
         if constexpr (GRAD) {
             double g[4] = {0.0, 0.0, 0.0, 0.0};
             rt_apply_grad(v, w, m, fr, fi, lanes, buf, sa, na, g);

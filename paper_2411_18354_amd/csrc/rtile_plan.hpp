@@ -73,7 +73,8 @@ struct RtPat {
 };
 
 // Where a layout's amplitudes live in global memory: the qubits of its
-// thread and register bits, and the slot terms (bytes) of its thread bits.
+// thread and register bits, and the slot terms (bytes) of its thread bits (those
+// beyond the tile's give the lanes of a wider workgroup slots of their own).
 struct RtIO {
     uint8_t tq[kRtMaxThreadBits], rq[kRtMaxNB];
     uint32_t slot[kRtMaxThreadBits];
@@ -123,11 +124,11 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag)
 // that stay thread bits where tiles are loaded and stored (whole 128-byte
 // lines); block: fixed-point tiles, loaded and stored with tile-local bits 0
 // and 1 in registers and 2..5 on the lowest lane bits instead.
-// dual: the reverse sweep's passes.
+// nb: register bits (rt_pass_nb, or rt_nb_of).  dual: the reverse sweep's passes.
 // fixed_mask: outer index bits every launched tile has with the required
 // values.
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *tiles, int count,
-                     RtGateInfo *info, const std::vector<SweepPat> &pats, int coal, bool block, bool dual,
+                     RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
                      RtProgram &prog);
 
 // One pass over a complex128 or complex64 state.

@@ -175,3 +175,25 @@ def test_runs_of_x_only(gpu, dtype, n):
         ref = oracle.run_circuit(c, psi0=psi.cpu().numpy().astype(np.complex128))
         gpu.Circuit(n, c, dtype=gpu.SV_C128 if dtype == "c128" else gpu.SV_C64).run(psi)
         assert np.array_equal(psi.cpu().numpy().astype(np.complex128), ref)
+
+
+@pytest.mark.parametrize("dtype,m", [("c128", m) for m in (8, 10, 11, 12)] + [("c64", m) for m in (8, 11, 12, 13)])
+def test_batched(gpu, dtype, m):
+    """Batched circuits on a workgroup of 256 lanes: tiles that leave part of
+    a wavefront or whole wavefronts idle, states of one tile and of many, the
+    smallest states on register tiles and the largest that stay in LDS."""
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    ns = [9, 10, 11, 12, 13, 14, 15, 10]
+    circs = [_random_circuit(n, 90, 50 * m + i, params=8) for i, n in enumerate(ns)]
+    circs[-1] = W.Circuit(ns[-1], _diagonal_circuit(ns[-1], 60, m).gates, np.zeros(0))
+    psi0 = [W.random_state(n, 5 + i) for i, n in enumerate(ns)]
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    psis = [torch.tensor(p, device="cuda").to(tdt) for p in psi0]
+    starts = [p.cpu().numpy().astype(np.complex128) for p in psis]
+    params = torch.tensor(np.concatenate([c.params for c in circs]), device="cuda")
+    gpu.sv_apply_circuits_batched(psis, circs, params)
+    for c, psi, start in zip(circs, psis, starts):
+        ref = oracle.run_circuit(c, params=c.params, psi0=start)
+        got = psi.cpu().numpy().astype(np.complex128)
+        slack = 2 * np.pi * 60 ** 2 * 2.0 ** -53 if c is circs[-1] else 0.0
+        assert np.abs(got - ref).max() <= (TOL[dtype] + slack) * np.abs(ref).max()
