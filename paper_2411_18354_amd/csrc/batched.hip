@@ -781,14 +781,24 @@ struct BatchHost {
 constexpr uint64_t kWaitLimitSeconds = 10;
 
 // A circuit that costs more than the batch's mean load per workgroup is
-// split into that many workgroups' worth of work items (at most the
-// "batch_split" knob): else the widest circuits, started first, still run
-// long after the rest of the batch is done.  A split circuit's passes are cut
-// into chunk tickets of whole tiles (fused passes) or whole pair-loop steps
-// (single gates), kChunksPerWorker per joining workgroup.  Measured on the
-// 4096-circuit batch (widths 10-20): splitting also the circuits above a
-// quarter or a half of the mean load, or into items of half of it, was
-// slower, and so were 8 or 16 chunks per workgroup.
+// split into that many workgroups' worth of work items (rounded; at most the
+// "batch_split" knob, and the tiles or pair steps of its largest pass): else
+// the widest circuits, started first, still run long after the rest of the
+// batch is done.  A split circuit's passes are cut into chunk tickets of whole
+// tiles (fused passes) or whole pair-loop steps (single gates),
+// kChunksPerWorker per joining workgroup.  Measured on the 4096-circuit batch
+// (widths 10-20), with LDS tiles: splitting also the circuits above a quarter
+// or a half of the mean load, or into items of half of it, was slower, and so
+// were 8 or 16 chunks per workgroup.
+//  - Rounded: rounded up, the items outnumber the workgroups, and the last
+//    circuits' items all wait for a second turn (128 circuits of 16 qubits:
+//    1094 items for 1024 workgroups, 1.46 ms, against 1.23 ms); rounded down,
+//    circuits of nearly twice the mean stay whole (512 of widths 10-20: 12.8
+//    ms, against 11.1 ms).
+//  - A knob of 64: 64 circuits of widths 10-18 took 1.27 ms with at most 16
+//    workgroups each, 0.52 ms with 64; four of width 18 0.91 and 0.39 ms; the
+//    512 circuits the same.  Workgroups beyond a pass's tiles would only wait
+//    (the 64 circuits: 0.64 ms without that limit).
 constexpr int kChunksPerWorker = 4;
 
 static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &cost, std::vector<int32_t> *workers) {
@@ -806,22 +816,28 @@ static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &c
         BCirc &bc = h->circs[c];
         if (bc.npasses == 0 || bc.n <= rt_nb_of(dtype) + kFwdThreadBits || !(cost[c] > load))
             continue;  // LDS-resident, empty, one workgroup's registers, or short enough
-        const int g = (int)std::min<double>(gmax, std::ceil(cost[c] / load));
+        // a pass's tiles or pairs, and how many of them a workgroup takes at least
+        auto extent = [&](const BPass &p, uint64_t *total, uint64_t *unit) {
+            if (p.fused) {
+                *total = p.tm.ntiles;
+                *unit = 1;
+            } else {
+                const BGate &gt = h->gates[bc.first_gate + p.gate];
+                *total = 1ull << (bc.n - 1 - popcount64(gt.cmask));
+                *unit = (uint64_t)kBatchPairUnroll * kFwdThreads;
+            }
+            return (*total + *unit - 1) / *unit;
+        };
+        uint64_t total, unit, most = 0;
+        for (int pi = 0; pi < bc.npasses; ++pi)
+            most = std::max(most, extent(h->passes[bc.first_pass + pi], &total, &unit));
+        const int g = (int)std::min<double>(std::min<double>(gmax, (double)most), std::floor(cost[c] / load + 0.5));
         if (g < 2 || (int64_t)bc.npasses * g * kc > (1 << 30))
             continue;
         int64_t k = 0;
         for (int pi = 0; pi < bc.npasses; ++pi) {
             BPass &p = h->passes[bc.first_pass + pi];
-            uint64_t total, unit;
-            if (p.fused) {
-                total = p.tm.ntiles;
-                unit = 1;
-            } else {
-                const BGate &gt = h->gates[bc.first_gate + p.gate];
-                total = 1ull << (bc.n - 1 - popcount64(gt.cmask));
-                unit = (uint64_t)kBatchPairUnroll * kFwdThreads;
-            }
-            const uint64_t steps = (total + unit - 1) / unit;
+            const uint64_t steps = extent(p, &total, &unit);
             const uint64_t want = std::max<uint64_t>(1, std::min<uint64_t>(steps, (uint64_t)g * kc));
             const uint64_t len = (steps + want - 1) / want * unit;
             p.chunk0 = (int32_t)k;

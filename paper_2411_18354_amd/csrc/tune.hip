@@ -32,7 +32,7 @@ Tuning &tuning() {
     //    256-lane workgroups and one pair per lane (10.8 ms against 12.5 ms
     //    with four per lane, 16.1 ms with 64-lane workgroups, whose many
     //    workgroups cost more when most lanes only test and exit).
-    static Tuning t = {{3, 4}, 1, 1, {12, 13}, {3, 5}, 2, 4, 16, 1, 1, 256, 1, 1, 2, 1, 16, {4, 8}};
+    static Tuning t = {{3, 4}, 1, 1, {12, 13}, {3, 5}, 2, 4, 16, 1, 1, 256, 1, 1, 2, 1, 64, {4, 8}};
     return t;
 }
 
