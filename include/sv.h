@@ -477,7 +477,9 @@ int sv_apply_circuits_batched(const sv_state_t *states, int ncirc, const sv_gate
  * distinct workspace state of the same shape, its Hamiltonian is
  * terms[term_offsets[c] .. term_offsets[c+1]) (at least one term),
  * grad_dev[param_offsets[c] + j] receives dL_c/dtheta_j and loss_dev[c] the
- * loss.  One workgroup per circuit; sums are reduced in a fixed order.
+ * loss.  Circuits are split over workgroups as in the forward run; partial
+ * sums are added in a fixed order, so a batch gives the same gradients on
+ * every run (the grouping of the sums depends on the batch's circuits).
  * n <= 31 per circuit. */
 int sv_adjoint_grad_batched(const sv_state_t *psi_states, const sv_state_t *lam_states, int ncirc,
                             const sv_gate_t *gates, const int64_t *gate_offsets, const double *params_dev,
@@ -511,7 +513,8 @@ int sv_batch_destroy(sv_batch_t *b);
  * the device's constant-rate clock when a workgroup starts a work item
  * (stamps_dev[2i]) and when that workgroup has finished it (stamps_dev[2i +
  * 1]).  sv_batch_run's items are those sv_batch_info lists (i in queue
- * order); sv_batch_adjoint's are the circuits (i = c).  stamps_dev holds
+ * order); sv_batch_adjoint's are the circuits (i = c; the start of its first
+ * pass and the end of its last).  stamps_dev holds
  * 2 * max(ncirc, nitems) uint64 values on the batch's device and must
  * outlive those runs.  NULL turns the stamps off.  ns_per_tick (may be NULL)
  * receives the clock period in nanoseconds.  Results of the runs are

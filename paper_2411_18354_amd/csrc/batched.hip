@@ -28,14 +28,13 @@
 #include "gates.hpp"
 #include "pauli.hpp"
 #include "rtile.hpp"
-#include "tile_adj.hpp"
 
 namespace sv {
 
 int validate_circuit_gate(int n, int nparams, const sv_gate_t &g, int index);
 int validate_unitary_gate(const sv_gate_t &g, int index);
 
-// Forward: workgroups of 256 lanes, four per CU (128 registers per lane),
+// Workgroups of 256 lanes, four per CU (128 registers per lane),
 // with the exchange buffer of the widest tile (2^12 complex128 or 2^13
 // complex64 amplitudes; one component of each) before the work-item slot.
 // Bound by the tiles' arithmetic once every workgroup has work; with LDS
@@ -43,18 +42,10 @@ int validate_unitary_gate(const sv_gate_t &g, int index);
 // LDS bound it.  512 circuits of widths 10-20, 100-400 gates, complex128:
 // 21.9 ms with LDS tiles, 11.5 ms; 300 of widths 10-18, complex64: 1.89 ms,
 // 1.23 ms; 400 of widths 8-12: 0.49 ms, 0.42 ms.
-constexpr int kFwdThreads = 256, kFwdThreadBits = 8;
-constexpr unsigned kFwdPerCu = 4;
+constexpr int kBatchThreads = 256, kBatchThreadBits = 8;
+constexpr unsigned kBatchPerCu = 4;
 constexpr size_t kBatchSlot = 64;
-constexpr size_t kFwdLds = kBatchSlot + 32768;
-// Adjoint: 512 lanes, or 1024 where the batch has at most one circuit per CU.
-constexpr int kBatchThreads = 512;
-constexpr int kBatchAdjMaxThreads = 1024;
-// amplitudes per lane in flight when the batched adjoint writes a tile pair
-// back (the batched kernels have fewer registers to spare than the
-// single-circuit ones: they load tiles by direct HBM-to-LDS copies)
-constexpr int kBatchCopy = 2;
-
+constexpr size_t kBatchExchange = 32768, kBatchLds = kBatchExchange + kBatchSlot;
 struct BGate {
     double m[8];      // matrix of a fixed gate
     int32_t kind;     // matrix recomputed from params[param] when param >= 0
@@ -64,13 +55,22 @@ struct BGate {
     uint64_t cmask, cvals;
 };
 
-// One pass of a circuit's fused plan.
+// One pass of a circuit's fused plan.  The reverse sweep has two of its own:
+// lambda = H psi before the others (one partial sum: the loss) and the sums
+// over the partials after them; states below 2^kSweepLdsBelow amplitudes take
+// one pass for the gates, with psi and lambda in LDS.
+constexpr int32_t kPassGate = 0, kPassTiles = 1, kPassPauli = 2, kPassSums = 3, kPassSmall = 4;
+constexpr int kSweepLdsBelow = 5;  // fewer amplitudes than a lane's registers hold
 struct BPass {
     TileMap tm;       // fused: the tiles' qubit set
-    RtPass rt;        // fused, forward: the register tiles' operations
-    int32_t fused;    // 1: tile descriptors [first, first + count); 0: gate `gate`
+    RtPass rt;        // fused: the register tiles' operations
+    int32_t kind;     // kPassTiles: tile descriptors [first, first + count); kPassGate: gate `gate`; ..
     int32_t gate;     // single: index among the circuit's gates
     int32_t first, count;
+    // adjoint: gradient sums the pass leaves per chunk, chunk k's at
+    // part + k * nacc in the batch's partial sums
+    int32_t nacc;
+    int64_t part;
     // circuits split over several workgroups: the pass's chunks are tickets
     // [chunk0, chunk0 + nchunks) of the circuit, each chunk_len tiles (fused)
     // or pairs (single gate)
@@ -82,22 +82,30 @@ struct BPass {
 // phases) is recomputed from the angle before each batched run.
 struct BTileJob {
     int32_t kind, param, tile;
-    int32_t op[2];    // forward: the operations holding its matrix, or -1
+    int32_t op[2];    // the operations holding its matrix, or -1
 };
 
 struct BCirc {
     void *psi;
     void *lam;           // adjoint only
     int32_t n;
-    int32_t m;           // tile width of the fused plan
-    int32_t first_pass, npasses;  // forward: the fused plan
-    int32_t first_apass, napasses;  // adjoint: the fused plan of the reverse sweep
+    int32_t first_pass, npasses;  // the fused plan (adjoint: of the reverse sweep)
     int32_t first_gate;  // gates [first_gate, first_gate + ngates), in program order
     int32_t ngates;
     int32_t first_param, nparams;  // adjoint: gradient slots
     int32_t first_term, nterms;    // adjoint: Hamiltonian terms
-    int32_t group;       // forward: >= 0 when split over workgroups (its ticket counters)
-    int32_t nchunks;     // forward, split: tickets over all passes
+    int32_t first_gen;             // adjoint: first generator
+    int32_t first_slot, nslots;    // adjoint: partial sums, grouped by parameter, the loss last
+    int32_t first_csr;             // adjoint: each parameter's range among them
+    int32_t group;       // >= 0 when split over workgroups (its ticket counters)
+    int32_t nchunks;     // split: tickets over all passes
+};
+
+// Adjoint: a gate's gradient term (or the loss) as `count` partial sums at
+// first, first + stride, ...
+struct BSlot {
+    int64_t first;
+    int32_t stride, count;
 };
 
 // Insert the target bit (0) and the control bits (their values) into x,
@@ -172,13 +180,14 @@ template <typename R>
 __device__ __forceinline__ void gate_on_block(cplx_t<R> *base, int nbits, int target, uint64_t cmask, uint64_t cvals,
                                               const Mat2<R> &mm, uint64_t lo, uint64_t hi) {
     if (nbits <= 32)
-        gate_on_block_i<R, uint32_t, kFwdThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint32_t, kBatchThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
     else
-        gate_on_block_i<R, uint64_t, kFwdThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint64_t, kBatchThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
 }
 
-// Device tables of the forward run.
-struct FwdTables {
+// Device tables of a run.
+struct BatchTables {
+    const BCirc *circs;
     const BGate *gates;
     const BPass *passes;
     const TileGate *tiles;
@@ -186,11 +195,25 @@ struct FwdTables {
     const RtPat *pats;
     const SweepMember *mems;
     const double *params;
+    unsigned int *gstate;  // split circuits: ticket counters
+    uint64_t limit;        // clock ticks a chunk wait may take
+    unsigned int *err;     // counts waits that took longer
+    double *part;          // adjoint: partial sums
+};
+// The adjoint's others.
+struct SweepTables {
+    const DTerm *terms;
+    const double *gens;
+    const int32_t *gen_of;
+    const BSlot *slots;
+    const int32_t *csr;
+    double *grad, *loss;
+    uint64_t *stamps;      // start and end clock of every circuit, or none
 };
 
 // Tiles [lo, hi) of a fused pass over the state in global memory.
 template <typename R>
-__device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, const FwdTables &d, unsigned char *lds,
+__device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, const BatchTables &d, unsigned char *lds,
                                             uint64_t lo, uint64_t hi) {
     constexpr int NB = rt_nb<R>();
     const DeviceGates dg{d.tiles + p.first, p.count};
@@ -230,11 +253,11 @@ __device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, cons
 __host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 10 : 11; }
 
 template <typename R>
-__device__ void run_circuit_resident(const BCirc &c, const FwdTables &d, unsigned char *buf) {
+__device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsigned char *buf) {
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     const uint64_t N = 1ull << c.n;
     cplx_t<R> *lds = reinterpret_cast<cplx_t<R> *>(buf);
-    for (uint64_t k = threadIdx.x; k < N; k += kFwdThreads)
+    for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
         lds[k] = psi[k];
     __syncthreads();
     for (int i = 0; i < c.ngates; ++i) {
@@ -242,8 +265,206 @@ __device__ void run_circuit_resident(const BCirc &c, const FwdTables &d, unsigne
         gate_on_block<R>(lds, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), 0, ~0ull);
         __syncthreads();
     }
-    for (uint64_t k = threadIdx.x; k < N; k += kFwdThreads)
+    for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
         psi[k] = lds[k];
+}
+
+// ----------------------------------------------------------------- adjoint
+//
+// One circuit's gradients: lambda = H psi (and the loss), the reverse sweep
+// (the fused plan of the inverse circuit on register tiles holding psi and
+// lambda, as the single-circuit sweep has them, and single gates as pair
+// loops), then the sums.  Every chunk of a pass leaves its gradient terms as
+// partial sums (per wavefront, wavefronts in index order), which the last
+// pass adds in chunk and pass order: results are reproducible, and a circuit's
+// passes split over workgroups exactly as in the forward run.
+// Before, one workgroup of 512 or 1024 lanes took a whole circuit with both
+// tiles in LDS: bound by the LDS, and by few workgroups.  Ansatz circuits of
+// three layers, complex128: 160 of 15 qubits 4.71 -> 1.17 ms, 160 of 13 1.31 ->
+// 0.36 ms, 4 of 15 4.39 -> 0.27 ms, 600 of 8 0.63 -> 0.12 ms; complex64: 160 of
+// 15 2.36 -> 1.02 ms, 4 of 8 0.34 -> 0.11 ms.
+
+// Tiles [lo, hi) of a fused reverse pass.
+template <typename R>
+__device__ __forceinline__ void sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, const BPass &p, const BatchTables &d,
+                                            unsigned char *lds, uint64_t lo, uint64_t hi, int chunk) {
+    constexpr int NB = rt_nb<R>(), H = 1 << (NB - 1), NW = kBatchThreads / 64;
+    const DeviceGates dg{d.tiles + p.first, p.count};
+    const int tb = (int)p.tm.m - NB + 1;
+    double *accl = reinterpret_cast<double *>(lds + kBatchExchange);
+    for (uint32_t k = threadIdx.x; k < p.rt.acc_count * NW; k += kBatchThreads)
+        accl[k] = 0.0;
+    __syncthreads();
+    for (uint64_t tt = lo; tt < hi; ++tt) {
+        const uint64_t base = expand_index<uint64_t>(p.tm.outer, tt);
+        if (!p.rt.always && !tile_touched(base, dg))
+            continue;  // uniform
+        RtRegs<R, NB> v;
+        const uint32_t tid = rt_fresh(threadIdx.x);
+        const uint64_t src = base | rt_thread_offset(p.rt.in, (tid >> tb) == 0 ? tid : 0u, tb);
+        SV_RT_FOR(H, r) {
+            const cplx_t<R> a = psi[src + rt_reg_offset<NB - 1>(p.rt.in, r)];
+            v.x[r] = rt_own(a.x);
+            v.y[r] = rt_own(a.y);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        SV_RT_FOR(H, r) {
+            const cplx_t<R> a = lam[src + rt_reg_offset<NB - 1>(p.rt.in, r)];
+            v.x[r + H] = rt_own(a.x);
+            v.y[r + H] = rt_own(a.y);
+        });
+        rt_run<R, NB, true, true>(v, lds, rt_xor_terms(tid, p.rt.in.slot), base, d.ops + p.rt.first, p.rt.count,
+                                  d.pats, d.mems, accl, tb);
+        const uint32_t tod = rt_fresh(threadIdx.x);
+        if ((tod >> tb) == 0) {
+            const uint64_t dst = base | rt_thread_offset(p.rt.out, tod, tb);
+            SV_RT_FOR(H, r) {
+                const uint64_t k = dst + rt_reg_offset<NB - 1>(p.rt.out, r);
+                cplx_t<R> a, b;
+                a.x = rt_own(v.x[r]);
+                a.y = rt_own(v.y[r]);
+                b.x = rt_own(v.x[r + H]);
+                b.y = rt_own(v.y[r + H]);
+                psi[k] = a;
+                lam[k] = b;
+            });
+        }
+    }
+    __syncthreads();
+    double *part = d.part + p.part + (int64_t)chunk * p.nacc;
+    for (uint32_t k = threadIdx.x; k < p.rt.acc_count; k += kBatchThreads) {
+        double sum = 0.0;
+        for (int q = 0; q < NW; ++q)
+            sum += accl[k * NW + q];
+        part[k] = sum;
+    }
+}
+
+// One gate of the reverse sweep on the amplitudes at psi and lam (global
+// memory or LDS): gradient term (when parameterised) and un-apply, the pairs
+// [lo, min(hi, pairs)).  Returns the workgroup's sum of the term.
+template <typename R>
+__device__ __forceinline__ double sweep_gate(int n, const BGate &g, const double *gen, const double *params,
+                                          cplx_t<R> *psi, cplx_t<R> *lam, uint64_t lo, uint64_t hi,
+                                          double *scratch) {
+    const Mat2<R> ud = bgate_mat<R>(g, params, true);
+    const uint64_t pos = g.cmask | (1ull << g.target);
+    const uint64_t all = 1ull << (n - 1 - __popcll(g.cmask));
+    const uint64_t npairs = hi < all ? hi : all;
+    const uint64_t st = 1ull << g.target;
+    double acc = 0.0;
+    for (uint64_t it = lo + threadIdx.x; it < npairs; it += kBatchThreads) {
+        const uint64_t p1 = insert_bits<uint64_t>(it, pos, g.cvals);
+        cplx_t<R> x = psi[p1], y = psi[p1 | st], lx = lam[p1], ly = lam[p1 | st];
+        if (gen) {
+            const double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
+            const double axr = gen[0] * xr - gen[1] * xi + gen[2] * yr - gen[3] * yi;
+            const double axi = gen[0] * xi + gen[1] * xr + gen[2] * yi + gen[3] * yr;
+            const double ayr = gen[4] * xr - gen[5] * xi + gen[6] * yr - gen[7] * yi;
+            const double ayi = gen[4] * xi + gen[5] * xr + gen[6] * yi + gen[7] * yr;
+            acc += 2.0 * ((double)lx.x * axr + (double)lx.y * axi + (double)ly.x * ayr + (double)ly.y * ayi);
+        }
+        apply_pair<R>(ud, x, y);
+        apply_pair<R>(ud, lx, ly);
+        psi[p1] = x;
+        psi[p1 | st] = y;
+        lam[p1] = lx;
+        lam[p1 | st] = ly;
+    }
+    return gen ? block_sum(acc, scratch) : 0.0;  // uniform
+}
+
+// The other passes.
+template <typename R>
+__device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass &p, const BGate *gates,
+                                         const double *params, double *parts, SweepTables d, unsigned char *buf,
+                                         double *scratch, uint64_t lo, uint64_t hi, int chunk) {
+    cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
+    cplx_t<R> *lam = reinterpret_cast<cplx_t<R> *>(c.lam);
+    const uint64_t N = 1ull << c.n;
+    double *part = parts + p.part + (int64_t)chunk * p.nacc;
+    const int tid = (int)threadIdx.x;
+    if (p.kind == kPassGate) {
+        const int gs = d.gen_of[c.first_gate + p.gate];
+        const double sum = sweep_gate<R>(c.n, gates[c.first_gate + p.gate], gs >= 0 ? d.gens + 8 * gs : nullptr,
+                                         params, psi, lam, lo, hi, scratch);
+        if (gs >= 0 && tid == 0)
+            part[0] = sum;
+    } else if (p.kind == kPassPauli) {
+        if (d.stamps && chunk == 0 && tid == 0)
+            d.stamps[2 * ci] = wall_clock64();
+        const uint64_t end = hi < N ? hi : N;
+        double lp = 0.0;
+        for (uint64_t k = lo + tid; k < end; k += kBatchThreads) {
+            const cplx_t<R> at = psi[k];
+            cplx_t<R> v = at;
+            uint64_t X = 0;
+            double ar = 0.0, ai = 0.0;
+            for (int j = 0; j < c.nterms; ++j) {
+                const DTerm T = d.terms[c.first_term + j];
+                const uint64_t x = (uint64_t)T.idx;  // the term's x mask (stored in idx for the batch)
+                if (x != X) {  // uniform
+                    X = x;
+                    v = psi[k ^ X];
+                }
+                const double s = odd_parity(T.z & (k ^ X)) ? -T.coef : T.coef;
+                const double cr = re_ipow(T.ny, s, 0.0), cim = im_ipow(T.ny, s, 0.0);
+                ar += cr * (double)v.x - cim * (double)v.y;
+                ai += cr * (double)v.y + cim * (double)v.x;
+            }
+            cplx_t<R> o;
+            o.x = (R)ar;
+            o.y = (R)ai;
+            lam[k] = o;
+            lp += (double)at.x * ar + (double)at.y * ai;
+        }
+        const double sum = block_sum(lp, scratch);
+        if (tid == 0)
+            part[0] = sum;
+    } else if (p.kind == kPassSmall) {
+        cplx_t<R> *tp = reinterpret_cast<cplx_t<R> *>(buf), *tl = tp + N;
+        if ((uint64_t)tid < N) {
+            tp[tid] = psi[tid];
+            tl[tid] = lam[tid];
+        }
+        __syncthreads();
+        for (int f = c.ngates - 1; f >= 0; --f) {
+            const int gs = d.gen_of[c.first_gate + f];
+            const double sum = sweep_gate<R>(c.n, gates[c.first_gate + f], gs >= 0 ? d.gens + 8 * gs : nullptr,
+                                             params, tp, tl, 0, ~0ull, scratch);
+            if (gs >= 0 && tid == 0)
+                part[gs - c.first_gen] = sum;
+            __syncthreads();
+        }
+        if ((uint64_t)tid < N) {
+            psi[tid] = tp[tid];
+            lam[tid] = tl[tid];
+        }
+    } else {  // kPassSums: over the chunks, then over the gates that share a parameter
+        for (int s = tid; s < c.nslots; s += kBatchThreads) {
+            const BSlot a = d.slots[c.first_slot + s];
+            double *q = parts + a.first;
+            double sum = 0.0;
+#pragma unroll 8
+            for (int k = 0; k < a.count; ++k)
+                sum += q[(int64_t)k * a.stride];
+            q[0] = sum;
+        }
+        __syncthreads();
+        for (int j = tid; j <= c.nparams; j += kBatchThreads) {
+            const int s0 = d.csr[c.first_csr + j], s1 = d.csr[c.first_csr + j + 1];
+            double sum = 0.0;
+#pragma unroll 4
+            for (int s = s0; s < s1; ++s)
+                sum += parts[d.slots[c.first_slot + s].first];
+            if (j < c.nparams)
+                d.grad[c.first_param + j] = sum;
+            else
+                d.loss[ci] = sum;
+        }
+        if (d.stamps && tid == 0)
+            d.stamps[2 * ci + 1] = wall_clock64();
+    }
 }
 
 // Wait (lane 0 polling, the workgroup held at a barrier) until *ctr >= target,
@@ -281,16 +502,18 @@ __device__ __forceinline__ void wait_count(unsigned int *ctr, unsigned int targe
 // tickets used up goes back to the work queue.  Each tile or pair is
 // computed exactly as by one workgroup, so results do not depend on the
 // split.  (One loop for both: the tile code is in the kernel once.)
-template <typename R>
-__device__ void run_circuit(const BCirc &c, const FwdTables &d, unsigned int *gstate, uint64_t limit,
-                            unsigned int *err, unsigned char *buf, int *slot) {
+template <typename R, bool ADJ>
+__device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const SweepTables &a, unsigned char *buf,
+                                            double *scratch, int *slot) {
+    const BCirc &c = d.circs[ci];
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     const BPass *passes = d.passes + c.first_pass;
     const bool split = c.group >= 0;  // uniform
-    unsigned int *next = gstate + 2 * c.group, *done = next + 1;
+    unsigned int *next = d.gstate + 2 * c.group, *done = next + 1;
     int pi = 0, ready = -1;
     for (;;) {
         uint64_t lo = 0, hi = ~0ull;
+        int chunk = 0;  // of its pass
         if (split) {
             if (threadIdx.x == 0)
                 *slot = (int)__hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -302,17 +525,24 @@ __device__ void run_circuit(const BCirc &c, const FwdTables &d, unsigned int *gs
             while (k >= passes[pi].chunk0 + passes[pi].nchunks)
                 ++pi;  // tickets only grow
             if (ready != pi) {
-                wait_count(done, (unsigned int)passes[pi].chunk0, limit, err);
+                wait_count(done, (unsigned int)passes[pi].chunk0, d.limit, d.err);
                 ready = pi;
             }
-            lo = (uint64_t)(k - passes[pi].chunk0) * passes[pi].chunk_len;
+            chunk = k - passes[pi].chunk0;
+            lo = (uint64_t)chunk * passes[pi].chunk_len;
             hi = lo + passes[pi].chunk_len;
         } else if (pi >= c.npasses) {
             break;
         }
         const BPass &p = passes[pi];
-        if (p.fused) {  // uniform
-            fused_tiles<R>(psi, p, d, buf, lo, hi < p.tm.ntiles ? hi : p.tm.ntiles);
+        if (p.kind == kPassTiles) {  // uniform
+            const uint64_t end = hi < p.tm.ntiles ? hi : p.tm.ntiles;
+            if constexpr (ADJ)
+                sweep_tiles<R>(psi, reinterpret_cast<cplx_t<R> *>(c.lam), p, d, buf, lo, end, chunk);
+            else
+                fused_tiles<R>(psi, p, d, buf, lo, end);
+        } else if constexpr (ADJ) {
+            sweep_other<R>(c, ci, p, d.gates, d.params, d.part, a, buf, scratch, lo, hi, chunk);
         } else {
             const BGate &g = d.gates[c.first_gate + p.gate];
             gate_on_block<R>(psi, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), lo, hi);
@@ -361,27 +591,22 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
                 rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
 }
 
-// Work items: items[i] is a circuit; a circuit split over workgroups appears
-// once per workgroup that may join it.
-template <typename R>
-__global__ __launch_bounds__(kFwdThreads, 4) void k_batched(const BCirc *__restrict__ circs,
-                                                         const int32_t *__restrict__ items, int nitems,
-                                                         const BGate *__restrict__ gates,
-                                                         const BPass *__restrict__ passes,
-                                                         const TileGate *__restrict__ tiles,
-                                                         const RtOp *__restrict__ ops,
-                                                         const RtPat *__restrict__ pats,
-                                                         const SweepMember *__restrict__ mems,
-                                                         const double *__restrict__ params,
-                                                         unsigned int *__restrict__ queue, unsigned int *gstate,
-                                                         uint64_t limit, unsigned int *err,
-                                                         uint64_t *__restrict__ stamps) {
+// ADJ: the adjoint gradients, else the forward run.  tail: LDS bytes before
+// the work-item slot.
+template <typename R, bool ADJ>
+__global__ __launch_bounds__(kBatchThreads, 4) void k_batched(
+    const BCirc *__restrict__ circs, const int32_t *__restrict__ items, int nitems, const BGate *__restrict__ gates,
+    const BPass *__restrict__ passes, const TileGate *__restrict__ tiles, const RtOp *__restrict__ ops,
+    const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems, const double *__restrict__ params,
+    unsigned int *__restrict__ queue, unsigned int *gstate, uint64_t limit, unsigned int *err,
+    uint64_t *__restrict__ stamps, double *part, SweepTables a, uint32_t tail) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     // the exchange buffer first: its addresses step by xor
     unsigned char *buf = lds_raw;
-    int *item = reinterpret_cast<int *>(lds_raw + (kFwdLds - kBatchSlot));
+    double *scratch = reinterpret_cast<double *>(lds_raw + tail);
+    int *item = reinterpret_cast<int *>(scratch + kBatchThreads / 64);
     int *ticket = item + 1;
-    const FwdTables d{gates, passes, tiles, ops, pats, mems, params};
+    const BatchTables d{circs, gates, passes, tiles, ops, pats, mems, params, gstate, limit, err, part};
     for (;;) {
         if (threadIdx.x == 0)
             *item = (int)atomicAdd(queue, 1u);
@@ -390,14 +615,14 @@ __global__ __launch_bounds__(kFwdThreads, 4) void k_batched(const BCirc *__restr
         __syncthreads();
         if (it >= nitems)
             break;
-        const uint64_t t0 = stamps ? wall_clock64() : 0;
-        const BCirc &c = circs[items[it]];
-        if (c.n < resident_below(sizeof(R) == 8))  // uniform
-            run_circuit_resident<R>(c, d, buf);
+        const uint64_t t0 = !ADJ && stamps ? wall_clock64() : 0;
+        const int ci = items[it];  // one that is split appears once per workgroup that may join it
+        if (!ADJ && circs[ci].n < resident_below(sizeof(R) == 8))  // uniform
+            run_circuit_resident<R>(circs[ci], d, buf);
         else
-            run_circuit<R>(c, d, gstate, limit, err, buf, ticket);
+            run_circuit<R, ADJ>(ci, d, a, buf, scratch, ticket);
         __syncthreads();
-        if (stamps && threadIdx.x == 0) {
+        if (!ADJ && stamps && threadIdx.x == 0) {
             stamps[2 * it] = t0;
             stamps[2 * it + 1] = wall_clock64();
         }
@@ -412,156 +637,6 @@ __global__ void k_zero_words(unsigned int *p, int count) {
         p[i] = 0u;
 }
 
-// ----------------------------------------------------------------- adjoint
-
-// One gate of the reverse sweep over the whole state in global memory:
-// gradient term (when parameterised) and un-apply on psi and lambda.
-template <typename R, int THREADS>
-__device__ void adj_gate_global(const BCirc &c, const BGate &g, int gs, const double *__restrict__ params,
-                                const double *__restrict__ gens, cplx_t<R> *psi, cplx_t<R> *lam,
-                                double *__restrict__ grad, double *scratch) {
-    const Mat2<R> ud = bgate_mat<R>(g, params, true);
-    double a[8];
-    for (int k = 0; k < 8; ++k)
-        a[k] = gs >= 0 ? gens[8 * gs + k] : 0.0;
-    const uint64_t pos = g.cmask | (1ull << g.target);
-    const uint64_t npairs = 1ull << (c.n - 1 - __popcll(g.cmask));
-    const uint64_t st = 1ull << g.target;
-    double acc = 0.0;
-    for (uint64_t it = threadIdx.x; it < npairs; it += THREADS) {
-        const uint64_t p1 = insert_bits<uint64_t>(it, pos, g.cvals);
-        cplx_t<R> x = psi[p1], y = psi[p1 | st], lx = lam[p1], ly = lam[p1 | st];
-        if (gs >= 0) {
-            const double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
-            const double axr = a[0] * xr - a[1] * xi + a[2] * yr - a[3] * yi;
-            const double axi = a[0] * xi + a[1] * xr + a[2] * yi + a[3] * yr;
-            const double ayr = a[4] * xr - a[5] * xi + a[6] * yr - a[7] * yi;
-            const double ayi = a[4] * xi + a[5] * xr + a[6] * yi + a[7] * yr;
-            acc += 2.0 * ((double)lx.x * axr + (double)lx.y * axi + (double)ly.x * ayr + (double)ly.y * ayi);
-        }
-        apply_pair<R>(ud, x, y);
-        apply_pair<R>(ud, lx, ly);
-        psi[p1] = x;
-        psi[p1 | st] = y;
-        lam[p1] = lx;
-        lam[p1 | st] = ly;
-    }
-    if (gs >= 0) {  // uniform
-        const double s = block_sum(acc, scratch);
-        if (threadIdx.x == 0)
-            grad[g.param] += s;
-    }
-    __syncthreads();
-}
-
-// One circuit's adjoint inside one workgroup: lambda = H psi (and the loss),
-// then the reverse sweep: the fused plan of the inverse circuit, tiles of psi
-// and lambda together in LDS (adj_tile_run, shared with the single-circuit
-// adjoint), and single gates over global memory.  Gradient sums are reduced
-// in a fixed order (per wavefront, then wavefronts in index order, then
-// passes in order), so results are reproducible.
-template <typename R, int THREADS>
-__device__ void adjoint_block(const BCirc &c, const BGate *__restrict__ gates, const BPass *__restrict__ apasses,
-                              const TileGate *__restrict__ atiles, const int32_t *__restrict__ atslot,
-                              const int32_t *__restrict__ slot_param, const double *__restrict__ params,
-                              const DTerm *__restrict__ terms, const double *__restrict__ gens,
-                              const int32_t *__restrict__ gen_of, double *__restrict__ grad,
-                              double *__restrict__ loss, double *scratch, unsigned char *dyn) {
-    cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
-    cplx_t<R> *lam = reinterpret_cast<cplx_t<R> *>(c.lam);
-    const uint64_t N = 1ull << c.n;
-    for (int j = threadIdx.x; j < c.nparams; j += THREADS)
-        grad[c.first_param + j] = 0.0;
-    // lambda = H psi; terms are sorted by x mask
-    double lp = 0.0;
-    for (uint64_t k = threadIdx.x; k < N; k += THREADS) {
-        double ar = 0.0, ai = 0.0;
-        for (int j = 0; j < c.nterms; ++j) {
-            const DTerm T = terms[c.first_term + j];
-            const uint64_t X = (uint64_t)T.idx;  // the term's x mask (stored in idx for the batch)
-            const uint64_t kx = k ^ X;
-            const cplx_t<R> v = psi[kx];
-            const double s = odd_parity(T.z & kx) ? -T.coef : T.coef;
-            const double cr = re_ipow(T.ny, s, 0.0), ci = im_ipow(T.ny, s, 0.0);
-            ar += cr * (double)v.x - ci * (double)v.y;
-            ai += cr * (double)v.y + ci * (double)v.x;
-        }
-        cplx_t<R> o;
-        o.x = (R)ar;
-        o.y = (R)ai;
-        lam[k] = o;
-        const cplx_t<R> p = psi[k];
-        lp += (double)p.x * ar + (double)p.y * ai;
-    }
-    const double L = block_sum(lp, scratch);
-    if (threadIdx.x == 0)
-        loss[0] = L;
-    __syncthreads();
-    cplx_t<R> *tp = reinterpret_cast<cplx_t<R> *>(dyn);
-    for (int pi = 0; pi < c.napasses; ++pi) {
-        const BPass &p = apasses[c.first_apass + pi];
-        if (p.fused) {  // uniform
-            const DeviceGates dg{atiles + p.first, p.count};
-            const int32_t *gs = atslot + p.first;
-            const uint32_t T = 1u << p.tm.m;
-            cplx_t<R> *tl = tp + T;
-            double *accl = reinterpret_cast<double *>(tl + T);
-            const int npg = adj_acc_zero(dg, gs, accl);
-            for (uint64_t tt = 0; tt < p.tm.ntiles; ++tt) {
-                const uint64_t base = expand_index<uint64_t>(p.tm.outer, tt);
-                if (!adj_tile_touched(base, dg))
-                    continue;  // uniform
-                tile_load_dma<R, THREADS>(tp, psi, base, p.tm, T);
-                tile_load_dma<R, THREADS>(tl, lam, base, p.tm, T);
-                __syncthreads();
-                adj_tile_run<R, THREADS>(tp, tl, base, T, dg, gs, gens, accl);
-                tile_store2<R, THREADS, false, kBatchCopy>(psi, lam, tp, tl, base, p.tm, T);
-                __syncthreads();
-            }
-            if (threadIdx.x == 0)  // in order: gates may share a parameter
-                for (int k = 0; k < npg; ++k)
-                    grad[slot_param[adj_acc_slot(dg, gs, k)]] += adj_acc_sum(accl, k);
-            __syncthreads();
-        } else {
-            const int f = p.gate;  // forward index of the gate un-applied here
-            adj_gate_global<R, THREADS>(c, gates[c.first_gate + f], gen_of[c.first_gate + f], params, gens, psi, lam, grad,
-                               scratch);
-        }
-    }
-}
-
-// THREADS = 512 (two workgroups per CU) or 1024 (one per CU, for batches of
-// at most one circuit per CU: twice the wavefronts on each circuit).
-template <typename R, int THREADS>
-__global__ __launch_bounds__(THREADS, 2048 / THREADS) void k_batched_adjoint(
-    const BCirc *__restrict__ circs, const int32_t *__restrict__ order, int ncirc, const BGate *__restrict__ gates,
-    const BPass *__restrict__ apasses, const TileGate *__restrict__ atiles, const int32_t *__restrict__ atslot,
-    const int32_t *__restrict__ slot_param, const double *__restrict__ params, const DTerm *__restrict__ terms,
-    const double *__restrict__ gens, const int32_t *__restrict__ gen_of, double *__restrict__ grad,
-    double *__restrict__ loss, unsigned int *__restrict__ queue, uint64_t *__restrict__ stamps) {
-    extern __shared__ unsigned char lds_raw[];  // psi and lambda tiles, then gradient accumulators
-    __shared__ double scratch[THREADS / 64];
-    __shared__ int item;
-    for (;;) {
-        if (threadIdx.x == 0)
-            item = (int)atomicAdd(queue, 1u);
-        __syncthreads();
-        const int it = item;
-        __syncthreads();
-        if (it >= ncirc)
-            break;
-        const int ci = order[it];
-        const uint64_t t0 = stamps ? wall_clock64() : 0;
-        adjoint_block<R, THREADS>(circs[ci], gates, apasses, atiles, atslot, slot_param, params, terms, gens, gen_of, grad,
-                         loss + ci, scratch, lds_raw);
-        __syncthreads();
-        if (stamps && threadIdx.x == 0) {
-            stamps[2 * ci] = t0;
-            stamps[2 * ci + 1] = wall_clock64();
-        }
-    }
-}
-
 // ----------------------------------------------------------------- host
 
 // One circuit's tables, built independently of the others (so circuits can
@@ -569,18 +644,18 @@ __global__ __launch_bounds__(THREADS, 2048 / THREADS) void k_batched_adjoint(
 struct CircBuild {
     BCirc bc;
     std::vector<BGate> gates;
-    std::vector<BPass> passes;     // forward plan (circuit-local indices)
+    std::vector<BPass> passes;     // the plan (circuit-local indices; adjoint: of the reverse sweep)
     std::vector<TileGate> tiles;
     PlanRt rt;                     // register tile operations (circuit-local)
     std::vector<SweepMember> mems; // members of their phase patterns
     std::vector<BTileJob> jobs;    // tile and operation indices circuit-local
-    // adjoint: the reverse sweep's fused plan, each descriptor's generator
-    // slot (circuit-local, -1 none), each slot's parameter (batch-global)
-    std::vector<BPass> apasses;
-    std::vector<TileGate> atiles;
-    std::vector<BTileJob> ajobs;
-    std::vector<int32_t> atslot, slot_param;
-    size_t adj_lds = 0;            // dynamic LDS its fused passes need
+    // adjoint: per gradient slot (a parameterised gate; numbered in the order
+    // of the reverse sweep), then for the loss: its parameter (circuit-local;
+    // the loss: nparams) and where its partial sums are
+    struct Sum {
+        int32_t param, pass, acc;
+    };
+    std::vector<Sum> sums;
     std::vector<double> gens;      // generators of the parameterised gates
     std::vector<int32_t> gen_of;   // per gate: index into gens / 8, or -1
     std::vector<DTerm> terms;
@@ -599,9 +674,113 @@ struct BatchArgs {
     const int64_t *term_off;
 };
 
+// The fused plan of one circuit's gates (those of the reverse sweep when
+// out->rt.dual) into out's passes, tiles and jobs.
+static int plan_passes(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int32_t param0, int m_cap,
+                       CircBuild *out) {
+    std::vector<PlanPass> pp;
+    std::vector<SweepPat> pats;
+    SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr, &pats, &out->mems,
+                              &out->rt));
+    for (const PlanPass &q : pp) {
+        BPass b;
+        memset(&b, 0, sizeof(b));
+        b.kind = q.fused ? kPassTiles : kPassGate;
+        b.gate = q.gate;
+        b.first = q.first;
+        b.count = q.count;
+        if (q.fused) {
+            if (q.tm.m > (uint32_t)m_cap)
+                return fail(SV_EINVAL, "tile width %u beyond the batch limit", q.tm.m);
+            if (!q.rt || q.rp.lds > kBatchExchange)
+                return fail(SV_EINVAL, "fused pass beyond the batch's register tiles");
+            b.tm = q.tm;
+            b.rt = q.rp;
+            b.nacc = (int32_t)q.rp.acc_count;
+        }
+        out->passes.push_back(b);
+    }
+    for (const ParamJob &j : out->rt.jobs)
+        if (j.tile_slot >= 0)
+            out->jobs.push_back(BTileJob{j.kind, param0 + j.param, j.tile_slot, {j.op[0], j.op[1]}});
+    return SV_OK;
+}
+
+// The reverse sweep of circuit c: its passes, generators and partial sums.
+static int build_sweep(const BatchArgs &A, int c, int dtype, int m_cap, CircBuild *out) {
+    BCirc &bc = out->bc;
+    const int64_t g0 = A.gate_off[c], p0 = A.param_off[c];
+    const int G = bc.ngates;
+    // inverses in reverse order, planned like a forward circuit; a lane's
+    // registers hold psi and lambda, so tiles are half as wide
+    std::vector<sv_gate_t> rev(G);
+    std::vector<int32_t> slot_of(G, -1);  // per gate of rev
+    out->gen_of.assign(G, -1);
+    for (int r = 0; r < G; ++r) {
+        const sv_gate_t &g = A.gates[g0 + G - 1 - r];
+        rev[r] = g;
+        rev[r].kind ^= SV_G_ADJOINT;
+        if (g.param < 0)
+            continue;
+        double a[8];
+        gate_generator(g.kind, a);
+        if (g.kind & SV_G_ADJOINT) {
+            for (int q = 1; q < 8; q += 2)
+                a[q] = -a[q];
+            std::swap(a[2], a[4]);
+            std::swap(a[3], a[5]);
+        }
+        slot_of[r] = out->gen_of[G - 1 - r] = (int32_t)out->sums.size();
+        out->gens.insert(out->gens.end(), a, a + 8);
+        out->sums.push_back({g.param, -1, 0});
+    }
+    auto extra = [&](int32_t kind, int32_t nacc) {
+        BPass b;
+        memset(&b, 0, sizeof(b));
+        b.kind = kind;
+        b.nacc = nacc;
+        out->passes.push_back(b);
+    };
+    extra(kPassPauli, 1);
+    if (G > 0 && bc.n < kSweepLdsBelow) {
+        extra(kPassSmall, (int32_t)out->sums.size());
+        for (size_t k = 0; k < out->sums.size(); ++k) {
+            out->sums[k].pass = 1;
+            out->sums[k].acc = (int32_t)k;
+        }
+    } else if (G > 0) {
+        out->rt.dual = true;
+        SV_TRY(plan_passes(bc.n, dtype, rev.data(), G, bc.nparams, (int32_t)p0, m_cap, out));
+        for (size_t pi = 1; pi < out->passes.size(); ++pi) {
+            BPass &b = out->passes[pi];
+            if (b.kind == kPassTiles) {
+                for (int32_t k = 0; k < b.nacc; ++k) {
+                    CircBuild::Sum &u = out->sums[out->rt.prog.acc[b.rt.acc_first + k]];
+                    u.pass = (int32_t)pi;
+                    u.acc = k;
+                }
+                continue;
+            }
+            const int32_t sl = slot_of[b.gate];
+            b.gate = G - 1 - b.gate;  // forward index
+            if (sl >= 0) {
+                b.nacc = 1;
+                out->sums[sl].pass = (int32_t)pi;
+            }
+        }
+    }
+    for (const CircBuild::Sum &u : out->sums)
+        if (u.pass < 0)
+            return fail(SV_EINVAL, "a gradient term without a pass");
+    out->sums.push_back({bc.nparams, 0, 0});
+    extra(kPassSums, 0);
+    return SV_OK;
+}
+
 // Tables of circuit c: its gates in program order, and either the forward
 // fused plan (passes, tile descriptors, parameter jobs; none when the state
-// is LDS-resident) or, for the adjoint, generators and the Hamiltonian.
+// is LDS-resident) or, for the adjoint, the reverse sweep's, with generators
+// and the Hamiltonian.
 static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, CircBuild *out) {
     const sv_state_t &s = A.states[c];
     const int64_t g0 = A.gate_off[c], g1 = A.gate_off[c + 1];
@@ -612,10 +791,7 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
     bc.psi = s.data;
     bc.lam = adjoint ? A.lams[c].data : nullptr;
     bc.n = s.n;
-    // the fused tiles must fit the workgroup's LDS buffer
-    const int m_cap = rt_nb_of(dtype) + kFwdThreadBits;  // one workgroup's registers
-    const int tl = tuning().tile_log2[dtype == SV_C128 ? 0 : 1];
-    bc.m = std::min(std::min(tl, s.n), m_cap);
+    const int m_cap = rt_nb_of(dtype) + kBatchThreadBits - (adjoint ? 1 : 0);  // one workgroup's registers
     bc.ngates = (int32_t)(g1 - g0);
     bc.first_param = (int32_t)p0;
     bc.nparams = (int32_t)(p1 - p0);
@@ -625,37 +801,11 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
             if (adjoint)
                 SV_TRY(validate_unitary_gate(A.gates[i], (int)(i - g0)));
         }
-        const bool resident = s.n < resident_below(dtype == SV_C128);
-        if (!adjoint && !resident) {
-            std::vector<PlanPass> pp;
-            int m_used = 0;
-            std::vector<SweepPat> pats;
-            SV_TRY(circuit_plan_tiles(s.n, dtype, A.gates + g0, bc.ngates, (int)(p1 - p0), m_cap, &pp, &out->tiles,
-                                      &m_used, &pats, &out->mems, &out->rt));
-            if (m_used != bc.m)
-                return fail(SV_EINVAL, "planner tile width %d != %d", m_used, bc.m);
-            for (const PlanPass &q : pp) {
-                BPass b;
-                memset(&b, 0, sizeof(b));
-                b.fused = q.fused;
-                b.gate = q.gate;
-                b.first = q.first;
-                b.count = q.count;
-                if (q.fused) {
-                    if (q.tm.m > (uint32_t)m_cap)
-                        return fail(SV_EINVAL, "tile width %u beyond the batch limit", q.tm.m);
-                    if (!q.rt || q.rp.lds > kFwdLds - kBatchSlot)
-                        return fail(SV_EINVAL, "fused pass beyond the batch's register tiles");
-                    b.tm = q.tm;
-                    b.rt = q.rp;
-                }
-                out->passes.push_back(b);
-            }
-            for (const ParamJob &j : out->rt.jobs)
-                if (j.tile_slot >= 0)
-                    out->jobs.push_back(BTileJob{j.kind, (int32_t)p0 + j.param, j.tile_slot, {j.op[0], j.op[1]}});
-        }
     }
+    if (adjoint)
+        SV_TRY(build_sweep(A, c, dtype, m_cap, out));
+    else if (bc.ngates > 0 && s.n >= resident_below(dtype == SV_C128))
+        SV_TRY(plan_passes(s.n, dtype, A.gates + g0, bc.ngates, (int)(p1 - p0), (int32_t)p0, m_cap, out));
     bc.npasses = (int32_t)out->passes.size();
     double work = 0.0;
     out->gates.reserve(bc.ngates);
@@ -673,65 +823,8 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
         b.target = g.target;
         b.cmask = g.ctrl_mask;
         b.cvals = g.ctrl_vals;
-        int gs = -1;
-        if (adjoint && g.param >= 0) {
-            double a[8];
-            gate_generator(g.kind, a);
-            if (g.kind & SV_G_ADJOINT) {
-                for (int q = 1; q < 8; q += 2)
-                    a[q] = -a[q];
-                std::swap(a[2], a[4]);
-                std::swap(a[3], a[5]);
-            }
-            gs = (int)(out->gens.size() / 8);
-            out->gens.insert(out->gens.end(), a, a + 8);
-            out->slot_param.push_back((int32_t)(p0 + g.param));
-        }
-        out->gen_of.push_back(gs);
         out->gates.push_back(b);
         work += std::ldexp(1.0, s.n - popcount64(g.ctrl_mask));
-    }
-    if (adjoint && bc.ngates > 0) {
-        // the reverse sweep: inverses in reverse order, planned like a forward
-        // circuit with two tiles (psi and lambda) in the LDS of one
-        const int m_cap_adj = m_cap - 1;
-        std::vector<sv_gate_t> rev(bc.ngates);
-        for (int r = 0; r < bc.ngates; ++r) {
-            rev[r] = A.gates[g0 + bc.ngates - 1 - r];
-            rev[r].kind ^= SV_G_ADJOINT;
-        }
-        std::vector<PlanPass> pp;
-        int m_used = 0;
-        SV_TRY(circuit_plan_tiles(s.n, dtype, rev.data(), bc.ngates, (int)(p1 - p0), m_cap_adj, &pp, &out->atiles,
-                                  &m_used));
-        for (const PlanPass &q : pp) {
-            BPass b;
-            memset(&b, 0, sizeof(b));
-            b.fused = q.fused;
-            b.first = q.first;
-            b.count = q.count;
-            if (q.fused) {
-                if (q.tm.m > (uint32_t)m_cap_adj)
-                    return fail(SV_EINVAL, "tile width %u beyond the batch limit", q.tm.m);
-                b.tm = q.tm;
-                size_t npg = 0;
-                for (int j = 0; j < q.count; ++j)
-                    npg += out->gen_of[bc.ngates - 1 - out->atiles[q.first + j].src_gate] >= 0 ? 1 : 0;
-                out->adj_lds = std::max(out->adj_lds, ((size_t)2 << q.tm.m) * amp_bytes(dtype) +
-                                                          npg * (kBatchAdjMaxThreads / 64) * sizeof(double));
-            } else {
-                b.gate = bc.ngates - 1 - q.gate;  // forward index
-            }
-            out->apasses.push_back(b);
-        }
-        for (size_t t = 0; t < out->atiles.size(); ++t) {
-            const int f = bc.ngates - 1 - out->atiles[t].src_gate;
-            out->atslot.push_back(out->gen_of[f]);
-            const sv_gate_t &g = A.gates[g0 + f];
-            if (g.param >= 0)
-                out->ajobs.push_back(BTileJob{g.kind ^ SV_G_ADJOINT, (int32_t)(p0 + g.param), (int32_t)t, {-1, -1}});
-        }
-        bc.napasses = (int32_t)out->apasses.size();
     }
     if (adjoint) {
         const int64_t t0 = A.term_off[c], t1 = A.term_off[c + 1];
@@ -763,11 +856,10 @@ struct BatchHost {
     RtProgram prog;
     std::vector<SweepMember> mems;
     std::vector<BTileJob> jobs;
-    std::vector<BPass> apasses;
-    std::vector<TileGate> atiles;
-    std::vector<BTileJob> ajobs;
-    std::vector<int32_t> atslot, slot_param;
-    size_t adj_lds = 0;
+    std::vector<BSlot> slots;
+    std::vector<int32_t> csr;
+    int64_t npart = 0;             // partial sums
+    size_t lds = kBatchExchange;   // exchange buffer, then gradient accumulators of a pass
     std::vector<int32_t> order;    // work items in queue order (each a circuit)
     int ngroups = 0;               // circuits split over workgroups
     std::vector<double> gens;
@@ -801,12 +893,13 @@ constexpr uint64_t kWaitLimitSeconds = 10;
 //    (the 64 circuits: 0.64 ms without that limit).
 constexpr int kChunksPerWorker = 4;
 
-static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &cost, std::vector<int32_t> *workers) {
+static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vector<double> &cost,
+                           std::vector<int32_t> *workers) {
     const int gmax = tuning().batch_split;
     if (gmax <= 1)
         return;
     DeviceInfo di;
-    const double P = (double)kFwdPerCu * (device_info(&di) == SV_OK ? di.num_cus : 256);  // persistent workgroups
+    const double P = (double)kBatchPerCu * (device_info(&di) == SV_OK ? di.num_cus : 256);  // persistent workgroups
     double W = 0.0;
     for (double c : cost)
         W += c;
@@ -814,23 +907,27 @@ static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &c
     const int kc = kChunksPerWorker;
     for (size_t c = 0; c < h->circs.size(); ++c) {
         BCirc &bc = h->circs[c];
-        if (bc.npasses == 0 || bc.n <= rt_nb_of(dtype) + kFwdThreadBits || !(cost[c] > load))
+        if (bc.npasses == 0 || bc.n <= rt_nb_of(dtype) + kBatchThreadBits - (adjoint ? 1 : 0) || !(cost[c] > load))
             continue;  // LDS-resident, empty, one workgroup's registers, or short enough
         // a pass's tiles or pairs, and how many of them a workgroup takes at least
         auto extent = [&](const BPass &p, uint64_t *total, uint64_t *unit) {
-            if (p.fused) {
+            *total = *unit = 1;
+            if (p.kind == kPassTiles) {
                 *total = p.tm.ntiles;
-                *unit = 1;
-            } else {
+            } else if (p.kind == kPassPauli) {
+                *total = 1ull << bc.n;
+                *unit = (uint64_t)kBatchPairUnroll * kBatchThreads;
+            } else if (p.kind == kPassGate) {
                 const BGate &gt = h->gates[bc.first_gate + p.gate];
                 *total = 1ull << (bc.n - 1 - popcount64(gt.cmask));
-                *unit = (uint64_t)kBatchPairUnroll * kFwdThreads;
+                *unit = (uint64_t)kBatchPairUnroll * kBatchThreads;
             }
             return (*total + *unit - 1) / *unit;
         };
         uint64_t total, unit, most = 0;
         for (int pi = 0; pi < bc.npasses; ++pi)
-            most = std::max(most, extent(h->passes[bc.first_pass + pi], &total, &unit));
+            if (h->passes[bc.first_pass + pi].kind <= kPassTiles)
+                most = std::max(most, extent(h->passes[bc.first_pass + pi], &total, &unit));
         const int g = (int)std::min<double>(std::min<double>(gmax, (double)most), std::floor(cost[c] / load + 0.5));
         if (g < 2 || (int64_t)bc.npasses * g * kc > (1 << 30))
             continue;
@@ -848,6 +945,30 @@ static void split_circuits(BatchHost *h, int dtype, const std::vector<double> &c
         bc.group = h->ngroups++;
         bc.nchunks = (int32_t)k;  // at most npasses * 4 * 64
         (*workers)[c] = g;
+    }
+}
+
+// Where the passes of a circuit leave their partial sums, and the list of
+// them by parameter.
+static void place_sums(const std::vector<CircBuild::Sum> &sums, BCirc *bc, BatchHost *h) {
+    BPass *ps = &h->passes[bc->first_pass];
+    for (int pi = 0; pi < bc->npasses; ++pi) {
+        ps[pi].part = h->npart;
+        h->npart += (int64_t)ps[pi].nacc * (bc->group >= 0 ? ps[pi].nchunks : 1);
+        h->lds = std::max(h->lds, kBatchExchange + (size_t)ps[pi].rt.acc_count * (kBatchThreads / 64) * sizeof(double));
+    }
+    bc->first_slot = (int32_t)h->slots.size();
+    bc->nslots = (int32_t)sums.size();
+    bc->first_csr = (int32_t)h->csr.size();
+    std::vector<int32_t> at(bc->nparams + 2, 0);
+    for (const CircBuild::Sum &u : sums)
+        ++at[u.param + 1];
+    std::partial_sum(at.begin(), at.end(), at.begin());
+    h->csr.insert(h->csr.end(), at.begin(), at.end());
+    h->slots.resize(h->slots.size() + sums.size());
+    for (const CircBuild::Sum &u : sums) {  // in the sweep's order where gates share a parameter
+        const BPass &p = ps[u.pass];
+        h->slots[bc->first_slot + at[u.param]++] = BSlot{p.part + u.acc, p.nacc, bc->group >= 0 ? p.nchunks : 1};
     }
 }
 
@@ -899,7 +1020,7 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         }
     };
     unsigned nth = std::min(16u, std::max(1u, std::thread::hardware_concurrency()));
-    if (total_gates < 20000)
+    if (total_gates < 2000)  // one thread plans these in 3 ms
         nth = 1;
     nth = std::min<unsigned>(nth, (unsigned)A.ncirc);
     if (nth <= 1) {
@@ -909,7 +1030,7 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         const bool have_dev = hipGetDevice(&dev) == hipSuccess;
         std::vector<std::thread> pool;
         std::atomic<int> next{0};
-        constexpr int kChunk = 16;
+        constexpr int kChunk = 4;
         for (unsigned t = 0; t < nth; ++t)
             pool.emplace_back([&, have_dev, dev] {
                 if (have_dev)
@@ -925,6 +1046,16 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
             t.join();
     }
     std::vector<double> cost(A.ncirc);
+    size_t nops = 0, ntiles = 0, nmems = 0;
+    for (const CircBuild &b : cb) {
+        nops += b.rt.prog.ops.size();
+        ntiles += b.tiles.size();
+        nmems += b.mems.size();
+    }
+    h->gates.reserve((size_t)total_gates);
+    h->prog.ops.reserve(nops);
+    h->tiles.reserve(ntiles);
+    h->mems.reserve(nmems);
     for (int c = 0; c < A.ncirc; ++c) {
         CircBuild &b = cb[c];
         if (b.err != SV_OK)
@@ -935,7 +1066,7 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         const int32_t tbase = (int32_t)h->tiles.size(), obase = (int32_t)h->prog.ops.size();
         const uint32_t pbase = (uint32_t)h->prog.pats.size(), mbase = (uint32_t)h->mems.size();
         for (BPass p : b.passes) {
-            if (p.fused) {
+            if (p.kind == kPassTiles) {
                 p.first += tbase;
                 p.rt.first += (uint32_t)obase;
             }
@@ -948,40 +1079,23 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
                     j.op[s] += obase;
             h->jobs.push_back(j);
         }
-        for (RtOp o : b.rt.prog.ops) {
+        for (RtOp &o : b.rt.prog.ops)
             if (o.w[0] >> 3 == kRtPrep)
                 o.w[2] += pbase;
-            h->prog.ops.push_back(o);
-        }
+        h->prog.ops.insert(h->prog.ops.end(), b.rt.prog.ops.begin(), b.rt.prog.ops.end());
         for (RtPat p : b.rt.prog.pats) {
             p.first += mbase;
             h->prog.pats.push_back(p);
         }
-        for (TileGate t : b.tiles) {
+        for (TileGate &t : b.tiles)
             if (t.diag)
                 for (int s = 0; s < 2; ++s)
                     if (t.mem[s] >= 0)
                         t.mem[s] += (int32_t)mbase;
-            h->tiles.push_back(t);
-        }
+        h->tiles.insert(h->tiles.end(), b.tiles.begin(), b.tiles.end());
         h->mems.insert(h->mems.end(), b.mems.begin(), b.mems.end());
-        const int32_t gbase = (int32_t)(h->gens.size() / 8);  // generator slots before this circuit's
-        b.bc.first_apass = (int32_t)h->apasses.size();
-        const int32_t abase = (int32_t)h->atiles.size();
-        for (BPass p : b.apasses) {
-            if (p.fused)
-                p.first += abase;
-            h->apasses.push_back(p);
-        }
-        for (BTileJob j : b.ajobs) {
-            j.tile += abase;
-            h->ajobs.push_back(j);
-        }
-        h->atiles.insert(h->atiles.end(), b.atiles.begin(), b.atiles.end());
-        for (int32_t sl : b.atslot)
-            h->atslot.push_back(sl >= 0 ? sl + gbase : -1);
-        h->slot_param.insert(h->slot_param.end(), b.slot_param.begin(), b.slot_param.end());
-        h->adj_lds = std::max(h->adj_lds, b.adj_lds);
+        const int32_t gbase = (int32_t)(h->gens.size() / 8);  // generators before this circuit's
+        b.bc.first_gen = gbase;
         for (int32_t g : b.gen_of)
             h->gen_of.push_back(g >= 0 ? g + gbase : -1);
         h->gates.insert(h->gates.end(), b.gates.begin(), b.gates.end());
@@ -991,8 +1105,10 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         cost[c] = b.cost;
     }
     std::vector<int32_t> workers(A.ncirc, 1);
-    if (!adjoint)
-        split_circuits(h, *dtype, cost, &workers);
+    split_circuits(h, *dtype, adjoint, cost, &workers);
+    if (adjoint)
+        for (int c = 0; c < A.ncirc; ++c)
+            place_sums(cb[c].sums, &h->circs[c], h);
     std::vector<int32_t> circ(A.ncirc);
     std::iota(circ.begin(), circ.end(), 0);
     std::stable_sort(circ.begin(), circ.end(),
@@ -1012,12 +1128,10 @@ struct BatchDevice {
     SweepMember *mems = nullptr;
     BTileJob *jobs = nullptr;
     int njobs = 0;
-    BPass *apasses = nullptr;
-    TileGate *atiles = nullptr;
-    BTileJob *ajobs = nullptr;
-    int najobs = 0;
-    int32_t *atslot = nullptr, *slot_param = nullptr;
-    size_t adj_lds = 0;
+    BSlot *slots = nullptr;
+    int32_t *csr = nullptr;
+    double *part = nullptr;
+    size_t lds = 0;
     int32_t *order = nullptr, *gen_of = nullptr;
     int nitems = 0;
     double *gens = nullptr;
@@ -1033,9 +1147,8 @@ struct BatchDevice {
 // Stream-ordered release when async (after the kernels enqueued on st),
 // otherwise an immediate free.
 static void batch_release(BatchDevice *d, bool async, hipStream_t st) {
-    void *ps[] = {d->circs,  d->gates,  d->passes, d->tiles,  d->ops, d->pats, d->mems, d->jobs,  d->apasses,
-                  d->atiles, d->ajobs,  d->atslot, d->slot_param, d->order, d->gen_of, d->gens,    d->terms,
-                  d->queue, d->gstate};
+    void *ps[] = {d->circs, d->gates, d->passes, d->tiles,  d->ops,  d->pats,  d->mems,  d->jobs,  d->slots,
+                  d->csr,   d->part,  d->order,  d->gen_of, d->gens, d->terms, d->queue, d->gstate};
     for (void *p : ps)
         if (p)
             (void)(async ? hipFreeAsync(p, st) : hipFree(p));
@@ -1081,17 +1194,12 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
         r = dev_copy(&d->jobs, h.jobs, async, st, 1);
     d->njobs = (int)h.jobs.size();
     if (r == SV_OK)
-        r = dev_copy(&d->apasses, h.apasses, async, st, 1);
+        r = dev_copy(&d->slots, h.slots, async, st, 1);
     if (r == SV_OK)
-        r = dev_copy(&d->atiles, h.atiles, async, st, 1);
+        r = dev_copy(&d->csr, h.csr, async, st, 1);
     if (r == SV_OK)
-        r = dev_copy(&d->ajobs, h.ajobs, async, st, 1);
-    d->najobs = (int)h.ajobs.size();
-    if (r == SV_OK)
-        r = dev_copy(&d->atslot, h.atslot, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->slot_param, h.slot_param, async, st, 1);
-    d->adj_lds = h.adj_lds;
+        r = dev_copy(&d->part, std::vector<double>(), async, st, (size_t)h.npart);
+    d->lds = h.lds;
     if (r == SV_OK)
         r = dev_copy(&d->order, h.order, async, st);
     d->nitems = (int)h.order.size();
@@ -1136,18 +1244,17 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     return r;
 }
 
-// Workgroups of a persistent launch, `per_cu` resident per CU.
-static unsigned persistent_grid(int ncirc, unsigned per_cu) {
+// One persistent launch: the forward run, or (grad) the adjoint.
+static int launch_batch(int dtype, const BatchDevice &d, const double *params, double *grad, double *loss,
+                        hipStream_t s, uint64_t *stamps) {
+    constexpr size_t kLdsPerWorkgroup = 160 * 1024;  // gfx950, with the opt-in limit raised
+    const size_t lds = d.lds + kBatchSlot;
+    if (lds > kLdsPerWorkgroup)
+        return fail(SV_ENOTSUP, "a fused reverse pass needs %zu bytes of LDS", lds);
     DeviceInfo di;
-    if (device_info(&di) != SV_OK)
-        return 256;
-    return std::min<unsigned>((unsigned)di.num_cus * per_cu, (unsigned)ncirc);
-}
-
-static int launch_forward(int dtype, const BatchDevice &d, int ncirc, const double *params, hipStream_t s,
-                          uint64_t *stamps = nullptr) {
-    (void)ncirc;
-    const unsigned grid = persistent_grid(d.nitems, kFwdPerCu);
+    const unsigned cus = device_info(&di) == SV_OK ? (unsigned)di.num_cus : 256u;
+    const unsigned per_cu = std::min<unsigned>(kBatchPerCu, (unsigned)(kLdsPerWorkgroup / lds));
+    const unsigned grid = std::min<unsigned>(cus * per_cu, (unsigned)d.nitems);
     if (d.njobs > 0)
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.njobs + 255) / 256), dim3(256), 0, s, d.jobs, d.njobs, params,
                            d.tiles, d.mems, d.ops, dtype == SV_C64 ? 1 : 0);
@@ -1155,59 +1262,19 @@ static int launch_forward(int dtype, const BatchDevice &d, int ncirc, const doub
     if (d.ngroups > 0)  // the ticket counters, not the timeout count after them
         hipLaunchKernelGGL(k_zero_words, dim3((2 * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,
                            2 * d.ngroups);
-    unsigned int *err = d.gstate ? d.gstate + 2 * d.ngroups : nullptr;
+    const SweepTables a{d.terms, d.gens, d.gen_of, d.slots, d.csr, grad, loss, stamps};
+    auto go = [&](auto fn) -> int {
+        if (lds > 65536)
+            SV_HIP_TRY(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(kBatchThreads), lds, s, d.circs, d.order, d.nitems, d.gates, d.passes,
+                           d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
+                           d.gstate ? d.gstate + 2 * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds);
+        SV_LAUNCH_CHECK();
+        return SV_OK;
+    };
     if (dtype == SV_C128)
-        hipLaunchKernelGGL(k_batched<double>, dim3(grid), dim3(kFwdThreads), kFwdLds, s, d.circs, d.order, d.nitems,
-                           d.gates, d.passes, d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
-                           err, stamps);
-    else
-        hipLaunchKernelGGL(k_batched<float>, dim3(grid), dim3(kFwdThreads), kFwdLds, s, d.circs, d.order, d.nitems,
-                           d.gates, d.passes, d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
-                           err, stamps);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return fail(SV_EHIP, "batched launch failed: %s", hipGetErrorString(e));
-    return SV_OK;
-}
-
-template <typename R, int THREADS>
-static int go_adjoint(const BatchDevice &d, int ncirc, unsigned grid, size_t lds, const double *params, double *grad,
-                      double *loss, hipStream_t s, uint64_t *stamps) {
-    hipError_t a = hipFuncSetAttribute((const void *)k_batched_adjoint<R, THREADS>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (a != hipSuccess)
-        return fail(SV_EHIP, "LDS limit: %s", hipGetErrorString(a));
-    hipLaunchKernelGGL((k_batched_adjoint<R, THREADS>), dim3(grid), dim3(THREADS), lds, s, d.circs, d.order, ncirc,
-                       d.gates, d.apasses, d.atiles, d.atslot, d.slot_param, params, d.terms, d.gens, d.gen_of, grad,
-                       loss, d.queue, stamps);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return fail(SV_EHIP, "batched adjoint launch failed: %s", hipGetErrorString(e));
-    return SV_OK;
-}
-
-// A batch of at most one circuit per CU runs one 1024-lane workgroup per
-// circuit (two 512-lane ones per CU would leave half the workgroups idle);
-// larger batches run two 512-lane workgroups per CU.
-static int launch_adjoint(int dtype, const BatchDevice &d, int ncirc, const double *params, double *grad,
-                          double *loss, hipStream_t s, uint64_t *stamps = nullptr) {
-    constexpr size_t kLdsPerWorkgroup = 160 * 1024;  // gfx950, with the opt-in limit raised
-    const size_t lds = std::max<size_t>(d.adj_lds, 8);
-    if (lds + 1024 > kLdsPerWorkgroup)
-        return fail(SV_ENOTSUP, "a fused reverse pass needs %zu bytes of LDS", lds);
-    DeviceInfo di;
-    const int cus = device_info(&di) == SV_OK ? di.num_cus : 256;
-    const bool wide = ncirc <= cus;
-    const unsigned grid = wide ? (unsigned)std::max(1, ncirc) : persistent_grid(ncirc, 2);
-    if (d.najobs > 0)
-        hipLaunchKernelGGL(k_batch_tile_params, dim3((d.najobs + 255) / 256), dim3(256), 0, s, d.ajobs, d.najobs,
-                           params, d.atiles, nullptr, nullptr, 0);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
-    if (dtype == SV_C128)
-        return wide ? go_adjoint<double, kBatchAdjMaxThreads>(d, ncirc, grid, lds, params, grad, loss, s, stamps)
-                    : go_adjoint<double, kBatchThreads>(d, ncirc, grid, lds, params, grad, loss, s, stamps);
-    return wide ? go_adjoint<float, kBatchAdjMaxThreads>(d, ncirc, grid, lds, params, grad, loss, s, stamps)
-                : go_adjoint<float, kBatchThreads>(d, ncirc, grid, lds, params, grad, loss, s, stamps);
+        return grad ? go(k_batched<double, true>) : go(k_batched<double, false>);
+    return grad ? go(k_batched<float, true>) : go(k_batched<float, false>);
 }
 
 } // namespace sv
@@ -1284,7 +1351,7 @@ static int batch_done(sv_batch_t *b, hipStream_t st) {
 int sv_batch_run(sv_batch_t *b, const double *params_dev, sv_stream_t st) {
     clear_error();
     SV_TRY(batch_check(b, params_dev));
-    SV_TRY(launch_forward(b->dtype, b->fwd, b->ncirc, params_dev, (hipStream_t)st, b->stamps));
+    SV_TRY(launch_batch(b->dtype, b->fwd, params_dev, nullptr, nullptr, (hipStream_t)st, b->stamps));
     return batch_done(b, (hipStream_t)st);
 }
 
@@ -1295,7 +1362,7 @@ int sv_batch_adjoint(sv_batch_t *b, const double *params_dev, double *grad_dev, 
         return fail(SV_EINVAL, "batch was created without lambda states and terms");
     if (!grad_dev || !loss_dev)
         return fail(SV_EINVAL, "grad_dev and loss_dev are required");
-    SV_TRY(launch_adjoint(b->dtype, b->adj, b->ncirc, params_dev, grad_dev, loss_dev, (hipStream_t)st, b->stamps));
+    SV_TRY(launch_batch(b->dtype, b->adj, params_dev, grad_dev, loss_dev, (hipStream_t)st, b->stamps));
     return batch_done(b, (hipStream_t)st);
 }
 
@@ -1329,13 +1396,14 @@ int sv_batch_info(sv_batch_t *b, int64_t *nitems, int32_t *item_circuit, int64_t
     }
     if (wait_timeouts) {
         *wait_timeouts = 0;
-        if (b->fwd.ngroups > 0) {
-            if (b->done)
-                SV_HIP_TRY(hipEventSynchronize(b->done));
-            unsigned int v = 0;
-            SV_HIP_TRY(hipMemcpy(&v, b->fwd.gstate + 2 * b->fwd.ngroups, sizeof(v), hipMemcpyDeviceToHost));
-            *wait_timeouts = v;
-        }
+        for (const BatchDevice *d : {&b->fwd, &b->adj})
+            if (d->ngroups > 0) {
+                if (b->done)
+                    SV_HIP_TRY(hipEventSynchronize(b->done));
+                unsigned int v = 0;
+                SV_HIP_TRY(hipMemcpy(&v, d->gstate + 2 * d->ngroups, sizeof(v), hipMemcpyDeviceToHost));
+                *wait_timeouts += v;
+            }
     }
     return SV_OK;
 }
@@ -1367,7 +1435,7 @@ int sv_apply_circuits_batched(const sv_state_t *states, int ncirc, const sv_gate
     BatchDevice d;
     hipStream_t s = (hipStream_t)st;
     SV_TRY(upload_batch(h, true, s, &d));
-    const int r = launch_forward(dtype, d, ncirc, params_dev, s);
+    const int r = launch_batch(dtype, d, params_dev, nullptr, nullptr, s, nullptr);
     batch_release(&d, true, s);
     return r;
 }
@@ -1389,7 +1457,7 @@ int sv_adjoint_grad_batched(const sv_state_t *psi_states, const sv_state_t *lam_
     BatchDevice d;
     hipStream_t s = (hipStream_t)st;
     SV_TRY(upload_batch(h, true, s, &d));
-    const int r = launch_adjoint(dtype, d, ncirc, params_dev, grad_dev, loss_dev, s);
+    const int r = launch_batch(dtype, d, params_dev, grad_dev, loss_dev, s, nullptr);
     batch_release(&d, true, s);
     return r;
 }

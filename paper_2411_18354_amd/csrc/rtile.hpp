@@ -160,7 +160,9 @@ __device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const
     RtPhase *ph = reinterpret_cast<RtPhase *>(fr + (1 << NB));
     __syncthreads();  // the buffer's last readers are done
     for (uint32_t p = tid; p < np; p += blockDim.x) {
-        const RtPat q = pats[w[2] + p];
+        // (a byte offset below 2^32 from a uniform base: no 64-bit lane address)
+        const RtPat q = *reinterpret_cast<const RtPat *>(reinterpret_cast<const char *>(pats) +
+                                                         (uint32_t)((w[2] + p) * sizeof(RtPat)));
         double th = 0.0;
 #pragma unroll 1
         for (uint32_t k = 0; k < q.count; ++k) {
@@ -276,21 +278,31 @@ __device__ __forceinline__ float rt_own(float v) {
     return o;
 }
 
+// Byte i of a descriptor's byte array: by whole words, which are scalar loads
+// where the descriptor lies in memory.
+__device__ __forceinline__ uint32_t rt_byte(const uint8_t *b, int i) {
+    return reinterpret_cast<const uint32_t *>(b)[i >> 2] >> (8 * (i & 3)) & 63u;
+}
+
 // The lane's part of a global amplitude index, and one register's.
 __device__ __forceinline__ uint64_t rt_thread_offset(const RtIO &io, uint32_t tid, int bits) {
-    uint64_t a = 0;
+    uint32_t lo = 0, hi = 0;
 #pragma unroll
     for (int i = 0; i < kRtMaxThreadBits; ++i)
-        if (i < bits)  // uniform
-            a |= (uint64_t)((tid >> i) & 1u) << io.tq[i];
-    return a;
+        if (i < bits) {  // uniform
+            const uint64_t q = 1ull << rt_byte(io.tq, i);
+            const uint32_t on = 0u - ((tid >> i) & 1u);
+            lo |= on & (uint32_t)q;
+            hi |= on & (uint32_t)(q >> 32);
+        }
+    return (uint64_t)hi << 32 | lo;
 }
 template <int NB> __device__ __forceinline__ uint64_t rt_reg_offset(const RtIO &io, int r) {
     uint64_t a = 0;
 #pragma unroll
     for (int k = 0; k < NB; ++k)
         if ((r >> k) & 1)
-            a |= 1ull << io.rq[k];
+            a |= 1ull << rt_byte(io.rq, k);
     return a;
 }
 

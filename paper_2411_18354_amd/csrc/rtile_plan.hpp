@@ -76,7 +76,7 @@ struct RtPat {
 // thread and register bits, and the slot terms (bytes) of its thread bits (those
 // beyond the tile's give the lanes of a wider workgroup slots of their own).
 struct RtIO {
-    uint8_t tq[kRtMaxThreadBits], rq[kRtMaxNB];
+    uint8_t tq[12], rq[8];  // (whole words: kernels read them as such)
     uint32_t slot[kRtMaxThreadBits];
 };
 

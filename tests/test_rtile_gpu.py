@@ -197,3 +197,43 @@ def test_batched(gpu, dtype, m):
         got = psi.cpu().numpy().astype(np.complex128)
         slack = 2 * np.pi * 60 ** 2 * 2.0 ** -53 if c is circs[-1] else 0.0
         assert np.abs(got - ref).max() <= (TOL[dtype] + slack) * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("m", [7, 9, 13])
+def test_batched_gradients(gpu, dtype, m):
+    """Batched reverse sweeps: states swept in LDS, tiles that leave lanes
+    idle, one tile and many, angles that several gates share, diagonal and
+    single-gate passes; in a batch of few circuits the wide ones are split
+    over workgroups, with the same gradients however far.  Tolerances as for
+    the single sweep above."""
+    gpu.sv_tune_set("tile_log2_" + dtype, m)
+    ns = [2, 4, 5, 7, 10, 12, 13, 15]
+    circs = [_random_circuit(n, 40, 30 * m + i, params=4) if n > 3 else W.hea(n, 2, seed=i) for i, n in enumerate(ns)]
+    for c in circs:  # unitary gates only
+        c.gates[:] = [g for g in c.gates if g.kind[-1] != "U"]
+    hams = [W.zz_x_hamiltonian(n, 70 + n) for n in ns]
+    tdt = torch.complex128 if dtype == "c128" else torch.complex64
+    params = torch.tensor(np.concatenate([c.params for c in circs]), device="cuda")
+    finals = [torch.tensor(oracle.run_circuit(c, params=c.params), device="cuda").to(tdt) for c in circs]
+    got = []
+    for split in (1, 64):
+        gpu.sv_tune_set("batch_split", split)
+        psis = [f.clone() for f in finals]
+        lams = [torch.empty_like(f) for f in finals]
+        grad, loss = gpu.sv_adjoint_grad_batched(psis, lams, circs, params, hams)
+        got.append((grad.cpu().numpy(), loss.cpu().numpy(), psis))
+    off = 0
+    for i, (c, h) in enumerate(zip(circs, hams)):
+        p = slice(off, off + c.nparams)
+        off += c.nparams
+        l1 = sum(abs(t.coef) for t in h)
+        uses = max(sum(g.param == j for g in c.gates) for j in range(c.nparams))
+        # the same terms in other partial sums: at most 2^15 additions of 53 bits
+        assert np.abs(got[0][0][p] - got[1][0][p]).max() <= 2.0 ** -37 * l1 * uses
+        assert abs(got[0][1][i] - got[1][1][i]) <= 2.0 ** -37 * l1
+        assert torch.equal(got[0][2][i], got[1][2][i])
+        ref = oracle.grad_param_shift(c, c.params, h)
+        tol = 1e-8 * max(1.0, np.abs(ref).max()) if dtype == "c128" else 2e-5 * l1 * uses
+        assert np.abs(got[0][0][p] - ref).max() <= tol, c.n
+        assert abs(got[0][1][i] - oracle.loss(c, c.params, h)) <= (1e-10 if dtype == "c128" else 2e-5 * l1)
