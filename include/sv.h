@@ -448,11 +448,10 @@ int sv_adjoint_destroy(sv_adjoint_t *plan);
  * Many independent circuits, each on its own state (n may differ; one dtype
  * per batch), run by one persistent launch: each workgroup takes the next
  * work item from a device work queue (longest first) and applies all its
- * gates; a state of at most 2^9 complex128 or 2^10 complex64 amplitudes stays
- * in LDS for the whole circuit, a larger one runs its fused plan pass by pass
- * (a fused run through register tiles over the run's qubit set, other gates
- * as pair loops over the state).  A
- * forward circuit that costs more than the batch's mean load per workgroup
+ * gates; a state below 5 qubits (complex64: 7) stays in LDS for the whole
+ * circuit, a larger one runs its fused plan pass by pass (a fused run through
+ * register tiles over the run's qubit set, other gates as pair loops over the
+ * state).  A circuit that costs more than the batch's mean load per workgroup
  * is split over about cost / mean workgroups (at most the "batch_split"
  * knob): its passes are cut into chunks of whole tiles or pair-loop steps
  * that the workgroups joining it take in order, a pass's chunks starting once

@@ -12,8 +12,8 @@
 //    operations act on it; other gates are pair loops over the state.  A
 //    workgroup barrier separates passes.  A state of at most one tile is read
 //    and written once per pass, mostly once in all.
-//  - The smallest states (below one wavefront of register tiles) are read
-//    into LDS, all gates are applied there, and written back.
+//  - The smallest states (below 5 qubits, complex64: 7) are read into LDS, all
+//    gates are applied there, and written back.
 // Each gate visits only the amplitude pairs whose controls hold: the pair
 // index is built by inserting the target bit (0) and the control bits (their
 // values) into the iteration counter, lowest position first (Sec. III-B).
@@ -246,11 +246,15 @@ __device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, cons
     }
 }
 
-// States held in LDS for the whole circuit, gate by gate: those whose
-// register tile would leave a wavefront's lanes without amplitudes.  (400
-// circuits of widths 8-9: 0.41 ms, as before the wider ones moved to
-// register tiles.)
-__host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 10 : 11; }
+// States held in LDS for the whole circuit, gate by gate, rather than on
+// register tiles: those a wavefront's registers would hold many times over.
+// Above that register tiles win however few of their lanes have amplitudes,
+// as most operations need no barrier.  Ansatz circuits of three layers, LDS
+// against register tiles, 32 and 600 at once: complex128 n=5 61 and 79 us
+// against 53 and 70, n=8 89 and 119 against 56 and 74, n=9 101 and 143 against
+// 59 and 75; complex64 n=6 71 and 92 against 74 and 95, n=8 90 and 120 against
+// 66 and 91, n=10 112 and 160 against 70 and 92.
+__host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 5 : 7; }
 
 template <typename R>
 __device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsigned char *buf) {
