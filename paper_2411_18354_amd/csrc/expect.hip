@@ -14,19 +14,20 @@
 // that of the decoded state with the same double arithmetic.
 //
 // Tile passes.  A tile is the 2^m amplitudes (m = min(n, 12)) whose indices
-// agree outside a qubit set T made of qubits 0..5 and m - 6 others.  A term
-// whose x mask lies inside T pairs amplitudes of one tile only, so one read
-// of the state into LDS serves every such term: the terms are split into
-// tile sets (the first is qubits 0..m-1; the others take the remaining x
-// masks' qubits above 5, first fit, then are filled up to m with the lowest
-// unused qubits), and one pass per set (<= 64 terms) evaluates them all.
-// Diagonal terms join the first set.  Groups whose x mask has more than
-// m - 6 qubits above 5 keep the one-pass-per-group kernel.
+// agree outside a qubit set T made of the lowest qubits (as many as fill a
+// 128-byte line: kLow) and others.  A term whose x mask lies inside T pairs
+// amplitudes of one tile only, so one read of the state into LDS serves every
+// such term: the terms are split into tile sets (the first is qubits 0..m-1;
+// the others take the remaining x masks' upper qubits, first fit, then are
+// filled up to m with the lowest unused qubits), and one pass per set (<= 64
+// terms) evaluates them all.  Diagonal terms join the first set.  Groups whose
+// x mask has too many upper qubits keep the one-pass-per-group kernel.
 #include <algorithm>
 #include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <numeric>
+#include <utility>
 
 #include "pauli.hpp"
 
@@ -101,38 +102,52 @@ void pauli_release(PauliDevice *d, hipStream_t st) {
     *d = PauliDevice();
 }
 
-// Amplitude sources for the expectation passes: amplitude k as two doubles.
+// Amplitude sources for the expectation passes: what is loaded of amplitude k
+// (raw), and the amplitude as two doubles.
 template <typename R> struct CplxAmps {
-    const cplx_t<R> *__restrict__ psi;
-    __device__ void get(uint64_t k, double &re, double &im) const {
-        const cplx_t<R> v = psi[k];
+    static constexpr int kLow = sizeof(R) == 8 ? 3 : 4;  // qubits of a 128-byte line
+    using Raw = cplx_t<R>;
+    const Raw *__restrict__ psi;
+    __device__ Raw raw(uint64_t k) const { return psi[k]; }
+    static __device__ void decode(const Raw &v, double &re, double &im) {
         re = (double)v.x;
         im = (double)v.y;
     }
+    __device__ void get(uint64_t k, double &re, double &im) const { decode(raw(k), re, im); }
 };
 
 // SV_CQ16: one 32-bit word per amplitude, re in the low half.
 struct Q16Amps {
+    static constexpr int kLow = 5;
+    struct Raw {
+        uint32_t w;
+        int s;
+    };
     const uint32_t *__restrict__ codes;
     const int8_t *__restrict__ scales;
-    __device__ void get(uint64_t k, double &re, double &im) const {
-        const uint32_t w = codes[k];
-        const int s = scales[k >> 6];
-        re = ldexp((double)(int16_t)(w & 0xffffu), s);
-        im = ldexp((double)(int16_t)(w >> 16), s);
+    __device__ Raw raw(uint64_t k) const { return Raw{codes[k], scales[k >> 6]}; }
+    static __device__ void decode(const Raw &v, double &re, double &im) {
+        re = ldexp((double)(int16_t)(v.w & 0xffffu), v.s);
+        im = ldexp((double)(int16_t)(v.w >> 16), v.s);
     }
+    __device__ void get(uint64_t k, double &re, double &im) const { decode(raw(k), re, im); }
 };
 
 // SV_CQ32: two 32-bit words per amplitude (re, im).
 struct Q32Amps {
+    static constexpr int kLow = 4;
+    struct Raw {
+        uint2 w;
+        int s;
+    };
     const uint2 *__restrict__ codes;
     const int8_t *__restrict__ scales;
-    __device__ void get(uint64_t k, double &re, double &im) const {
-        const uint2 w = codes[k];
-        const int s = scales[k >> 6];
-        re = ldexp((double)(int32_t)w.x, s);
-        im = ldexp((double)(int32_t)w.y, s);
+    __device__ Raw raw(uint64_t k) const { return Raw{codes[k], scales[k >> 6]}; }
+    static __device__ void decode(const Raw &v, double &re, double &im) {
+        re = ldexp((double)(int32_t)v.w.x, v.s);
+        im = ldexp((double)(int32_t)v.w.y, v.s);
     }
+    __device__ void get(uint64_t k, double &re, double &im) const { decode(raw(k), re, im); }
 };
 
 // One pass for one group (<= kMaxT terms sharing the x mask X).
@@ -217,7 +232,6 @@ __global__ __launch_bounds__(kRedThreads) void k_expect_group(const A amps, uint
 }
 
 constexpr int kTileBits = 12;                                 // tile: 2^12 amplitudes, 64 KiB of double2
-constexpr int kTileLow = 6;                                   // qubits 0..5 are in every tile
 constexpr int kTileTerms = 64;                                // terms per tile pass: one lane each
 constexpr int kTileThreads = 256;
 constexpr int kTilePerLane = (1 << kTileBits) / kTileThreads;  // amplitudes per lane and tile
@@ -230,13 +244,16 @@ struct TTerm {
     int32_t slot;     // the term's position in the plan: its row of partials
 };
 
-// One tile pass.  Tile-local bit r < L (L = min(m, 6)) is qubit r; bit L + q
-// is the q-th lowest qubit of himask; the tile number's bit r is the r-th
-// lowest qubit of frmask.
+// One tile pass.  Tile-local bit r < L is qubit r; bit L + q is the q-th
+// lowest qubit of himask; the tile number's bit r is the r-th lowest qubit of
+// frmask.  Terms in order: the diagonal ones by the upper four bits of zl (ends in
+// end); those whose x mask is one of kRegMasks in tile-local bits 8 - 4 p ..
+// 11 - 4 p, by p and mask; the others.
+constexpr int kRegMasks[7] = {1, 2, 4, 8, 3, 6, 12};  // one bit or two neighbours
 struct TilePass {
     uint64_t himask, frmask;
-    int32_t m, nfree;
-    int32_t nt, nd, ne, pad;  // terms: nd diagonal, then ne with even ny, then odd ny
+    int32_t m, L, nfree, nt;
+    int32_t end[37];    // ends: 16 of diagonal terms, then 7 of each p
     TTerm t[kTileTerms];
 };
 
@@ -252,30 +269,65 @@ __device__ __forceinline__ uint64_t deposit_bits(uint64_t v, uint64_t mask) {
     return out;
 }
 
-// Four terms of a tile pass at a time (independent chains for the
-// scheduler to interleave): slots past the end repeat the last term and are
-// dropped.  s(k) = (-1)^{zl.k}.  Lane tid's r-th amplitude of a tile is
-// l = tid | (r << 8), and its r-th pair index tid | (r << 8); inserting a
-// cleared bit b is linear over xor, so each sign splits into a lane part
-// and a part per r (uniform), and every update is one fused multiply-add by
-// +-1.  Off-diagonal terms take Re(i^ny w) from Re w (IM false, ny even) or
-// Im w (IM true, ny odd) and add twice the sum over the lane's pairs
-// (l, l ^ xl) of s(l ^ xl) Re(i^ny conj(t_l) t_{l^xl}).
+// LDS slot of a tile's amplitude l: linear over xor, and without bank
+// conflicts whichever four bits of l number a lane's registers.
+__device__ __forceinline__ uint32_t tile_slot(uint32_t l) { return l ^ ((l >> 4) & 15u); }
+
+// The lane whose index differs in bit 0 or bit 1.
+template <int X> __device__ __forceinline__ double quad_xor(double v) {
+    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] or [2,3,0,1]
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// The lane N before in its row of 16, cyclically.
+template <int N> __device__ __forceinline__ double row_rotate(double v) {
+    constexpr int ctl = 0x120 + N;  // row_ror
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// The sums of four values over each row of 16 lanes: lane i gets that of
+// v[i & 3].  Values are folded two lanes to one as the lanes' share of them
+// narrows: 5 additions and shuffles where four separate sums take 16.
+__device__ __forceinline__ double row_sum4(double v0, double v1, double v2, double v3, uint32_t lane) {
+    const bool o1 = lane & 1u, o2 = lane & 2u;
+    const double a = (o1 ? v1 : v0) + quad_xor<1>(o1 ? v0 : v1);
+    const double b = (o1 ? v3 : v2) + quad_xor<1>(o1 ? v2 : v3);
+    double c = (o2 ? b : a) + quad_xor<2>(o2 ? a : b);
+    c += row_rotate<4>(c);
+    return c + row_rotate<8>(c);
+}
+
+// The pass's terms.  Lane j holds term j's masks; acck of lane i is the sum
+// of term 16 k + (i & 15) over its row of lanes and the wavefront's tiles, in
+// tile order.
 struct TileTerms {
-    uint32_t txl, tzl, tzh_lo, tzh_hi;
-    int tny;
+    uint32_t txl, tzl;
+    int tny, tend;          // tend: the pass's ends
+    uint64_t tzh;
+    uint64_t minus;         // bit j: term j changes sign in this tile (z outside the tile)
+    double acc0, acc1, acc2, acc3;
+    double v0, v1, v2, v3;  // values of the last four terms
 };
 
-__device__ __forceinline__ void tile_accumulate(const TileTerms &T, int j, int end, const double (&ts)[4],
-                                                uint64_t base, uint32_t lane, double &acc) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int jq = j + q;
-        if (jq < end) {
-            const uint64_t zh = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)T.tzh_hi, jq) << 32) |
-                                (uint32_t)__builtin_amdgcn_readlane((int)T.tzh_lo, jq);
-            if (lane == (uint32_t)jq)
-                acc += odd_parity(zh & base) ? -ts[q] : ts[q];
+// Value of term j in this lane (the lane's part of the sum over the tile).
+// Every fourth term the four are summed.
+__device__ __forceinline__ void tile_push(TileTerms &T, int j, double v, uint32_t lane) {
+    T.v0 = T.v1;
+    T.v1 = T.v2;
+    T.v2 = T.v3;
+    T.v3 = v;
+    if ((j & 3) == 3) {  // uniform
+        double c = row_sum4(T.v0, T.v1, T.v2, T.v3, lane);
+        if ((lane >> 2 & 3u) == ((uint32_t)j >> 2 & 3u)) {
+            c = (T.minus >> (j & 48) >> (lane & 15u)) & 1ull ? -c : c;
+            // (one addend each: an index would put the sums into scratch memory)
+            T.acc0 += j < 16 ? c : 0.0;
+            T.acc1 += j >> 4 == 1 ? c : 0.0;
+            T.acc2 += j >> 4 == 2 ? c : 0.0;
+            T.acc3 += j >= 48 ? c : 0.0;
         }
     }
 }
@@ -293,131 +345,96 @@ __device__ __forceinline__ void walsh16(double (&v)[kTilePerLane]) {
             }
 }
 
-// v[s] for a uniform s < 16 (static register indices).
-__device__ __forceinline__ double pick16(const double (&v)[kTilePerLane], uint32_t s) {
-    switch (s) {
-    case 0: return v[0];
-    case 1: return v[1];
-    case 2: return v[2];
-    case 3: return v[3];
-    case 4: return v[4];
-    case 5: return v[5];
-    case 6: return v[6];
-    case 7: return v[7];
-    case 8: return v[8];
-    case 9: return v[9];
-    case 10: return v[10];
-    case 11: return v[11];
-    case 12: return v[12];
-    case 13: return v[13];
-    case 14: return v[14];
-    default: return v[15];
-    }
-}
-
-// Diagonal terms: the lane's sum of s(l) |t_l|^2 over l = tid | (r << 8) is
-// (-1)^{zl.tid} times the Walsh coefficient of its |t|^2 at zl >> 8.
-__device__ __forceinline__ void tile_diag(const TileTerms &T, int j0, int j1, const double (&wc)[kTilePerLane],
-                                          uint32_t tid, uint64_t base, uint32_t lane, double &acc) {
-    for (int j = j0; j < j1; j += 4) {
-        double ts[4];
+// A lane's 16 amplitudes t_r: sum over the pairs (r, r ^ X), the lowest bit of
+// X clear in r, of (-1)^{zr.r} Re or Im conj(t_r) t_{r^X}.
+template <int X>
+__device__ __forceinline__ double reg_pairs(const double (&tr)[kTilePerLane], const double (&ti)[kTilePerLane], bool im,
+                                            uint32_t zr) {
+    constexpr int low = X & -X;
+    double s = 0.0, q = 0.0;
+    if (!im && zr == 0) {  // uniform; a product of X only
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t zl = (uint32_t)__builtin_amdgcn_readlane((int)T.tzl, min(j + q, j1 - 1));
-            ts[q] = pick16(wc, zl >> 8);
-            if (__popc(zl & tid) & 1)
-                ts[q] = -ts[q];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            ts[q] = wave_sum(ts[q]);
-        tile_accumulate(T, j, j1, ts, base, lane, acc);
-    }
-}
-
-template <bool IM>
-__device__ __forceinline__ void tile_offdiag(const TileTerms &T, int j0, int j1, const double2 *tile, uint32_t tid,
-                                             uint32_t M, uint64_t base, uint32_t lane, double &acc) {
-    for (int j = j0; j < j1; j += 4) {
-        uint32_t xl[4], zl[4], b[4], lt[4];
-        double ts[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int jq = min(j + q, j1 - 1);
-            xl[q] = (uint32_t)__builtin_amdgcn_readlane((int)T.txl, jq);
-            zl[q] = (uint32_t)__builtin_amdgcn_readlane((int)T.tzl, jq);
-            b[q] = (uint32_t)__builtin_ctz(xl[q]);
-            lt[q] = ((tid >> b[q]) << (b[q] + 1)) | (tid & ((1u << b[q]) - 1));
-            ts[q] = 0.0;
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < (uint32_t)kTilePerLane / 2; ++r) {
-            if ((tid | (r << 8)) < M / 2) {
-                const uint32_t ir = r << 8;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t lr = ((ir >> b[q]) << (b[q] + 1)) | (ir & ((1u << b[q]) - 1));
-                    const uint32_t l = lt[q] ^ lr;
-                    const double2 u = tile[l], v = tile[l ^ xl[q]];
-                    const double w = IM ? u.x * v.y - u.y * v.x : u.x * v.x + u.y * v.y;
-                    ts[q] = __builtin_fma((__popc(zl[q] & lr) & 1) ? -1.0 : 1.0, w, ts[q]);
-                }
+        for (int r = 0; r < kTilePerLane; ++r)
+            if (!(r & low)) {
+                s = __builtin_fma(tr[r], tr[r ^ X], s);
+                q = __builtin_fma(ti[r], ti[r ^ X], q);
             }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            // Re(i^ny w): ny = 0, 1, 2, 3 give Re w, -Im w, -Re w, Im w
-            const int ny = __builtin_amdgcn_readlane(T.tny, min(j + q, j1 - 1));
-            const bool neg = (ny == 1 || ny == 2) != (bool)(__popc(zl[q] & (lt[q] ^ xl[q])) & 1);
-            ts[q] = wave_sum(neg ? -2.0 * ts[q] : 2.0 * ts[q]);
-        }
-        tile_accumulate(T, j, j1, ts, base, lane, acc);
+        return s + q;
     }
+#pragma unroll
+    for (int r = 0; r < kTilePerLane; ++r)
+        if (!(r & low)) {
+            const double sg = (__popc(zr & (uint32_t)r) & 1) ? -1.0 : 1.0;  // uniform
+            const double w = im ? tr[r] * ti[r ^ X] - ti[r] * tr[r ^ X] : tr[r] * tr[r ^ X] + ti[r] * ti[r ^ X];
+            s = __builtin_fma(sg, w, s);
+        }
+    return s;
+}
+
+// f(std::integral_constant<int, I>) for the numbers of the sequence.
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(const F &f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
 }
 
 // Every tile of the pass into LDS once, then, once the next tile's loads
-// are issued, every term of the pass over it: diagonal terms from a Walsh
-// transform of the lane's |t|^2, then the pairs read from LDS.  Lane j of each
-// wavefront holds term j's masks (read by every lane with readlane, so the
-// term loops load nothing from memory) and accumulates term j over the
-// wavefront's tiles, in tile order; the four wavefronts' sums are added in
-// order at the end.
+// are issued, every term of the pass over it (each adds, over the pairs
+// (l, l ^ xl) with the lowest bit of xl clear in l, twice
+// (-1)^{zl.(l^xl)} Re(i^ny conj(t_l) t_{l^xl})):
+//  - diagonal terms from a Walsh transform of the lane's |t|^2: the lane's sum
+//    over l = tid | (r << 8) is (-1)^{zl.tid} times its coefficient at zl >> 8;
+//  - terms whose x mask is one bit or two neighbours of a group of four
+//    tile-local bits: the tile is read from LDS once per group, that group's
+//    bits numbering a lane's registers, and their pairs are in registers;
+//  - the other terms' pairs from LDS.
+// A pass over 2^26 amplitudes takes 0.23 ms in complex128 and 0.16 in complex64
+// with few terms (reading the state alone 0.18 and 0.14); a further term adds
+// 1 to 7 us from registers (bound by FP64 arithmetic, two wavefronts per SIMD),
+// 20 from LDS (by its bandwidth).  With both amplitudes of every pair read from
+// LDS for every term, a sum over the wavefront for each, and six low qubits in
+// every tile, the 51 terms of a chain model took four passes and 1.45 ms
+// (complex64 1.35), now three and 0.86 (0.77); 20 strings of up to four
+// operators 1.08 -> 0.78 ms.
 template <typename A>
-__global__ __launch_bounds__(kTileThreads) void k_expect_tile(const A amps, const TilePass P,
-                                                              double *__restrict__ partials) {
+__global__ __launch_bounds__(kTileThreads, 2) void k_expect_tile(const A amps, const TilePass P,
+                                                                 double *__restrict__ partials) {
     __shared__ double2 tile[1 << kTileBits];
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t M = 1u << P.m;
-    const int L = P.m < kTileLow ? P.m : kTileLow;
-    const uint32_t lowmask = (1u << L) - 1;
+    const int L = P.L, nt = P.nt;
     const uint64_t ntiles = 1ull << P.nfree, himask = P.himask, frmask = P.frmask;
-    const int nt = P.nt, nd = P.nd, ne = P.ne;
-    // this lane's amplitudes of a tile, l = tid | (r << 8): index bits on the
-    // tile's qubits (lanes past a small tile's end take its last amplitude,
-    // unused)
-    uint64_t off[kTilePerLane];
+    // index bits on the tile's qubits of the lane's amplitudes l = tid | (r << 8):
+    // those of tid, and those of r's bits (uniform)
+    const uint32_t lt = min(tid, M - 1);
+    const uint64_t off = (lt & ((1u << L) - 1)) | deposit_bits(lt >> L, himask);
+    uint64_t rb[4];
 #pragma unroll
-    for (int r = 0; r < kTilePerLane; ++r) {
-        const uint32_t l = min(tid | ((uint32_t)r << 8), M - 1);
-        off[r] = (l & lowmask) | deposit_bits(l >> L, himask);
-    }
-    TileTerms T{0, 0, 0, 0, 0};
+    for (int k = 0; k < 4; ++k)
+        rb[k] = 8 + k < P.m ? deposit_bits(1ull << (8 + k - L), himask) : 0;
+    TileTerms T;
+    T.txl = T.tzl = 0;
+    T.tny = 0;
+    T.tzh = 0;
+    T.minus = 0;
+    T.tend = lane < 37 ? P.end[lane] : 0;
+    T.v0 = T.v1 = T.v2 = T.v3 = 0.0;
+    T.acc0 = T.acc1 = T.acc2 = T.acc3 = 0.0;
     if ((int)lane < nt) {
         T.txl = P.t[lane].xl;
         T.tzl = P.t[lane].zl;
         T.tny = P.t[lane].ny;
-        T.tzh_lo = (uint32_t)P.t[lane].zh;
-        T.tzh_hi = (uint32_t)(P.t[lane].zh >> 32);
+        T.tzh = P.t[lane].zh;
     }
-    double acc = 0.0;
-    double vr[kTilePerLane], vi[kTilePerLane];
-    uint64_t tl = blockIdx.x;
-    if (tl < ntiles) {
-        const uint64_t base = deposit_bits(tl, frmask);
+    typename A::Raw raw[kTilePerLane];
+    auto load = [&](uint64_t t) {
+        const uint64_t at = deposit_bits(t, frmask) | off;
 #pragma unroll
-        for (int r = 0; r < kTilePerLane; ++r)
-            amps.get(base | off[r], vr[r], vi[r]);
-    }
+        for (int r = 0; r < kTilePerLane; ++r)  // (past a small tile's end: an amplitude of it, unused)
+            raw[r] = amps.raw(at | (r & 1 ? rb[0] : 0) | (r & 2 ? rb[1] : 0) | (r & 4 ? rb[2] : 0) | (r & 8 ? rb[3] : 0));
+    };
+    uint64_t tl = blockIdx.x;
+    if (tl < ntiles)
+        load(tl);
     for (; tl < ntiles; tl += gridDim.x) {
         const uint64_t base = deposit_bits(tl, frmask);
         __syncthreads();  // every read of the previous tile is done
@@ -425,32 +442,96 @@ __global__ __launch_bounds__(kTileThreads) void k_expect_tile(const A amps, cons
 #pragma unroll
         for (int r = 0; r < kTilePerLane; ++r) {
             const uint32_t l = tid | ((uint32_t)r << 8);
+            double re = 0.0, im = 0.0;
             if (l < M)
-                tile[l] = make_double2(vr[r], vi[r]);
-            wc[r] = l < M ? vr[r] * vr[r] + vi[r] * vi[r] : 0.0;
+                A::decode(raw[r], re, im);
+            tile[tile_slot(l)] = make_double2(re, im);
+            wc[r] = re * re + im * im;
         }
         __syncthreads();
-        if (tl + gridDim.x < ntiles) {
-            const uint64_t nb = deposit_bits(tl + gridDim.x, frmask);
-#pragma unroll
-            for (int r = 0; r < kTilePerLane; ++r)
-                amps.get(nb | off[r], vr[r], vi[r]);
-        }
-        if (nd) {
+        if (tl + gridDim.x < ntiles)
+            load(tl + gridDim.x);
+        T.minus = __ballot(odd_parity(T.tzh & base));
+        int j = 0;
+        if (__builtin_amdgcn_readlane(T.tend, 15)) {
             walsh16(wc);
-            tile_diag(T, 0, nd, wc, tid, base, lane, acc);
+            unrolled([&](auto q) __attribute__((always_inline)) {
+#pragma unroll 1
+                for (const int end = __builtin_amdgcn_readlane(T.tend, q); j < end; ++j) {
+                    const uint32_t zl = (uint32_t)__builtin_amdgcn_readlane((int)T.tzl, j);
+                    tile_push(T, j, (__popc(zl & tid) & 1) ? -wc[q] : wc[q], lane);
+                }
+            }, std::make_integer_sequence<int, kTilePerLane>());
         }
-        tile_offdiag<false>(T, nd, nd + ne, tile, tid, M, base, lane, acc);
-        tile_offdiag<true>(T, nd + ne, nt, tile, tid, M, base, lane, acc);
+#pragma unroll 1
+        for (int p = 0; p < 3; ++p) {
+            if (j == __builtin_amdgcn_readlane(T.tend, 16 + 7 * p + 6))
+                continue;  // uniform
+            const int sh = 8 - 4 * p;
+            // tid's bits around the register bits sh .. sh + 3
+            const uint32_t l0 = ((tid >> sh) << (sh + 4)) | (tid & ((1u << sh) - 1u));
+            double tr[kTilePerLane], ti[kTilePerLane];
+#pragma unroll
+            for (int r = 0; r < kTilePerLane; ++r) {
+                const double2 t = tile[tile_slot(l0) ^ tile_slot((uint32_t)r << sh)];
+                tr[r] = t.x;
+                ti[r] = t.y;
+            }
+            unrolled([&](auto k) __attribute__((always_inline)) {
+                constexpr int X = kRegMasks[k];
+#pragma unroll 1
+                for (const int end = __builtin_amdgcn_readlane(T.tend, 16 + 7 * p + k); j < end; ++j) {
+                    // (not known to the compiler, which would otherwise form
+                    // every kind of product ahead of the loop)
+#pragma unroll
+                    for (int r = 0; r < kTilePerLane; ++r)
+                        asm volatile("" : "+v"(tr[r]), "+v"(ti[r]));
+                    const uint32_t zl = (uint32_t)__builtin_amdgcn_readlane((int)T.tzl, j);
+                    const int ny = __builtin_amdgcn_readlane(T.tny, j);
+                    const double s = reg_pairs<X>(tr, ti, ny & 1, (zl >> sh) & 15u);
+                    // Re(i^ny w): ny = 0, 1, 2, 3 give Re w, -Im w, -Re w, Im w
+                    const bool neg =
+                        (ny == 1 || ny == 2) != (bool)(__popc(zl & (l0 ^ ((uint32_t)X << sh))) & 1);
+                    tile_push(T, j, neg ? -2.0 * s : 2.0 * s, lane);
+                }
+            }, std::make_integer_sequence<int, 7>());
+        }
+#pragma unroll 1
+        for (; j < nt; ++j) {
+            const uint32_t xl = (uint32_t)__builtin_amdgcn_readlane((int)T.txl, j);
+            const uint32_t zl = (uint32_t)__builtin_amdgcn_readlane((int)T.tzl, j);
+            const int ny = __builtin_amdgcn_readlane(T.tny, j);
+            const uint32_t b = (uint32_t)__builtin_ctz(xl), sx = tile_slot(xl);
+            const uint32_t l0 = ((tid >> b) << (b + 1)) | (tid & ((1u << b) - 1)), s0 = tile_slot(l0);
+            const bool im = ny & 1;
+            double s = 0.0;
+#pragma unroll
+            for (uint32_t r = 0; r < (uint32_t)kTilePerLane / 2; ++r) {
+                const uint32_t ir = r << 8;  // pair number tid | ir; a cleared bit goes in linearly over xor
+                const uint32_t lr = ((ir >> b) << (b + 1)) | (ir & ((1u << b) - 1));
+                const uint32_t at = s0 ^ tile_slot(lr);
+                const double2 u = tile[at], v = tile[at ^ sx];
+                const double w = im ? u.x * v.y - u.y * v.x : u.x * v.x + u.y * v.y;
+                s = __builtin_fma((__popc(zl & lr) & 1) ? -1.0 : 1.0, w, s);
+            }
+            const bool neg = (ny == 1 || ny == 2) != (bool)(__popc(zl & (l0 ^ xl)) & 1);
+            tile_push(T, j, neg ? -2.0 * s : 2.0 * s, lane);
+        }
+        for (; j & 3; ++j)
+            tile_push(T, j, 0.0, lane);
     }
-    __syncthreads();  // the tile's LDS now holds the wavefronts' sums
+    __syncthreads();  // the tile's LDS now holds the rows' sums
     double *wsum = reinterpret_cast<double *>(tile);
-    wsum[tid] = acc;
+    double *row = wsum + (tid >> 4) * kTileTerms + (tid & 15u);
+    row[0] = T.acc0;
+    row[16] = T.acc1;
+    row[32] = T.acc2;
+    row[48] = T.acc3;
     __syncthreads();
     if ((int)tid < nt) {
         double s = 0.0;
-        for (int q = 0; q < kTileThreads / 64; ++q)
-            s += wsum[q * 64 + tid];
+        for (int q = 0; q < kTileThreads / 16; ++q)
+            s += wsum[q * kTileTerms + tid];
         partials[(size_t)P.t[tid].slot * kMaxPartials + blockIdx.x] = s;
     }
 }
@@ -563,13 +644,17 @@ static void tile_split(uint64_t mask, int L, uint64_t himask, uint32_t *local, u
     *outside = mask & ~lowm & ~himask;
 }
 
-static int make_expect_plan(int n, const sv_pauli_t *terms, int nterms, ExpectPlan *e) {
+static int make_expect_plan(int n, int dtype, const sv_pauli_t *terms, int nterms, ExpectPlan *e) {
     SV_TRY(make_pauli_plan(n, terms, nterms, &e->pp));
     const PauliPlan &pp = e->pp;
     e->tiles.clear();
     e->rest.clear();
     e->nblk.assign(pp.terms.size(), 0);
-    const int m = std::min(n, kTileBits), L = std::min(m, kTileLow), nh = m - L;
+    const int low = dtype == SV_C128 ? CplxAmps<double>::kLow
+                    : dtype == SV_C64 ? CplxAmps<float>::kLow
+                    : dtype == SV_CQ16 ? Q16Amps::kLow
+                                       : Q32Amps::kLow;
+    const int m = std::min(n, kTileBits), L = std::min(m, low), nh = m - L;
     const uint64_t lowm = (1ull << L) - 1;
     DeviceInfo di;
     const uint64_t cus = device_info(&di) == SV_OK ? (uint64_t)di.num_cus : 256;
@@ -607,6 +692,7 @@ static int make_expect_plan(int n, const sv_pauli_t *terms, int nterms, ExpectPl
         TilePass P;
         memset(&P, 0, sizeof(P));
         P.m = m;
+        P.L = L;
         P.nfree = n - m;
         P.himask = set;
         P.frmask = ((n >= 64) ? ~0ull : ((1ull << n) - 1)) & ~lowm & ~set;
@@ -632,11 +718,22 @@ static int make_expect_plan(int n, const sv_pauli_t *terms, int nterms, ExpectPl
         if (P.nt)
             e->tiles.push_back(P);
     }
-    for (TilePass &P : e->tiles) {  // diagonal terms first, then even ny, then odd ny
-        auto kind = [](const TTerm &t) { return t.xl == 0 ? 0 : 1 + (t.ny & 1); };
-        std::stable_sort(P.t, P.t + P.nt, [&](const TTerm &a, const TTerm &b) { return kind(a) < kind(b); });
-        P.nd = (int32_t)std::count_if(P.t, P.t + P.nt, [&](const TTerm &t) { return kind(t) == 0; });
-        P.ne = (int32_t)std::count_if(P.t, P.t + P.nt, [&](const TTerm &t) { return kind(t) == 1; });
+    for (TilePass &P : e->tiles) {
+        // place of a term in the pass's order: 0..15 diagonal, 16.. register
+        // groups and masks, 37 the others
+        auto place = [](const TTerm &t) {
+            if (t.xl == 0)
+                return (int)(t.zl >> 8);
+            for (int p = 0; p < 3; ++p)
+                for (int k = 0; k < 7; ++k)
+                    if (t.xl == (uint32_t)kRegMasks[k] << (8 - 4 * p))
+                        return 16 + 7 * p + k;
+            return 37;
+        };
+        std::stable_sort(P.t, P.t + P.nt, [&](const TTerm &a, const TTerm &b) { return place(a) < place(b); });
+        for (int j = 0; j < P.nt; ++j)
+            for (int at = place(P.t[j]); at < 37; ++at)
+                P.end[at] = j + 1;
     }
     return SV_OK;
 }
@@ -703,7 +800,7 @@ static int expect_impl(const sv_state_t *s, const sv_pauli_t *terms, int nterms,
                        double *out_terms, hipStream_t st) {
     SV_TRY(validate_state(s, true));
     ExpectPlan plan;
-    SV_TRY(make_expect_plan(s->n, terms, nterms, &plan));
+    SV_TRY(make_expect_plan(s->n, s->dtype, terms, nterms, &plan));
     const std::vector<int32_t> &nblk = plan.nblk;
     PauliDevice d;
     SV_TRY(pauli_upload(plan.pp, (size_t)plan.pp.terms.size() * (kMaxPartials + 1), st, &d));
@@ -791,7 +888,7 @@ static int expect_noalloc_impl(const sv_state_t *s, const sv_pauli_t *terms, int
     if (nterms > kNoAllocTerms)
         return fail(SV_EINVAL, "nterms %d exceeds the allocation-free limit of %d terms", nterms, kNoAllocTerms);
     ExpectPlan plan;
-    SV_TRY(make_expect_plan(s->n, terms, nterms, &plan));
+    SV_TRY(make_expect_plan(s->n, s->dtype, terms, nterms, &plan));
     ExpectTables t;
     memset(&t, 0, sizeof(t));
     t.nterms = (int32_t)plan.pp.terms.size();
