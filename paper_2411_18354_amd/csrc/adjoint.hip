@@ -254,7 +254,9 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     const int nslots = (int)(gen.size() / 8);
     a->nslots = nslots;
     const int m_cap = std::max(1, tuning().tile_log2[dtype == SV_C128 ? 0 : 1] - 1);
-    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, true, true, &a->rc));
+    // (complex64: LDS tiles, as its forward circuit)
+    SV_TRY(circuit_create(n, dtype, rev.data(), ngates, nparams, SV_FUSE, async, st, m_cap, dtype == SV_C128, true,
+                          &a->rc));
     sv_circuit *rc = a->rc;
 
     // per pass: single passes need pair plans, fused ones per-descriptor slots
@@ -332,7 +334,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
         for (int j = 0; j < p.count; ++j)
             npg += dslot[p.first + j] >= 0 ? 1 : 0;
         if (p.rt) {
-            a->pass_lds[pi] = rt_adjoint_lds(dtype, p.tm, p.rp);
+            a->pass_lds[pi] = rt_adjoint_lds(p.tm, p.rp);
             lds_rt = std::max(lds_rt, a->pass_lds[pi]);
             continue;
         }
@@ -343,7 +345,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     if (std::max(lds, lds_rt) > kLdsPerWorkgroup)
         return fail(SV_ENOTSUP, "adjoint pass needs %zu bytes of LDS", std::max(lds, lds_rt));
     if (lds_rt > 65536)
-        SV_TRY(rt_adjoint_lds_limit(dtype, lds_rt));
+        SV_TRY(rt_adjoint_lds_limit(lds_rt));
     if (lds > 65536) {
         const hipError_t e = dtype == SV_C128 ? hipFuncSetAttribute((const void *)k_adj_tile<double>,
                                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -376,7 +378,7 @@ static int adjoint_enqueue(AdjointPlan *a, const sv_state_t *psi, const sv_state
             const unsigned grid = (unsigned)std::min<uint64_t>(p.tm.ntiles, kMaxPartials);
             const DeviceGates dg{rc->d_tiles + p.first, p.count, rc->d_pats, rc->d_mems};
             if (p.rt) {
-                SV_TRY(launch_rt_adjoint(dtype, psi->data, lam->data, p.tm, p.rp, rc->rt, dg, grid, a->d_partials,
+                SV_TRY(launch_rt_adjoint(psi->data, lam->data, p.tm, p.rp, rc->rt, dg, grid, a->d_partials,
                                          kMaxPartials, st));
                 continue;
             }

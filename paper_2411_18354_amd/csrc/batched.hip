@@ -28,6 +28,7 @@
 #include "gates.hpp"
 #include "pauli.hpp"
 #include "rtile.hpp"
+#include "tile_adj.hpp"
 
 namespace sv {
 
@@ -44,8 +45,21 @@ int validate_unitary_gate(const sv_gate_t &g, int index);
 // 1.23 ms; 400 of widths 8-12: 0.49 ms, 0.42 ms.
 constexpr int kBatchThreads = 256, kBatchThreadBits = 8;
 constexpr unsigned kBatchPerCu = 4;
-constexpr size_t kBatchSlot = 64;
+constexpr size_t kBatchSlot = 128;  // reduction scratch, work item and ticket
 constexpr size_t kBatchExchange = 32768, kBatchLds = kBatchExchange + kBatchSlot;
+// Complex64 batches that take gradients keep LDS tiles, 512 lanes: a tile's
+// gates in program order, one rounding per gate and amplitude.  Register tiles
+// reorder commuting gates and share diagonal factors, which moves a complex64
+// state by single-precision rounding, and with it losses and gradients, which
+// are given in double.
+constexpr int kLdsThreads = 512;
+__host__ __device__ constexpr int batch_threads(bool lds) { return lds ? kLdsThreads : kBatchThreads; }
+constexpr int kLdsTileBits = 13;  // 64 KiB of complex64: the tile, or a resident state
+constexpr size_t kLdsBytes = 65536 + sizeof(double) * diag_table_doubles(kLdsTileBits);
+// amplitudes per lane in flight when a tile pair is written back (tiles are
+// loaded by direct HBM-to-LDS copies)
+constexpr int kLdsCopy = 2;
+
 struct BGate {
     double m[8];      // matrix of a fixed gate
     int32_t kind;     // matrix recomputed from params[param] when param >= 0
@@ -176,13 +190,13 @@ __device__ __forceinline__ void gate_on_block_i(cplx_t<R> *base, int nbits, int 
 
 // 32-bit index arithmetic whenever the block's indices fit (always for LDS
 // tiles; for global memory up to n = 32).
-template <typename R>
+template <typename R, int THREADS>
 __device__ __forceinline__ void gate_on_block(cplx_t<R> *base, int nbits, int target, uint64_t cmask, uint64_t cvals,
                                               const Mat2<R> &mm, uint64_t lo, uint64_t hi) {
     if (nbits <= 32)
-        gate_on_block_i<R, uint32_t, kBatchThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint32_t, THREADS>(base, nbits, target, cmask, cvals, mm, lo, hi);
     else
-        gate_on_block_i<R, uint64_t, kBatchThreads>(base, nbits, target, cmask, cvals, mm, lo, hi);
+        gate_on_block_i<R, uint64_t, THREADS>(base, nbits, target, cmask, cvals, mm, lo, hi);
 }
 
 // Device tables of a run.
@@ -193,6 +207,7 @@ struct BatchTables {
     const TileGate *tiles;
     const RtOp *ops;
     const RtPat *pats;
+    const SweepPat *lpats;  // LDS tiles: phase patterns
     const SweepMember *mems;
     const double *params;
     unsigned int *gstate;  // split circuits: ticket counters
@@ -205,6 +220,7 @@ struct SweepTables {
     const DTerm *terms;
     const double *gens;
     const int32_t *gen_of;
+    const int32_t *tslot;  // LDS tiles: generator of every tile descriptor, or -1
     const BSlot *slots;
     const int32_t *csr;
     double *grad, *loss;
@@ -246,6 +262,25 @@ __device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, cons
     }
 }
 
+// The same on LDS tiles.
+template <typename R>
+__device__ __forceinline__ void lds_tiles(cplx_t<R> *psi, const BPass &p, const BatchTables &d, unsigned char *buf,
+                                          uint64_t lo, uint64_t hi) {
+    const DeviceGates dg{d.tiles + p.first, p.count, d.lpats, d.mems};
+    cplx_t<R> *lds = reinterpret_cast<cplx_t<R> *>(buf);
+    const uint32_t T = 1u << p.tm.m;
+    for (uint64_t tt = lo; tt < hi; ++tt) {
+        const uint64_t base = expand_index<uint64_t>(p.tm.outer, tt);
+        if (!tile_touched(base, dg))
+            continue;  // uniform
+        tile_load_dma<R, kLdsThreads>(lds, psi, base, p.tm, T);
+        __syncthreads();
+        tile_run<R, kLdsThreads, false>(lds, base, p.tm, dg);  // at its register limit
+        tile_store<R, kLdsThreads, false, 1>(psi, lds, base, p.tm, T);
+        __syncthreads();
+    }
+}
+
 // States held in LDS for the whole circuit, gate by gate, rather than on
 // register tiles: those a wavefront's registers would hold many times over.
 // Above that register tiles win however few of their lanes have amplitudes,
@@ -256,20 +291,20 @@ __device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, cons
 // 66 and 91, n=10 112 and 160 against 70 and 92.
 __host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 5 : 7; }
 
-template <typename R>
+template <typename R, int THREADS>
 __device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsigned char *buf) {
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     const uint64_t N = 1ull << c.n;
     cplx_t<R> *lds = reinterpret_cast<cplx_t<R> *>(buf);
-    for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
+    for (uint64_t k = threadIdx.x; k < N; k += THREADS)
         lds[k] = psi[k];
     __syncthreads();
     for (int i = 0; i < c.ngates; ++i) {
         const BGate &g = d.gates[c.first_gate + i];
-        gate_on_block<R>(lds, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), 0, ~0ull);
+        gate_on_block<R, THREADS>(lds, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), 0, ~0ull);
         __syncthreads();
     }
-    for (uint64_t k = threadIdx.x; k < N; k += kBatchThreads)
+    for (uint64_t k = threadIdx.x; k < N; k += THREADS)
         psi[k] = lds[k];
 }
 
@@ -285,8 +320,10 @@ __device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsig
 // Before, one workgroup of 512 or 1024 lanes took a whole circuit with both
 // tiles in LDS: bound by the LDS, and by few workgroups.  Ansatz circuits of
 // three layers, complex128: 160 of 15 qubits 4.71 -> 1.17 ms, 160 of 13 1.31 ->
-// 0.36 ms, 4 of 15 4.39 -> 0.27 ms, 600 of 8 0.63 -> 0.12 ms; complex64: 160 of
-// 15 2.36 -> 1.02 ms, 4 of 8 0.34 -> 0.11 ms.
+// 0.36 ms, 4 of 15 4.39 -> 0.27 ms, 600 of 8 0.63 -> 0.12 ms.  Complex64 keeps
+// its LDS tiles and gains from the split alone, forward and gradients together:
+// 160 of 15 qubits (two layers) 1.88 -> 1.30 ms, 4 of 15 (four) 3.27 -> 0.62 ms,
+// 4 of 8 0.25 -> 0.13 ms.
 
 // Tiles [lo, hi) of a fused reverse pass.
 template <typename R>
@@ -344,10 +381,37 @@ __device__ __forceinline__ void sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, cons
     }
 }
 
+// The same on LDS tiles.
+template <typename R>
+__device__ __forceinline__ void lds_sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, const BPass &p, const BatchTables &d,
+                                                const SweepTables &a, unsigned char *buf, uint64_t lo, uint64_t hi,
+                                                int chunk) {
+    const DeviceGates dg{d.tiles + p.first, p.count};
+    const int32_t *gs = a.tslot + p.first;
+    const uint32_t T = 1u << p.tm.m;
+    cplx_t<R> *tp = reinterpret_cast<cplx_t<R> *>(buf), *tl = tp + T;
+    double *accl = reinterpret_cast<double *>(tl + T);
+    const int npg = adj_acc_zero(dg, gs, accl);
+    for (uint64_t tt = lo; tt < hi; ++tt) {
+        const uint64_t base = expand_index<uint64_t>(p.tm.outer, tt);
+        if (!adj_tile_touched(base, dg))
+            continue;  // uniform
+        tile_load_dma<R, kLdsThreads>(tp, psi, base, p.tm, T);
+        tile_load_dma<R, kLdsThreads>(tl, lam, base, p.tm, T);
+        __syncthreads();
+        adj_tile_run<R, kLdsThreads>(tp, tl, base, T, dg, gs, a.gens, accl);
+        tile_store2<R, kLdsThreads, false, kLdsCopy>(psi, lam, tp, tl, base, p.tm, T);
+        __syncthreads();
+    }
+    double *part = d.part + p.part + (int64_t)chunk * p.nacc;
+    for (int k = threadIdx.x; k < npg; k += kLdsThreads)
+        part[k] = adj_acc_sum(accl, k);
+}
+
 // One gate of the reverse sweep on the amplitudes at psi and lam (global
 // memory or LDS): gradient term (when parameterised) and un-apply, the pairs
 // [lo, min(hi, pairs)).  Returns the workgroup's sum of the term.
-template <typename R>
+template <typename R, int THREADS>
 __device__ __forceinline__ double sweep_gate(int n, const BGate &g, const double *gen, const double *params,
                                           cplx_t<R> *psi, cplx_t<R> *lam, uint64_t lo, uint64_t hi,
                                           double *scratch) {
@@ -357,7 +421,7 @@ __device__ __forceinline__ double sweep_gate(int n, const BGate &g, const double
     const uint64_t npairs = hi < all ? hi : all;
     const uint64_t st = 1ull << g.target;
     double acc = 0.0;
-    for (uint64_t it = lo + threadIdx.x; it < npairs; it += kBatchThreads) {
+    for (uint64_t it = lo + threadIdx.x; it < npairs; it += THREADS) {
         const uint64_t p1 = insert_bits<uint64_t>(it, pos, g.cvals);
         cplx_t<R> x = psi[p1], y = psi[p1 | st], lx = lam[p1], ly = lam[p1 | st];
         if (gen) {
@@ -379,7 +443,7 @@ __device__ __forceinline__ double sweep_gate(int n, const BGate &g, const double
 }
 
 // The other passes.
-template <typename R>
+template <typename R, int THREADS>
 __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass &p, const BGate *gates,
                                          const double *params, double *parts, SweepTables d, unsigned char *buf,
                                          double *scratch, uint64_t lo, uint64_t hi, int chunk) {
@@ -390,7 +454,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
     const int tid = (int)threadIdx.x;
     if (p.kind == kPassGate) {
         const int gs = d.gen_of[c.first_gate + p.gate];
-        const double sum = sweep_gate<R>(c.n, gates[c.first_gate + p.gate], gs >= 0 ? d.gens + 8 * gs : nullptr,
+        const double sum = sweep_gate<R, THREADS>(c.n, gates[c.first_gate + p.gate], gs >= 0 ? d.gens + 8 * gs : nullptr,
                                          params, psi, lam, lo, hi, scratch);
         if (gs >= 0 && tid == 0)
             part[0] = sum;
@@ -399,7 +463,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
             d.stamps[2 * ci] = wall_clock64();
         const uint64_t end = hi < N ? hi : N;
         double lp = 0.0;
-        for (uint64_t k = lo + tid; k < end; k += kBatchThreads) {
+        for (uint64_t k = lo + tid; k < end; k += THREADS) {
             const cplx_t<R> at = psi[k];
             cplx_t<R> v = at;
             uint64_t X = 0;
@@ -434,7 +498,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
         __syncthreads();
         for (int f = c.ngates - 1; f >= 0; --f) {
             const int gs = d.gen_of[c.first_gate + f];
-            const double sum = sweep_gate<R>(c.n, gates[c.first_gate + f], gs >= 0 ? d.gens + 8 * gs : nullptr,
+            const double sum = sweep_gate<R, THREADS>(c.n, gates[c.first_gate + f], gs >= 0 ? d.gens + 8 * gs : nullptr,
                                              params, tp, tl, 0, ~0ull, scratch);
             if (gs >= 0 && tid == 0)
                 part[gs - c.first_gen] = sum;
@@ -445,7 +509,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
             lam[tid] = tl[tid];
         }
     } else {  // kPassSums: over the chunks, then over the gates that share a parameter
-        for (int s = tid; s < c.nslots; s += kBatchThreads) {
+        for (int s = tid; s < c.nslots; s += THREADS) {
             const BSlot a = d.slots[c.first_slot + s];
             double *q = parts + a.first;
             double sum = 0.0;
@@ -455,7 +519,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
             q[0] = sum;
         }
         __syncthreads();
-        for (int j = tid; j <= c.nparams; j += kBatchThreads) {
+        for (int j = tid; j <= c.nparams; j += THREADS) {
             const int s0 = d.csr[c.first_csr + j], s1 = d.csr[c.first_csr + j + 1];
             double sum = 0.0;
 #pragma unroll 4
@@ -506,7 +570,7 @@ __device__ __forceinline__ void wait_count(unsigned int *ctr, unsigned int targe
 // tickets used up goes back to the work queue.  Each tile or pair is
 // computed exactly as by one workgroup, so results do not depend on the
 // split.  (One loop for both: the tile code is in the kernel once.)
-template <typename R, bool ADJ>
+template <typename R, bool ADJ, bool LDS>
 __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const SweepTables &a, unsigned char *buf,
                                             double *scratch, int *slot) {
     const BCirc &c = d.circs[ci];
@@ -541,15 +605,20 @@ __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const 
         const BPass &p = passes[pi];
         if (p.kind == kPassTiles) {  // uniform
             const uint64_t end = hi < p.tm.ntiles ? hi : p.tm.ntiles;
-            if constexpr (ADJ)
+            if constexpr (ADJ && LDS)
+                lds_sweep_tiles<R>(psi, reinterpret_cast<cplx_t<R> *>(c.lam), p, d, a, buf, lo, end, chunk);
+            else if constexpr (ADJ)
                 sweep_tiles<R>(psi, reinterpret_cast<cplx_t<R> *>(c.lam), p, d, buf, lo, end, chunk);
+            else if constexpr (LDS)
+                lds_tiles<R>(psi, p, d, buf, lo, end);
             else
                 fused_tiles<R>(psi, p, d, buf, lo, end);
         } else if constexpr (ADJ) {
-            sweep_other<R>(c, ci, p, d.gates, d.params, d.part, a, buf, scratch, lo, hi, chunk);
+            sweep_other<R, batch_threads(LDS)>(c, ci, p, d.gates, d.params, d.part, a, buf, scratch, lo, hi, chunk);
         } else {
             const BGate &g = d.gates[c.first_gate + p.gate];
-            gate_on_block<R>(psi, c.n, g.target, g.cmask, g.cvals, bgate_mat<R>(g, d.params, false), lo, hi);
+            gate_on_block<R, batch_threads(LDS)>(psi, c.n, g.target, g.cmask, g.cvals,
+                                                 bgate_mat<R>(g, d.params, false), lo, hi);
         }
         if (split) {
             // Publish the chunk: every wavefront waits until its own stores
@@ -595,22 +664,22 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
                 rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
 }
 
-// ADJ: the adjoint gradients, else the forward run.  tail: LDS bytes before
+// ADJ: the adjoint gradients, else the forward run.  LDS: on LDS tiles.  tail: LDS bytes before
 // the work-item slot.
-template <typename R, bool ADJ>
-__global__ __launch_bounds__(kBatchThreads, 4) void k_batched(
+template <typename R, bool ADJ, bool LDS>
+__global__ __launch_bounds__(batch_threads(LDS), 4) void k_batched(
     const BCirc *__restrict__ circs, const int32_t *__restrict__ items, int nitems, const BGate *__restrict__ gates,
     const BPass *__restrict__ passes, const TileGate *__restrict__ tiles, const RtOp *__restrict__ ops,
-    const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems, const double *__restrict__ params,
-    unsigned int *__restrict__ queue, unsigned int *gstate, uint64_t limit, unsigned int *err,
+    const RtPat *__restrict__ pats, const SweepPat *__restrict__ lpats, const SweepMember *__restrict__ mems,
+    const double *__restrict__ params, unsigned int *__restrict__ queue, unsigned int *gstate, uint64_t limit, unsigned int *err,
     uint64_t *__restrict__ stamps, double *part, SweepTables a, uint32_t tail) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     // the exchange buffer first: its addresses step by xor
     unsigned char *buf = lds_raw;
     double *scratch = reinterpret_cast<double *>(lds_raw + tail);
-    int *item = reinterpret_cast<int *>(scratch + kBatchThreads / 64);
+    int *item = reinterpret_cast<int *>(scratch + batch_threads(LDS) / 64);
     int *ticket = item + 1;
-    const BatchTables d{circs, gates, passes, tiles, ops, pats, mems, params, gstate, limit, err, part};
+    const BatchTables d{circs, gates, passes, tiles, ops, pats, lpats, mems, params, gstate, limit, err, part};
     for (;;) {
         if (threadIdx.x == 0)
             *item = (int)atomicAdd(queue, 1u);
@@ -621,10 +690,10 @@ __global__ __launch_bounds__(kBatchThreads, 4) void k_batched(
             break;
         const uint64_t t0 = !ADJ && stamps ? wall_clock64() : 0;
         const int ci = items[it];  // one that is split appears once per workgroup that may join it
-        if (!ADJ && circs[ci].n < resident_below(sizeof(R) == 8))  // uniform
-            run_circuit_resident<R>(circs[ci], d, buf);
+        if (!ADJ && circs[ci].n < (LDS ? kLdsTileBits + 1 : resident_below(sizeof(R) == 8)))  // uniform
+            run_circuit_resident<R, batch_threads(LDS)>(circs[ci], d, buf);
         else
-            run_circuit<R, ADJ>(ci, d, a, buf, scratch, ticket);
+            run_circuit<R, ADJ, LDS>(ci, d, a, buf, scratch, ticket);
         __syncthreads();
         if (!ADJ && stamps && threadIdx.x == 0) {
             stamps[2 * it] = t0;
@@ -652,6 +721,9 @@ struct CircBuild {
     std::vector<TileGate> tiles;
     PlanRt rt;                     // register tile operations (circuit-local)
     std::vector<SweepMember> mems; // members of their phase patterns
+    bool lds = false;              // LDS tiles
+    std::vector<SweepPat> lpats;   // their phase patterns
+    std::vector<int32_t> tslot;    // adjoint: gradient slot of every tile descriptor, or -1
     std::vector<BTileJob> jobs;    // tile and operation indices circuit-local
     // adjoint: per gradient slot (a parameterised gate; numbered in the order
     // of the reverse sweep), then for the loss: its parameter (circuit-local;
@@ -684,8 +756,12 @@ static int plan_passes(int n, int dtype, const sv_gate_t *gates, int ngates, int
                        CircBuild *out) {
     std::vector<PlanPass> pp;
     std::vector<SweepPat> pats;
-    SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr, &pats, &out->mems,
-                              &out->rt));
+    if (out->lds)  // (a reverse sweep applies diagonal gates without patterns)
+        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr,
+                                  out->rt.dual ? nullptr : &out->lpats, out->rt.dual ? nullptr : &out->mems));
+    else
+        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr, &pats,
+                                  &out->mems, &out->rt));
     for (const PlanPass &q : pp) {
         BPass b;
         memset(&b, 0, sizeof(b));
@@ -696,13 +772,25 @@ static int plan_passes(int n, int dtype, const sv_gate_t *gates, int ngates, int
         if (q.fused) {
             if (q.tm.m > (uint32_t)m_cap)
                 return fail(SV_EINVAL, "tile width %u beyond the batch limit", q.tm.m);
-            if (!q.rt || q.rp.lds > kBatchExchange)
-                return fail(SV_EINVAL, "fused pass beyond the batch's register tiles");
             b.tm = q.tm;
-            b.rt = q.rp;
-            b.nacc = (int32_t)q.rp.acc_count;
+            if (out->lds) {
+                b.tm.tab = 1;  // the launch reserves the tables
+            } else {
+                if (!q.rt || q.rp.lds > kBatchExchange)
+                    return fail(SV_EINVAL, "fused pass beyond the batch's register tiles");
+                b.rt = q.rp;
+                b.nacc = (int32_t)q.rp.acc_count;
+            }
         }
         out->passes.push_back(b);
+    }
+    if (out->lds) {
+        for (size_t t = 0; t < out->tiles.size(); ++t) {
+            const sv_gate_t &g = gates[out->tiles[t].src_gate];
+            if (g.param >= 0)
+                out->jobs.push_back(BTileJob{g.kind, param0 + g.param, (int32_t)t, {-1, -1}});
+        }
+        return SV_OK;
     }
     for (const ParamJob &j : out->rt.jobs)
         if (j.tile_slot >= 0)
@@ -746,7 +834,7 @@ static int build_sweep(const BatchArgs &A, int c, int dtype, int m_cap, CircBuil
         out->passes.push_back(b);
     };
     extra(kPassPauli, 1);
-    if (G > 0 && bc.n < kSweepLdsBelow) {
+    if (G > 0 && bc.n < kSweepLdsBelow && !out->lds) {
         extra(kPassSmall, (int32_t)out->sums.size());
         for (size_t k = 0; k < out->sums.size(); ++k) {
             out->sums[k].pass = 1;
@@ -755,14 +843,24 @@ static int build_sweep(const BatchArgs &A, int c, int dtype, int m_cap, CircBuil
     } else if (G > 0) {
         out->rt.dual = true;
         SV_TRY(plan_passes(bc.n, dtype, rev.data(), G, bc.nparams, (int32_t)p0, m_cap, out));
+        out->tslot.assign(out->tiles.size(), -1);
         for (size_t pi = 1; pi < out->passes.size(); ++pi) {
             BPass &b = out->passes[pi];
             if (b.kind == kPassTiles) {
-                for (int32_t k = 0; k < b.nacc; ++k) {
-                    CircBuild::Sum &u = out->sums[out->rt.prog.acc[b.rt.acc_first + k]];
-                    u.pass = (int32_t)pi;
-                    u.acc = k;
+                auto place = [&](int32_t slot, int32_t k) {
+                    out->sums[slot].pass = (int32_t)pi;
+                    out->sums[slot].acc = k;
+                };
+                if (out->lds) {
+                    for (int t = b.first; t < b.first + b.count; ++t) {
+                        out->tslot[t] = slot_of[out->tiles[t].src_gate];
+                        if (out->tslot[t] >= 0)
+                            place(out->tslot[t], b.nacc++);
+                    }
+                    continue;
                 }
+                for (int32_t k = 0; k < b.nacc; ++k)
+                    place(out->rt.prog.acc[b.rt.acc_first + k], k);
                 continue;
             }
             const int32_t sl = slot_of[b.gate];
@@ -795,7 +893,8 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
     bc.psi = s.data;
     bc.lam = adjoint ? A.lams[c].data : nullptr;
     bc.n = s.n;
-    const int m_cap = rt_nb_of(dtype) + kBatchThreadBits - (adjoint ? 1 : 0);  // one workgroup's registers
+    // one workgroup's LDS or registers
+    const int m_cap = (out->lds ? kLdsTileBits : rt_nb_of(dtype) + kBatchThreadBits) - (adjoint ? 1 : 0);
     bc.ngates = (int32_t)(g1 - g0);
     bc.first_param = (int32_t)p0;
     bc.nparams = (int32_t)(p1 - p0);
@@ -808,7 +907,7 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
     }
     if (adjoint)
         SV_TRY(build_sweep(A, c, dtype, m_cap, out));
-    else if (bc.ngates > 0 && s.n >= resident_below(dtype == SV_C128))
+    else if (bc.ngates > 0 && s.n >= (out->lds ? kLdsTileBits + 1 : resident_below(dtype == SV_C128)))
         SV_TRY(plan_passes(s.n, dtype, A.gates + g0, bc.ngates, (int)(p1 - p0), (int32_t)p0, m_cap, out));
     bc.npasses = (int32_t)out->passes.size();
     double work = 0.0;
@@ -858,12 +957,15 @@ struct BatchHost {
     std::vector<BPass> passes;
     std::vector<TileGate> tiles;
     RtProgram prog;
+    bool lds = false;              // LDS tiles
+    std::vector<SweepPat> lpats;
+    std::vector<int32_t> tslot;
     std::vector<SweepMember> mems;
     std::vector<BTileJob> jobs;
     std::vector<BSlot> slots;
     std::vector<int32_t> csr;
     int64_t npart = 0;             // partial sums
-    size_t lds = kBatchExchange;   // exchange buffer, then gradient accumulators of a pass
+    size_t lds_bytes = 0;          // exchange buffer or tiles, then gradient accumulators of a pass
     std::vector<int32_t> order;    // work items in queue order (each a circuit)
     int ngroups = 0;               // circuits split over workgroups
     std::vector<double> gens;
@@ -903,15 +1005,16 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
     if (gmax <= 1)
         return;
     DeviceInfo di;
-    const double P = (double)kBatchPerCu * (device_info(&di) == SV_OK ? di.num_cus : 256);  // persistent workgroups
+    const double P = (double)(h->lds ? 2 : kBatchPerCu) * (device_info(&di) == SV_OK ? di.num_cus : 256);  // persistent workgroups
     double W = 0.0;
     for (double c : cost)
         W += c;
     const double load = W / P;
     const int kc = kChunksPerWorker;
+    const int m_cap = (h->lds ? kLdsTileBits : rt_nb_of(dtype) + kBatchThreadBits) - (adjoint ? 1 : 0);
     for (size_t c = 0; c < h->circs.size(); ++c) {
         BCirc &bc = h->circs[c];
-        if (bc.npasses == 0 || bc.n <= rt_nb_of(dtype) + kBatchThreadBits - (adjoint ? 1 : 0) || !(cost[c] > load))
+        if (bc.npasses == 0 || bc.n <= m_cap || !(cost[c] > load))
             continue;  // LDS-resident, empty, one workgroup's registers, or short enough
         // a pass's tiles or pairs, and how many of them a workgroup takes at least
         auto extent = [&](const BPass &p, uint64_t *total, uint64_t *unit) {
@@ -920,11 +1023,11 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
                 *total = p.tm.ntiles;
             } else if (p.kind == kPassPauli) {
                 *total = 1ull << bc.n;
-                *unit = (uint64_t)kBatchPairUnroll * kBatchThreads;
+                *unit = (uint64_t)kBatchPairUnroll * batch_threads(h->lds);
             } else if (p.kind == kPassGate) {
                 const BGate &gt = h->gates[bc.first_gate + p.gate];
                 *total = 1ull << (bc.n - 1 - popcount64(gt.cmask));
-                *unit = (uint64_t)kBatchPairUnroll * kBatchThreads;
+                *unit = (uint64_t)kBatchPairUnroll * batch_threads(h->lds);
             }
             return (*total + *unit - 1) / *unit;
         };
@@ -959,7 +1062,9 @@ static void place_sums(const std::vector<CircBuild::Sum> &sums, BCirc *bc, Batch
     for (int pi = 0; pi < bc->npasses; ++pi) {
         ps[pi].part = h->npart;
         h->npart += (int64_t)ps[pi].nacc * (bc->group >= 0 ? ps[pi].nchunks : 1);
-        h->lds = std::max(h->lds, kBatchExchange + (size_t)ps[pi].rt.acc_count * (kBatchThreads / 64) * sizeof(double));
+        const size_t acc = (size_t)ps[pi].nacc * (batch_threads(h->lds) / 64) * sizeof(double);
+        if (ps[pi].kind == kPassTiles)
+            h->lds_bytes = std::max(h->lds_bytes, (h->lds ? ((size_t)2 << ps[pi].tm.m) * sizeof(float2) : kBatchExchange) + acc);
     }
     bc->first_slot = (int32_t)h->slots.size();
     bc->nslots = (int32_t)sums.size();
@@ -1013,9 +1118,12 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
     if (total_gates > INT32_MAX)
         return fail(SV_EINVAL, "batch holds %lld gates (at most 2^31 - 1)", (long long)total_gates);
     std::vector<CircBuild> cb(A.ncirc);
+    h->lds = *dtype == SV_C64 && A.lams;
+    h->lds_bytes = h->lds ? (adjoint ? 0 : kLdsBytes) : kBatchExchange;
     auto work = [&](int lo, int hi) {
         for (int c = lo; c < hi; ++c) {
             CircBuild &b = cb[c];
+            b.lds = h->lds;
             b.err = build_circuit(A, c, *dtype, adjoint, &b);
             if (b.err != SV_OK) {
                 b.msg = sv_last_error();  // error text is per thread
@@ -1091,15 +1199,24 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
             p.first += mbase;
             h->prog.pats.push_back(p);
         }
+        const uint32_t lbase = (uint32_t)h->lpats.size();
         for (TileGate &t : b.tiles)
-            if (t.diag)
+            if (t.diag) {
+                t.pat0 += lbase;
                 for (int s = 0; s < 2; ++s)
                     if (t.mem[s] >= 0)
                         t.mem[s] += (int32_t)mbase;
+            }
+        for (SweepPat p : b.lpats) {
+            p.first += mbase;
+            h->lpats.push_back(p);
+        }
         h->tiles.insert(h->tiles.end(), b.tiles.begin(), b.tiles.end());
         h->mems.insert(h->mems.end(), b.mems.begin(), b.mems.end());
         const int32_t gbase = (int32_t)(h->gens.size() / 8);  // generators before this circuit's
         b.bc.first_gen = gbase;
+        for (int32_t t : b.tslot)
+            h->tslot.push_back(t >= 0 ? t + gbase : -1);
         for (int32_t g : b.gen_of)
             h->gen_of.push_back(g >= 0 ? g + gbase : -1);
         h->gates.insert(h->gates.end(), b.gates.begin(), b.gates.end());
@@ -1132,10 +1249,13 @@ struct BatchDevice {
     SweepMember *mems = nullptr;
     BTileJob *jobs = nullptr;
     int njobs = 0;
+    bool lds = false;
+    SweepPat *lpats = nullptr;
+    int32_t *tslot = nullptr;
     BSlot *slots = nullptr;
     int32_t *csr = nullptr;
     double *part = nullptr;
-    size_t lds = 0;
+    size_t lds_bytes = 0;
     int32_t *order = nullptr, *gen_of = nullptr;
     int nitems = 0;
     double *gens = nullptr;
@@ -1152,7 +1272,7 @@ struct BatchDevice {
 // otherwise an immediate free.
 static void batch_release(BatchDevice *d, bool async, hipStream_t st) {
     void *ps[] = {d->circs, d->gates, d->passes, d->tiles,  d->ops,  d->pats,  d->mems,  d->jobs,  d->slots,
-                  d->csr,   d->part,  d->order,  d->gen_of, d->gens, d->terms, d->queue, d->gstate};
+                  d->csr,   d->part,  d->lpats, d->tslot, d->order,  d->gen_of, d->gens, d->terms, d->queue, d->gstate};
     for (void *p : ps)
         if (p)
             (void)(async ? hipFreeAsync(p, st) : hipFree(p));
@@ -1203,7 +1323,12 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
         r = dev_copy(&d->csr, h.csr, async, st, 1);
     if (r == SV_OK)
         r = dev_copy(&d->part, std::vector<double>(), async, st, (size_t)h.npart);
+    if (r == SV_OK)
+        r = dev_copy(&d->lpats, h.lpats, async, st, 1);
+    if (r == SV_OK)
+        r = dev_copy(&d->tslot, h.tslot, async, st, 1);
     d->lds = h.lds;
+    d->lds_bytes = h.lds_bytes;
     if (r == SV_OK)
         r = dev_copy(&d->order, h.order, async, st);
     d->nitems = (int)h.order.size();
@@ -1252,33 +1377,35 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
 static int launch_batch(int dtype, const BatchDevice &d, const double *params, double *grad, double *loss,
                         hipStream_t s, uint64_t *stamps) {
     constexpr size_t kLdsPerWorkgroup = 160 * 1024;  // gfx950, with the opt-in limit raised
-    const size_t lds = d.lds + kBatchSlot;
+    const size_t lds = d.lds_bytes + kBatchSlot;
     if (lds > kLdsPerWorkgroup)
         return fail(SV_ENOTSUP, "a fused reverse pass needs %zu bytes of LDS", lds);
     DeviceInfo di;
     const unsigned cus = device_info(&di) == SV_OK ? (unsigned)di.num_cus : 256u;
-    const unsigned per_cu = std::min<unsigned>(kBatchPerCu, (unsigned)(kLdsPerWorkgroup / lds));
+    const unsigned per_cu = std::min<unsigned>(d.lds ? 2 : kBatchPerCu, (unsigned)(kLdsPerWorkgroup / lds));
     const unsigned grid = std::min<unsigned>(cus * per_cu, (unsigned)d.nitems);
     if (d.njobs > 0)
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.njobs + 255) / 256), dim3(256), 0, s, d.jobs, d.njobs, params,
-                           d.tiles, d.mems, d.ops, dtype == SV_C64 ? 1 : 0);
+                           d.tiles, d.lds && grad ? nullptr : d.mems, d.lds ? nullptr : d.ops, dtype == SV_C64 ? 1 : 0);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
     if (d.ngroups > 0)  // the ticket counters, not the timeout count after them
         hipLaunchKernelGGL(k_zero_words, dim3((2 * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,
                            2 * d.ngroups);
-    const SweepTables a{d.terms, d.gens, d.gen_of, d.slots, d.csr, grad, loss, stamps};
+    const SweepTables a{d.terms, d.gens, d.gen_of, d.tslot, d.slots, d.csr, grad, loss, stamps};
     auto go = [&](auto fn) -> int {
         if (lds > 65536)
             SV_HIP_TRY(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(fn, dim3(grid), dim3(kBatchThreads), lds, s, d.circs, d.order, d.nitems, d.gates, d.passes,
-                           d.tiles, d.ops, d.pats, d.mems, params, d.queue, d.gstate, d.wait_limit,
-                           d.gstate ? d.gstate + 2 * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds);
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(batch_threads(d.lds)), lds, s, d.circs, d.order, d.nitems, d.gates, d.passes,
+                           d.tiles, d.ops, d.pats, d.lpats, d.mems, params, d.queue, d.gstate, d.wait_limit,
+                           d.gstate ? d.gstate + 2 * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes);
         SV_LAUNCH_CHECK();
         return SV_OK;
     };
     if (dtype == SV_C128)
-        return grad ? go(k_batched<double, true>) : go(k_batched<double, false>);
-    return grad ? go(k_batched<float, true>) : go(k_batched<float, false>);
+        return grad ? go(k_batched<double, true, false>) : go(k_batched<double, false, false>);
+    if (d.lds)
+        return grad ? go(k_batched<float, true, true>) : go(k_batched<float, false, true>);
+    return go(k_batched<float, false, false>);  // gradients: LDS tiles
 }
 
 } // namespace sv

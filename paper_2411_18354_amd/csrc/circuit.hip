@@ -670,7 +670,13 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
     c->nparams = nparams;
     c->async_buffers = async;
     c->m_cap = m_cap;
-    c->want_rt = rt;
+    // A parameterised complex64 circuit keeps LDS tiles, which apply a tile's
+    // gates in program order with one rounding each: register tiles reorder
+    // commuting gates and share diagonal factors, and losses and gradients,
+    // which are given in double, would follow the state's single-precision
+    // rounding (4.6e-7 of a gradient at 12 qubits).
+    const bool angles = std::any_of(gates, gates + ngates, [](const sv_gate_t &g) { return g.param >= 0; });
+    c->want_rt = rt && !(dtype == SV_C64 && angles);
     c->dual = dual;
     // a one-shot plan (stream-ordered buffers, run once) keeps planning cheap:
     // the two-step lookahead pays for itself only over repeated runs

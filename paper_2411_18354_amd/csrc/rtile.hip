@@ -650,30 +650,23 @@ __global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(cplx_t<R> *__restrict
     }
 }
 
-static unsigned rt_adjoint_lanes(int dtype, const TileMap &tm) { return 1u << ((int)tm.m - rt_nb_of(dtype) + 1); }
+static unsigned rt_adjoint_lanes(const TileMap &tm) { return 1u << ((int)tm.m - rt_nb<double>() + 1); }
 
-size_t rt_adjoint_lds(int dtype, const TileMap &tm, const RtPass &p) {
-    return p.lds + (size_t)p.acc_count * (rt_adjoint_lanes(dtype, tm) / 64) * sizeof(double);
+size_t rt_adjoint_lds(const TileMap &tm, const RtPass &p) {
+    return p.lds + (size_t)p.acc_count * (rt_adjoint_lanes(tm) / 64) * sizeof(double);
 }
 
-int rt_adjoint_lds_limit(int dtype, size_t lds) {
-    const void *fn = dtype == SV_C128 ? (const void *)k_radj<double> : (const void *)k_radj<float>;
-    SV_HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+int rt_adjoint_lds_limit(size_t lds) {
+    SV_HIP_TRY(hipFuncSetAttribute((const void *)k_radj<double>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     return SV_OK;
 }
 
-int launch_rt_adjoint(int dtype, void *psi, void *lam, const TileMap &tm, const RtPass &p, const RtDevice &d,
+int launch_rt_adjoint(void *psi, void *lam, const TileMap &tm, const RtPass &p, const RtDevice &d,
                       const DeviceGates &gates, unsigned grid, double *partials, int stride, hipStream_t st) {
-    if (!rt_tile_ok(dtype, (int)tm.m, true))
+    if (!rt_tile_ok(SV_C128, (int)tm.m, true))
         return fail(SV_EINVAL, "register tiles of 2^%u amplitudes", tm.m);
-    const dim3 lanes(rt_adjoint_lanes(dtype, tm));
-    const size_t lds = rt_adjoint_lds(dtype, tm, p);
-    if (dtype == SV_C128)
-        hipLaunchKernelGGL(k_radj<double>, dim3(grid), lanes, lds, st, (double2 *)psi, (double2 *)lam, tm, p, d.ops,
-                           d.pats, gates.mm, d.acc, gates, partials, stride);
-    else
-        hipLaunchKernelGGL(k_radj<float>, dim3(grid), lanes, lds, st, (float2 *)psi, (float2 *)lam, tm, p, d.ops,
-                           d.pats, gates.mm, d.acc, gates, partials, stride);
+    hipLaunchKernelGGL(k_radj<double>, dim3(grid), dim3(rt_adjoint_lanes(tm)), rt_adjoint_lds(tm, p), st,
+                       (double2 *)psi, (double2 *)lam, tm, p, d.ops, d.pats, gates.mm, d.acc, gates, partials, stride);
     SV_LAUNCH_CHECK();
     return SV_OK;
 }

@@ -83,13 +83,9 @@ namespace sv {
     "v_fma_" SZ " " RT_N(y, i) ", %[t2], " RT_N(y, i) ", %[t1]\n"
 
 // Gradient terms of a reverse sweep, where registers i, j are psi and I, J the
-// same amplitudes of lambda: sums over pairs (or registers) into a0 .. a3, in
-// double precision for either type; the term is (a0 + a1) - (a2 + a3).
+// same amplitudes of lambda: sums over pairs (or registers) into a0 .. a3; the
+// term is (a0 + a1) - (a2 + a3).
 #define RT_DOT_f64(a, p, q) "v_fma_f64 %[" #a "], " p ", " q ", %[" #a "]\n"
-#define RT_DOT_f32(a, p, q)                                                                                        \
-    "v_cvt_f64_f32 %[e0], " p "\n"                                                                                 \
-    "v_cvt_f64_f32 %[e1], " q "\n"                                                                                 \
-    "v_fma_f64 %[" #a "], %[e0], %[e1], %[" #a "]\n"
 // Re(conj(lambda_1) psi_0) - Re(conj(lambda_0) psi_1)
 #define RT_STEP_GY(D, i, j, I, J)                                                                                  \
     D(a0, RT_N(x, J), RT_N(x, i)) D(a1, RT_N(y, J), RT_N(y, i)) D(a2, RT_N(x, I), RT_N(x, j))                      \
@@ -196,26 +192,6 @@ namespace sv {
     RT_BOTH(D, 0, 8) RT_BOTH(D, 1, 9) RT_BOTH(D, 2, 10) RT_BOTH(D, 3, 11) RT_BOTH(D, 4, 12) RT_BOTH(D, 5, 13)      \
     RT_BOTH(D, 6, 14) RT_BOTH(D, 7, 15)
 // and among 16
-#define RT_QUADS5_0(S, D, V)                                                                                       \
-    RT_QUAD(S, D, V, 0, 0, 1, 16, 17) RT_QUAD(S, D, V, 1, 2, 3, 18, 19) RT_QUAD(S, D, V, 2, 4, 5, 20, 21)          \
-    RT_QUAD(S, D, V, 3, 6, 7, 22, 23) RT_QUAD(S, D, V, 4, 8, 9, 24, 25) RT_QUAD(S, D, V, 5, 10, 11, 26, 27)        \
-    RT_QUAD(S, D, V, 6, 12, 13, 28, 29) RT_QUAD(S, D, V, 7, 14, 15, 30, 31)
-#define RT_QUADS5_1(S, D, V)                                                                                       \
-    RT_QUAD(S, D, V, 0, 0, 2, 16, 18) RT_QUAD(S, D, V, 1, 1, 3, 17, 19) RT_QUAD(S, D, V, 2, 4, 6, 20, 22)          \
-    RT_QUAD(S, D, V, 3, 5, 7, 21, 23) RT_QUAD(S, D, V, 4, 8, 10, 24, 26) RT_QUAD(S, D, V, 5, 9, 11, 25, 27)        \
-    RT_QUAD(S, D, V, 6, 12, 14, 28, 30) RT_QUAD(S, D, V, 7, 13, 15, 29, 31)
-#define RT_QUADS5_2(S, D, V)                                                                                       \
-    RT_QUAD(S, D, V, 0, 0, 4, 16, 20) RT_QUAD(S, D, V, 1, 1, 5, 17, 21) RT_QUAD(S, D, V, 2, 2, 6, 18, 22)          \
-    RT_QUAD(S, D, V, 3, 3, 7, 19, 23) RT_QUAD(S, D, V, 4, 8, 12, 24, 28) RT_QUAD(S, D, V, 5, 9, 13, 25, 29)        \
-    RT_QUAD(S, D, V, 6, 10, 14, 26, 30) RT_QUAD(S, D, V, 7, 11, 15, 27, 31)
-#define RT_QUADS5_3(S, D, V)                                                                                       \
-    RT_QUAD(S, D, V, 0, 0, 8, 16, 24) RT_QUAD(S, D, V, 1, 1, 9, 17, 25) RT_QUAD(S, D, V, 2, 2, 10, 18, 26)         \
-    RT_QUAD(S, D, V, 3, 3, 11, 19, 27) RT_QUAD(S, D, V, 4, 4, 12, 20, 28) RT_QUAD(S, D, V, 5, 5, 13, 21, 29)       \
-    RT_QUAD(S, D, V, 6, 6, 14, 22, 30) RT_QUAD(S, D, V, 7, 7, 15, 23, 31)
-#define RT_BOTHS5(D)                                                                                               \
-    RT_BOTH(D, 0, 16) RT_BOTH(D, 1, 17) RT_BOTH(D, 2, 18) RT_BOTH(D, 3, 19) RT_BOTH(D, 4, 20) RT_BOTH(D, 5, 21)    \
-    RT_BOTH(D, 6, 22) RT_BOTH(D, 7, 23) RT_BOTH(D, 8, 24) RT_BOTH(D, 9, 25) RT_BOTH(D, 10, 26)                     \
-    RT_BOTH(D, 11, 27) RT_BOTH(D, 12, 28) RT_BOTH(D, 13, 29) RT_BOTH(D, 14, 30) RT_BOTH(D, 15, 31)
 
 // The registers in Gray-code order, S a step and F(b) the flip of register bit
 // b between two; R: the same order backwards.
@@ -334,20 +310,6 @@ namespace sv {
     RT_AT("gx1") RT_QUADS4_1(RT_STEP_GX, RT_DOT_f64, "gx1") RT_END                                                 \
     RT_AT("gx2") RT_QUADS4_2(RT_STEP_GX, RT_DOT_f64, "gx2") RT_END                                                 \
     RT_AT("gd") RT_BOTHS4(RT_DOT_f64) RT_END RT_TAIL(4, f64)
-#define RT_BLOCK_GRAD_f32                                                                                          \
-    RT_HEAD(5) RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                         \
-    RT_GO("gy0") RT_GO("gy1") RT_GO("gy2") RT_GO("gy3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
-    RT_GO("gx0") RT_GO("gx1") RT_GO("gx2") RT_GO("gx3") RT_NONE RT_NONE RT_NONE RT_NONE                            \
-    RT_BODY(5, f32)                                                                                                \
-    RT_AT("gy0") RT_QUADS5_0(RT_STEP_GY, RT_DOT_f32, "gy0") RT_END                                                 \
-    RT_AT("gy1") RT_QUADS5_1(RT_STEP_GY, RT_DOT_f32, "gy1") RT_END                                                 \
-    RT_AT("gy2") RT_QUADS5_2(RT_STEP_GY, RT_DOT_f32, "gy2") RT_END                                                 \
-    RT_AT("gy3") RT_QUADS5_3(RT_STEP_GY, RT_DOT_f32, "gy3") RT_END                                                 \
-    RT_AT("gx0") RT_QUADS5_0(RT_STEP_GX, RT_DOT_f32, "gx0") RT_END                                                 \
-    RT_AT("gx1") RT_QUADS5_1(RT_STEP_GX, RT_DOT_f32, "gx1") RT_END                                                 \
-    RT_AT("gx2") RT_QUADS5_2(RT_STEP_GX, RT_DOT_f32, "gx2") RT_END                                                 \
-    RT_AT("gx3") RT_QUADS5_3(RT_STEP_GX, RT_DOT_f32, "gx3") RT_END                                                 \
-    RT_AT("gd") RT_BOTHS5(RT_DOT_f32) RT_END RT_TAIL(5, f32)
 
 #define RT_AMP(i) [x##i] "+v"(v.x[i]), [y##i] "+v"(v.y[i])
 #define RT_AMPS8                                                                                                   \
@@ -428,19 +390,6 @@ __device__ __forceinline__ void rt_apply_grad(RtRegs<double, 4> &v, const uint32
     asm volatile(RT_BLOCK_GRAD_f64
                  : RT_AMPS16, RT_SCRATCH, RT_GRAD_OUT
                  : RT_OPERANDS, [pm2] "s"(w[12])
-                 : "scc", "vcc", "memory");
-}
-__device__ __forceinline__ void rt_apply_grad(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m,
-                                              float fr, float fi, uint64_t lanes, uint32_t table, uint32_t &slot,
-                                              uint32_t &next, double (&g)[4]) {
-    float t0, t1, t2, t3;
-    double e0, e1;
-    uint64_t save;
-    // an exchange's fifth new register term and a gradient's second mask
-    // share w[12]
-    asm volatile(RT_BLOCK_GRAD_f32
-                 : RT_AMPS32, RT_SCRATCH, RT_GRAD_OUT, [e0] "=&v"(e0), [e1] "=&v"(e1)
-                 : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12]), [pm2] "s"(w[12])
                  : "scc", "vcc", "memory");
 }
 

@@ -135,13 +135,13 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
 int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,
                    const DeviceGates &gates, hipStream_t st);
 
-// One pass of the reverse sweep over psi and lambda (dual program): partials
+// One pass of the reverse sweep over complex128 psi and lambda (dual program): partials
 // [slot * stride + workgroup] receive every accumulator's sum per workgroup of
 // the grid.
-int launch_rt_adjoint(int dtype, void *psi, void *lam, const TileMap &tm, const RtPass &p, const RtDevice &d,
+int launch_rt_adjoint(void *psi, void *lam, const TileMap &tm, const RtPass &p, const RtDevice &d,
                       const DeviceGates &gates, unsigned grid, double *partials, int stride, hipStream_t st);
 // Dynamic LDS of such a pass, and the per-kernel limit raised to lds bytes.
-size_t rt_adjoint_lds(int dtype, const TileMap &tm, const RtPass &p);
-int rt_adjoint_lds_limit(int dtype, size_t lds);
+size_t rt_adjoint_lds(const TileMap &tm, const RtPass &p);
+int rt_adjoint_lds_limit(size_t lds);
 
 } // namespace sv
