@@ -248,7 +248,7 @@ __device__ __forceinline__ void fused_tiles(cplx_t<R> *psi, const BPass &p, cons
             v.y[r] = rt_own(a.y);
         });
         rt_run<R, NB, false, true>(v, lds, rt_xor_terms(tid, p.rt.in.slot), base, d.ops + p.rt.first, p.rt.count,
-                                   d.pats, d.mems, nullptr, tb);
+                                   d.pats, d.mems, nullptr, 0, tb);
         const uint32_t tod = rt_fresh(threadIdx.x);
         if ((tod >> tb) == 0) {
             cplx_t<R> *dst = psi + (base | rt_thread_offset(p.rt.out, tod, tb));
@@ -333,7 +333,7 @@ __device__ __forceinline__ void sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, cons
     const DeviceGates dg{d.tiles + p.first, p.count};
     const int tb = (int)p.tm.m - NB + 1;
     double *accl = reinterpret_cast<double *>(lds + kBatchExchange);
-    for (uint32_t k = threadIdx.x; k < p.rt.acc_count * NW; k += kBatchThreads)
+    for (uint32_t k = threadIdx.x; k < rt_acc_slots(p.rt) * NW; k += kBatchThreads)
         accl[k] = 0.0;
     __syncthreads();
     for (uint64_t tt = lo; tt < hi; ++tt) {
@@ -355,7 +355,7 @@ __device__ __forceinline__ void sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, cons
             v.y[r + H] = rt_own(a.y);
         });
         rt_run<R, NB, true, true>(v, lds, rt_xor_terms(tid, p.rt.in.slot), base, d.ops + p.rt.first, p.rt.count,
-                                  d.pats, d.mems, accl, tb);
+                                  d.pats, d.mems, accl, p.rt.acc_count, tb);
         const uint32_t tod = rt_fresh(threadIdx.x);
         if ((tod >> tb) == 0) {
             const uint64_t dst = base | rt_thread_offset(p.rt.out, tod, tb);
@@ -1062,7 +1062,7 @@ static void place_sums(const std::vector<CircBuild::Sum> &sums, BCirc *bc, Batch
     for (int pi = 0; pi < bc->npasses; ++pi) {
         ps[pi].part = h->npart;
         h->npart += (int64_t)ps[pi].nacc * (bc->group >= 0 ? ps[pi].nchunks : 1);
-        const size_t acc = (size_t)ps[pi].nacc * (batch_threads(h->lds) / 64) * sizeof(double);
+        const size_t acc = (size_t)(h->lds ? ps[pi].nacc : rt_acc_slots(ps[pi].rt)) * (batch_threads(h->lds) / 64) * sizeof(double);
         if (ps[pi].kind == kPassTiles)
             h->lds_bytes = std::max(h->lds_bytes, (h->lds ? ((size_t)2 << ps[pi].tm.m) * sizeof(float2) : kBatchExchange) + acc);
     }

@@ -273,33 +273,6 @@ __device__ __forceinline__ uint64_t deposit_bits(uint64_t v, uint64_t mask) {
 // conflicts whichever four bits of l number a lane's registers.
 __device__ __forceinline__ uint32_t tile_slot(uint32_t l) { return l ^ ((l >> 4) & 15u); }
 
-// The lane whose index differs in bit 0 or bit 1.
-template <int X> __device__ __forceinline__ double quad_xor(double v) {
-    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] or [2,3,0,1]
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-// The lane N before in its row of 16, cyclically.
-template <int N> __device__ __forceinline__ double row_rotate(double v) {
-    constexpr int ctl = 0x120 + N;  // row_ror
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-// The sums of four values over each row of 16 lanes: lane i gets that of
-// v[i & 3].  Values are folded two lanes to one as the lanes' share of them
-// narrows: 5 additions and shuffles where four separate sums take 16.
-__device__ __forceinline__ double row_sum4(double v0, double v1, double v2, double v3, uint32_t lane) {
-    const bool o1 = lane & 1u, o2 = lane & 2u;
-    const double a = (o1 ? v1 : v0) + quad_xor<1>(o1 ? v0 : v1);
-    const double b = (o1 ? v3 : v2) + quad_xor<1>(o1 ? v2 : v3);
-    double c = (o2 ? b : a) + quad_xor<2>(o2 ? a : b);
-    c += row_rotate<4>(c);
-    return c + row_rotate<8>(c);
-}
-
 // The pass's terms.  Lane j holds term j's masks; acck of lane i is the sum
 // of term 16 k + (i & 15) over its row of lanes and the wavefront's tiles, in
 // tile order.
@@ -320,7 +293,8 @@ __device__ __forceinline__ void tile_push(TileTerms &T, int j, double v, uint32_
     T.v2 = T.v3;
     T.v3 = v;
     if ((j & 3) == 3) {  // uniform
-        double c = row_sum4(T.v0, T.v1, T.v2, T.v3, lane);
+        double c = row_sum_over4(
+            fold_pair<1>(fold_pair<0>(T.v0, T.v1, lane), fold_pair<0>(T.v2, T.v3, lane), lane));
         if ((lane >> 2 & 3u) == ((uint32_t)j >> 2 & 3u)) {
             c = (T.minus >> (j & 48) >> (lane & 15u)) & 1ull ? -c : c;
             // (one addend each: an index would put the sums into scratch memory)

@@ -37,6 +37,22 @@ __device__ __forceinline__ double wave_sum(double v) {
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Two values folded into one: lanes with bit B (0 or 1) clear get v0 + that of
+// their partner in the bit, the others v1.  Two folds and a sum over the lanes
+// that share the two bits give the sums of four values, lane i that of
+// v[i & 3], in fewer additions and shuffles than four separate sums (5 instead
+// of 16 over a row of 16 lanes).
+template <int B> __device__ __forceinline__ double fold_pair(double v0, double v1, uint32_t lane) {
+    const bool o = (lane >> B) & 1u;
+    return (o ? v1 : v0) + dpp_double<B == 0 ? 0xB1 : 0x4E>(o ? v0 : v1);  // quad_perm: the partner
+}
+
+// Sum over the four lanes of a row of 16 that share bits 0 and 1.
+__device__ __forceinline__ double row_sum_over4(double c) {
+    c += dpp_double<0x124>(c);         // row_ror:4
+    return c + dpp_double<0x128>(c);   // row_ror:8
+}
+
 // Sum of v over the whole workgroup (blockDim.x lanes, a multiple of 64);
 // valid in every lane.  scratch: blockDim.x / 64 doubles of LDS.
 __device__ __forceinline__ double block_sum(double v, double *scratch) {

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(cplx_t<R> *__restrict
     double *accl = reinterpret_cast<double *>(lds + p.lds);
     const uint32_t nw = blockDim.x >> 6;
     const int tb = (int)tm.m - NB + 1;
-    for (uint32_t k = threadIdx.x; k < p.acc_count * nw; k += blockDim.x)
+    for (uint32_t k = threadIdx.x; k < rt_acc_slots(p) * nw; k += blockDim.x)
         accl[k] = 0.0;
     __syncthreads();
     for (uint64_t t = blockIdx.x; t < tm.ntiles; t += gridDim.x) {
@@ -628,7 +628,7 @@ __global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(cplx_t<R> *__restrict
             v.y[r + H] = rt_own(b.y);
         });
         const uint32_t slot = rt_xor_terms(rt_fresh(threadIdx.x), p.in.slot);
-        rt_run<R, NB, true>(v, lds, slot, base, ops + p.first, p.count, pats, mems, accl);
+        rt_run<R, NB, true>(v, lds, slot, base, ops + p.first, p.count, pats, mems, accl, p.acc_count);
         const uint64_t dst = base | rt_thread_offset(p.out, rt_fresh(threadIdx.x), tb);
         SV_RT_FOR(H, r) {
             const uint64_t k = dst + rt_reg_offset<NB - 1>(p.out, r);
@@ -653,7 +653,7 @@ __global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(cplx_t<R> *__restrict
 static unsigned rt_adjoint_lanes(const TileMap &tm) { return 1u << ((int)tm.m - rt_nb<double>() + 1); }
 
 size_t rt_adjoint_lds(const TileMap &tm, const RtPass &p) {
-    return p.lds + (size_t)p.acc_count * (rt_adjoint_lanes(tm) / 64) * sizeof(double);
+    return p.lds + (size_t)rt_acc_slots(p) * (rt_adjoint_lanes(tm) / 64) * sizeof(double);
 }
 
 int rt_adjoint_lds_limit(size_t lds) {

@@ -198,17 +198,35 @@ __device__ __forceinline__ uint32_t rt_xor_terms(uint32_t tid, const uint32_t *t
 // A run's operations on the tile in registers.  slot: the lane's byte offset
 // in the exchange buffer in the current layout.  GRAD: the reverse sweep; accl
 // holds one accumulator per parameterised gate and wavefront (accl[k * nw +
-// wavefront]).  tb: thread bits of the tile; in a wider workgroup (PART) the
+// wavefront]; acc_count gates rounded up to four).  Terms come in the order of
+// their accumulators, and four at a time are summed over the wavefront.  tb: thread bits of the tile; in a wider workgroup (PART) the
 // lanes beyond them only take part in the exchanges, on slots of their own.
 template <typename R, int NB, bool GRAD = false, bool PART = false>
 __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uint32_t slot, uint64_t base,
                                        const RtOp *__restrict__ ops, uint32_t count,
                                        const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems,
-                                       double *accl = nullptr, int tb = kRtMaxThreadBits) {
+                                       double *accl = nullptr, uint32_t acc_count = 0, int tb = kRtMaxThreadBits) {
     const uint32_t tid = threadIdx.x;
     // LDS byte address of the buffer
     const uint32_t buf = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
     const RtPhase *ph = reinterpret_cast<const RtPhase *>(reinterpret_cast<cplx_t<R> *>(lds) + (1 << NB));
+    // gradient terms not yet summed: this lane's last one, and two before it
+    // folded (lanes of either value of bit 0 hold one of them)
+    double one_term = 0.0, two_terms = 0.0;
+    auto take = [&](uint32_t k, double t) __attribute__((always_inline)) {
+        if (k & 1u) {  // uniform
+            const double a = fold_pair<0>(one_term, t, tid);
+            if (k & 2u) {
+                double s = row_sum_over4(fold_pair<1>(two_terms, a, tid));
+                s += __shfl_xor(s, 16);
+                s += __shfl_xor(s, 32);
+                if ((tid & 63u) < 4u)
+                    accl[((k & ~3u) + (tid & 3u)) * (blockDim.x >> 6) + (tid >> 6)] += s;
+            }
+            two_terms = a;
+        }
+        one_term = t;
+    };
     for (uint32_t i = 0; i < count; ++i) {
         const RtOp &o = ops[i];
         uint32_t w[16];
@@ -250,18 +268,19 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
         if constexpr (GRAD) {
             double g[4] = {0.0, 0.0, 0.0, 0.0};
             rt_apply_grad(v, w, m, fr, fi, lanes, buf, sa, na, g);
-            if (kind == kRtGrad && lanes) {  // uniform in the wavefront
+            if (kind == kRtGrad) {  // uniform
                 const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
                 const bool one = (tid & w[4]) != 0 || (base & ob) != 0;
-                const double s = wave_sum((one ? o.m[1] : o.m[0]) * ((g[0] + g[1]) - (g[2] + g[3])));
-                if ((tid & 63u) == 0)
-                    accl[w[13] * (blockDim.x >> 6) + (tid >> 6)] += s;
+                take(w[13], (one ? m.ai : m.ar) * ((g[0] + g[1]) - (g[2] + g[3])));
             }
         } else {
             rt_apply(v, w, m, fr, fi, lanes, buf, sa, na);
         }
         slot = next;
     }
+    if constexpr (GRAD)
+        for (uint32_t k = acc_count; k & 3u; ++k)
+            take(k, 0.0);
 }
 
 // A component in registers of its own.  Amplitudes are loaded and stored as

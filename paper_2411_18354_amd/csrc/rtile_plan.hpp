@@ -89,6 +89,9 @@ struct RtPass {
     uint32_t acc_first, acc_count;  // dual: gradient accumulators (RtProgram::acc)
 };
 
+// Accumulators in LDS: whole groups of four.
+__host__ __device__ inline uint32_t rt_acc_slots(const RtPass &p) { return (p.acc_count + 3u) & ~3u; }
+
 // Host-side program of a circuit's fused passes.
 struct RtProgram {
     std::vector<RtOp> ops;
