@@ -23,7 +23,6 @@
 // terms) evaluates them all.  Diagonal terms join the first set.  Groups whose
 // x mask has too many upper qubits keep the one-pass-per-group kernel.
 #include <algorithm>
-#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <numeric>
@@ -150,12 +149,18 @@ struct Q32Amps {
     __device__ void get(uint64_t k, double &re, double &im) const { decode(raw(k), re, im); }
 };
 
+// A group's terms as a kernel argument.
+struct GroupTerms {
+    uint64_t z[kMaxT];
+    int32_t ny[kMaxT];
+};
+
 // One pass for one group (<= kMaxT terms sharing the x mask X).
 // partials[(first + j) * kMaxPartials + block] receives the workgroup's sum
 // of <P_j> contributions.
 template <typename A>
 __global__ __launch_bounds__(kRedThreads) void k_expect_group(const A amps, uint64_t count, uint64_t X, uint32_t b,
-                                                              const DTerm *__restrict__ terms, int first, int nt,
+                                                              const GroupTerms terms, int first, int nt,
                                                               double *__restrict__ partials) {
     __shared__ double red[kRedThreads / 64];
     uint64_t z[kMaxT];
@@ -164,8 +169,8 @@ __global__ __launch_bounds__(kRedThreads) void k_expect_group(const A amps, uint
 #pragma unroll
     for (int j = 0; j < kMaxT; ++j) {
         acc[j] = 0.0;
-        z[j] = j < nt ? terms[first + j].z : 0;
-        ny[j] = j < nt ? terms[first + j].ny : 0;
+        z[j] = terms.z[j];
+        ny[j] = terms.ny[j];
     }
     // Each lane visits i0, i0 + stride, i0 + 2 stride, ...; kExpectLoads of
     // those visits load before any of them is summed, so enough bytes are in
@@ -538,6 +543,42 @@ __global__ __launch_bounds__(64) void k_expect_final(const DTerm *__restrict__ t
     }
 }
 
+// Both for few terms, whose table comes as a kernel argument: one workgroup, a
+// wavefront per term (its partials in index order by lanes).  Small states
+// spend their time in launches and copies: with the tables copied to the device
+// and two kernels a call at 8 to 20 qubits took 72 to 79 us, now 31 to 40; one
+// at 26 qubits 861 and 839.
+constexpr int kFewTerms = SV_EXPECT_NOALLOC_MAX_TERMS, kFewThreads = 1024;
+struct FewTerms {
+    int32_t nterms, nblk[kFewTerms], idx[kFewTerms];
+    double coef[kFewTerms];
+};
+__global__ __launch_bounds__(kFewThreads) void k_expect_few(const FewTerms t, const double *__restrict__ partials,
+                                                            double *__restrict__ out_total,
+                                                            double *__restrict__ out_terms) {
+    __shared__ double sums[kFewTerms];
+    const int lane = threadIdx.x & 63;
+    for (int j = threadIdx.x >> 6; j < t.nterms; j += kFewThreads / 64) {
+        double v = 0.0;
+#pragma unroll 8
+        for (int i = lane; i < t.nblk[j]; i += 64)
+            v += partials[(size_t)j * kMaxPartials + i];
+        v = wave_sum(v);
+        if (lane == 0) {
+            sums[j] = v;
+            if (out_terms)
+                out_terms[t.idx[j]] = v;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && out_total) {
+        double total = 0.0;
+        for (int j = 0; j < t.nterms; ++j)
+            total += t.coef[j] * sums[j];
+        out_total[0] = total;
+    }
+}
+
 // out_k = sum_groups sum_terms coef i^ny (-1)^{z.(k^X)} psi_{k^X}; partials
 // of Re conj(psi_k) out_k per workgroup.
 template <typename R>
@@ -732,11 +773,9 @@ template <typename F> static void with_amps(const sv_state_t *s, F &&f) {
     }
 }
 
-// The passes and the final sums.  terms (the plan's terms), nblk (their
-// partial counts), partials (terms * kMaxPartials doubles) and sums (terms
-// doubles) are device arrays, the first two already filled or enqueued on st.
-static int expect_launch(const sv_state_t *s, const ExpectPlan &plan, const DTerm *terms, const int32_t *nblk,
-                         double *partials, double *sums, double *out_total, double *out_terms, hipStream_t st) {
+// The passes: every plan term's partial sums, plan.nblk[j] of them at
+// partials[j * kMaxPartials].
+static int expect_passes(const sv_state_t *s, const ExpectPlan &plan, double *partials, hipStream_t st) {
     const int n = s->n;
     for (const TilePass &P : plan.tiles) {
         with_amps(s, [&](auto amps) {
@@ -752,21 +791,38 @@ static int expect_launch(const sv_state_t *s, const ExpectPlan &plan, const DTer
         const uint64_t count = g.x == 0 ? (1ull << n) : (1ull << (n - 1));
         const unsigned grid = reduce_grid(count);
         const uint32_t b = g.x ? (uint32_t)__builtin_ctzll(g.x) : 0;
+        GroupTerms t;
+        memset(&t, 0, sizeof(t));
+        for (int j = 0; j < g.count; ++j) {
+            t.z[j] = plan.pp.terms[g.first + j].z;
+            t.ny[j] = plan.pp.terms[g.first + j].ny;
+        }
         with_amps(s, [&](auto amps) {
             using A = decltype(amps);
-            hipLaunchKernelGGL((k_expect_group<A>), dim3(grid), dim3(kRedThreads), 0, st, amps, count, g.x, b, terms,
+            hipLaunchKernelGGL((k_expect_group<A>), dim3(grid), dim3(kRedThreads), 0, st, amps, count, g.x, b, t,
                                g.first, g.count, partials);
         });
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return fail(SV_EHIP, "expectation launch failed: %s", hipGetErrorString(e));
     }
-    const int nt = (int)plan.pp.terms.size();
-    hipLaunchKernelGGL(k_expect_sums, dim3(nt), dim3(kRedThreads), 0, st, nblk, partials, sums);
-    hipLaunchKernelGGL(k_expect_final, dim3(1), dim3(64), 0, st, terms, nt, sums, out_total, out_terms);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return fail(SV_EHIP, "expectation launch failed: %s", hipGetErrorString(e));
+    return SV_OK;
+}
+
+// Passes and sums for at most kFewTerms terms.
+static int expect_few(const sv_state_t *s, const ExpectPlan &plan, double *partials, double *out_total,
+                      double *out_terms, hipStream_t st) {
+    SV_TRY(expect_passes(s, plan, partials, st));
+    FewTerms t;
+    memset(&t, 0, sizeof(t));
+    t.nterms = (int32_t)plan.pp.terms.size();
+    for (int j = 0; j < t.nterms; ++j) {
+        t.nblk[j] = plan.nblk[j];
+        t.idx[j] = plan.pp.terms[j].idx;
+        t.coef[j] = plan.pp.terms[j].coef;
+    }
+    hipLaunchKernelGGL(k_expect_few, dim3(1), dim3(kFewThreads), 0, st, t, partials, out_total, out_terms);
+    SV_LAUNCH_CHECK();
     return SV_OK;
 }
 
@@ -775,63 +831,57 @@ static int expect_impl(const sv_state_t *s, const sv_pauli_t *terms, int nterms,
     SV_TRY(validate_state(s, true));
     ExpectPlan plan;
     SV_TRY(make_expect_plan(s->n, s->dtype, terms, nterms, &plan));
-    const std::vector<int32_t> &nblk = plan.nblk;
-    PauliDevice d;
-    SV_TRY(pauli_upload(plan.pp, (size_t)plan.pp.terms.size() * (kMaxPartials + 1), st, &d));
-    int32_t *d_nblk = nullptr;
-    int r = SV_OK;
-    hipError_t e = hipMallocAsync((void **)&d_nblk, nblk.size() * sizeof(int32_t), st);
-    if (e != hipSuccess) {
+    const size_t nt = plan.pp.terms.size();
+    auto alloc = [&](void **p, size_t bytes) -> int {
+        hipError_t e = hipMallocAsync(p, bytes, st);
+        if (e == hipSuccess)
+            return SV_OK;
         (void)hipGetLastError();
-        d_nblk = nullptr;
-        r = fail(SV_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
-    } else {
-        e = hipMemcpyAsync(d_nblk, nblk.data(), nblk.size() * sizeof(int32_t), hipMemcpyHostToDevice, st);
+        *p = nullptr;
+        return fail(SV_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+    };
+    if (nt <= (size_t)kFewTerms) {
+        double *partials = nullptr;
+        SV_TRY(alloc((void **)&partials, nt * kMaxPartials * sizeof(double)));
+        const int r = expect_few(s, plan, partials, out_total, out_terms, st);
+        (void)hipFreeAsync(partials, st);
+        return r;
+    }
+    PauliDevice d;
+    SV_TRY(pauli_upload(plan.pp, nt * (kMaxPartials + 1), st, &d));
+    int32_t *nblk = nullptr;
+    int r = alloc((void **)&nblk, nt * sizeof(int32_t));
+    if (r == SV_OK) {
+        hipError_t e = hipMemcpyAsync(nblk, plan.nblk.data(), nt * sizeof(int32_t), hipMemcpyHostToDevice, st);
         if (e != hipSuccess)
             r = fail(SV_EHIP, "copy failed: %s", hipGetErrorString(e));
     }
     if (r == SV_OK)
-        r = expect_launch(s, plan, d.terms, d_nblk, d.partials, d.partials + plan.pp.terms.size() * kMaxPartials,
-                          out_total, out_terms, st);
-    if (d_nblk)
-        (void)hipFreeAsync(d_nblk, st);
+        r = expect_passes(s, plan, d.partials, st);
+    if (r == SV_OK) {
+        double *sums = d.partials + nt * kMaxPartials;
+        hipLaunchKernelGGL(k_expect_sums, dim3((unsigned)nt), dim3(kRedThreads), 0, st, nblk, d.partials, sums);
+        hipLaunchKernelGGL(k_expect_final, dim3(1), dim3(64), 0, st, d.terms, (int)nt, sums, out_total, out_terms);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            r = fail(SV_EHIP, "expectation launch failed: %s", hipGetErrorString(e));
+    }
+    if (nblk)
+        (void)hipFreeAsync(nblk, st);
     pauli_release(&d, st);
     return r;
 }
 
 // ---------------------------------------------------------------------------
-// Allocation-free expectation.  The term table, the partial counts and the
-// partial sums live in one file-scope device array.  Host code never passes
-// the array's name to a kernel: its device address is looked up once per
-// device with hipGetSymbolAddress and kept.  The tables travel to the device
-// as a kernel argument (no host-to-device copy), and every partial a call
-// reads is written by that call first, so nothing needs clearing.  Every
-// call on one device shares the array: calls that overlap on one device
-// race.
+// Allocation-free expectation.  The partial sums live in one file-scope
+// device array.  Host code never passes the array's name to a kernel: its
+// device address is looked up once per device with hipGetSymbolAddress and
+// kept.  The term tables travel as kernel arguments (no host-to-device copy),
+// and every partial a call reads is written by that call first, so nothing
+// needs clearing.  Every call on one device shares the array: calls that
+// overlap on one device race.
 // ---------------------------------------------------------------------------
-constexpr int kNoAllocTerms = SV_EXPECT_NOALLOC_MAX_TERMS;
-
-struct ExpectScratch {
-    DTerm terms[kNoAllocTerms];
-    int32_t nblk[kNoAllocTerms];
-    double partials[(size_t)kNoAllocTerms * kMaxPartials];
-    double sums[kNoAllocTerms];
-};
-
-struct ExpectTables {
-    int32_t nterms, pad;
-    DTerm terms[kNoAllocTerms];
-    int32_t nblk[kNoAllocTerms];
-};
-
-static __device__ __align__(256) unsigned char scratch[sizeof(ExpectScratch)];
-
-__global__ __launch_bounds__(64) void k_expect_tables(ExpectTables t, ExpectScratch *w) {
-    for (int i = threadIdx.x; i < t.nterms; i += blockDim.x) {
-        w->terms[i] = t.terms[i];
-        w->nblk[i] = t.nblk[i];
-    }
-}
+static __device__ __align__(256) unsigned char scratch[(size_t)kFewTerms * kMaxPartials * sizeof(double)];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -839,7 +889,7 @@ static void *g_scratch_ptr[kMaxDevices];
 
 // Device address of the scratch array on the current device (looked up on
 // the first call per device).
-static int scratch_address(ExpectScratch **out) {
+static int scratch_address(double **out) {
     int dev = 0;
     SV_HIP_TRY(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices)
@@ -852,34 +902,20 @@ static int scratch_address(ExpectScratch **out) {
             return fail(SV_EHIP, "hipGetSymbolAddress(scratch) failed on device %d: %s", dev, hipGetErrorString(e));
         g_scratch_ptr[dev] = p;
     }
-    *out = static_cast<ExpectScratch *>(g_scratch_ptr[dev]);
+    *out = static_cast<double *>(g_scratch_ptr[dev]);
     return SV_OK;
 }
 
 static int expect_noalloc_impl(const sv_state_t *s, const sv_pauli_t *terms, int nterms, double *out_total,
                                hipStream_t st) {
     SV_TRY(validate_state(s, true));
-    if (nterms > kNoAllocTerms)
-        return fail(SV_EINVAL, "nterms %d exceeds the allocation-free limit of %d terms", nterms, kNoAllocTerms);
+    if (nterms > kFewTerms)
+        return fail(SV_EINVAL, "nterms %d exceeds the allocation-free limit of %d terms", nterms, kFewTerms);
     ExpectPlan plan;
     SV_TRY(make_expect_plan(s->n, s->dtype, terms, nterms, &plan));
-    ExpectTables t;
-    memset(&t, 0, sizeof(t));
-    t.nterms = (int32_t)plan.pp.terms.size();
-    for (size_t j = 0; j < plan.pp.terms.size(); ++j) {
-        t.terms[j] = plan.pp.terms[j];
-        t.nblk[j] = plan.nblk[j];
-    }
-    ExpectScratch *w = nullptr;
-    SV_TRY(scratch_address(&w));
-    hipLaunchKernelGGL(k_expect_tables, dim3(1), dim3(64), 0, st, t, w);
-    SV_LAUNCH_CHECK();
-    // member addresses inside the device array (w is never dereferenced on the host)
-    char *base = reinterpret_cast<char *>(w);
-    return expect_launch(s, plan, reinterpret_cast<const DTerm *>(base + offsetof(ExpectScratch, terms)),
-                         reinterpret_cast<const int32_t *>(base + offsetof(ExpectScratch, nblk)),
-                         reinterpret_cast<double *>(base + offsetof(ExpectScratch, partials)),
-                         reinterpret_cast<double *>(base + offsetof(ExpectScratch, sums)), out_total, nullptr, st);
+    double *partials = nullptr;
+    SV_TRY(scratch_address(&partials));
+    return expect_few(s, plan, partials, out_total, nullptr, st);
 }
 
 } // namespace sv
