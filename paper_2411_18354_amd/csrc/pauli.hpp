@@ -40,6 +40,22 @@ __device__ __forceinline__ double im_ipow(int ny, double wr, double wi) {
 
 __device__ __forceinline__ bool odd_parity(uint64_t v) { return __popcll(v) & 1; }
 
+// One term's part of its group's factor: c += coef i^ny (-1)^{z.kx}.  I:
+// uint32_t where every mask fits 32 bits, as a 64-bit parity takes twice the
+// instructions.  (ny is uniform, so a real term costs one addition; kx and z
+// select its sign bit.)
+template <typename I>
+__device__ __forceinline__ void add_term(const DTerm &T, uint64_t kx, double &cr, double &ci) {
+    const I b = (I)(T.z & kx);
+    const uint32_t odd = (uint32_t)(sizeof(I) == 8 ? __popcll((uint64_t)b) : __popc((uint32_t)b)) << 31;
+    const uint32_t flip = odd ^ ((T.ny & 2) ? 0x80000000u : 0u);
+    const double s = __hiloint2double(__double2hiint(T.coef) ^ (int)flip, __double2loint(T.coef));
+    if (T.ny & 1)  // uniform
+        ci += s;
+    else
+        cr += s;
+}
+
 // Device copy of a Pauli plan plus the partial-sum workspace, allocated
 // stream-ordered on the caller's stream.
 struct PauliDevice {
