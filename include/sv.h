@@ -456,7 +456,8 @@ int sv_adjoint_destroy(sv_adjoint_t *plan);
  * knob): its passes are cut into chunks of whole tiles or pair-loop steps
  * that the workgroups joining it take in order, a pass's chunks starting once
  * every chunk of the earlier passes is written (device-scope counters; no
- * workgroup waits for another to arrive).  Results do not depend on the
+ * workgroup waits for another to arrive).  Workgroups that run out of items
+ * of their own help the circuits still running.  Results do not depend on the
  * split.
  *   states        ncirc state views (device buffers must not overlap)
  *   gates         all circuits' gates concatenated; circuit c owns

@@ -668,8 +668,8 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
 // the work-item slot.
 template <typename R, bool ADJ, bool LDS>
 __global__ __launch_bounds__(batch_threads(LDS), 4) void k_batched(
-    const BCirc *__restrict__ circs, const int32_t *__restrict__ items, int nitems, const BGate *__restrict__ gates,
-    const BPass *__restrict__ passes, const TileGate *__restrict__ tiles, const RtOp *__restrict__ ops,
+    const BCirc *__restrict__ circs, const int32_t *__restrict__ items, int nitems, int nlisted,
+    const BGate *__restrict__ gates, const BPass *__restrict__ passes, const TileGate *__restrict__ tiles, const RtOp *__restrict__ ops,
     const RtPat *__restrict__ pats, const SweepPat *__restrict__ lpats, const SweepMember *__restrict__ mems,
     const double *__restrict__ params, unsigned int *__restrict__ queue, unsigned int *gstate, uint64_t limit, unsigned int *err,
     uint64_t *__restrict__ stamps, double *part, SweepTables a, uint32_t tail) {
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(batch_threads(LDS), 4) void k_batched(
         else
             run_circuit<R, ADJ, LDS>(ci, d, a, buf, scratch, ticket);
         __syncthreads();
-        if (!ADJ && stamps && threadIdx.x == 0) {
+        if (!ADJ && stamps && it < nlisted && threadIdx.x == 0) {
             stamps[2 * it] = t0;
             stamps[2 * it + 1] = wall_clock64();
         }
@@ -966,7 +966,8 @@ struct BatchHost {
     std::vector<int32_t> csr;
     int64_t npart = 0;             // partial sums
     size_t lds_bytes = 0;          // exchange buffer or tiles, then gradient accumulators of a pass
-    std::vector<int32_t> order;    // work items in queue order (each a circuit)
+    std::vector<int32_t> order;    // work items in queue order (each a circuit), then helpers'
+    int nlisted = 0;               // the former
     int ngroups = 0;               // circuits split over workgroups
     std::vector<double> gens;
     std::vector<int32_t> gen_of;
@@ -997,10 +998,19 @@ constexpr uint64_t kWaitLimitSeconds = 10;
 //    workgroups each, 0.52 ms with 64; four of width 18 0.91 and 0.39 ms; the
 //    512 circuits the same.  Workgroups beyond a pass's tiles would only wait
 //    (the 64 circuits: 0.64 ms without that limit).
-constexpr int kChunksPerWorker = 4;
+// Workgroups that find nothing else to do help: after the circuits' own work
+// items the queue lists every ticketed circuit again, costliest first, once for
+// each further workgroup its chunks have work for (a circuit that is done by
+// then costs one ticket).  Circuits from half the mean load on have tickets,
+// cut for at least kMinShares workgroups.  Without helpers the last circuits ran
+// on their own shares while the rest of the chip was done: 512 circuits of
+// widths 10-20 10.9 -> 10.05 ms, mean workgroups busy 867 -> 939 of 1024; 300 in
+// complex64 1.16 -> 1.09 ms.  Tickets from a fifth of the mean on: 10.15 ms;
+// chunks for eight: 10.75.
+constexpr int kChunksPerWorker = 4, kMinShares = 4;
 
 static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vector<double> &cost,
-                           std::vector<int32_t> *workers) {
+                           std::vector<int32_t> *workers, std::vector<int32_t> *helpers) {
     const int gmax = tuning().batch_split;
     if (gmax <= 1)
         return;
@@ -1014,7 +1024,7 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
     const int m_cap = (h->lds ? kLdsTileBits : rt_nb_of(dtype) + kBatchThreadBits) - (adjoint ? 1 : 0);
     for (size_t c = 0; c < h->circs.size(); ++c) {
         BCirc &bc = h->circs[c];
-        if (bc.npasses == 0 || bc.n <= m_cap || !(cost[c] > load))
+        if (bc.npasses == 0 || bc.n <= m_cap || !(cost[c] > 0.5 * load))
             continue;  // LDS-resident, empty, one workgroup's registers, or short enough
         // a pass's tiles or pairs, and how many of them a workgroup takes at least
         auto extent = [&](const BPass &p, uint64_t *total, uint64_t *unit) {
@@ -1035,14 +1045,16 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
         for (int pi = 0; pi < bc.npasses; ++pi)
             if (h->passes[bc.first_pass + pi].kind <= kPassTiles)
                 most = std::max(most, extent(h->passes[bc.first_pass + pi], &total, &unit));
-        const int g = (int)std::min<double>(std::min<double>(gmax, (double)most), std::floor(cost[c] / load + 0.5));
-        if (g < 2 || (int64_t)bc.npasses * g * kc > (1 << 30))
+        const int limit = (int)std::min<uint64_t>((uint64_t)gmax, most);
+        const int g = std::max(1, (int)std::min<double>(limit, std::floor(cost[c] / load + 0.5)));
+        const int shares = std::max(g, std::min(limit, kMinShares));  // chunks are cut for
+        if (limit < 2 || (int64_t)bc.npasses * shares * kc > (1 << 30))
             continue;
         int64_t k = 0;
         for (int pi = 0; pi < bc.npasses; ++pi) {
             BPass &p = h->passes[bc.first_pass + pi];
             const uint64_t steps = extent(p, &total, &unit);
-            const uint64_t want = std::max<uint64_t>(1, std::min<uint64_t>(steps, (uint64_t)g * kc));
+            const uint64_t want = std::max<uint64_t>(1, std::min<uint64_t>(steps, (uint64_t)shares * kc));
             const uint64_t len = (steps + want - 1) / want * unit;
             p.chunk0 = (int32_t)k;
             p.nchunks = (int32_t)((total + len - 1) / len);
@@ -1052,6 +1064,7 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
         bc.group = h->ngroups++;
         bc.nchunks = (int32_t)k;  // at most npasses * 4 * 64
         (*workers)[c] = g;
+        (*helpers)[c] = std::min(limit, shares * kc) - g;
     }
 }
 
@@ -1226,7 +1239,8 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
         cost[c] = b.cost;
     }
     std::vector<int32_t> workers(A.ncirc, 1);
-    split_circuits(h, *dtype, adjoint, cost, &workers);
+    std::vector<int32_t> helpers(A.ncirc, 0);
+    split_circuits(h, *dtype, adjoint, cost, &workers, &helpers);
     if (adjoint)
         for (int c = 0; c < A.ncirc; ++c)
             place_sums(cb[c].sums, &h->circs[c], h);
@@ -1236,6 +1250,16 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
                      [&](int a, int b) { return cost[a] / workers[a] > cost[b] / workers[b]; });
     for (int c : circ)
         h->order.insert(h->order.end(), (size_t)workers[c], c);
+    h->nlisted = (int)h->order.size();
+    std::stable_sort(circ.begin(), circ.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+    for (bool more = true; more;) {
+        more = false;
+        for (int c : circ)
+            if (helpers[c] > 0) {
+                h->order.push_back(c);
+                more |= --helpers[c] > 0;
+            }
+    }
     return SV_OK;
 }
 
@@ -1257,7 +1281,7 @@ struct BatchDevice {
     double *part = nullptr;
     size_t lds_bytes = 0;
     int32_t *order = nullptr, *gen_of = nullptr;
-    int nitems = 0;
+    int nitems = 0, nlisted = 0;
     double *gens = nullptr;
     DTerm *terms = nullptr;
     unsigned int *queue = nullptr;
@@ -1332,6 +1356,7 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     if (r == SV_OK)
         r = dev_copy(&d->order, h.order, async, st);
     d->nitems = (int)h.order.size();
+    d->nlisted = h.nlisted;
     if (r == SV_OK)
         r = dev_copy(&d->gen_of, h.gen_of, async, st, 1);
     if (r == SV_OK)
@@ -1395,7 +1420,7 @@ static int launch_batch(int dtype, const BatchDevice &d, const double *params, d
     auto go = [&](auto fn) -> int {
         if (lds > 65536)
             SV_HIP_TRY(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(fn, dim3(grid), dim3(batch_threads(d.lds)), lds, s, d.circs, d.order, d.nitems, d.gates, d.passes,
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(batch_threads(d.lds)), lds, s, d.circs, d.order, d.nitems, d.nlisted, d.gates, d.passes,
                            d.tiles, d.ops, d.pats, d.lpats, d.mems, params, d.queue, d.gstate, d.wait_limit,
                            d.gstate ? d.gstate + 2 * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes);
         SV_LAUNCH_CHECK();
@@ -1445,7 +1470,7 @@ int sv_batch_create(const sv_state_t *states, const sv_state_t *lam_states, int 
     b->nparams_total = nparams_total;
     b->has_adjoint = adj;
     int r = hipGetDevice(&b->device) == hipSuccess ? SV_OK : fail(SV_EHIP, "no current device");
-    b->items = hf.order;
+    b->items.assign(hf.order.begin(), hf.order.begin() + hf.nlisted);
     if (r == SV_OK)
         r = upload_batch(hf, false, nullptr, &b->fwd);
     if (r == SV_OK && adj)

@@ -149,3 +149,18 @@ def test_item_stamps(gpu):
     ref = oracle.run_circuit(circs[0], circs[0].params)
     got = views[0].cpu().numpy()
     assert float(np.max(np.abs(got - ref))) <= 1e-12
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_helpers_leave_bits_alone(gpu, dtype):
+    """More circuits than workgroups' shares, most above half the mean cost and
+    few above it: every wide circuit has tickets and workgroups that finish
+    early join others' passes.  Two runs equal the unsplit one bit for bit,
+    and the listed items stay one per circuit and share."""
+    circs = _circuits(91, [14, 15, 14, 16, 14, 15, 13, 14] * 4, ngates=80)
+    angles = [[c.params for c in circs], [c.params + 0.21 for c in circs]]
+    items1, out1, _ = _run(gpu, circs, dtype, 1, angles)
+    items, out, _ = _run(gpu, circs, dtype, 64, angles)
+    assert len(items1) == len(circs) and sorted(set(items)) == list(range(len(circs)))
+    for a, b in zip(out1, out):
+        assert bool((a == b).all())
