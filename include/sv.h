@@ -186,7 +186,7 @@ int sv_hbm_probe(const sv_state_t *s, uint64_t fixed_mask, uint64_t fixed_vals, 
  *   "low_policy"      [0, 1]  0: such failing pairs are skipped; 1: they are
  *       read and rewritten unchanged so writes cover whole cache lines
  *   "wave_auto"       [0, 1]  SV_MODE_AUTO may choose the wavefront kernel
- *   "tile_log2_c128" [6, 13], "tile_log2_c64" [6, 14]  LDS tile width m of
+ *   "tile_log2_c128" [6, 13], "tile_log2_c64" [6, 14]  tile width m of
  *       the fused pass and of SV_MODE_TILE (2^m amplitudes per tile)
  *   "tile_low_bits_c128" [1, 13], "tile_low_bits_c64" [1, 14]  lowest
  *       qubits every fused tile holds (runs of 2^bits contiguous amplitudes);
@@ -277,7 +277,7 @@ typedef struct sv_gate {
 } sv_gate_t;
 
 /* Circuit flags. */
-#define SV_FUSE 1    /* fuse runs of gates into one pass over LDS tiles: a
+#define SV_FUSE 1    /* fuse runs of gates into one pass over tiles: a
                         tile spans the lowest qubits plus qubits the planner
                         picks per run (gate fusion, the future work of
                         Sec. V); diagonal gates join a run whatever their

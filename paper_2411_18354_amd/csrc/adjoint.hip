@@ -224,7 +224,7 @@ static int adjoint_plan(int n, int dtype, const sv_gate_t *gates, int ngates, in
     SV_HIP_TRY(hipGetDevice(&a->device));
 
     // The reverse sweep is the circuit of inverses in reverse order, planned
-    // like a forward circuit (fused runs of two LDS tiles, so one size down).
+    // like a forward circuit (fused runs of two tiles, so one size down).
     std::vector<sv_gate_t> rev(ngates);
     for (int r = 0; r < ngates; ++r) {
         rev[r] = gates[ngates - 1 - r];

@@ -46,7 +46,7 @@ int validate_unitary_gate(const sv_gate_t &g, int index);
 constexpr int kBatchThreads = 256, kBatchThreadBits = 8;
 constexpr unsigned kBatchPerCu = 4;
 constexpr size_t kBatchSlot = 128;  // reduction scratch, work item and ticket
-constexpr size_t kBatchExchange = 32768, kBatchLds = kBatchExchange + kBatchSlot;
+constexpr size_t kBatchExchange = 32768;
 // Complex64 batches that take gradients keep LDS tiles, 512 lanes: a tile's
 // gates in program order, one rounding per gate and amplitude.  Register tiles
 // reorder commuting gates and share diagonal factors, which moves a complex64
@@ -757,11 +757,11 @@ static int plan_passes(int n, int dtype, const sv_gate_t *gates, int ngates, int
     std::vector<PlanPass> pp;
     std::vector<SweepPat> pats;
     if (out->lds)  // (a reverse sweep applies diagonal gates without patterns)
-        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr,
+        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles,
                                   out->rt.dual ? nullptr : &out->lpats, out->rt.dual ? nullptr : &out->mems));
     else
-        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, nullptr, &pats,
-                                  &out->mems, &out->rt));
+        SV_TRY(circuit_plan_tiles(n, dtype, gates, ngates, nparams, m_cap, &pp, &out->tiles, &pats, &out->mems,
+                                  &out->rt));
     for (const PlanPass &q : pp) {
         BPass b;
         memset(&b, 0, sizeof(b));
@@ -1264,6 +1264,7 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
 }
 
 struct BatchDevice {
+    void *block = nullptr;  // the tables below, one allocation
     BCirc *circs = nullptr;
     BGate *gates = nullptr;
     BPass *passes = nullptr;
@@ -1295,103 +1296,50 @@ struct BatchDevice {
 // Stream-ordered release when async (after the kernels enqueued on st),
 // otherwise an immediate free.
 static void batch_release(BatchDevice *d, bool async, hipStream_t st) {
-    void *ps[] = {d->circs, d->gates, d->passes, d->tiles,  d->ops,  d->pats,  d->mems,  d->jobs,  d->slots,
-                  d->csr,   d->part,  d->lpats, d->tslot, d->order,  d->gen_of, d->gens, d->terms, d->queue, d->gstate};
-    for (void *p : ps)
-        if (p)
-            (void)(async ? hipFreeAsync(p, st) : hipFree(p));
+    if (d->block)
+        (void)(async ? hipFreeAsync(d->block, st) : hipFree(d->block));
     *d = BatchDevice();
 }
 
-template <typename T>
-static int dev_copy(T **dst, const std::vector<T> &src, bool async, hipStream_t st, size_t min_count = 0) {
-    const size_t cnt = std::max(src.size(), min_count);
-    *dst = nullptr;
-    if (cnt == 0)
-        return SV_OK;
-    hipError_t e = async ? hipMallocAsync((void **)dst, cnt * sizeof(T), st) : hipMalloc((void **)dst, cnt * sizeof(T));
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        *dst = nullptr;
-        return fail(SV_ENOMEM, "device allocation failed: %s", hipGetErrorString(e));
-    }
-    if (!src.empty()) {
-        if (async)
-            SV_HIP_TRY(hipMemcpyAsync(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, st));
-        else
-            SV_HIP_TRY(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
-    }
-    return SV_OK;
-}
-
 static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDevice *d) {
-    int r = dev_copy(&d->circs, h.circs, async, st);
-    if (r == SV_OK)
-        r = dev_copy(&d->gates, h.gates, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->passes, h.passes, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->tiles, h.tiles, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->ops, h.prog.ops, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->pats, h.prog.pats, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->mems, h.mems, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->jobs, h.jobs, async, st, 1);
+    TableBlock tb;
+    tb.add(&d->circs, h.circs);
+    tb.add(&d->gates, h.gates);
+    tb.add(&d->passes, h.passes);
+    tb.add(&d->tiles, h.tiles);
+    tb.add(&d->ops, h.prog.ops);
+    tb.add(&d->pats, h.prog.pats);
+    tb.add(&d->mems, h.mems);
+    tb.add(&d->jobs, h.jobs);
+    tb.add(&d->slots, h.slots);
+    tb.add(&d->csr, h.csr);
+    tb.add(&d->lpats, h.lpats);
+    tb.add(&d->tslot, h.tslot);
+    tb.add(&d->order, h.order);
+    tb.add(&d->gen_of, h.gen_of);
+    tb.add(&d->gens, h.gens);
+    tb.add(&d->terms, h.terms);
+    tb.add((void **)&d->queue, nullptr, sizeof(unsigned int));
+    const int words = h.ngroups > 0 ? 2 * h.ngroups + 1 : 0;
+    tb.add((void **)&d->gstate, nullptr, words * sizeof(unsigned int));
+    tb.add((void **)&d->part, nullptr, (size_t)h.npart * sizeof(double));
+    int r = tb.upload(&d->block, async, st);
     d->njobs = (int)h.jobs.size();
-    if (r == SV_OK)
-        r = dev_copy(&d->slots, h.slots, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->csr, h.csr, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->part, std::vector<double>(), async, st, (size_t)h.npart);
-    if (r == SV_OK)
-        r = dev_copy(&d->lpats, h.lpats, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->tslot, h.tslot, async, st, 1);
     d->lds = h.lds;
     d->lds_bytes = h.lds_bytes;
-    if (r == SV_OK)
-        r = dev_copy(&d->order, h.order, async, st);
     d->nitems = (int)h.order.size();
     d->nlisted = h.nlisted;
-    if (r == SV_OK)
-        r = dev_copy(&d->gen_of, h.gen_of, async, st, 1);
-    if (r == SV_OK)
-        r = dev_copy(&d->gens, h.gens, async, st, 8);
-    if (r == SV_OK)
-        r = dev_copy(&d->terms, h.terms, async, st, 1);
-    if (r == SV_OK) {
-        hipError_t e = async ? hipMallocAsync((void **)&d->queue, sizeof(unsigned int), st)
-                             : hipMalloc((void **)&d->queue, sizeof(unsigned int));
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            d->queue = nullptr;
-            r = fail(SV_ENOMEM, "device allocation failed");
-        }
-    }
     d->ngroups = h.ngroups;
     if (r == SV_OK && h.ngroups > 0) {
-        const int words = 2 * h.ngroups + 1;
-        hipError_t e = async ? hipMallocAsync((void **)&d->gstate, words * sizeof(unsigned int), st)
-                             : hipMalloc((void **)&d->gstate, words * sizeof(unsigned int));
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            d->gstate = nullptr;
-            r = fail(SV_ENOMEM, "device allocation failed");
-        } else {
-            hipLaunchKernelGGL(k_zero_words, dim3((words + 255) / 256), dim3(256), 0, st, d->gstate, words);
-            if (!async)
-                r = hipStreamSynchronize(st) == hipSuccess ? SV_OK : fail(SV_EHIP, "clearing the batch counters failed");
-            int dev = 0, khz = 0;
-            if (r == SV_OK && (hipGetDevice(&dev) != hipSuccess ||
-                               hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess ||
-                               khz <= 0))
-                r = fail(SV_EHIP, "device reports no constant-rate clock");
-            d->wait_limit = (uint64_t)khz * 1000ull * kWaitLimitSeconds;
-        }
+        hipLaunchKernelGGL(k_zero_words, dim3((words + 255) / 256), dim3(256), 0, st, d->gstate, words);
+        if (!async)
+            r = hipStreamSynchronize(st) == hipSuccess ? SV_OK : fail(SV_EHIP, "clearing the batch counters failed");
+        int dev = 0, khz = 0;
+        if (r == SV_OK && (hipGetDevice(&dev) != hipSuccess ||
+                           hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess ||
+                           khz <= 0))
+            r = fail(SV_EHIP, "device reports no constant-rate clock");
+        d->wait_limit = (uint64_t)khz * 1000ull * kWaitLimitSeconds;
     }
     if (r != SV_OK)
         batch_release(d, async, st);

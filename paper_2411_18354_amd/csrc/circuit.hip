@@ -588,41 +588,6 @@ static void free_buffers(sv_circuit *c, hipStream_t st) {
     c->rt = RtDevice{nullptr, nullptr, nullptr};
 }
 
-// A plan's device tables, packed into one allocation and one copy (ten of
-// each cost a small plan more than its planning did).
-struct TableBlock {
-    std::vector<char> host;
-    std::vector<std::pair<void **, size_t>> at;  // device pointer, offset
-    template <typename T> void add(T **dst, const std::vector<T> &src) {
-        *dst = nullptr;
-        if (src.empty())
-            return;
-        const size_t off = (host.size() + 255) / 256 * 256;
-        host.resize(off + src.size() * sizeof(T));
-        memcpy(host.data() + off, src.data(), src.size() * sizeof(T));
-        at.push_back({(void **)dst, off});
-    }
-    int upload(void **block, bool async, hipStream_t st) {
-        *block = nullptr;
-        if (host.empty())
-            return SV_OK;
-        const size_t bytes = host.size();
-        const hipError_t e = async ? hipMallocAsync(block, bytes, st) : hipMalloc(block, bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            *block = nullptr;
-            return fail(SV_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
-        }
-        for (auto &p : at)
-            *p.first = (char *)*block + p.second;
-        if (async)
-            SV_HIP_TRY(hipMemcpyAsync(*block, host.data(), bytes, hipMemcpyHostToDevice, st));
-        else
-            SV_HIP_TRY(hipMemcpy(*block, host.data(), bytes, hipMemcpyHostToDevice));
-        return SV_OK;
-    }
-};
-
 // Dynamic LDS of a fused pass: the tile (in the arithmetic type), then the
 // diagonal-sweep tables.
 static size_t fused_lds(int m, int dtype) {
@@ -880,8 +845,8 @@ int sv_circuit_plan(int n, int dtype, const sv_gate_t *gates, int ngates, int np
 namespace sv {
 
 int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int m_cap,
-                       std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, int *m_used,
-                       std::vector<SweepPat> *pats, std::vector<SweepMember> *mems, PlanRt *rt) {
+                       std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, std::vector<SweepPat> *pats,
+                       std::vector<SweepMember> *mems, PlanRt *rt) {
     if (dtype != SV_C128 && dtype != SV_C64)
         return fail(SV_EINVAL, "unknown dtype %d", dtype);
     if (n < 1 || n > max_qubits(dtype))
@@ -932,8 +897,6 @@ int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int
         rt->prog = std::move(c.prog);
         rt->jobs = std::move(jobs);
     }
-    if (m_used)
-        *m_used = c.m;
     return SV_OK;
 }
 

@@ -78,6 +78,60 @@ struct sv_circuit {
 
 namespace sv {
 
+// A plan's device tables in one allocation, small ones in one copy: separate
+// allocations and copies cost more than planning a short circuit.
+struct TableBlock {
+    struct Part {
+        void **dst;
+        const void *src;  // stays in place until upload; none: room only
+        size_t bytes, off;
+    };
+    std::vector<Part> parts;
+    size_t bytes = 0;
+    void add(void **dst, const void *src, size_t n) {
+        *dst = nullptr;
+        if (n == 0)
+            return;
+        const size_t off = (bytes + 255) / 256 * 256;
+        parts.push_back({dst, src, n, off});
+        bytes = off + n;
+    }
+    template <typename T> void add(T **dst, const std::vector<T> &src) {
+        add((void **)dst, src.data(), src.size() * sizeof(T));
+    }
+    int upload(void **block, bool async, hipStream_t st) {
+        *block = nullptr;
+        if (parts.empty())
+            return SV_OK;
+        const hipError_t e = async ? hipMallocAsync(block, bytes, st) : hipMalloc(block, bytes);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            *block = nullptr;
+            return fail(SV_ENOMEM, "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+        }
+        for (const Part &p : parts)
+            *p.dst = (char *)*block + p.off;
+        auto copy = [&](size_t off, const void *src, size_t n) -> int {
+            if (async)
+                SV_HIP_TRY(hipMemcpyAsync((char *)*block + off, src, n, hipMemcpyHostToDevice, st));
+            else
+                SV_HIP_TRY(hipMemcpy((char *)*block + off, src, n, hipMemcpyHostToDevice));
+            return SV_OK;
+        };
+        if (bytes > (1u << 20)) {  // large tables: no second host copy
+            for (const Part &p : parts)
+                if (p.src)
+                    SV_TRY(copy(p.off, p.src, p.bytes));
+            return SV_OK;
+        }
+        std::vector<char> host(bytes);
+        for (const Part &p : parts)
+            if (p.src)
+                memcpy(host.data() + p.off, p.src, p.bytes);
+        return copy(0, host.data(), bytes);
+    }
+};
+
 // Validate, plan and upload a circuit (the body of sv_circuit_create).
 // async: device buffers are allocated and released stream-ordered on st.
 // m_cap bounds the tile width (callers with a fixed LDS budget).
@@ -102,9 +156,8 @@ struct PlanRt {
 // pats/mems (optional): the phase patterns of the table sweeps, indexed
 // from 0 (pat0 and mem[] of the descriptors refer to them).
 int circuit_plan_tiles(int n, int dtype, const sv_gate_t *gates, int ngates, int nparams, int m_cap,
-                       std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, int *m_used,
-                       std::vector<SweepPat> *pats = nullptr, std::vector<SweepMember> *mems = nullptr,
-                       PlanRt *rt = nullptr);
+                       std::vector<PlanPass> *passes, std::vector<TileGate> *tiles, std::vector<SweepPat> *pats = nullptr,
+                       std::vector<SweepMember> *mems = nullptr, PlanRt *rt = nullptr);
 
 // rt: fused runs on register tiles where their width allows (the caller runs
 // Pass::rt passes with launch_rt_pass).  dual: a reverse sweep; the gradient
