@@ -475,8 +475,8 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
                     X = x;
                     v = psi[k ^ X];
                 }
-                const double s = odd_parity(T.z & (k ^ X)) ? -T.coef : T.coef;
-                const double cr = re_ipow(T.ny, s, 0.0), cim = im_ipow(T.ny, s, 0.0);
+                double cr = 0.0, cim = 0.0;
+                add_term<uint32_t>(T, k ^ X, cr, cim);
                 ar += cr * (double)v.x - cim * (double)v.y;
                 ai += cr * (double)v.y + cim * (double)v.x;
             }
