@@ -462,11 +462,13 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 // for each of its gates and lose on complex128 (streaming
                 // circuit, n = 12: 12.4 against 10.8 us, n = 26: 447 against
                 // 431 us; n = 16 to 22 even or faster) and where the other
-                // dtypes have a few tiles only (complex64 n = 13: 15.2 against
-                // 13.4 us, n = 14: 17.8 against 15.5; n = 16: 21.2 against
-                // 21.9, n = 26: 232 against 255; 32-bit codes n = 13: 16.2
-                // against 14.7, n = 27: 476 against 574).
-                bool gather = tuning().fuse_perm && !c->dual && !c->rt_nb && (c->dtype == SV_C128 || p.tm.ntiles <= 4) &&
+                // dtypes have few tiles (complex64 n = 13: 15.2 against 13.4
+                // us, n = 14: 17.8 against 15.5; n = 16: 21.2 against 21.9,
+                // n = 26: 232 against 255; 32-bit codes n = 16: 24.4 against
+                // 23.9, n = 20: 36.4 against 35.2; n = 22: 53.6 against 64.8,
+                // n = 27: 476 against 574).
+                bool gather = tuning().fuse_perm && !c->dual && !c->rt_nb &&
+                              (c->dtype == SV_C128 || p.tm.ntiles <= (is_fixed(c->dtype) ? kRtFewTiles : 4)) &&
                               (1u << m) <= 512u * (tdt == SV_C128 ? perm_per_lane<double>() : perm_per_lane<float>());
                 if (gather) {
                     mark_permutation_runs(&tiles[p.first], p.count);
