@@ -508,10 +508,18 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_expect_tile(const A amps, c
     row[48] = T.acc3;
     __syncthreads();
     if ((int)tid < nt) {
-        double s = 0.0;
+        // (by pairs: added one after another, terms of one sign in the whole
+        // tile lost twice as much to rounding)
+        double s[kTileThreads / 16];
+#pragma unroll
         for (int q = 0; q < kTileThreads / 16; ++q)
-            s += wsum[q * kTileTerms + tid];
-        partials[(size_t)P.t[tid].slot * kMaxPartials + blockIdx.x] = s;
+            s[q] = wsum[q * kTileTerms + tid];
+#pragma unroll
+        for (int h = 1; h < kTileThreads / 16; h <<= 1)
+#pragma unroll
+            for (int q = 0; q < kTileThreads / 16; q += 2 * h)
+                s[q] += s[q + h];
+        partials[(size_t)P.t[tid].slot * kMaxPartials + blockIdx.x] = s[0];
     }
 }
 
@@ -559,11 +567,22 @@ __global__ __launch_bounds__(kFewThreads) void k_expect_few(const FewTerms t, co
     __shared__ double sums[kFewTerms];
     const int lane = threadIdx.x & 63;
     for (int j = threadIdx.x >> 6; j < t.nterms; j += kFewThreads / 64) {
-        double v = 0.0;
+        // What the additions round off is kept beside the sum.  (The partials of
+        // a term may be all of one sign in a lane and cancel between lanes: plain
+        // sums left up to twice the error of the partials themselves.)
+        double v = 0.0, e = 0.0;
+        auto add = [&](double p, double pe) {
+            const double s = v + p, b = s - v;
+            e += pe + ((v - (s - b)) + (p - b));
+            v = s;
+        };
 #pragma unroll 8
         for (int i = lane; i < t.nblk[j]; i += 64)
-            v += partials[(size_t)j * kMaxPartials + i];
-        v = wave_sum(v);
+            add(partials[(size_t)j * kMaxPartials + i], 0.0);
+#pragma unroll
+        for (int h = 1; h < 64; h <<= 1)
+            add(__shfl_xor(v, h), __shfl_xor(e, h));
+        v += e == e ? e : 0.0;  // (infinite sums leave none)
         if (lane == 0) {
             sums[j] = v;
             if (out_terms)
