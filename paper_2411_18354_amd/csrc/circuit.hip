@@ -492,13 +492,21 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                             r.slot = grad_slot[gi];
                         }
                     }
-                    p.rt = true;
+                    const size_t nops = c->prog.ops.size(), npats = c->prog.pats.size();
+                    bool slow = false;
                     p.rp = build_rt_pass(p.tm, fmask, tdt, &tiles[p.first], p.count, info.data(), pats,
                                          c->rt_nb ? c->rt_nb : rt_pass_nb(tdt, m, c->dual, p.tm.ntiles),
-                                         tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->dual, c->prog);
-                    for (int k = 0; k < p.count; ++k)
-                        op_slot[tiles[p.first + k].src_gate] = {info[k].op, info[k].op2};
-                } else {
+                                         tdt == SV_C128 ? 3 : 4, is_fixed(c->dtype), c->dual, c->prog, &slow);
+                    p.rt = !slow || c->rt_nb;
+                    if (p.rt) {
+                        for (int k = 0; k < p.count; ++k)
+                            op_slot[tiles[p.first + k].src_gate] = {info[k].op, info[k].op2};
+                    } else {
+                        c->prog.ops.resize(nops);
+                        c->prog.pats.resize(npats);
+                    }
+                }
+                if (!p.rt) {
                     if (tuning().fuse_pairs)
                         mark_coset_pairs(&tiles[p.first], p.count);
                     if (tuning().fuse_perm)  // checked first by the tile loops

@@ -223,7 +223,8 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *m, bool diag) {
 
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *t, int count,
                      RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
-                     RtProgram &prog) {
+                     RtProgram &prog, bool *slow) {
+    *slow = false;
     // nr: register bits of the layouts; nb: with the bit telling psi and lambda apart
     const int m = (int)tm.m, nr = nb - (dual ? 1 : 0);
     RtPass pass;
@@ -263,6 +264,32 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
         Cond c;
         RtPat p;
     };
+    auto put_pats = [&](const std::vector<Part> &v) {
+        for (const Part &a : v)
+            prog.pats.push_back(a.p);
+    };
+    auto prepare = [&](size_t np, size_t r_first, size_t r_count) {
+        RtOp o;
+        memset(&o, 0, sizeof(o));
+        o.w[0] = kRtPrep * 8;
+        o.w[1] = (uint32_t)np;
+        o.w[2] = (uint32_t)prog.pats.size();
+        o.w[3] = (uint32_t)r_first;
+        o.w[4] = (uint32_t)r_count;
+        prog.ops.push_back(o);
+        lds = std::max(lds, np * sizeof(RtPat) + ((size_t)16 << nb));
+    };
+    auto factor = [&](uint32_t regs, size_t first, size_t cnt, uint32_t reg) {
+        RtOp f;
+        memset(&f, 0, sizeof(f));
+        f.w[0] = kRtFactor * 8;
+        f.w[1] = regs;
+        f.w[5] = rt_jump(kRtEntryMul);
+        f.w[12] = (uint32_t)first;
+        f.w[13] = (uint32_t)cnt;
+        f.w[14] = reg;
+        prog.ops.push_back(f);
+    };
     auto emit_phases = [&](const Part *parts, size_t np) {
         std::vector<Part> ts, rs, xs;
         for (size_t i = 0; i < np; ++i) {
@@ -276,29 +303,12 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
         std::stable_sort(xs.begin(), xs.end(), [](const Part &a, const Part &b) {
             return a.c.rm != b.c.rm ? a.c.rm < b.c.rm : a.c.rv < b.c.rv;
         });
-        RtOp o;
-        memset(&o, 0, sizeof(o));
-        o.w[0] = kRtPrep * 8;
-        o.w[1] = (uint32_t)np;
-        o.w[2] = (uint32_t)prog.pats.size();
-        o.w[3] = (uint32_t)ts.size();
-        o.w[4] = (uint32_t)rs.size();
-        prog.ops.push_back(o);
-        for (const std::vector<Part> *v : {&ts, &rs, &xs})
-            for (const Part &a : *v)
-                prog.pats.push_back(a.p);
-        auto factor = [&](uint32_t regs, size_t first, size_t cnt) {
-            RtOp f;
-            memset(&f, 0, sizeof(f));
-            f.w[0] = kRtFactor * 8;
-            f.w[1] = regs;
-            f.w[5] = rt_jump(kRtEntryMul);
-            f.w[12] = (uint32_t)first;
-            f.w[13] = (uint32_t)cnt;
-            prog.ops.push_back(f);
-        };
+        prepare(np, ts.size(), rs.size());
+        put_pats(ts);
+        put_pats(rs);
+        put_pats(xs);
         if (!ts.empty())
-            factor(regs_where(nb, 0, 0), 0, ts.size());
+            factor(regs_where(nb, 0, 0), 0, ts.size(), 0);
         if (!rs.empty()) {
             RtOp f;
             memset(&f, 0, sizeof(f));
@@ -310,10 +320,109 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
             size_t e = i;
             while (e < xs.size() && xs[e].c.rm == xs[i].c.rm && xs[e].c.rv == xs[i].c.rv)
                 ++e;
-            factor(regs_where(nb, xs[i].c.rm, xs[i].c.rv), ts.size() + rs.size() + i, e - i);
+            factor(regs_where(nb, xs[i].c.rm, xs[i].c.rv), ts.size() + rs.size() + i, e - i, 0);
             i = e;
         }
-        lds = std::max(lds, np * sizeof(RtPat) + ((size_t)16 << nb));
+    };
+    // complex64: one factor per amplitude.  Phases under one register bit and
+    // thread bits come as a factor per register bit (one asked to be 0 adds
+    // its phase to every register and takes it off where the bit is 1); a
+    // block with phases under several register bits and thread bits sums all
+    // of its phases once for each set of registers that they do not tell apart.
+    auto emit_block = [&](const Part *parts, size_t np) {
+        std::vector<Part> ts, rs, xs[kRtMaxNB];
+        bool split = true, bits = false;
+        for (size_t i = 0; i < np; ++i) {
+            Part a = parts[i];
+            if (!a.c.rm) {
+                ts.push_back(a);
+            } else if (!a.c.tm) {
+                a.p.cm = a.c.rm;
+                a.p.cv = a.c.rv;
+                rs.push_back(a);
+            } else {
+                split &= !(a.c.rm & (a.c.rm - 1));
+                if (!a.c.rv) {
+                    ts.push_back(a);
+                    a.p.count |= kRtPatNegative;
+                }
+                xs[__builtin_ctz(a.c.rm)].push_back(a);
+                bits = true;
+            }
+        }
+        if (!split) {
+            *slow = true;
+            std::vector<Part> all(parts, parts + np);
+            for (Part &a : all) {
+                a.p.cm |= a.c.rm << kRtRegBit;
+                a.p.cv |= a.c.rv << kRtRegBit;
+            }
+            prepare(np, 0, 0);
+            put_pats(all);
+            uint32_t todo = regs_where(nb, 0, 0);
+            while (todo) {
+                const uint32_t r = (uint32_t)__builtin_ctz(todo);
+                uint32_t same = todo;
+                bool any = false;
+                for (size_t i = 0; i < np; ++i) {
+                    const uint32_t in = regs_where(nb, parts[i].c.rm, parts[i].c.rv);
+                    same &= (in >> r) & 1u ? in : ~in;
+                    any |= (in >> r) & 1u;
+                }
+                if (any)
+                    factor(same, 0, np, r);
+                todo &= ~same;
+            }
+            return;
+        }
+        // all under one register bit (a QFT's target): the others keep their
+        // amplitudes
+        uint32_t one = parts[0].c.rm & parts[0].c.rv;
+        for (size_t i = 1; i < np; ++i)
+            one &= parts[i].c.rm & parts[i].c.rv;
+        if (one & (one - 1))
+            one = 0;
+        if (one) {
+            const int k = __builtin_ctz(one);
+            for (size_t i = rs.size(); i-- > 0;)
+                if (rs[i].c.rm == one) {  // no other register bit: a phase of the lane
+                    rs[i].p.cm = rs[i].p.cv = 0;
+                    xs[k].push_back(rs[i]);
+                    rs.erase(rs.begin() + (long)i);
+                }
+        }
+        size_t count = ts.size() + rs.size();
+        for (const std::vector<Part> &x : xs)
+            count += x.size();
+        prepare(count, ts.size(), rs.size());
+        put_pats(ts);
+        put_pats(rs);
+        if (one && rs.empty()) {
+            const std::vector<Part> &x = xs[__builtin_ctz(one)];
+            put_pats(x);
+            factor(regs_where(nb, one, one), 0, x.size(), 0);
+            return;
+        }
+        if (rs.empty() && !bits) {
+            factor(regs_where(nb, 0, 0), 0, ts.size(), 0);
+            return;
+        }
+        RtOp f;
+        memset(&f, 0, sizeof(f));
+        f.w[0] = kRtBlock * 8;
+        f.w[5] = rt_jump(one             ? kRtEntryOneBit + (uint32_t)__builtin_ctz(one)
+                         : !bits      ? kRtEntryTab
+                         : rs.empty() ? kRtEntryBitsOnly
+                                      : kRtEntryBits);
+        f.w[13] = (uint32_t)ts.size();
+        size_t at = ts.size() + rs.size();
+        for (int k = 0; k < nb; ++k) {
+            f.t[k] = (uint32_t)at;
+            f.t[8 + k] = (uint32_t)xs[k].size();
+            at += xs[k].size();
+            put_pats(xs[k]);
+        }
+        prog.ops.push_back(f);
     };
 
     // the gradient term of parameterised gate k: over its pairs, or over the
@@ -391,7 +500,10 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
                 }
             }
             for (size_t p0 = 0; p0 < parts.size(); p0 += kRtMaxPats)
-                emit_phases(&parts[p0], std::min<size_t>(kRtMaxPats, parts.size() - p0));
+                if (comp == 4)
+                    emit_block(&parts[p0], std::min<size_t>(kRtMaxPats, parts.size() - p0));
+                else
+                    emit_phases(&parts[p0], std::min<size_t>(kRtMaxPats, parts.size() - p0));
             for (int q = k; q < k + u.count; ++q)
                 info[q].op = info[q].op2 = -1;
             return;

@@ -74,6 +74,9 @@ __device__ __forceinline__ uint32_t rt_fresh(uint32_t v) {
     return v;
 }
 
+// Two values of which it may take anything.
+template <typename R> __device__ __forceinline__ void rt_unset(R &a, R &b) { asm volatile("" : "=v"(a), "=v"(b)); }
+
 // Coefficients of phase_factor's polynomials (tile.hpp): 2/pi, pi/2 in two
 // parts, the sine series from 1/17! down to 1, the cosine series from 1/16!
 // down to 1.  Read from memory as uniform operands, for the reason above.
@@ -83,44 +86,27 @@ static __device__ const double kRtSeries[21] = {
     1.0 / 5040.0, 1.0 / 120.0, 1.0 / 6.0, 1.0,
     1.0 / 20922789888000.0, 1.0 / 87178291200.0, 1.0 / 479001600.0, 1.0 / 3628800.0, 1.0 / 40320.0, 1.0 / 720.0,
     1.0 / 24.0, 1.0 / 2.0, 1.0};
-static __device__ const float kRtSeriesF[10] = {
-    1.0f / 362880.0f, 1.0f / 5040.0f, 1.0f / 120.0f, 1.0f / 6.0f, 1.0f,
-    1.0f / 40320.0f, 1.0f / 720.0f, 1.0f / 24.0f, 1.0f / 2.0f, 1.0f};
 
-// exp(i th) as phase_factor evaluates it.
-template <typename R> __device__ __forceinline__ void rt_phase_factor(double th, R *fr, R *fi) {
+// exp(i (th + e)) as phase_factor evaluates it, by polynomials of fewer terms
+// (errors below 1e-11) for a factor that is rounded to single precision.
+template <bool SHORT = false>
+__device__ __forceinline__ void rt_phase_factor(double th, double e, double *fr, double *fi) {
     const double *c = kRtSeries;
     asm volatile("" : "+s"(c));
     const double k = rint(th * c[0]);
     double rd = fma(-k, c[1], th);
-    rd = fma(-k, c[2], rd);
-    R s, co;
-    if constexpr (sizeof(R) == 8) {
-        const double r2 = rd * rd;
-        double ps = c[3], pc = c[12];
+    rd = fma(-k, c[2], rd) + e;
+    constexpr int first = SHORT ? 6 : 3, firstc = SHORT ? 15 : 12;
+    const double r2 = rd * rd;
+    double ps = c[first], pc = c[firstc];
 #pragma unroll
-        for (int i = 4; i < 12; ++i)
-            ps = fma(ps, -r2, c[i]);
+    for (int i = first + 1; i < 12; ++i)
+        ps = fma(ps, -r2, c[i]);
 #pragma unroll
-        for (int i = 13; i < 21; ++i)
-            pc = fma(pc, -r2, c[i]);
-        s = rd * ps;
-        co = pc;
-    } else {
-        const float *f = kRtSeriesF;
-        asm volatile("" : "+s"(f));
-        const float r = (float)rd, r2 = r * r;
-        float ps = f[0], pc = f[5];
-#pragma unroll
-        for (int i = 1; i < 5; ++i)
-            ps = fmaf(ps, -r2, f[i]);
-#pragma unroll
-        for (int i = 6; i < 10; ++i)
-            pc = fmaf(pc, -r2, f[i]);
-        s = r * ps;
-        co = pc;
-    }
-    const int q = (int)((int64_t)k & 3);
+    for (int i = firstc + 1; i < 21; ++i)
+        pc = fma(pc, -r2, c[i]);
+    const double s = rd * ps, co = pc;
+    const int q = (int)k & 3;  // |k| is far below 2^31
     *fi = q == 0 ? s : q == 1 ? co : q == 2 ? -s : -co;
     *fr = q == 0 ? co : q == 1 ? -s : q == 2 ? -co : s;
 }
@@ -131,16 +117,41 @@ struct RtPhase {
     double th;
 };
 
-// Sum of the phases of patterns [first, first + count) that index idx
-// selects.
-__device__ __forceinline__ double rt_phase_sum(const RtPhase *ph, uint32_t first, uint32_t count, uint32_t idx) {
-    double t = 0.0;
-#pragma unroll 4
-    for (uint32_t p = first; p < first + count; ++p) {
-        const RtPhase q = ph[p];
-        t += (idx & q.cm) == q.cv ? q.th : 0.0;
+// Sum of the phases of patterns [first, first + count) that index idx selects:
+// two sums, of half the patterns each, and *e what adding them rounds off.  (A
+// lane's phases reach the size of several turns; one sum left states of the
+// ansatz with 9% more error than two tables of six qubits did, n = 12.)
+__device__ __forceinline__ double rt_phase_sum(const RtPhase *ph, uint32_t first, uint32_t count, uint32_t idx,
+                                               double *e) {
+    const uint32_t half = count >> 1;
+    double t0 = 0.0, t1 = 0.0;
+#pragma unroll 2
+    for (uint32_t p = first; p < first + half; ++p) {
+        const RtPhase q0 = ph[p], q1 = ph[p + half];
+        t0 += (idx & q0.cm) == q0.cv ? q0.th : 0.0;
+        t1 += (idx & q1.cm) == q1.cv ? q1.th : 0.0;
     }
+    if (count & 1u) {  // uniform
+        const RtPhase q = ph[first + 2 * half];
+        t0 += (idx & q.cm) == q.cv ? q.th : 0.0;
+    }
+    const double t = t0 + t1, b = t - t0;
+    *e = (t0 - (t - b)) + (t1 - b);
     return t;
+}
+
+// The factor of those phases.
+template <bool SHORT>
+__device__ __forceinline__ void rt_phases(const RtPhase *ph, uint32_t first, uint32_t count, uint32_t idx, double *fr,
+                                          double *fi) {
+    if (SHORT && count == 0) {  // uniform
+        *fr = 1.0;
+        *fi = 0.0;
+        return;
+    }
+    double e;
+    const double t = rt_phase_sum(ph, first, count, idx, &e);
+    rt_phase_factor<SHORT>(t, e, fr, fi);
 }
 
 // A block of diagonal gates multiplies every amplitude by exp(i theta), theta
@@ -151,12 +162,16 @@ __device__ __forceinline__ double rt_phase_sum(const RtPhase *ph, uint32_t first
 // for each distinct register condition; so an amplitude costs a few complex
 // products and a lane a few sines and cosines, however many gates the block
 // has.  This operation sums every pattern's members for the tile and forms
-// the R patterns' table of factors; kRtFactor and kRtTable operations follow.
+// the R patterns' table of factors; kRtFactor and kRtTable operations follow
+// (each a product with the amplitudes), or, on complex64 tiles, one kRtBlock or
+// kRtFactor operation, as single precision has no roundings to spare: with a
+// product for each, the QFT's error was 4% (n = 20) to 7% (n = 29) larger than
+// with one factor for the sum of all phases.
 template <typename R, int NB>
 __device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const uint32_t (&w)[16],
                                         const RtPat *__restrict__ pats, const SweepMember *__restrict__ mems) {
     const uint32_t tid = rt_fresh(threadIdx.x), np = w[1];
-    cplx_t<R> *fr = reinterpret_cast<cplx_t<R> *>(lds);
+    double2 *fr = reinterpret_cast<double2 *>(lds);
     RtPhase *ph = reinterpret_cast<RtPhase *>(fr + (1 << NB));
     __syncthreads();  // the buffer's last readers are done
     for (uint32_t p = tid; p < np; p += blockDim.x) {
@@ -165,10 +180,12 @@ __device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const
                                                          (uint32_t)((w[2] + p) * sizeof(RtPat)));
         double th = 0.0;
 #pragma unroll 1
-        for (uint32_t k = 0; k < q.count; ++k) {
+        for (uint32_t k = 0; k < (q.count & ~kRtPatNegative); ++k) {
             const SweepMember mm = mems[q.first + k];
             th += (base & mm.om) == mm.ov ? mm.theta : 0.0;
         }
+        if (q.count & kRtPatNegative)
+            th = -th;
         RtPhase a;
         a.cm = q.cm;
         a.cv = q.cv;
@@ -178,8 +195,8 @@ __device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const
     __syncthreads();
     if (w[4]) {  // uniform
         if (tid < (1u << NB)) {
-            cplx_t<R> f;
-            rt_phase_factor<R>(rt_phase_sum(ph, w[3], w[4], tid), &f.x, &f.y);
+            double2 f;
+            rt_phases<sizeof(R) == 4>(ph, w[3], w[4], tid, &f.x, &f.y);
             fr[tid] = f;
         }
         __syncthreads();
@@ -209,7 +226,7 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
     const uint32_t tid = threadIdx.x;
     // LDS byte address of the buffer
     const uint32_t buf = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
-    const RtPhase *ph = reinterpret_cast<const RtPhase *>(reinterpret_cast<cplx_t<R> *>(lds) + (1 << NB));
+    const RtPhase *ph = reinterpret_cast<const RtPhase *>(reinterpret_cast<double2 *>(lds) + (1 << NB));
     // gradient terms not yet summed: this lane's last one, and two before it
     // folded (lanes of either value of bit 0 hold one of them)
     double one_term = 0.0, two_terms = 0.0;
@@ -240,7 +257,7 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
         // 12-qubit tile 120.9 -> 117.5 us; full lanes gain nothing)
         R fr = (R)0, fi = (R)0;
         if constexpr (NB < rt_nb<R>())
-            asm volatile("" : "=v"(fr), "=v"(fi));
+            rt_unset(fr, fi);
         uint64_t lanes = ~0ull;
         uint32_t next = slot;
         // every path meets at rt_apply (lanes 0: nothing to do): paths of
@@ -252,19 +269,35 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
             if ((base & om) != ov)
                 lanes = 0;
         }
+        RtPhases<NB> bl;  // complex64: the factors
         if (kind == kRtDiag) {
             const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
             const bool one = (tid & w[4]) != 0 || (base & ob) != 0 || (w[0] & 7u) != 0;
-            fr = one ? m.dr : m.ar;
-            fi = one ? m.di : m.ai;
+            if constexpr (sizeof(R) == 4) {
+                bl.gr = one ? m.dr : m.ar;
+                bl.gi = one ? m.di : m.ai;
+            } else {
+                fr = one ? m.dr : m.ar;
+                fi = one ? m.di : m.ai;
+            }
         } else if (!gate) {
-            if (kind == kRtFactor) {
-                rt_phase_factor<R>(rt_phase_sum(ph, w[12], w[13], tid), &fr, &fi);
+            if (kind == kRtFactor || (sizeof(R) == 4 && kind == kRtBlock)) {
+                if constexpr (sizeof(R) == 4)
+                    rt_phases<true>(ph, w[12], w[13], tid | w[14] << kRtRegBit, &bl.gr, &bl.gi);
+                else
+                    rt_phases<false>(ph, w[12], w[13], tid, &fr, &fi);
             } else if (kind == kRtExch) {
                 next = rt_xor_terms(rt_fresh(tid), o.t);
             } else if (kind == kRtPrep) {
                 rt_prep<R, NB>(lds, base, w, pats, mems);
                 lanes = 0;
+            }
+        }
+        if constexpr (sizeof(R) == 4) {
+            if (kind == kRtBlock) {
+                SV_RT_FOR(NB, b) { rt_phases<true>(ph, o.t[b], o.t[8 + b], tid, &bl.ur[b], &bl.ui[b]); });
+            } else {
+                SV_RT_FOR(NB, b) { rt_unset(bl.ur[b], bl.ui[b]); });
             }
         }
         uint32_t sa = buf + slot, na = buf + next;
@@ -278,6 +311,8 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
                 const bool one = (tid & w[4]) != 0 || (base & ob) != 0;
                 take(w[13], (one ? m.ai : m.ar) * ((g[0] + g[1]) - (g[2] + g[3])));
             }
+        } else if constexpr (sizeof(R) == 4) {
+            rt_apply(v, w, m, lanes, buf, sa, na, bl);
         } else {
             rt_apply(v, w, m, fr, fi, lanes, buf, sa, na);
         }

@@ -65,12 +65,12 @@ namespace sv {
 #define RT_STEP_SWAP_f32(i, j)                                                                                     \
     "v_swap_b32 " RT_N(x, i) ", " RT_N(x, j) "\n"                                                                  \
     "v_swap_b32 " RT_N(y, i) ", " RT_N(y, j) "\n"
-// one register times the lane's factor
-#define RT_STEP_MUL(SZ, i)                                                                                         \
-    "v_mul_" SZ " %[t0], %[fi], " RT_N(y, i) "\n"                                                                  \
-    "v_mul_" SZ " %[t1], %[fi], " RT_N(x, i) "\n"                                                                  \
-    "v_fma_" SZ " " RT_N(x, i) ", %[fr], " RT_N(x, i) ", -%[t0]\n"                                                 \
-    "v_fma_" SZ " " RT_N(y, i) ", %[fr], " RT_N(y, i) ", %[t1]\n"
+// one register times a factor
+#define RT_STEP_MUL(SZ, i, fr, fi)                                                                                 \
+    "v_mul_" SZ " %[t0], %[" #fi "], " RT_N(y, i) "\n"                                                             \
+    "v_mul_" SZ " %[t1], %[" #fi "], " RT_N(x, i) "\n"                                                             \
+    "v_fma_" SZ " " RT_N(x, i) ", %[" #fr "], " RT_N(x, i) ", -%[t0]\n"                                            \
+    "v_fma_" SZ " " RT_N(y, i) ", %[" #fr "], " RT_N(y, i) ", %[t1]\n"
 
 // one register times its own factor, read from the table at byte address ta
 // (two components of SB bytes each)
@@ -106,8 +106,8 @@ namespace sv {
 #define RT_GEN_f32(i, j) RT_STEP_GEN("f32", i, j)
 #define RT_SWAP_f64(i, j) RT_STEP_SWAP_f64(i, j)
 #define RT_SWAP_f32(i, j) RT_STEP_SWAP_f32(i, j)
-#define RT_MUL_f64(i) RT_STEP_MUL("f64", i)
-#define RT_MUL_f32(i) RT_STEP_MUL("f32", i)
+#define RT_MUL_f64(i) RT_STEP_MUL("f64", i, fr, fi)
+#define RT_MUL_f32(i) RT_STEP_MUL("f32", i, t2, t3)
 
 // Step of pair p = (i, j), skipped where the mask's bit is clear.
 #define RT_PAIR(OP, V, p, i, j)                                                                                    \
@@ -229,26 +229,89 @@ namespace sv {
     RT_MEET G(RT_WX_##SZ, RT_FW) RT_MEET G(RT_RX_##SZ, RT_FD) RT_MEET GR(RT_WY_##SZ, RT_FW)                        \
     RT_MEET GR(RT_RY_##SZ, RT_FD) "s_waitcnt lgkmcnt(0)\n"
 
-#define RT_TAB_f64(i, o0, o1) RT_STEP_TAB("f64", "ds_read_b64", i, o0, o1)
-#define RT_TAB_f32(i, o0, o1) RT_STEP_TAB("f32", "ds_read_b32", i, o0, o1)
+#define RT_TABLED_f64(i, o0, o1) RT_STEP_TAB("f64", "ds_read_b64", i, o0, o1)
 #define RT_TABLE3_f64                                                                                              \
-    RT_TAB_f64(0, 0, 8) RT_TAB_f64(1, 16, 24) RT_TAB_f64(2, 32, 40) RT_TAB_f64(3, 48, 56)                          \
-    RT_TAB_f64(4, 64, 72) RT_TAB_f64(5, 80, 88) RT_TAB_f64(6, 96, 104) RT_TAB_f64(7, 112, 120)
+    RT_TABLED_f64(0, 0, 8) RT_TABLED_f64(1, 16, 24) RT_TABLED_f64(2, 32, 40) RT_TABLED_f64(3, 48, 56)                          \
+    RT_TABLED_f64(4, 64, 72) RT_TABLED_f64(5, 80, 88) RT_TABLED_f64(6, 96, 104) RT_TABLED_f64(7, 112, 120)
 #define RT_TABLE4_f64                                                                                              \
     RT_TABLE3_f64                                                                                                  \
-    RT_TAB_f64(8, 128, 136) RT_TAB_f64(9, 144, 152) RT_TAB_f64(10, 160, 168) RT_TAB_f64(11, 176, 184)              \
-    RT_TAB_f64(12, 192, 200) RT_TAB_f64(13, 208, 216) RT_TAB_f64(14, 224, 232) RT_TAB_f64(15, 240, 248)
-#define RT_TABLE4_f32                                                                                              \
-    RT_TAB_f32(0, 0, 4) RT_TAB_f32(1, 8, 12) RT_TAB_f32(2, 16, 20) RT_TAB_f32(3, 24, 28)                           \
-    RT_TAB_f32(4, 32, 36) RT_TAB_f32(5, 40, 44) RT_TAB_f32(6, 48, 52) RT_TAB_f32(7, 56, 60)                        \
-    RT_TAB_f32(8, 64, 68) RT_TAB_f32(9, 72, 76) RT_TAB_f32(10, 80, 84) RT_TAB_f32(11, 88, 92)                      \
-    RT_TAB_f32(12, 96, 100) RT_TAB_f32(13, 104, 108) RT_TAB_f32(14, 112, 116) RT_TAB_f32(15, 120, 124)
-#define RT_TABLE5_f32                                                                                              \
-    RT_TABLE4_f32                                                                                                  \
-    RT_TAB_f32(16, 128, 132) RT_TAB_f32(17, 136, 140) RT_TAB_f32(18, 144, 148) RT_TAB_f32(19, 152, 156)            \
-    RT_TAB_f32(20, 160, 164) RT_TAB_f32(21, 168, 172) RT_TAB_f32(22, 176, 180) RT_TAB_f32(23, 184, 188)            \
-    RT_TAB_f32(24, 192, 196) RT_TAB_f32(25, 200, 204) RT_TAB_f32(26, 208, 212) RT_TAB_f32(27, 216, 220)            \
-    RT_TAB_f32(28, 224, 228) RT_TAB_f32(29, 232, 236) RT_TAB_f32(30, 240, 244) RT_TAB_f32(31, 248, 252)
+    RT_TABLED_f64(8, 128, 136) RT_TABLED_f64(9, 144, 152) RT_TABLED_f64(10, 160, 168) RT_TABLED_f64(11, 176, 184)              \
+    RT_TABLED_f64(12, 192, 200) RT_TABLED_f64(13, 208, 216) RT_TABLED_f64(14, 224, 232) RT_TABLED_f64(15, 240, 248)
+// A block of diagonal gates on complex64 registers.  A register's factor is
+// formed in double precision and rounded once, so a block costs an amplitude
+// the rounding of one factor and one product, however many phases it sums:
+// the factor of the lane (g, then h and g in turn), which follows the
+// registers in Gray-code order, one product with the factor (u<b>) of the
+// register bit that flips (U: it is set, V: cleared), times the register's own
+// from the table.  The product is rounded to single precision and multiplies
+// the register.
+#define RT_PHASES4(T, U, V)                                                                                            \
+    T(g, h, 0) U(g, h, 0) T(h, g, 1) U(h, g, 1) T(g, h, 3) V(g, h, 0) T(h, g, 2) U(h, g, 2) T(g, h, 6) U(g, h, 0)      \
+    T(h, g, 7) V(h, g, 1) T(g, h, 5) V(g, h, 0) T(h, g, 4) U(h, g, 3) T(g, h, 12) U(g, h, 0) T(h, g, 13) U(h, g, 1)    \
+    T(g, h, 15) V(g, h, 0) T(h, g, 14) V(h, g, 2) T(g, h, 10) U(g, h, 0) T(h, g, 11) V(h, g, 1) T(g, h, 9)             \
+    V(g, h, 0) T(h, g, 8)
+#define RT_PHASES5(T, U, V)                                                                                            \
+    T(g, h, 0) U(g, h, 0) T(h, g, 1) U(h, g, 1) T(g, h, 3) V(g, h, 0) T(h, g, 2) U(h, g, 2) T(g, h, 6) U(g, h, 0)      \
+    T(h, g, 7) V(h, g, 1) T(g, h, 5) V(g, h, 0) T(h, g, 4) U(h, g, 3) T(g, h, 12) U(g, h, 0) T(h, g, 13) U(h, g, 1)    \
+    T(g, h, 15) V(g, h, 0) T(h, g, 14) V(h, g, 2) T(g, h, 10) U(g, h, 0) T(h, g, 11) V(h, g, 1) T(g, h, 9)             \
+    V(g, h, 0) T(h, g, 8) U(h, g, 4) T(g, h, 24) U(g, h, 0) T(h, g, 25) U(h, g, 1) T(g, h, 27) V(g, h, 0)              \
+    T(h, g, 26) U(h, g, 2) T(g, h, 30) U(g, h, 0) T(h, g, 31) V(h, g, 1) T(g, h, 29) V(g, h, 0) T(h, g, 28)            \
+    V(h, g, 3) T(g, h, 20) U(g, h, 0) T(h, g, 21) U(h, g, 1) T(g, h, 23) V(g, h, 0) T(h, g, 22) V(h, g, 2)             \
+    T(g, h, 18) U(g, h, 0) T(h, g, 19) V(h, g, 1) T(g, h, 17) V(g, h, 0) T(h, g, 16)
+#define RT_PH_APPLY(p, i)                                                                                              \
+    "v_cvt_f32_f64 %[t2], %[" #p "r]\n"                                                                                \
+    "v_cvt_f32_f64 %[t3], %[" #p "i]\n" RT_MUL_f32(i)
+#define RT_PH_TABLED(g, h, i)                                                                                          \
+    "ds_read_b64 %[qr], %[ta] offset:16*" #i "\n"                                                                      \
+    "ds_read_b64 %[qi], %[ta] offset:16*" #i "+8\n"                                                                    \
+    "s_waitcnt lgkmcnt(0)\n"                                                                                           \
+    "v_mul_f64 %[" #h "r], %[" #g "i], %[qi]\n"                                                                        \
+    "v_mul_f64 %[" #h "i], %[" #g "i], %[qr]\n"                                                                        \
+    "v_fma_f64 %[qr], %[" #g "r], %[qr], -%[" #h "r]\n"                                                                \
+    "v_fma_f64 %[qi], %[" #g "r], %[qi], %[" #h "i]\n" RT_PH_APPLY(q, i)
+#define RT_PH_LANE(g_, h_, i) RT_PH_TABLED(g, h, i)
+#define RT_PH_PLAIN(g, h, i) RT_PH_APPLY(g, i)
+#define RT_PH_UP(g, h, b)                                                                                              \
+    "v_mul_f64 %[" #h "r], %[" #g "i], %[ui" #b "]\n"                                                                  \
+    "v_mul_f64 %[" #h "i], %[" #g "i], %[ur" #b "]\n"                                                                  \
+    "v_fma_f64 %[" #h "r], %[" #g "r], %[ur" #b "], -%[" #h "r]\n"                                                     \
+    "v_fma_f64 %[" #h "i], %[" #g "r], %[ui" #b "], %[" #h "i]\n"
+#define RT_PH_DOWN(g, h, b)                                                                                            \
+    "v_mul_f64 %[" #h "r], %[" #g "i], %[ui" #b "]\n"                                                                  \
+    "v_mul_f64 %[" #h "i], %[" #g "r], %[ui" #b "]\n"                                                                  \
+    "v_fma_f64 %[" #h "r], %[" #g "r], %[ur" #b "], %[" #h "r]\n"                                                      \
+    "v_fma_f64 %[" #h "i], %[" #g "i], %[ur" #b "], -%[" #h "i]\n"
+#define RT_PH_STAY(g, h, b)
+// Registers of a list times u<b> and the table's factor.
+#define RT_PH_BIT(b, i)                                                                                                \
+    "ds_read_b64 %[qr], %[ta] offset:16*" #i "\n"                                                                      \
+    "ds_read_b64 %[qi], %[ta] offset:16*" #i "+8\n"                                                                    \
+    "s_waitcnt lgkmcnt(0)\n"                                                                                           \
+    "v_mul_f64 %[hr], %[ui" #b "], %[qi]\n"                                                                            \
+    "v_mul_f64 %[hi], %[ui" #b "], %[qr]\n"                                                                            \
+    "v_fma_f64 %[qr], %[ur" #b "], %[qr], -%[hr]\n"                                                                    \
+    "v_fma_f64 %[qi], %[ur" #b "], %[qi], %[hi]\n" RT_PH_APPLY(q, i)
+// the second registers of the pairs of bit b
+#define RT_PH_SECOND(b, V, p, i, j) RT_PH_BIT(b, j)
+#define RT_PH_BITS4                                                                                                    \
+    RT_AT("po0") RT_PAIRS4_0(RT_PH_SECOND, 0, "") RT_END RT_AT("po1") RT_PAIRS4_1(RT_PH_SECOND, 1, "") RT_END          \
+    RT_AT("po2") RT_PAIRS4_2(RT_PH_SECOND, 2, "") RT_END RT_AT("po3") RT_PAIRS4_3(RT_PH_SECOND, 3, "") RT_END
+#define RT_PH_BITS5                                                                                                    \
+    RT_AT("po0") RT_PAIRS5_0(RT_PH_SECOND, 0, "") RT_END RT_AT("po1") RT_PAIRS5_1(RT_PH_SECOND, 1, "") RT_END          \
+    RT_AT("po2") RT_PAIRS5_2(RT_PH_SECOND, 2, "") RT_END RT_AT("po3") RT_PAIRS5_3(RT_PH_SECOND, 3, "") RT_END          \
+    RT_AT("po4") RT_PAIRS5_4(RT_PH_SECOND, 4, "") RT_END
+// lane's factor and table; register bits too; those without a table; one
+// register bit and table
+#define RT_ENTRIES_f32(B) RT_GO("pg") RT_GO("pn") RT_ENTRIES##B("po")
+#define RT_TAB_f32(B) RT_PHASES##B(RT_PH_LANE, RT_PH_STAY, RT_PH_STAY)
+#define RT_MORE_f32(B)                                                                                                 \
+    RT_AT("pg") RT_PHASES##B(RT_PH_TABLED, RT_PH_UP, RT_PH_DOWN) RT_END                                                \
+    RT_AT("pn") RT_PHASES##B(RT_PH_PLAIN, RT_PH_UP, RT_PH_DOWN) RT_END RT_PH_BITS##B
+#define RT_FACTOR_f32 "v_cvt_f32_f64 %[t2], %[gr]\nv_cvt_f32_f64 %[t3], %[gi]\n"
+#define RT_FACTOR_f64
+#define RT_ENTRIES_f64(B)
+#define RT_TAB_f64(B) RT_TABLE##B##_f64
+#define RT_MORE_f64(B)
 
 // The lanes' condition, then a jump into the branch table that follows, whose
 // entry k (4 k bytes into it) is the branch to a variant; %[jo] = rt_jump(k)
@@ -280,7 +343,7 @@ namespace sv {
     RT_AT(K "2") RT_PAIRS5_2(P, OP, K "2") RT_END RT_AT(K "3") RT_PAIRS5_3(P, OP, K "3") RT_END                    \
     RT_AT(K "4") RT_PAIRS5_4(P, OP, K "4") RT_END
 // every variant: entry kind * 8 + register bit of the pair kinds, again with
-// every pair from kRtEntryFull on, then the rest
+// every pair from kRtEntryFull on, then the rest (RT_ENTRIES_f32: complex64's own)
 #define RT_HEAD(B)                                                                                                 \
     RT_DISPATCH RT_ENTRIES##B("r") RT_ENTRIES##B("c") RT_ENTRIES##B("g") RT_ENTRIES##B("s")                        \
     RT_ENTRIES##B("rf") RT_ENTRIES##B("cf") RT_ENTRIES##B("gf") RT_ENTRIES##B("sf") RT_GO("mul") RT_GO("tab") RT_GO("ex")
@@ -293,10 +356,10 @@ namespace sv {
     RT_KIND##B(RT_FULL, RT_CROSS_##SZ, "cf")                                                                       \
     RT_KIND##B(RT_FULL, RT_GEN_##SZ, "gf")                                                                         \
     RT_KIND##B(RT_FULL, RT_SWAP_##SZ, "sf")                                                                        \
-    RT_AT("tab") RT_TABLE##B##_##SZ RT_END RT_AT("ex") RT_EXCH(RT_GRAY##B, RT_GRAY##B##R, SZ) RT_END
+    RT_AT("tab") RT_TAB_##SZ(B) RT_END RT_AT("ex") RT_EXCH(RT_GRAY##B, RT_GRAY##B##R, SZ) RT_END
 #define RT_TAIL(B, SZ)                                                                                             \
-    RT_AT("mul") RT_REGS##B(RT_MUL_##SZ) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
-#define RT_BLOCK(B, SZ) RT_HEAD(B) RT_BODY(B, SZ) RT_TAIL(B, SZ)
+    RT_AT("mul") RT_FACTOR_##SZ RT_REGS##B(RT_MUL_##SZ) RT_AT("end") "s_mov_b64 exec, %[sv]\n"
+#define RT_BLOCK(B, SZ) RT_HEAD(B) RT_ENTRIES_##SZ(B) RT_BODY(B, SZ) RT_MORE_##SZ(B) RT_TAIL(B, SZ)
 // the same with the gradient terms
 #define RT_BLOCK_GRAD_f64                                                                                          \
     RT_HEAD(4) RT_GO("gd") RT_NONE RT_NONE RT_NONE RT_NONE                                                         \
@@ -323,9 +386,10 @@ namespace sv {
 
 #define RT_OPERANDS                                                                                                \
     [ar] "s"(m.ar), [ai] "s"(m.ai), [br] "s"(m.br), [bi] "s"(m.bi), [cr] "s"(m.cr), [ci] "s"(m.ci), [dr] "s"(m.dr), \
-        [di] "s"(m.di), [fr] "v"(fr), [fi] "v"(fi), [pm] "s"(w[1]), [lm] "s"(lanes), [jo] "s"(w[5]),               \
+        [di] "s"(m.di), [pm] "s"(w[1]), [lm] "s"(lanes), [jo] "s"(w[5]),                                           \
         [ta] "v"(table), [w0] "s"(w[2]), [w1] "s"(w[3]), [w2] "s"(w[4]), [w3] "s"(w[6]), [d0] "s"(w[8]),           \
         [d1] "s"(w[9]), [d2] "s"(w[10]), [d3] "s"(w[11])
+#define RT_FACTOR_IN [fr] "v"(fr), [fi] "v"(fi)
 #define RT_SCRATCH                                                                                                 \
     [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3), [sv] "=&s"(save), [sa] "+v"(slot),             \
         [na] "+v"(next)
@@ -335,15 +399,23 @@ template <typename R, int NB> struct RtRegs {
     R x[1 << NB], y[1 << NB];
 };
 
-constexpr uint32_t kRtEntryFull = 32, kRtEntryMul = 64, kRtEntryTab = 65, kRtEntryExch = 66,
-                   kRtEntryGradD = 67, kRtEntryGradY = 72, kRtEntryGradX = 80;
+// Factors of a block of diagonal gates (kRtBlock): the lane's, and the one an
+// amplitude takes with each register bit that is set.
+template <int NB> struct RtPhases {
+    double gr, gi, ur[NB], ui[NB];
+};
+
+constexpr uint32_t kRtEntryFull = 32, kRtEntryMul = 64, kRtEntryTab = 65, kRtEntryExch = 66;
+constexpr uint32_t kRtEntryGradD = 67, kRtEntryGradY = 72, kRtEntryGradX = 80;  // reverse sweep
+constexpr uint32_t kRtEntryBits = 67, kRtEntryBitsOnly = 68, kRtEntryOneBit = 69;  // complex64, kRtBlock
 constexpr uint32_t rt_jump(uint32_t entry) { return 4 * entry + 12; }
 
 // One operation in the lanes of `lanes` (uniform).  w: the operation's first
 // 16 words: w[1] the pairs or registers, w[5] rt_jump(entry); an exchange has
 // the register terms of the old layout in w[2], w[3], w[4], w[6], w[7] and of
 // the new one in w[8] .. w[12].  m: the matrix; fr, fi: the lane's factor
-// (entry kRtEntryMul); table: byte address in LDS (kRtEntryTab); slot, next:
+// (entry kRtEntryMul); table: byte address in LDS (kRtEntryTab); ph: factors
+// (kRtBlock); slot, next:
 // the lane's byte address in the exchange buffer in the old and new layout.
 // All lanes of the workgroup call together, with every load of LDS done.
 __device__ __forceinline__ void rt_apply(RtRegs<double, 4> &v, const uint32_t (&w)[16], const Mat2<double> &m,
@@ -351,15 +423,21 @@ __device__ __forceinline__ void rt_apply(RtRegs<double, 4> &v, const uint32_t (&
                                          uint32_t &next) {
     double t0, t1, t2, t3;
     uint64_t save;
-    asm volatile(RT_BLOCK(4, f64) : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+    asm volatile(RT_BLOCK(4, f64) : RT_AMPS16, RT_SCRATCH : RT_OPERANDS, RT_FACTOR_IN : "scc", "vcc", "memory");
 }
-__device__ __forceinline__ void rt_apply(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m, float fr,
-                                         float fi, uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next) {
+#define RT_PHASE_OUT                                                                                                   \
+    [gr] "+v"(ph.gr), [gi] "+v"(ph.gi), [hr] "=&v"(hr), [hi] "=&v"(hi), [qr] "=&v"(qr), [qi] "=&v"(qi)
+#define RT_UNIT(b) [ur##b] "v"(ph.ur[b]), [ui##b] "v"(ph.ui[b])
+#define RT_PHASE_IN RT_UNIT(0), RT_UNIT(1), RT_UNIT(2), RT_UNIT(3)
+__device__ __forceinline__ void rt_apply(RtRegs<float, 5> &v, const uint32_t (&w)[16], const Mat2<float> &m,
+                                         uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next,
+                                         RtPhases<5> &ph) {
     float t0, t1, t2, t3;
+    double hr, hi, qr, qi;
     uint64_t save;
     asm volatile(RT_BLOCK(5, f32)
-                 : RT_AMPS32, RT_SCRATCH
-                 : RT_OPERANDS, [w4] "s"(w[7]), [d4] "s"(w[12])
+                 : RT_AMPS32, RT_SCRATCH, RT_PHASE_OUT
+                 : RT_OPERANDS, RT_PHASE_IN, RT_UNIT(4), [w4] "s"(w[7]), [d4] "s"(w[12])
                  : "scc", "vcc", "memory");
 }
 
@@ -369,13 +447,18 @@ __device__ __forceinline__ void rt_apply(RtRegs<double, 3> &v, const uint32_t (&
                                          uint32_t &next) {
     double t0, t1, t2, t3;
     uint64_t save;
-    asm volatile(RT_BLOCK(3, f64) : RT_AMPS8, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+    asm volatile(RT_BLOCK(3, f64) : RT_AMPS8, RT_SCRATCH : RT_OPERANDS, RT_FACTOR_IN : "scc", "vcc", "memory");
 }
-__device__ __forceinline__ void rt_apply(RtRegs<float, 4> &v, const uint32_t (&w)[16], const Mat2<float> &m, float fr,
-                                         float fi, uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next) {
+__device__ __forceinline__ void rt_apply(RtRegs<float, 4> &v, const uint32_t (&w)[16], const Mat2<float> &m,
+                                         uint64_t lanes, uint32_t table, uint32_t &slot, uint32_t &next,
+                                         RtPhases<4> &ph) {
     float t0, t1, t2, t3;
+    double hr, hi, qr, qi;
     uint64_t save;
-    asm volatile(RT_BLOCK(4, f32) : RT_AMPS16, RT_SCRATCH : RT_OPERANDS : "scc", "vcc", "memory");
+    asm volatile(RT_BLOCK(4, f32)
+                 : RT_AMPS16, RT_SCRATCH, RT_PHASE_OUT
+                 : RT_OPERANDS, RT_PHASE_IN
+                 : "scc", "vcc", "memory");
 }
 
 // The same on a lane's amplitudes of psi (registers with the top bit 0) and
@@ -389,7 +472,7 @@ __device__ __forceinline__ void rt_apply_grad(RtRegs<double, 4> &v, const uint32
     uint64_t save;
     asm volatile(RT_BLOCK_GRAD_f64
                  : RT_AMPS16, RT_SCRATCH, RT_GRAD_OUT
-                 : RT_OPERANDS, [pm2] "s"(w[12])
+                 : RT_OPERANDS, RT_FACTOR_IN, [pm2] "s"(w[12])
                  : "scc", "vcc", "memory");
 }
 

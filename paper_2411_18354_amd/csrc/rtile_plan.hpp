@@ -41,6 +41,7 @@ constexpr uint32_t kRtTable = 6;   // registers times the prepared table's facto
 constexpr uint32_t kRtExch = 7;    // to another layout
 constexpr uint32_t kRtPrep = 8;    // phases of a block of diagonal gates in this tile
 constexpr uint32_t kRtGrad = 9;    // gradient term of a parameterised gate (reverse sweep)
+constexpr uint32_t kRtBlock = 10;  // complex64 tiles: registers times the prepared block's factors
 
 struct RtOp {
     uint32_t w[16];
@@ -48,7 +49,10 @@ struct RtOp {
     //  gates: w[2] w[3] condition on the thread index (mask, value), w[4] thread bit of a diagonal
     //    gate's target, w[6] w[7] and w[8] w[9] condition on the tile's base index (low and high
     //    words), w[10] w[11] base-index bit of a diagonal gate's target
-    //  kRtFactor: w[12] first and w[13] number of its patterns
+    //  kRtFactor: w[12] first and w[13] number of its patterns, w[14] the register number they
+    //    are asked about beside the thread index
+    //  kRtBlock: w[12] first and w[13] number of the patterns of thread bits alone; t[k] first and
+    //    t[8 + k] number of those of register bit k and thread bits
     //  kRtPrep: w[1] patterns, w[2] first pattern, w[3] first and w[4] number of the R patterns
     //  kRtExch: register terms as rt_apply takes them
     //  kRtGrad: as a gate; w[12] the registers subtracted (diagonal gates), w[13] its accumulator;
@@ -64,12 +68,16 @@ static_assert(sizeof(RtOp) == 128, "descriptor layout");
 
 // A phase pattern in a layout: the sum of its members' phases (those whose
 // outer predicate holds) is added where (index & cm) == cv, the index being
-// the register number for R patterns and the thread index otherwise.  A
+// the register number for R patterns and the thread index (the register
+// number above it, from kRtRegBit on) otherwise.  A
 // pattern with more than kRtPatMembers members is split, so that the lanes
-// share the members of a long one; one preparation holds at most kRtMaxPats.
-constexpr uint32_t kRtPatMembers = 4, kRtMaxPats = 1024;
+// share the members of a long one; one preparation holds at most kRtMaxPats
+// (twice that where kRtBlock lists a pattern once more with its sign changed,
+// which still fits the smallest exchange buffer of batches, 32 KiB).
+constexpr uint32_t kRtPatMembers = 4, kRtMaxPats = 1000, kRtPatNegative = 1u << 31;
+constexpr int kRtRegBit = 16;
 struct RtPat {
-    uint32_t cm, cv, first, count;
+    uint32_t cm, cv, first, count;  // count: | kRtPatNegative to subtract the phases
 };
 
 // Where a layout's amplitudes live in global memory: the qubits of its
@@ -129,10 +137,12 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag)
 // and 1 in registers and 2..5 on the lowest lane bits instead.
 // nb: register bits (rt_pass_nb, or rt_nb_of).  dual: the reverse sweep's passes.
 // fixed_mask: outer index bits every launched tile has with the required
-// values.
+// values.  *slow: a complex64 block that sums its phases once for each set of
+// registers (LDS tiles take no longer: 60 phases under up to three controls,
+// n = 24: 611 against 731 us, 200 of them 1080 against 917, n = 12 72 against 49).
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *tiles, int count,
                      RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
-                     RtProgram &prog);
+                     RtProgram &prog, bool *slow);
 
 // One pass over a complex128 or complex64 state.
 int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,

@@ -18,3 +18,60 @@ def test_expectation_sums_by_pairs(gpu):
         psi = torch.full((1 << n,), complex(a), dtype=torch.complex128, device="cuda")
         got = float(gpu.sv_expect(psi, gpu.pauli_terms([W.PauliTerm(1.0, 0, 0)]))[0])
         assert got == (1 << n) * (a * a), a
+
+
+def _phases(n, count, controls, seed):
+    """Diagonal gates on every qubit in turn, each under `controls` controls of
+    either value, and the phase they give every basis state."""
+    rng = np.random.default_rng(seed)
+    k = np.arange(1 << n)
+    gates, phase = [], np.zeros(1 << n)
+    for i in range(count):
+        kind, t, theta = ("P", "RZ", "P")[i % 3], i % n, float(rng.uniform(-np.pi, np.pi))
+        nc = int(rng.integers(0, controls + 1))
+        ctrls = tuple(int(q) for q in rng.choice([q for q in range(n) if q != t], size=nc, replace=False))
+        vals = tuple(int(v) for v in rng.integers(0, 2, size=nc))
+        gates.append(W.Gate(kind, t, ctrls, vals, theta))
+        on = np.ones(1 << n, dtype=bool)
+        for c, v in zip(ctrls, vals):
+            on &= ((k >> c) & 1) == v
+        bit = (k >> t) & 1
+        phase += np.where(on, theta * bit if kind == "P" else theta * (bit - 0.5), 0.0)
+    return W.Circuit(n, gates), phase
+
+
+@pytest.mark.parametrize("m", [11, 12, 13, 14])
+@pytest.mark.parametrize("extra", [0, 9])
+@pytest.mark.parametrize("controls", [0, 1, 3])
+def test_complex64_phase_block_rounds_once(gpu, m, extra, controls):
+    """However many diagonal gates a block has, an amplitude a of a complex64
+    state is multiplied by one factor f: with u = 2^-24, each part of f is off
+    by u / 2 at most (|f| <= 1: sqrt(2)/2 u |a| in all), a part of the product
+    by u (|f_i a_i| + |result|), which is at most 2 u |a| for both; the factor
+    itself is formed in double, to 1e-7 u.  One tile per workgroup and more
+    tiles than CUs (other numbers of amplitudes per lane), no controls, one,
+    and up to three."""
+    if m + extra > 21:
+        extra = 21 - m
+    n = m + extra
+    gpu.sv_tune_set("tile_log2_c64", m)
+    c, phase = _phases(n, 4 * n, controls, 10 * m + controls)
+    psi = torch.tensor(W.random_state(n, m), device="cuda").to(torch.complex64)
+    a = psi.cpu().numpy().astype(np.complex128)
+    gpu.Circuit(n, c, dtype=gpu.SV_C64).run(psi)
+    err = np.abs(psi.cpu().numpy() - a * np.exp(1j * phase))
+    assert (err <= 2.75 * 2.0 ** -24 * np.abs(a)).all(), (err / np.abs(a)).max() * 2.0 ** 24
+
+
+@pytest.mark.parametrize("controls", [0, 1, 3])
+def test_complex64_phase_block_rounds_once_in_batches(gpu, controls):
+    """The same bound for batched circuits, whose tiles are loaded by
+    workgroups of one size: states of a part of a tile, one, and many."""
+    ns = [8, 10, 13, 14, 16]
+    made = [_phases(n, 4 * n, controls, n + controls) for n in ns]
+    psis = [torch.tensor(W.random_state(n, n), device="cuda").to(torch.complex64) for n in ns]
+    starts = [p.cpu().numpy().astype(np.complex128) for p in psis]
+    gpu.sv_apply_circuits_batched(psis, [c for c, _ in made])
+    for n, (_, phase), psi, a in zip(ns, made, psis, starts):
+        err = np.abs(psi.cpu().numpy() - a * np.exp(1j * phase))
+        assert (err <= 2.75 * 2.0 ** -24 * np.abs(a)).all(), (n, (err / np.abs(a)).max() * 2.0 ** 24)
