@@ -212,6 +212,10 @@ int sv_hbm_probe(const sv_state_t *s, uint64_t fixed_mask, uint64_t fixed_vals, 
  *       of a fused run as one permutation of the tile
  *   "batch_split"     [1, 64]  most workgroups a batched circuit may be split
  *       over (read when a batch is planned; 1: one workgroup per circuit)
+ *   "batch_wait_ms"   [0, 600000]  a workgroup of a split circuit gives up
+ *       waiting for others once no chunk of the circuit has been completed for
+ *       this long and the time its largest chunk may take (read when a batch
+ *       is planned; 0: at once)
  *   "phase_sweep_min_c128", "phase_sweep_min_c64" [1, 64]  a fused run's
  *       diagonal block with at least this many gates reading tile-local bits
  *       is one sweep adding phases; the gates of shorter blocks run as pair
@@ -479,7 +483,9 @@ int sv_apply_circuits_batched(const sv_state_t *states, int ncirc, const sv_gate
  * grad_dev[param_offsets[c] + j] receives dL_c/dtheta_j and loss_dev[c] the
  * loss.  Circuits are split over workgroups as in the forward run; partial
  * sums are added in a fixed order, so a batch gives the same gradients on
- * every run (the grouping of the sums depends on the batch's circuits).
+ * every run (the grouping of the sums depends on the batch's circuits).  Where
+ * a wait between workgroups gives up ("batch_wait_ms"), which only a device
+ * stalled from outside brings about, that circuit's loss and gradients are NaN.
  * n <= 31 per circuit. */
 int sv_adjoint_grad_batched(const sv_state_t *psi_states, const sv_state_t *lam_states, int ncirc,
                             const sv_gate_t *gates, const int64_t *gate_offsets, const double *params_dev,
@@ -525,7 +531,7 @@ int sv_batch_set_timing(sv_batch_t *b, uint64_t *stamps_dev, double *ns_per_tick
  * number (ncirc plus one more per extra workgroup a split circuit may take),
  * item_circuit (host, may be NULL, cap >= nitems entries) the circuit of
  * each item in queue order.  wait_timeouts (may be NULL) receives the number
- * of chunk waits of split circuits that gave up (after 10 s; the run's
+ * of chunk waits of split circuits that gave up ("batch_wait_ms"; the run's
  * results are then undefined) over all runs so far: it waits for b's last
  * run.  SV_EINVAL when cap is too small. */
 int sv_batch_info(sv_batch_t *b, int64_t *nitems, int32_t *item_circuit, int64_t cap, uint64_t *wait_timeouts);

@@ -199,6 +199,10 @@ __device__ __forceinline__ void gate_on_block(cplx_t<R> *base, int nbits, int ta
         gate_on_block_i<R, uint64_t, THREADS>(base, nbits, target, cmask, cvals, mm, lo, hi);
 }
 
+// A split circuit's words: the next ticket, the chunks completed, and whether
+// a wait has given up.
+constexpr int kGroupWords = 3;
+
 // Device tables of a run.
 struct BatchTables {
     const BCirc *circs;
@@ -210,9 +214,9 @@ struct BatchTables {
     const SweepPat *lpats;  // LDS tiles: phase patterns
     const SweepMember *mems;
     const double *params;
-    unsigned int *gstate;  // split circuits: ticket counters
-    uint64_t limit;        // clock ticks a chunk wait may take
-    unsigned int *err;     // counts waits that took longer
+    unsigned int *gstate;  // split circuits: kGroupWords each
+    uint64_t limit;        // clock ticks a wait may see no chunk completed
+    unsigned int *err;     // counts waits that did
     double *part;          // adjoint: partial sums
 };
 // The adjoint's others.
@@ -446,7 +450,8 @@ __device__ __forceinline__ double sweep_gate(int n, const BGate &g, const double
 template <typename R, int THREADS>
 __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass &p, const BGate *gates,
                                          const double *params, double *parts, SweepTables d, unsigned char *buf,
-                                         double *scratch, uint64_t lo, uint64_t hi, int chunk) {
+                                         double *scratch, uint64_t lo, uint64_t hi, int chunk,
+                                         const unsigned int *gave_up) {
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     cplx_t<R> *lam = reinterpret_cast<cplx_t<R> *>(c.lam);
     const uint64_t N = 1ull << c.n;
@@ -509,6 +514,9 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
             lam[tid] = tl[tid];
         }
     } else {  // kPassSums: over the chunks, then over the gates that share a parameter
+        // (NaN where a wait has given up: partial sums of half-written states
+        // look like any others)
+        const bool undefined = gave_up && __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (int s = tid; s < c.nslots; s += THREADS) {
             const BSlot a = d.slots[c.first_slot + s];
             double *q = parts + a.first;
@@ -525,6 +533,7 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
 #pragma unroll 4
             for (int s = s0; s < s1; ++s)
                 sum += parts[d.slots[c.first_slot + s].first];
+            sum = undefined ? __builtin_nan("") : sum;
             if (j < c.nparams)
                 d.grad[c.first_param + j] = sum;
             else
@@ -535,22 +544,28 @@ __device__ __forceinline__ void sweep_other(const BCirc &c, int ci, const BPass 
     }
 }
 
-// Wait (lane 0 polling, the workgroup held at a barrier) until *ctr >= target,
-// then make other workgroups' writes visible to this one.  The wait is
-// bounded: after `limit` clock ticks it gives up and counts a timeout in
-// *err (the results of that run are then undefined).
-__device__ __forceinline__ void wait_count(unsigned int *ctr, unsigned int target, uint64_t limit,
+// Wait (lane 0 polling, the workgroup held at a barrier) until the circuit's
+// completed chunks are at least target, then make other workgroups' writes
+// visible to this one.  The wait is bounded: once no chunk has completed for
+// `limit` clock ticks it gives up, counts that in *err and marks the circuit
+// (the results of that run are then undefined), before the workgroup counts
+// any chunk it goes on to compute.
+__device__ __forceinline__ void wait_count(unsigned int *done, unsigned int target, uint64_t limit,
                                            unsigned int *err) {
     if (threadIdx.x == 0) {
-        if (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            const uint64_t t0 = wall_clock64();
-            do {
-                __builtin_amdgcn_s_sleep(2);
-                if (wall_clock64() - t0 > limit) {
-                    atomicAdd(err, 1u);
-                    break;
-                }
-            } while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target);
+        unsigned int seen = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t t0 = seen < target ? wall_clock64() : 0;
+        while (seen < target) {
+            __builtin_amdgcn_s_sleep(2);
+            const unsigned int now = __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (now != seen) {
+                seen = now;
+                t0 = wall_clock64();
+            } else if (wall_clock64() - t0 > limit) {
+                atomicAdd(err, 1u);
+                __hip_atomic_store(done + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the CU's and the XCD's caches refetch
     }
@@ -577,7 +592,7 @@ __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const 
     cplx_t<R> *psi = reinterpret_cast<cplx_t<R> *>(c.psi);
     const BPass *passes = d.passes + c.first_pass;
     const bool split = c.group >= 0;  // uniform
-    unsigned int *next = d.gstate + 2 * c.group, *done = next + 1;
+    unsigned int *next = d.gstate + kGroupWords * c.group, *done = next + 1;
     int pi = 0, ready = -1;
     for (;;) {
         uint64_t lo = 0, hi = ~0ull;
@@ -614,7 +629,8 @@ __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const 
             else
                 fused_tiles<R>(psi, p, d, buf, lo, end);
         } else if constexpr (ADJ) {
-            sweep_other<R, batch_threads(LDS)>(c, ci, p, d.gates, d.params, d.part, a, buf, scratch, lo, hi, chunk);
+            sweep_other<R, batch_threads(LDS)>(c, ci, p, d.gates, d.params, d.part, a, buf, scratch, lo, hi, chunk,
+                                               split ? done + 1 : nullptr);
         } else {
             const BGate &g = d.gates[c.first_gate + p.gate];
             gate_on_block<R, batch_threads(LDS)>(psi, c.n, g.target, g.cmask, g.cvals,
@@ -969,15 +985,19 @@ struct BatchHost {
     std::vector<int32_t> order;    // work items in queue order (each a circuit), then helpers'
     int nlisted = 0;               // the former
     int ngroups = 0;               // circuits split over workgroups
+    double chunk_work = 0.0;       // amplitudes times gates (or terms) of the largest chunk
     std::vector<double> gens;
     std::vector<int32_t> gen_of;
     std::vector<DTerm> terms;
 };
 
-// A chunk wait gives up after this long.  A chunk takes far less (its tiles
-// or pair steps are bounded), so only a workgroup stalled from outside (the
-// device preempted, a fault elsewhere) can reach it.
-constexpr uint64_t kWaitLimitSeconds = 10;
+// A chunk wait gives up once no chunk of its circuit has completed for the
+// "batch_wait_ms" knob and the time the largest chunk can take at kSlowestRate
+// amplitudes times gates (terms) a second.  (A workgroup reaches 1e9 to 1e10;
+// a chunk's gates and Hamiltonian terms have no bound, so it may take long.)
+// Only a workgroup stalled from outside, the device preempted or a fault
+// elsewhere, can take longer than both.
+constexpr double kSlowestRate = 1e8;
 
 // A circuit that costs more than the batch's mean load per workgroup is
 // split into that many workgroups' worth of work items (rounded; at most the
@@ -1060,6 +1080,11 @@ static void split_circuits(BatchHost *h, int dtype, bool adjoint, const std::vec
             p.nchunks = (int32_t)((total + len - 1) / len);
             p.chunk_len = len;
             k += p.nchunks;
+            const double amps = (double)std::min(len, total);
+            const double work = p.kind == kPassTiles   ? std::ldexp(amps, (int)p.tm.m) * std::max<double>(p.count, p.rt.count)
+                                : p.kind == kPassPauli ? amps * bc.nterms
+                                                       : 2.0 * amps;
+            h->chunk_work = std::max(h->chunk_work, work);
         }
         bc.group = h->ngroups++;
         bc.nchunks = (int32_t)k;  // at most npasses * 4 * 64
@@ -1286,8 +1311,7 @@ struct BatchDevice {
     double *gens = nullptr;
     DTerm *terms = nullptr;
     unsigned int *queue = nullptr;
-    // split circuits: two ticket counters each, then the count of waits
-    // that timed out
+    // split circuits: kGroupWords each, then the count of waits that gave up
     unsigned int *gstate = nullptr;
     int ngroups = 0;
     uint64_t wait_limit = 0;  // clock ticks
@@ -1320,7 +1344,7 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     tb.add(&d->gens, h.gens);
     tb.add(&d->terms, h.terms);
     tb.add((void **)&d->queue, nullptr, sizeof(unsigned int));
-    const int words = h.ngroups > 0 ? 2 * h.ngroups + 1 : 0;
+    const int words = h.ngroups > 0 ? kGroupWords * h.ngroups + 1 : 0;
     tb.add((void **)&d->gstate, nullptr, words * sizeof(unsigned int));
     tb.add((void **)&d->part, nullptr, (size_t)h.npart * sizeof(double));
     int r = tb.upload(&d->block, async, st);
@@ -1339,7 +1363,8 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
                            hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess ||
                            khz <= 0))
             r = fail(SV_EHIP, "device reports no constant-rate clock");
-        d->wait_limit = (uint64_t)khz * 1000ull * kWaitLimitSeconds;
+        const int ms = tuning().batch_wait_ms;  // 0: give up at once
+        d->wait_limit = ms ? (uint64_t)((double)khz * (ms + 1e3 * h.chunk_work / kSlowestRate)) : 0;
     }
     if (r != SV_OK)
         batch_release(d, async, st);
@@ -1361,16 +1386,16 @@ static int launch_batch(int dtype, const BatchDevice &d, const double *params, d
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.njobs + 255) / 256), dim3(256), 0, s, d.jobs, d.njobs, params,
                            d.tiles, d.lds && grad ? nullptr : d.mems, d.lds ? nullptr : d.ops, dtype == SV_C64 ? 1 : 0);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
-    if (d.ngroups > 0)  // the ticket counters, not the timeout count after them
-        hipLaunchKernelGGL(k_zero_words, dim3((2 * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,
-                           2 * d.ngroups);
+    if (d.ngroups > 0)  // not the count of waits after them
+        hipLaunchKernelGGL(k_zero_words, dim3((kGroupWords * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,
+                           kGroupWords * d.ngroups);
     const SweepTables a{d.terms, d.gens, d.gen_of, d.tslot, d.slots, d.csr, grad, loss, stamps};
     auto go = [&](auto fn) -> int {
         if (lds > 65536)
             SV_HIP_TRY(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(fn, dim3(grid), dim3(batch_threads(d.lds)), lds, s, d.circs, d.order, d.nitems, d.nlisted, d.gates, d.passes,
                            d.tiles, d.ops, d.pats, d.lpats, d.mems, params, d.queue, d.gstate, d.wait_limit,
-                           d.gstate ? d.gstate + 2 * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes);
+                           d.gstate ? d.gstate + kGroupWords * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes);
         SV_LAUNCH_CHECK();
         return SV_OK;
     };
@@ -1505,7 +1530,7 @@ int sv_batch_info(sv_batch_t *b, int64_t *nitems, int32_t *item_circuit, int64_t
                 if (b->done)
                     SV_HIP_TRY(hipEventSynchronize(b->done));
                 unsigned int v = 0;
-                SV_HIP_TRY(hipMemcpy(&v, d->gstate + 2 * d->ngroups, sizeof(v), hipMemcpyDeviceToHost));
+                SV_HIP_TRY(hipMemcpy(&v, d->gstate + kGroupWords * d->ngroups, sizeof(v), hipMemcpyDeviceToHost));
                 *wait_timeouts += v;
             }
     }
