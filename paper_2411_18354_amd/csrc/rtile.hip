@@ -106,15 +106,32 @@ struct Deferred {
     }
 };
 
-// Pair gates a segment with the register bits of rmask would take.
-int taken(const std::vector<Unit> &units, uint32_t rmask) {
+// Units a segment's register bits are chosen by, and at most deferred from one
+// segment to the next: on a state of one tile a run is the whole circuit, and
+// looking through all of it for every segment took 10 s for 64,000 gates.
+constexpr size_t kSegmentWindow = 1024;
+
+// The bits that pair gates among the units mix.
+uint32_t pair_bits(const std::vector<Unit> &units) {
+    uint32_t b = 0;
+    for (const Unit &u : units)
+        b |= u.nd;
+    return b;
+}
+
+// Pair gates a segment with the register bits of rmask would take; bits:
+// pair_bits (once all of them are deferred, no further pair gate is free).
+int taken(const std::vector<Unit> &units, uint32_t rmask, uint32_t bits) {
     Deferred d;
     int n = 0;
     for (const Unit &u : units) {
-        if (d.free(u) && (u.diag || ((rmask >> u.bit) & 1u)))
+        if (d.free(u) && (u.diag || ((rmask >> u.bit) & 1u))) {
             n += u.diag ? 0 : 1;
-        else
+        } else {
             d.add(u);
+            if (!(bits & ~d.nd))
+                break;
+        }
     }
     return n;
 }
@@ -124,14 +141,15 @@ int taken(const std::vector<Unit> &units, uint32_t rmask) {
 // fixed bits are kept.  Bits left over go to the highest allowed positions,
 // so a layout kept for the store leaves the low bits to the lanes.
 uint32_t choose_regs(const std::vector<Unit> &units, int m, int nb, uint32_t fixed, uint32_t allowed) {
+    const uint32_t bits = pair_bits(units);
     uint32_t r = fixed;
-    int cur = taken(units, r);
+    int cur = taken(units, r, bits);
     while (__builtin_popcount(r) < nb) {
         int best = -1, best_n = cur;
         for (int q = 0; q < m; ++q) {
             if (!((allowed >> q) & 1u) || ((r >> q) & 1u))
                 continue;
-            const int n = taken(units, r | (1u << q));
+            const int n = taken(units, r | (1u << q), bits);
             if (n > best_n) {
                 best_n = n;
                 best = q;
@@ -576,31 +594,44 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
     const uint32_t io_fixed = block ? 3u : 0u;
     const uint32_t io_allowed = all & ~(block ? 63u : (1u << std::min(coal, m - nr)) - 1u);
     auto io_ok = [&](uint32_t r) { return (r & io_fixed) == io_fixed && !(r & ~(io_allowed | io_fixed)); };
-    uint32_t r = choose_regs(units, m, nr, io_fixed, io_allowed);
+    std::vector<Unit> open;  // the next units of the window, deferred ones first
+    size_t ahead = 0;        // the first unit beyond it
+    auto fill = [&]() {
+        while (open.size() < kSegmentWindow && ahead < units.size())
+            open.push_back(units[ahead++]);
+    };
+    fill();
+    uint32_t r = choose_regs(open, m, nr, io_fixed, io_allowed);
     Layout cur = make_layout(m, r, block);
     pass.in = make_io(tm, cur, comp, dual ? m + 1 : m);
     bool exch = false;
     while (true) {
         Deferred d;
         std::vector<Unit> rest;
-        for (const Unit &u : units) {
+        auto take = [&](const Unit &u) {
             if (d.free(u) && (u.diag || ((r >> u.bit) & 1u))) {
                 emit(u, cur);
             } else {
                 d.add(u);
                 rest.push_back(u);
             }
-        }
-        units.swap(rest);
-        if (units.empty())
+        };
+        for (const Unit &u : open)
+            take(u);
+        while (rest.size() < kSegmentWindow && ahead < units.size())
+            take(units[ahead++]);
+        open.swap(rest);
+        fill();
+        if (open.empty())
             break;
-        r = choose_regs(units, m, nr, 0u, all);
+        r = choose_regs(open, m, nr, 0u, all);
         // a last segment takes register bits a store layout may have, if they do
-        const int npair = (int)std::count_if(units.begin(), units.end(), [](const Unit &u) { return !u.diag; });
-        bool last = taken(units, r) == npair;
+        const int npair = (int)std::count_if(open.begin(), open.end(), [](const Unit &u) { return !u.diag; });
+        const uint32_t bits = pair_bits(open);
+        bool last = ahead == units.size() && taken(open, r, bits) == npair;
         if (last) {
-            const uint32_t rs = choose_regs(units, m, nr, io_fixed, io_allowed);
-            last = taken(units, rs) == npair;
+            const uint32_t rs = choose_regs(open, m, nr, io_fixed, io_allowed);
+            last = taken(open, rs, bits) == npair;
             if (last)
                 r = rs;
         }
