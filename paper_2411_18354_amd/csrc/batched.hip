@@ -54,6 +54,7 @@ constexpr size_t kBatchExchange = 32768;
 // are given in double.
 constexpr int kLdsThreads = 512;
 __host__ __device__ constexpr int batch_threads(bool lds) { return lds ? kLdsThreads : kBatchThreads; }
+// One-shot batches of states that all fit there run on the same kernel.
 constexpr int kLdsTileBits = 13;  // 64 KiB of complex64: the tile, or a resident state
 constexpr size_t kLdsBytes = 65536 + sizeof(double) * diag_table_doubles(kLdsTileBits);
 // amplitudes per lane in flight when a tile pair is written back (tiles are
@@ -293,7 +294,14 @@ __device__ __forceinline__ void lds_tiles(cplx_t<R> *psi, const BPass &p, const 
 // against 53 and 70, n=8 89 and 119 against 56 and 74, n=9 101 and 143 against
 // 59 and 75; complex64 n=6 71 and 92 against 74 and 95, n=8 90 and 120 against
 // 66 and 91, n=10 112 and 160 against 70 and 92.
-__host__ __device__ constexpr int resident_below(bool dbl) { return dbl ? 5 : 7; }
+// A plan costs the host about 1.5 us a gate on one thread, though, where a
+// resident state needs none: 400 circuits of 8 to 12 qubits and 150 gates take
+// 0.16 ms on register tiles and 0.25 in LDS, and their plan 7 ms on 16 threads.
+// So kept batches plan them, which about a hundred runs earn back, and one-shot
+// batches, which would plan at every call (9.0 ms instead of 1.2), do not: on
+// the LDS kernel where every state fits it, else up to the exchange buffer's
+// 32 KiB.
+constexpr int resident_below(bool dbl, bool once) { return once ? (dbl ? 12 : 13) : dbl ? 5 : 7; }
 
 template <typename R, int THREADS>
 __device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsigned char *buf) {
@@ -680,15 +688,16 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
                 rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
 }
 
-// ADJ: the adjoint gradients, else the forward run.  LDS: on LDS tiles.  tail: LDS bytes before
-// the work-item slot.
+// ADJ: the adjoint gradients, else the forward run.  LDS: on LDS tiles.  tail:
+// LDS bytes before the work-item slot.  resident: states of fewer qubits are
+// held in LDS, gate by gate.
 template <typename R, bool ADJ, bool LDS>
 __global__ __launch_bounds__(batch_threads(LDS), 4) void k_batched(
     const BCirc *__restrict__ circs, const int32_t *__restrict__ items, int nitems, int nlisted,
     const BGate *__restrict__ gates, const BPass *__restrict__ passes, const TileGate *__restrict__ tiles, const RtOp *__restrict__ ops,
     const RtPat *__restrict__ pats, const SweepPat *__restrict__ lpats, const SweepMember *__restrict__ mems,
     const double *__restrict__ params, unsigned int *__restrict__ queue, unsigned int *gstate, uint64_t limit, unsigned int *err,
-    uint64_t *__restrict__ stamps, double *part, SweepTables a, uint32_t tail) {
+    uint64_t *__restrict__ stamps, double *part, SweepTables a, uint32_t tail, int resident) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     // the exchange buffer first: its addresses step by xor
     unsigned char *buf = lds_raw;
@@ -706,7 +715,7 @@ __global__ __launch_bounds__(batch_threads(LDS), 4) void k_batched(
             break;
         const uint64_t t0 = !ADJ && stamps ? wall_clock64() : 0;
         const int ci = items[it];  // one that is split appears once per workgroup that may join it
-        if (!ADJ && circs[ci].n < (LDS ? kLdsTileBits + 1 : resident_below(sizeof(R) == 8)))  // uniform
+        if (!ADJ && circs[ci].n < resident)  // uniform
             run_circuit_resident<R, batch_threads(LDS)>(circs[ci], d, buf);
         else
             run_circuit<R, ADJ, LDS>(ci, d, a, buf, scratch, ticket);
@@ -738,6 +747,7 @@ struct CircBuild {
     PlanRt rt;                     // register tile operations (circuit-local)
     std::vector<SweepMember> mems; // members of their phase patterns
     bool lds = false;              // LDS tiles
+    int resident = 0;              // forward: states of fewer qubits have no plan
     std::vector<SweepPat> lpats;   // their phase patterns
     std::vector<int32_t> tslot;    // adjoint: gradient slot of every tile descriptor, or -1
     std::vector<BTileJob> jobs;    // tile and operation indices circuit-local
@@ -764,6 +774,7 @@ struct BatchArgs {
     int64_t nparams_total;
     const sv_pauli_t *terms;
     const int64_t *term_off;
+    bool once = false;  // run once: planning has to pay at once
 };
 
 // The fused plan of one circuit's gates (those of the reverse sweep when
@@ -923,7 +934,7 @@ static int build_circuit(const BatchArgs &A, int c, int dtype, bool adjoint, Cir
     }
     if (adjoint)
         SV_TRY(build_sweep(A, c, dtype, m_cap, out));
-    else if (bc.ngates > 0 && s.n >= (out->lds ? kLdsTileBits + 1 : resident_below(dtype == SV_C128)))
+    else if (bc.ngates > 0 && s.n >= out->resident)
         SV_TRY(plan_passes(s.n, dtype, A.gates + g0, bc.ngates, (int)(p1 - p0), (int32_t)p0, m_cap, out));
     bc.npasses = (int32_t)out->passes.size();
     double work = 0.0;
@@ -974,6 +985,7 @@ struct BatchHost {
     std::vector<TileGate> tiles;
     RtProgram prog;
     bool lds = false;              // LDS tiles
+    int resident = 0;
     std::vector<SweepPat> lpats;
     std::vector<int32_t> tslot;
     std::vector<SweepMember> mems;
@@ -1156,12 +1168,18 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
     if (total_gates > INT32_MAX)
         return fail(SV_EINVAL, "batch holds %lld gates (at most 2^31 - 1)", (long long)total_gates);
     std::vector<CircBuild> cb(A.ncirc);
-    h->lds = *dtype == SV_C64 && A.lams;
+    int widest = 0;
+    for (int c = 0; c < A.ncirc; ++c)
+        widest = std::max(widest, (int)A.states[c].n);
+    const int lds_bits = kLdsTileBits - (*dtype == SV_C128 ? 1 : 0);
+    h->lds = (*dtype == SV_C64 && A.lams) || (A.once && !adjoint && widest <= lds_bits);
+    h->resident = h->lds ? lds_bits + 1 : resident_below(*dtype == SV_C128, A.once);
     h->lds_bytes = h->lds ? (adjoint ? 0 : kLdsBytes) : kBatchExchange;
     auto work = [&](int lo, int hi) {
         for (int c = lo; c < hi; ++c) {
             CircBuild &b = cb[c];
             b.lds = h->lds;
+            b.resident = h->resident;
             b.err = build_circuit(A, c, *dtype, adjoint, &b);
             if (b.err != SV_OK) {
                 b.msg = sv_last_error();  // error text is per thread
@@ -1300,6 +1318,7 @@ struct BatchDevice {
     BTileJob *jobs = nullptr;
     int njobs = 0;
     bool lds = false;
+    int resident = 0;
     SweepPat *lpats = nullptr;
     int32_t *tslot = nullptr;
     BSlot *slots = nullptr;
@@ -1350,6 +1369,7 @@ static int upload_batch(const BatchHost &h, bool async, hipStream_t st, BatchDev
     int r = tb.upload(&d->block, async, st);
     d->njobs = (int)h.jobs.size();
     d->lds = h.lds;
+    d->resident = h.resident;
     d->lds_bytes = h.lds_bytes;
     d->nitems = (int)h.order.size();
     d->nlisted = h.nlisted;
@@ -1395,12 +1415,15 @@ static int launch_batch(int dtype, const BatchDevice &d, const double *params, d
             SV_HIP_TRY(hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(fn, dim3(grid), dim3(batch_threads(d.lds)), lds, s, d.circs, d.order, d.nitems, d.nlisted, d.gates, d.passes,
                            d.tiles, d.ops, d.pats, d.lpats, d.mems, params, d.queue, d.gstate, d.wait_limit,
-                           d.gstate ? d.gstate + kGroupWords * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes);
+                           d.gstate ? d.gstate + kGroupWords * d.ngroups : nullptr, stamps, d.part, a, (uint32_t)d.lds_bytes,
+                           d.resident);
         SV_LAUNCH_CHECK();
         return SV_OK;
     };
     if (dtype == SV_C128)
-        return grad ? go(k_batched<double, true, false>) : go(k_batched<double, false, false>);
+        return grad    ? go(k_batched<double, true, false>)
+               : d.lds ? go(k_batched<double, false, true>)
+                       : go(k_batched<double, false, false>);
     if (d.lds)
         return grad ? go(k_batched<float, true, true>) : go(k_batched<float, false, true>);
     return go(k_batched<float, false, false>);  // gradients: LDS tiles
@@ -1555,7 +1578,7 @@ int sv_apply_circuits_batched(const sv_state_t *states, int ncirc, const sv_gate
                               const double *params_dev, const int64_t *param_offsets, int64_t nparams_total,
                               sv_stream_t st) {
     clear_error();
-    BatchArgs A{states, nullptr, ncirc, gates, gate_offsets, param_offsets, nparams_total, nullptr, nullptr};
+    BatchArgs A{states, nullptr, ncirc, gates, gate_offsets, param_offsets, nparams_total, nullptr, nullptr, true};
     BatchHost h;
     int dtype = 0;
     SV_TRY(build_batch(A, false, &h, &dtype));
@@ -1577,7 +1600,7 @@ int sv_adjoint_grad_batched(const sv_state_t *psi_states, const sv_state_t *lam_
     if (!lam_states || !grad_dev || !loss_dev || !param_offsets)
         return fail(SV_EINVAL, "batched adjoint needs lambda states, param offsets, grad_dev and loss_dev");
     BatchArgs A{psi_states, lam_states, ncirc, gates, gate_offsets, param_offsets, nparams_total, terms,
-                term_offsets};
+                term_offsets, true};
     BatchHost h;
     int dtype = 0;
     SV_TRY(build_batch(A, true, &h, &dtype));

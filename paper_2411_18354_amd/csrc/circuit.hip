@@ -350,7 +350,10 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
             deferred.clear();
             high.clear();
             const int depth = std::min(tuning().plan_lookahead, c->max_lookahead);
-            if (depth > 0)
+            if (m == c->n)  // the tile is the state: nothing to choose
+                for (int q = a; q < m; ++q)
+                    high.push_back(q);
+            else if (depth > 0)
                 high = choose_high(stream, pos, depth);
             size_t i = pos;
             for (; i < stream.size(); ++i) {

@@ -46,3 +46,13 @@ def test_long_circuits_on_one_tile(n):
     looks through the whole run)."""
     short, long = [_plan_seconds([W.random_gates_n12(seed=n, n=n, ngates=g)]) for g in (4000, 32000)]
     assert long <= 24 * short, (short, long)
+
+
+def test_one_shot_batches_of_small_states_need_no_plan():
+    """States that fit a workgroup's LDS run gate by gate when the batch runs
+    once: a plan as kept batches have costs several times their whole call."""
+    circs = [W.random_gates_n12(seed=i, n=8 + i % 5, ngates=150) for i in range(400)]
+    states, gates, offsets, params = _arguments(circs)
+    once = _seconds(lambda: sv._L.sv_apply_circuits_batched(states, len(circs), gates, offsets, None, params, 0, None))
+    kept = _plan_seconds(circs)
+    assert once <= 0.5 * kept, (once, kept)

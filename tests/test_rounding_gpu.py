@@ -65,13 +65,15 @@ def test_complex64_phase_block_rounds_once(gpu, m, extra, controls):
 
 @pytest.mark.parametrize("controls", [0, 1, 3])
 def test_complex64_phase_block_rounds_once_in_batches(gpu, controls):
-    """The same bound for batched circuits, whose tiles are loaded by
-    workgroups of one size: states of a part of a tile, one, and many."""
+    """The same bound for planned batches, whose tiles are loaded by workgroups
+    of one size: states of a part of a tile, one, and many."""
     ns = [8, 10, 13, 14, 16]
     made = [_phases(n, 4 * n, controls, n + controls) for n in ns]
     psis = [torch.tensor(W.random_state(n, n), device="cuda").to(torch.complex64) for n in ns]
     starts = [p.cpu().numpy().astype(np.complex128) for p in psis]
-    gpu.sv_apply_circuits_batched(psis, [c for c, _ in made])
+    batch = gpu.Batch(psis, [c for c, _ in made])
+    batch.run()
+    batch.close()
     for n, (_, phase), psi, a in zip(ns, made, psis, starts):
         err = np.abs(psi.cpu().numpy() - a * np.exp(1j * phase))
         assert (err <= 2.75 * 2.0 ** -24 * np.abs(a)).all(), (n, (err / np.abs(a)).max() * 2.0 ** 24)
