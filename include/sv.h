@@ -452,10 +452,15 @@ int sv_adjoint_destroy(sv_adjoint_t *plan);
  * Many independent circuits, each on its own state (n may differ; one dtype
  * per batch), run by one persistent launch: each workgroup takes the next
  * work item from a device work queue (longest first) and applies all its
- * gates; a state below 5 qubits (complex64: 7) stays in LDS for the whole
- * circuit, a larger one runs its fused plan pass by pass (a fused run through
- * register tiles over the run's qubit set, other gates as pair loops over the
- * state).  A circuit that costs more than the batch's mean load per workgroup
+ * gates.  A small state stays in LDS for the whole circuit; a larger one runs
+ * its fused plan pass by pass (a fused run through tiles over the run's qubit
+ * set, other gates as pair loops over the state).  Planned batches: states from
+ * 5 qubits (complex64: 7) on run through register tiles; complex64 batches with
+ * a parameterised gate or with lambda states through LDS tiles, from 14 qubits
+ * on.  One-shot calls plan from 13 qubits (complex64: 14) on, or, where some
+ * state is that wide and tiles are in registers, from 12 (13) on.  These choices,
+ * as fusion choices do, change the order in which commuting operations are
+ * rounded.  A circuit that costs more than the batch's mean load per workgroup
  * is split over about cost / mean workgroups (at most the "batch_split"
  * knob): its passes are cut into chunks of whole tiles or pair-loop steps
  * that the workgroups joining it take in order, a pass's chunks starting once

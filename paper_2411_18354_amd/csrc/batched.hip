@@ -47,11 +47,12 @@ constexpr int kBatchThreads = 256, kBatchThreadBits = 8;
 constexpr unsigned kBatchPerCu = 4;
 constexpr size_t kBatchSlot = 128;  // reduction scratch, work item and ticket
 constexpr size_t kBatchExchange = 32768;
-// Complex64 batches that take gradients keep LDS tiles, 512 lanes: a tile's
-// gates in program order, one rounding per gate and amplitude.  Register tiles
-// reorder commuting gates and share diagonal factors, which moves a complex64
-// state by single-precision rounding, and with it losses and gradients, which
-// are given in double.
+// Complex64 batches with angles, or lambda states to take gradients with, keep
+// LDS tiles, 512 lanes, as a parameterised complex64 circuit alone does: a
+// tile's gates in program order, one rounding per gate and amplitude.  Register
+// tiles reorder commuting gates, which moves a complex64 state by
+// single-precision rounding, and with it expectation values and gradients,
+// which are given in double.
 constexpr int kLdsThreads = 512;
 __host__ __device__ constexpr int batch_threads(bool lds) { return lds ? kLdsThreads : kBatchThreads; }
 // One-shot batches of states that all fit there run on the same kernel.
@@ -1172,7 +1173,9 @@ static int build_batch(const BatchArgs &A, bool adjoint, BatchHost *h, int *dtyp
     for (int c = 0; c < A.ncirc; ++c)
         widest = std::max(widest, (int)A.states[c].n);
     const int lds_bits = kLdsTileBits - (*dtype == SV_C128 ? 1 : 0);
-    h->lds = (*dtype == SV_C64 && A.lams) || (A.once && !adjoint && widest <= lds_bits);
+    const bool angles = A.gates && std::any_of(A.gates, A.gates + A.gate_off[A.ncirc],
+                                               [](const sv_gate_t &g) { return g.param >= 0; });
+    h->lds = (*dtype == SV_C64 && (A.lams || angles)) || (A.once && !adjoint && widest <= lds_bits);
     h->resident = h->lds ? lds_bits + 1 : resident_below(*dtype == SV_C128, A.once);
     h->lds_bytes = h->lds ? (adjoint ? 0 : kLdsBytes) : kBatchExchange;
     auto work = [&](int lo, int hi) {

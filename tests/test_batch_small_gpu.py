@@ -49,3 +49,28 @@ def test_small_states(gpu, dtype, ns):
     for n, ref, a, b in zip(ns, refs, once, kept):
         for got in (a, b):
             assert np.abs(got.cpu().numpy() - ref).max() <= TOL[dtype] * np.abs(ref).max(), n
+
+
+@pytest.mark.parametrize("once", [False, True])
+def test_complex64_angles_round_alike_with_and_without_gradients(gpu, once):
+    """A parameterised complex64 batch gives the same bits whether or not it
+    has lambda states to take gradients with."""
+    ns = [9, 13, 14, 15]
+    circs = [_circuit(n, 90, 30 + n) for n in ns]
+    for c in circs:  # unitary gates only
+        c.gates[:] = [g for g in c.gates if g.kind[-1] != "U"]
+    params = torch.tensor(np.concatenate([c.params for c in circs]), device="cuda")
+    start = [torch.tensor(W.random_state(n, n), device="cuda").to(torch.complex64) for n in ns]
+    plain, both = [s.clone() for s in start], [s.clone() for s in start]
+    if once:
+        gpu.sv_apply_circuits_batched(plain, circs, params)
+    else:
+        batch = gpu.Batch(plain, circs)
+        batch.run(params)
+        batch.close()
+    batch = gpu.Batch(both, circs, lam_states=[torch.empty_like(s) for s in start],
+                      hamiltonians=[W.zz_x_hamiltonian(n, n) for n in ns])
+    batch.run(params)
+    batch.close()
+    for a, b in zip(plain, both):
+        assert torch.equal(torch.view_as_real(a), torch.view_as_real(b))
