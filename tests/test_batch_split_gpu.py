@@ -164,3 +164,65 @@ def test_helpers_leave_bits_alone(gpu, dtype):
     assert len(items1) == len(circs) and sorted(set(items)) == list(range(len(circs)))
     for a, b in zip(out1, out):
         assert bool((a == b).all())
+
+
+def _cost(c):
+    """What a circuit's share of the workgroups goes by."""
+    return float(sum(2.0 ** (c.n - len(g.controls)) for g in c.gates))
+
+
+def _helped(circs, per_cu, widest_whole):
+    """Circuits cut for at least four workgroups that get one item: wider than
+    one tile, and between a half and one and a half of the mean load, so the
+    other three or more shares are helpers'."""
+    import torch
+    load = sum(map(_cost, circs)) / (per_cu * torch.cuda.get_device_properties(0).multi_processor_count)
+    return [i for i, c in enumerate(circs) if c.n >= widest_whole + 2 and 0.5 < _cost(c) / load < 1.5]
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_helpers_join_and_leave_bits_alone(gpu, dtype):
+    """About as many circuits as workgroups, each cut into chunks but listed
+    once: workgroups that are done help the others' passes.  The same bits as
+    with every circuit on one workgroup."""
+    n = 14 if dtype == "c128" else 15
+    circs = [W.random_gates_n12(seed=i, n=n, ngates=6 + i % 5) for i in range(900)]
+    helped = _helped(circs, 4, 12 if dtype == "c128" else 13)
+    assert len(helped) > 500
+    items, outs, _ = _run(gpu, circs, dtype, 64, [[np.zeros(0)] * len(circs)] * 2)
+    assert all(items.count(i) == 1 for i in helped[:50])
+    _, ref, _ = _run(gpu, circs, dtype, 1, [[np.zeros(0)] * len(circs)])
+    for o in outs:
+        assert bool((o == ref[0]).all())
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_helpers_in_the_reverse_sweep(gpu, dtype):
+    """The same for batched gradients: every state swept back to the same bits;
+    gradients are the same terms in other partial sums (at most 2^15 additions
+    of 53 bits)."""
+    import torch
+    n, ncirc = (13, 900) if dtype == "c128" else (14, 450)
+    circs = [W.hea(n, 1, seed=i) for i in range(ncirc)]
+    assert len(_helped(circs, 4 if dtype == "c128" else 2, 11 if dtype == "c128" else 12)) == ncirc
+    terms = W.zz_x_hamiltonian(n, 5)[::6]
+    td = torch.complex128 if dtype == "c128" else torch.complex64
+    params = torch.tensor(np.concatenate([c.params for c in circs]), device="cuda")
+    got = []
+    for split in (1, 64):
+        gpu.sv_tune_set("batch_split", split)
+        psi = torch.zeros(ncirc, 1 << n, dtype=td, device="cuda")
+        lam = torch.empty_like(psi)
+        psi[:, 0] = 1
+        b = gpu.Batch(list(psi), circs, lam_states=list(lam), hamiltonians=[terms] * ncirc)
+        try:
+            b.run(params)
+            grad, loss = b.adjoint(params)
+            got.append((grad.cpu().numpy(), loss.cpu().numpy(), psi))
+            assert b.wait_timeouts() == 0
+        finally:
+            b.close()
+    l1 = sum(abs(t.coef) for t in terms)
+    assert torch.equal(torch.view_as_real(got[0][2]), torch.view_as_real(got[1][2]))
+    assert np.abs(got[0][0] - got[1][0]).max() <= 2.0 ** -37 * l1
+    assert np.abs(got[0][1] - got[1][1]).max() <= 2.0 ** -37 * l1

@@ -237,3 +237,10 @@ def test_batched_gradients(gpu, dtype, m):
         tol = 1e-8 * max(1.0, np.abs(ref).max()) if dtype == "c128" else 2e-5 * l1 * uses
         assert np.abs(got[0][0][p] - ref).max() <= tol, c.n
         assert abs(got[0][1][i] - oracle.loss(c, c.params, h)) <= (1e-10 if dtype == "c128" else 2e-5 * l1)
+
+
+def test_default_complex64_tiles_with_full_lanes(gpu):
+    """Random gates on the default complex64 width, 2^13, with more tiles than
+    CUs: 256 lanes of 32 amplitudes each, where up to 256 tiles have 512 of 16."""
+    gpu.sv_tune_set("tile_log2_c64", 13)
+    _check(gpu, _random_circuit(22, 60, 1322), "c64")
