@@ -338,10 +338,10 @@ __device__ void run_circuit_resident(const BCirc &c, const BatchTables &d, unsig
 // 160 of 15 qubits (two layers) 1.88 -> 1.30 ms, 4 of 15 (four) 3.27 -> 0.62 ms,
 // 4 of 8 0.25 -> 0.13 ms.
 
-// Tiles [lo, hi) of a fused reverse pass.
-template <typename R>
-__device__ __forceinline__ void sweep_tiles(cplx_t<R> *psi, cplx_t<R> *lam, const BPass &p, const BatchTables &d,
+// Tiles [lo, hi) of a fused reverse pass (complex128).
+__device__ __forceinline__ void sweep_tiles(double2 *psi, double2 *lam, const BPass &p, const BatchTables &d,
                                             unsigned char *lds, uint64_t lo, uint64_t hi, int chunk) {
+    using R = double;
     constexpr int NB = rt_nb<R>(), H = 1 << (NB - 1), NW = kBatchThreads / 64;
     const DeviceGates dg{d.tiles + p.first, p.count};
     const int tb = (int)p.tm.m - NB + 1;
@@ -632,7 +632,7 @@ __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const 
             if constexpr (ADJ && LDS)
                 lds_sweep_tiles<R>(psi, reinterpret_cast<cplx_t<R> *>(c.lam), p, d, a, buf, lo, end, chunk);
             else if constexpr (ADJ)
-                sweep_tiles<R>(psi, reinterpret_cast<cplx_t<R> *>(c.lam), p, d, buf, lo, end, chunk);
+                sweep_tiles(psi, reinterpret_cast<double2 *>(c.lam), p, d, buf, lo, end, chunk);
             else if constexpr (LDS)
                 lds_tiles<R>(psi, p, d, buf, lo, end);
             else
@@ -667,7 +667,7 @@ __device__ __forceinline__ void run_circuit(int ci, const BatchTables &d, const 
 // descriptors (matrix, and phases of diagonal ones) and register operations.
 __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs, const double *__restrict__ params,
                                     TileGate *__restrict__ tiles, SweepMember *__restrict__ mems,
-                                    RtOp *__restrict__ ops, int ops_f32) {
+                                    RtOp *__restrict__ ops) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= njobs)
         return;
@@ -686,7 +686,7 @@ __global__ void k_batch_tile_params(const BTileJob *__restrict__ jobs, int njobs
     if (ops)
         for (int s = 0; s < 2; ++s)
             if (j.op[s] >= 0)
-                rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
+                rt_set_matrix(ops[j.op[s]], m);
 }
 
 // ADJ: the adjoint gradients, else the forward run.  LDS: on LDS tiles.  tail:
@@ -1407,7 +1407,7 @@ static int launch_batch(int dtype, const BatchDevice &d, const double *params, d
     const unsigned grid = std::min<unsigned>(cus * per_cu, (unsigned)d.nitems);
     if (d.njobs > 0)
         hipLaunchKernelGGL(k_batch_tile_params, dim3((d.njobs + 255) / 256), dim3(256), 0, s, d.jobs, d.njobs, params,
-                           d.tiles, d.lds && grad ? nullptr : d.mems, d.lds ? nullptr : d.ops, dtype == SV_C64 ? 1 : 0);
+                           d.tiles, d.lds && grad ? nullptr : d.mems, d.lds ? nullptr : d.ops);
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, d.queue);
     if (d.ngroups > 0)  // not the count of waits after them
         hipLaunchKernelGGL(k_zero_words, dim3((kGroupWords * d.ngroups + 255) / 256), dim3(256), 0, s, d.gstate,

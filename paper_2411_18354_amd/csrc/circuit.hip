@@ -23,7 +23,7 @@ namespace sv {
 
 __global__ void k_param_mats(const ParamJob *__restrict__ jobs, int njobs, const double *__restrict__ params,
                              double *__restrict__ mats, TileGate *__restrict__ tiles, SweepMember *__restrict__ mems,
-                             RtOp *__restrict__ ops, int ops_f32) {
+                             RtOp *__restrict__ ops) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= njobs)
         return;
@@ -45,7 +45,7 @@ __global__ void k_param_mats(const ParamJob *__restrict__ jobs, int njobs, const
     }
     for (int s = 0; s < 2; ++s)
         if (j.op[s] >= 0)
-            rt_set_matrix(ops[j.op[s]], ops_f32 != 0, m);
+            rt_set_matrix(ops[j.op[s]], m);
 }
 
 // Gates a and b commute when every qubit they share is, in each of them,
@@ -711,8 +711,7 @@ int circuit_create(int n, int dtype, const sv_gate_t *gates, int ngates, int npa
 int circuit_param_mats(sv_circuit *c, const double *params, hipStream_t st) {
     if (c->njobs > 0) {
         hipLaunchKernelGGL(k_param_mats, dim3((c->njobs + 127) / 128), dim3(128), 0, st, c->d_jobs, c->njobs,
-                           params, c->d_mats, c->d_tiles, c->d_mems, c->rt.ops,
-                           tile_dtype(c->dtype) == SV_C64 ? 1 : 0);
+                           params, c->d_mats, c->d_tiles, c->d_mems, c->rt.ops);
         SV_LAUNCH_CHECK();
     }
     return SV_OK;

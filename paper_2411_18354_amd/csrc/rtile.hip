@@ -741,14 +741,14 @@ int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, con
 // 24-qubit, 768-angle ansatz step 33.7 -> 19.2 ms, its sweep 28.5 -> 14.4 ms;
 // what bounds it now is FP64 arithmetic on two states (tiles of 2^11
 // amplitudes of each, four per CU).
-template <typename R>
-__global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(cplx_t<R> *__restrict__ psi, cplx_t<R> *__restrict__ lam,
+__global__ __launch_bounds__(kRtMaxThreads, 4) void k_radj(double2 *__restrict__ psi, double2 *__restrict__ lam,
                                                            TileMap tm, RtPass p, const RtOp *__restrict__ ops,
                                                            const RtPat *__restrict__ pats,
                                                            const SweepMember *__restrict__ mems,
                                                            const int32_t *__restrict__ acc, DeviceGates gates,
                                                            double *__restrict__ partials, int stride) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    using R = double;
     constexpr int NB = rt_nb<R>(), H = 1 << (NB - 1);
     double *accl = reinterpret_cast<double *>(lds + p.lds);
     const uint32_t nw = blockDim.x >> 6;
@@ -800,7 +800,7 @@ size_t rt_adjoint_lds(const TileMap &tm, const RtPass &p) {
 }
 
 int rt_adjoint_lds_limit(size_t lds) {
-    SV_HIP_TRY(hipFuncSetAttribute((const void *)k_radj<double>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    SV_HIP_TRY(hipFuncSetAttribute((const void *)k_radj, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     return SV_OK;
 }
 
@@ -808,7 +808,7 @@ int launch_rt_adjoint(void *psi, void *lam, const TileMap &tm, const RtPass &p, 
                       const DeviceGates &gates, unsigned grid, double *partials, int stride, hipStream_t st) {
     if (!rt_tile_ok(SV_C128, (int)tm.m, true))
         return fail(SV_EINVAL, "register tiles of 2^%u amplitudes", tm.m);
-    hipLaunchKernelGGL(k_radj<double>, dim3(grid), dim3(rt_adjoint_lanes(tm)), rt_adjoint_lds(tm, p), st,
+    hipLaunchKernelGGL(k_radj, dim3(grid), dim3(rt_adjoint_lanes(tm)), rt_adjoint_lds(tm, p), st,
                        (double2 *)psi, (double2 *)lam, tm, p, d.ops, d.pats, gates.mm, d.acc, gates, partials, stride);
     SV_LAUNCH_CHECK();
     return SV_OK;

@@ -49,14 +49,11 @@ template <int N, typename F> __device__ __forceinline__ void rt_for(const F &f) 
 }
 #define SV_RT_FOR(N, i) rt_for<(N)>([&](auto i) __attribute__((always_inline))
 
-// A matrix formed on the device into an operation.
-__device__ __forceinline__ void rt_set_matrix(RtOp &o, bool f32, const double *m) {
-    for (int k = 0; k < 8; ++k) {
-        if (f32)
-            o.f[k] = (float)m[k];
-        else
-            o.m[k] = m[k];
-    }
+// A matrix formed on the device into an operation (of complex128 tiles: a
+// parameterised complex64 circuit has none).
+__device__ __forceinline__ void rt_set_matrix(RtOp &o, const double *m) {
+    for (int k = 0; k < 8; ++k)
+        o.m[k] = m[k];
 }
 
 template <typename R> __device__ __forceinline__ Mat2<R> rt_mat(const RtOp &o) {

@@ -191,7 +191,6 @@ namespace sv {
 #define RT_BOTHS4(D)                                                                                               \
     RT_BOTH(D, 0, 8) RT_BOTH(D, 1, 9) RT_BOTH(D, 2, 10) RT_BOTH(D, 3, 11) RT_BOTH(D, 4, 12) RT_BOTH(D, 5, 13)      \
     RT_BOTH(D, 6, 14) RT_BOTH(D, 7, 15)
-// and among 16
 
 // The registers in Gray-code order, S a step and F(b) the flip of register bit
 // b between two; R: the same order backwards.

@@ -37,7 +37,7 @@ constexpr uint32_t kRtSwap = 3;    // X
 constexpr uint32_t kRtDiag = 4;    // registers times entry a of a diagonal gate, or entry d where the lane's
                                    // or the tile's target bit is 1 (number 1: d everywhere)
 constexpr uint32_t kRtFactor = 5;  // registers times a factor per lane, exp(i sum of phases)
-constexpr uint32_t kRtTable = 6;   // registers times the prepared table's factors
+constexpr uint32_t kRtTable = 6;   // registers times the prepared table's factors (complex128)
 constexpr uint32_t kRtExch = 7;    // to another layout
 constexpr uint32_t kRtPrep = 8;    // phases of a block of diagonal gates in this tile
 constexpr uint32_t kRtGrad = 9;    // gradient term of a parameterised gate (reverse sweep)
