@@ -15,6 +15,9 @@
  *    (C_k, C_{k+2^t}) with bit t of k clear to (a C_k + b C_{k+2^t},
  *    c C_k + d C_{k+2^t}) (pair-update equation, Sec. III).  Matrices are
  *    passed as 8 doubles: a.re a.im b.re b.im c.re c.im d.re d.im.
+ *    Amplitudes are finite numbers.  A NaN or an infinity reaches the
+ *    amplitudes that nonzero matrix entries carry it to; whether an entry that
+ *    is exactly 0 times an infinity gives NaN depends on the kernel.
  *  - Controls are qubit-indexed: bit q of ctrl_mask marks qubit q as a
  *    control and bit q of ctrl_vals is its required value (the paper uses
  *    value 1; value 0 is the negative control of its Sec. I figure).

@@ -6,14 +6,15 @@
 // start first) and runs it alone, so no barrier ever spans workgroups and
 // every workgroup leaves the loop once the queue is empty.
 //  - A circuit follows its fused plan (the same planner and register tiles as
-//    single circuits, rtile.hpp): a fused run visits the state tile by tile,
+//    single circuits, rtile.hpp; some complex64 batches LDS tiles, below): a
+//    fused run visits the state tile by tile,
 //    a tile being the 2^m amplitudes that share the index bits outside the
 //    run's qubit set S, held in the workgroup's registers while the run's
 //    operations act on it; other gates are pair loops over the state.  A
 //    workgroup barrier separates passes.  A state of at most one tile is read
 //    and written once per pass, mostly once in all.
-//  - The smallest states (below 5 qubits, complex64: 7) are read into LDS, all
-//    gates are applied there, and written back.
+//  - Small states (resident_below; on LDS tiles those of one tile) are read
+//    into LDS, all gates are applied there, and written back.
 // Each gate visits only the amplitude pairs whose controls hold: the pair
 // index is built by inserting the target bit (0) and the control bits (their
 // values) into the iteration counter, lowest position first (Sec. III-B).
@@ -41,8 +42,10 @@ int validate_unitary_gate(const sv_gate_t &g, int index);
 // Bound by the tiles' arithmetic once every workgroup has work; with LDS
 // tiles (two workgroups of 512 lanes per CU, two barriers per operation) the
 // LDS bound it.  512 circuits of widths 10-20, 100-400 gates, complex128:
-// 21.9 ms with LDS tiles, 11.5 ms; 300 of widths 10-18, complex64: 1.89 ms,
-// 1.23 ms; 400 of widths 8-12: 0.49 ms, 0.42 ms.
+// 21.9 ms with LDS tiles, 11.5 ms (10.0 with the split and helpers of today);
+// 300 of widths 10-18, 100-300 gates, complex64: 1.89 and 1.04 ms; 400 of
+// widths 8-12, 50-200 gates, gate by gate in LDS or on register tiles:
+// complex128 0.25 and 0.16 ms, complex64 0.23 and 0.20.
 constexpr int kBatchThreads = 256, kBatchThreadBits = 8;
 constexpr unsigned kBatchPerCu = 4;
 constexpr size_t kBatchSlot = 128;  // reduction scratch, work item and ticket

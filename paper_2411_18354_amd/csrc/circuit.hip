@@ -461,15 +461,24 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 // Register tiles wherever a tile has 64 to 512 lanes: below
                 // that a wavefront would be partly idle (the LDS tiles stay),
                 // and wider tiles do not exist.  A run that is one permutation
-                // is a single gather through an LDS tile; register tiles pay
-                // for each of its gates and lose on complex128 (streaming
-                // circuit, n = 12: 12.4 against 10.8 us, n = 26: 447 against
-                // 431 us; n = 16 to 22 even or faster) and where the other
-                // dtypes have few tiles (complex64 n = 13: 15.2 against 13.4
-                // us, n = 14: 17.8 against 15.5; n = 16: 21.2 against 21.9,
-                // n = 26: 232 against 255; 32-bit codes n = 16: 24.4 against
-                // 23.9, n = 20: 36.4 against 35.2; n = 22: 53.6 against 64.8,
-                // n = 27: 476 against 574).
+                // may be a single gather through an LDS tile, where register
+                // tiles pay for each of its gates.  Gather against register
+                // tiles, us, streaming circuit and 40 random CNOTs:
+                //   complex128  n = 12  11.9 and 13.2   19.3 and 23.2
+                //               n = 16  17.6 and 19.6   28.9 and 28.4
+                //               n = 22  41.1 and 35.9   73.9 and 58.6
+                //               n = 26  424 and 444     928 and 849
+                //   complex64   n = 13  13.8 and 16.0   23.5 and 25.8
+                //               n = 16  19.0 and 21.5   33.9 and 32.1
+                //               n = 26  241 and 233     738 and 422
+                //   32-bit      n = 16  20.5 and 22.2   28.7 and 29.9
+                //               n = 20  28.8 and 30.9   31.6 and 35.7
+                //               n = 22  43.1 and 39.3   78.3 and 69.1
+                //               n = 26  305 and 248     962 and 767
+                // complex128 keeps the gather at every size, as the streaming
+                // circuit loses without it at both ends (40 CNOTs would gain
+                // from 22 qubits on); complex64 up to 4 tiles, 32-bit codes up
+                // to kRtFewTiles.
                 bool gather = tuning().fuse_perm && !c->dual && !c->rt_nb &&
                               (c->dtype == SV_C128 || p.tm.ntiles <= (is_fixed(c->dtype) ? kRtFewTiles : 4)) &&
                               (1u << m) <= 512u * (tdt == SV_C128 ? perm_per_lane<double>() : perm_per_lane<float>());

@@ -530,12 +530,14 @@ __global__ __launch_bounds__(512, 4) void k_fix_tile(char *__restrict__ codes, i
 // against k_fix_tile (MI355X, 32-bit codes, n = 27): QFT 9.20 -> 4.16 ms, a
 // layer of H, RY, CNOT and MCX gates 4.35 -> 2.38 ms; a pass reads and writes
 // 2.2 GB, 0.33 ms, so the arithmetic inside the tile is the bound.
-// 16-bit codes keep k_fix_tile: a register tile applies commuting gates in
-// another order, which moves a value by a float rounding and about one code in
-// a thousand by one, and each later pass re-encodes and multiplies such
-// differences, to as much as the format's own error (6e-5 at n = 27) after
-// three.  (Their QFT would take 2.1 instead of 5.6 ms.)  With 31 bits the
-// same differences stay near 1e-9.
+// 16-bit codes keep k_fix_tile: a register tile as scheduled here applies
+// commuting gates in another order, which moves a value by a float rounding and
+// about one code in a thousand by one, and each later pass re-encodes and
+// multiplies such differences, to as much as the format's own error (6e-5 at
+// n = 27) after three.  (Their QFT, read out as complex64, would take 2.5
+// instead of 5.9 ms.  A schedule in program order, with LDS tiles' phase
+// arithmetic, would leave the codes alone; there is none yet.)  With 31 bits
+// the same differences stay near 1e-9.
 template <typename Q, int NB>
 __global__ __launch_bounds__(kRtMaxThreads, 4) void k_fix_rtile(char *__restrict__ codes,
                                                                 int8_t *__restrict__ scales, TileMap tm, RtPass p,

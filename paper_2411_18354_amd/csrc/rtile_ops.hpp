@@ -10,7 +10,8 @@
 // the lanes' condition.
 //
 // The rounding of each update is that of apply_pair (gate_math.hpp), products
-// with an entry known to be zero left out.
+// with an entry known to be zero left out (with finite amplitudes they change
+// nothing; an infinite one stays infinite where 0 times it would be NaN).
 #pragma once
 
 #include "gate_math.hpp"
