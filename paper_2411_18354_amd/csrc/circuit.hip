@@ -66,6 +66,21 @@ static bool commute(const sv_gate_t &a, const sv_gate_t &b) {
     return true;
 }
 
+// A set of gates as commute() sees it: their qubits, and the targets of those
+// that are not diagonal.  A gate commutes with each of them when neither its
+// own target (unless it is diagonal) nor one of theirs is shared.
+struct GateSet {
+    uint64_t qubits = 0, targets = 0;
+    void add(const sv_gate_t &g) {
+        qubits |= g.ctrl_mask | (1ull << g.target);
+        targets |= gate_kind_diagonal(g.kind) ? 0 : 1ull << g.target;
+    }
+    bool commutes(const sv_gate_t &g) const {
+        const uint64_t t = 1ull << g.target;
+        return !((g.ctrl_mask | t) & targets) && (gate_kind_diagonal(g.kind) || !(t & qubits));
+    }
+};
+
 int validate_unitary_gate(const sv_gate_t &g, int index) {
     if ((g.kind & ~SV_G_ADJOINT) != SV_G_MATRIX)
         return SV_OK;  // named kinds are unitary for every angle
@@ -258,24 +273,19 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
     // planner's scan below, with no qubits added on the way).
     auto run_size = [&](const std::vector<int> &stream, size_t pos, const std::vector<int> &high,
                         size_t window) -> int {
-        std::vector<int> deferred;
+        GateSet deferred;
+        size_t ndeferred = 0;
         int taken = 0;
         const size_t end = std::min(stream.size(), pos + window);
         for (size_t i = pos; i < end; ++i) {
             const sv_gate_t &g = c->gates[stream[i]];
             const bool fits = diag[stream[i]] || g.target < a ||
                               std::find(high.begin(), high.end(), g.target) != high.end();
-            bool free = true;
-            for (int d : deferred)
-                if (!commute(g, c->gates[d])) {
-                    free = false;
-                    break;
-                }
-            if (fits && free) {
+            if (fits && deferred.commutes(g)) {
                 ++taken;
             } else if (taken > 0) {
-                deferred.push_back(stream[i]);
-                if (deferred.size() > 256)
+                deferred.add(g);
+                if (++ndeferred > 256)
                     break;
             } else {
                 return 0;
@@ -349,6 +359,7 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
             run.clear();
             deferred.clear();
             high.clear();
+            GateSet behind;  // the deferred gates
             const int depth = std::min(tuning().plan_lookahead, c->max_lookahead);
             if (m == c->n)  // the tile is the state: nothing to choose
                 for (int q = a; q < m; ++q)
@@ -362,13 +373,7 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                 bool fits = diag[gi] || g.target < a ||
                             std::find(high.begin(), high.end(), g.target) != high.end();
                 const bool can_add_high = !fits && (int)high.size() < m - a;
-                bool free = true;
-                for (int d : deferred)
-                    if (!commute(g, c->gates[d])) {
-                        free = false;
-                        break;
-                    }
-                if ((fits || can_add_high) && free) {
+                if ((fits || can_add_high) && behind.commutes(g)) {
                     if (!fits)
                         high.push_back(g.target);
                     run.push_back(gi);
@@ -378,6 +383,7 @@ static int plan_circuit(sv_circuit *c, std::vector<TileGate> &tiles, std::vector
                     SV_TRY(single(gi));
                 } else {
                     deferred.push_back(gi);
+                    behind.add(g);
                     if (deferred.size() > 256) {
                         ++i;
                         break;
