@@ -241,8 +241,8 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *m, bool diag) {
 
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *t, int count,
                      RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
-                     RtProgram &prog, bool *slow) {
-    *slow = false;
+                     RtProgram &prog, double *slow) {
+    *slow = 0.0;
     // nr: register bits of the layouts; nb: with the bit telling psi and lambda apart
     const int m = (int)tm.m, nr = nb - (dual ? 1 : 0);
     RtPass pass;
@@ -369,7 +369,6 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
             }
         }
         if (!split) {
-            *slow = true;
             std::vector<Part> all(parts, parts + np);
             for (Part &a : all) {
                 a.p.cm |= a.c.rm << kRtRegBit;
@@ -387,8 +386,10 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
                     same &= (in >> r) & 1u ? in : ~in;
                     any |= (in >> r) & 1u;
                 }
-                if (any)
+                if (any) {
                     factor(same, 0, np, r);
+                    *slow += 8.0 * (double)np + 60.0;  // a pattern's test and addition; sine, cosine, decoding
+                }
                 todo &= ~same;
             }
             return;

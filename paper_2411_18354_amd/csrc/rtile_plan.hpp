@@ -137,12 +137,11 @@ RtGateInfo rt_gate_info(int kind, bool from_param, const double *mat, bool diag)
 // and 1 in registers and 2..5 on the lowest lane bits instead.
 // nb: register bits (rt_pass_nb, or rt_nb_of).  dual: the reverse sweep's passes.
 // fixed_mask: outer index bits every launched tile has with the required
-// values.  *slow: a complex64 block that sums its phases once for each set of
-// registers (LDS tiles take no longer: 60 phases under up to three controls,
-// n = 24: 611 against 731 us, 200 of them 1080 against 917, n = 12 72 against 49).
+// values.  *slow: instructions, roughly, of complex64 blocks that sum their
+// phases once for each set of registers.
 RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const TileGate *tiles, int count,
                      RtGateInfo *info, const std::vector<SweepPat> &pats, int nb, int coal, bool block, bool dual,
-                     RtProgram &prog, bool *slow);
+                     RtProgram &prog, double *slow);
 
 // One pass over a complex128 or complex64 state.
 int launch_rt_pass(int dtype, void *psi, const TileMap &tm, const RtPass &p, const RtDevice &d,
