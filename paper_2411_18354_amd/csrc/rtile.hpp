@@ -266,7 +266,13 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
             if ((base & om) != ov)
                 lanes = 0;
         }
-        RtPhases<NB> bl;  // complex64: the factors
+        // complex64: the factors (left unset on every path of its own, where
+        // that costs no moves)
+        RtPhases<NB> bl;
+        auto no_bits = [&]() __attribute__((always_inline)) {
+            if constexpr (sizeof(R) == 4)
+                SV_RT_FOR(NB, b) { rt_unset(bl.ur[b], bl.ui[b]); });
+        };
         if (kind == kRtDiag) {
             const uint64_t ob = (uint64_t)w[11] << 32 | w[10];
             const bool one = (tid & w[4]) != 0 || (base & ob) != 0 || (w[0] & 7u) != 0;
@@ -277,25 +283,33 @@ __device__ __forceinline__ void rt_run(RtRegs<R, NB> &v, unsigned char *lds, uin
                 fr = one ? m.dr : m.ar;
                 fi = one ? m.di : m.ai;
             }
-        } else if (!gate) {
-            if (kind == kRtFactor || (sizeof(R) == 4 && kind == kRtBlock)) {
+            no_bits();
+        } else if (gate) {
+            if constexpr (sizeof(R) == 4)
+                rt_unset(bl.gr, bl.gi);
+            no_bits();
+        } else if (sizeof(R) == 4 && kind == kRtBlock) {
+            if constexpr (sizeof(R) == 4) {
+                rt_phases<true>(ph, w[12], w[13], tid, &bl.gr, &bl.gi);
+                SV_RT_FOR(NB, b) { rt_phases<true>(ph, o.t[b], o.t[8 + b], tid, &bl.ur[b], &bl.ui[b]); });
+            }
+        } else {
+            if (kind == kRtFactor) {
                 if constexpr (sizeof(R) == 4)
                     rt_phases<true>(ph, w[12], w[13], tid | w[14] << kRtRegBit, &bl.gr, &bl.gi);
                 else
                     rt_phases<false>(ph, w[12], w[13], tid, &fr, &fi);
-            } else if (kind == kRtExch) {
-                next = rt_xor_terms(rt_fresh(tid), o.t);
-            } else if (kind == kRtPrep) {
-                rt_prep<R, NB>(lds, base, w, pats, mems);
-                lanes = 0;
-            }
-        }
-        if constexpr (sizeof(R) == 4) {
-            if (kind == kRtBlock) {
-                SV_RT_FOR(NB, b) { rt_phases<true>(ph, o.t[b], o.t[8 + b], tid, &bl.ur[b], &bl.ui[b]); });
             } else {
-                SV_RT_FOR(NB, b) { rt_unset(bl.ur[b], bl.ui[b]); });
+                if constexpr (sizeof(R) == 4)
+                    rt_unset(bl.gr, bl.gi);
+                if (kind == kRtExch) {
+                    next = rt_xor_terms(rt_fresh(tid), o.t);
+                } else if (kind == kRtPrep) {
+                    rt_prep<R, NB>(lds, base, w, pats, mems);
+                    lanes = 0;
+                }
             }
+            no_bits();
         }
         uint32_t sa = buf + slot, na = buf + next;
         if (PART && kind != kRtExch)
