@@ -108,33 +108,44 @@ __device__ __forceinline__ void rt_phase_factor(double th, double e, double *fr,
     *fr = q == 0 ? co : q == 1 ? -s : q == 2 ? -co : s;
 }
 
-// One phase pattern of the current tile, kept in LDS.
+// One phase pattern of the current tile, kept in LDS: where the index and the
+// low half of c are its high half, hi + lo is added.  hi is a multiple of
+// 2^-47, so sums of less than 64 are exact, and lo the rest of the phase.  (A
+// lane's phases reach the size of several turns: summed as they are, nine
+// qubits' round off 6e-16, more than three times what multiplying the nine
+// factors one by one does; this way 6e-17.)
 struct RtPhase {
-    uint32_t cm, cv;
-    double th;
+    uint32_t c;
+    float lo;
+    double hi;
 };
 
-// Sum of the phases of patterns [first, first + count) that index idx selects:
-// two sums, of half the patterns each, and *e what adding them rounds off.  (A
-// lane's phases reach the size of several turns; one sum left states of the
-// ansatz with 9% more error than two tables of six qubits did, n = 12.)
+__device__ __forceinline__ double rt_phase_hi(double th) { return (th + 48.0) - 48.0; }  // |th| <= pi
+
+// Sum of the phases of patterns [first, first + count) that index idx selects,
+// and *e its small part.
 __device__ __forceinline__ double rt_phase_sum(const RtPhase *ph, uint32_t first, uint32_t count, uint32_t idx,
                                                double *e) {
-    const uint32_t half = count >> 1;
     double t0 = 0.0, t1 = 0.0;
+    float l0 = 0.0f, l1 = 0.0f;
+    const uint32_t end = first + (count & ~1u);
 #pragma unroll 2
-    for (uint32_t p = first; p < first + half; ++p) {
-        const RtPhase q0 = ph[p], q1 = ph[p + half];
-        t0 += (idx & q0.cm) == q0.cv ? q0.th : 0.0;
-        t1 += (idx & q1.cm) == q1.cv ? q1.th : 0.0;
+    for (uint32_t p = first; p < end; p += 2) {
+        const RtPhase q0 = ph[p], q1 = ph[p + 1];
+        const bool on0 = (idx & q0.c) == q0.c >> 16, on1 = (idx & q1.c) == q1.c >> 16;  // (idx is below 2^16)
+        t0 += on0 ? q0.hi : 0.0;
+        t1 += on1 ? q1.hi : 0.0;
+        l0 += on0 ? q0.lo : 0.0f;
+        l1 += on1 ? q1.lo : 0.0f;
     }
     if (count & 1u) {  // uniform
-        const RtPhase q = ph[first + 2 * half];
-        t0 += (idx & q.cm) == q.cv ? q.th : 0.0;
+        const RtPhase q = ph[end];
+        const bool on = (idx & q.c) == q.c >> 16;
+        t0 += on ? q.hi : 0.0;
+        l0 += on ? q.lo : 0.0f;
     }
-    const double t = t0 + t1, b = t - t0;
-    *e = (t0 - (t - b)) + (t1 - b);
-    return t;
+    *e = (double)(l0 + l1);
+    return t0 + t1;
 }
 
 // The factor of those phases.
@@ -175,18 +186,20 @@ __device__ __forceinline__ void rt_prep(unsigned char *lds, uint64_t base, const
         // (a byte offset below 2^32 from a uniform base: no 64-bit lane address)
         const RtPat q = *reinterpret_cast<const RtPat *>(reinterpret_cast<const char *>(pats) +
                                                          (uint32_t)((w[2] + p) * sizeof(RtPat)));
-        double th = 0.0;
+        double hi = 0.0;
+        float lo = 0.0f;
 #pragma unroll 1
         for (uint32_t k = 0; k < (q.count & ~kRtPatNegative); ++k) {
             const SweepMember mm = mems[q.first + k];
-            th += (base & mm.om) == mm.ov ? mm.theta : 0.0;
+            const double th = (base & mm.om) == mm.ov ? mm.theta : 0.0, h = rt_phase_hi(th);
+            hi += h;
+            lo += (float)(th - h);
         }
-        if (q.count & kRtPatNegative)
-            th = -th;
+        const bool minus = (q.count & kRtPatNegative) != 0;
         RtPhase a;
-        a.cm = q.cm;
-        a.cv = q.cv;
-        a.th = th;
+        a.c = q.cm | q.cv << 16;
+        a.lo = minus ? -lo : lo;
+        a.hi = minus ? -hi : hi;
         ph[p] = a;
     }
     __syncthreads();

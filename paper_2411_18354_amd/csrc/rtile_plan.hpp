@@ -75,7 +75,7 @@ static_assert(sizeof(RtOp) == 128, "descriptor layout");
 // (twice that where kRtBlock lists a pattern once more with its sign changed,
 // which still fits the smallest exchange buffer of batches, 32 KiB).
 constexpr uint32_t kRtPatMembers = 4, kRtMaxPats = 1000, kRtPatNegative = 1u << 31;
-constexpr int kRtRegBit = 16;
+constexpr int kRtRegBit = kRtMaxThreadBits;
 struct RtPat {
     uint32_t cm, cv, first, count;  // count: | kRtPatNegative to subtract the phases
 };
