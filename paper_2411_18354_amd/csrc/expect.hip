@@ -278,9 +278,17 @@ __device__ __forceinline__ uint64_t deposit_bits(uint64_t v, uint64_t mask) {
 // conflicts whichever four bits of l number a lane's registers.
 __device__ __forceinline__ uint32_t tile_slot(uint32_t l) { return l ^ ((l >> 4) & 15u); }
 
+// s + x, with what that rounds off added to e.
+__device__ __forceinline__ void add_exact(double &s, double &e, double x) {
+    const double t = s + x, b = t - s;
+    e += (s - (t - b)) + (x - b);
+    s = t;
+}
+// s + e (infinite sums leave no e)
+__device__ __forceinline__ double with_rest(double s, double e) { return s + (e == e ? e : 0.0); }
+
 // The pass's terms.  Lane j holds term j's masks; acck of lane i is the sum
-// of term 16 k + (i & 15) over its row of lanes and the wavefront's tiles, in
-// tile order.
+// of term 16 k + (i & 15) over its row of lanes in this tile.
 struct TileTerms {
     uint32_t txl, tzl;
     int tny, tend;          // tend: the pass's ends
@@ -397,7 +405,11 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_expect_tile(const A amps, c
     T.minus = 0;
     T.tend = lane < 37 ? P.end[lane] : 0;
     T.v0 = T.v1 = T.v2 = T.v3 = 0.0;
-    T.acc0 = T.acc1 = T.acc2 = T.acc3 = 0.0;
+    // the same over the wavefront's tiles, and what adding them rounded off: a
+    // term's rows may all have one sign in every tile and cancel between rows
+    // (neighbours among qubits 4 to 7 had ten times the error of one sum per
+    // wavefront and tile)
+    double sum0 = 0.0, sum1 = 0.0, sum2 = 0.0, sum3 = 0.0, rest0 = 0.0, rest1 = 0.0, rest2 = 0.0, rest3 = 0.0;
     if ((int)lane < nt) {
         T.txl = P.t[lane].xl;
         T.tzl = P.t[lane].zl;
@@ -431,6 +443,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_expect_tile(const A amps, c
         if (tl + gridDim.x < ntiles)
             load(tl + gridDim.x);
         T.minus = __ballot(odd_parity(T.tzh & base));
+        T.acc0 = T.acc1 = T.acc2 = T.acc3 = 0.0;
         int j = 0;
         if (__builtin_amdgcn_readlane(T.tend, 15)) {
             walsh16(wc);
@@ -498,28 +511,32 @@ __global__ __launch_bounds__(kTileThreads, 2) void k_expect_tile(const A amps, c
         }
         for (; j & 3; ++j)
             tile_push(T, j, 0.0, lane);
+        add_exact(sum0, rest0, T.acc0);
+        add_exact(sum1, rest1, T.acc1);
+        add_exact(sum2, rest2, T.acc2);
+        add_exact(sum3, rest3, T.acc3);
     }
     __syncthreads();  // the tile's LDS now holds the rows' sums
-    double *wsum = reinterpret_cast<double *>(tile);
-    double *row = wsum + (tid >> 4) * kTileTerms + (tid & 15u);
-    row[0] = T.acc0;
-    row[16] = T.acc1;
-    row[32] = T.acc2;
-    row[48] = T.acc3;
+    double2 *wsum = reinterpret_cast<double2 *>(tile);
+    double2 *row = wsum + (tid >> 4) * kTileTerms + (tid & 15u);
+    row[0] = make_double2(sum0, rest0);
+    row[16] = make_double2(sum1, rest1);
+    row[32] = make_double2(sum2, rest2);
+    row[48] = make_double2(sum3, rest3);
     __syncthreads();
     if ((int)tid < nt) {
-        // (by pairs: added one after another, terms of one sign in the whole
-        // tile lost twice as much to rounding)
-        double s[kTileThreads / 16];
+        double2 w[kTileThreads / 16];
 #pragma unroll
         for (int q = 0; q < kTileThreads / 16; ++q)
-            s[q] = wsum[q * kTileTerms + tid];
+            w[q] = wsum[q * kTileTerms + tid];
 #pragma unroll
         for (int h = 1; h < kTileThreads / 16; h <<= 1)
 #pragma unroll
-            for (int q = 0; q < kTileThreads / 16; q += 2 * h)
-                s[q] += s[q + h];
-        partials[(size_t)P.t[tid].slot * kMaxPartials + blockIdx.x] = s[0];
+            for (int q = 0; q < kTileThreads / 16; q += 2 * h) {
+                w[q].y += w[q + h].y;
+                add_exact(w[q].x, w[q].y, w[q + h].x);
+            }
+        partials[(size_t)P.t[tid].slot * kMaxPartials + blockIdx.x] = with_rest(w[0].x, w[0].y);
     }
 }
 
@@ -571,18 +588,15 @@ __global__ __launch_bounds__(kFewThreads) void k_expect_few(const FewTerms t, co
         // a term may be all of one sign in a lane and cancel between lanes: plain
         // sums left up to twice the error of the partials themselves.)
         double v = 0.0, e = 0.0;
-        auto add = [&](double p, double pe) {
-            const double s = v + p, b = s - v;
-            e += pe + ((v - (s - b)) + (p - b));
-            v = s;
-        };
 #pragma unroll 8
         for (int i = lane; i < t.nblk[j]; i += 64)
-            add(partials[(size_t)j * kMaxPartials + i], 0.0);
+            add_exact(v, e, partials[(size_t)j * kMaxPartials + i]);
 #pragma unroll
-        for (int h = 1; h < 64; h <<= 1)
-            add(__shfl_xor(v, h), __shfl_xor(e, h));
-        v += e == e ? e : 0.0;  // (infinite sums leave none)
+        for (int h = 1; h < 64; h <<= 1) {
+            e += __shfl_xor(e, h);
+            add_exact(v, e, __shfl_xor(v, h));
+        }
+        v = with_rest(v, e);
         if (lane == 0) {
             sums[j] = v;
             if (out_terms)
