@@ -63,6 +63,30 @@ def test_complex64_phase_block_rounds_once(gpu, m, extra, controls):
     assert (err <= 2.75 * 2.0 ** -24 * np.abs(a)).all(), (err / np.abs(a)).max() * 2.0 ** 24
 
 
+@pytest.mark.parametrize("m", [10, 12])
+@pytest.mark.parametrize("extra", [0, 9])
+def test_complex128_phase_sums(gpu, m, extra):
+    """RZ on every qubit, u = 2^-53: each gate's phase is off by the rounding of
+    its entries and of their angle, at most u / 2 rms together; the block's sums
+    add nothing, and its two factors per amplitude (of the lane and of the
+    register) and their products round 0.65 u rms each.  (A sum in double of
+    nine phases of several radians would add 5 u.)"""
+    n = m + extra
+    gpu.sv_tune_set("tile_log2_c128", m)
+    worst = 0.0
+    for seed in range(6):
+        rng = np.random.default_rng(100 * m + seed)
+        theta = rng.uniform(np.pi / 2, 2 * np.pi, n)  # long sums
+        k = np.arange(1 << n)
+        phase = sum(np.longdouble(t) * (((k >> q) & 1) - np.longdouble(0.5)) for q, t in enumerate(theta))
+        exact = np.cos(phase) + 1j * np.sin(phase)
+        psi = torch.ones(1 << n, dtype=torch.complex128, device="cuda")
+        gpu.Circuit(n, W.Circuit(n, [W.Gate("RZ", q, theta=float(t)) for q, t in enumerate(theta)])).run(psi)
+        err = (psi.cpu().numpy() - exact).astype(np.complex128)
+        worst = max(worst, float(np.sqrt((np.abs(err) ** 2).mean())))
+    assert worst <= np.sqrt(n * 0.25 + 2 * 0.65 ** 2) * 2.0 ** -53, worst * 2.0 ** 53
+
+
 @pytest.mark.parametrize("controls", [0, 1, 3])
 def test_complex64_phase_block_rounds_once_in_batches(gpu, controls):
     """The same bound for planned batches, whose tiles are loaded by workgroups
