@@ -671,8 +671,8 @@ RtPass build_rt_pass(const TileMap &tm, uint64_t fixed_mask, int tile_dt, const 
 // Measured against the LDS tiles of k_tile on one MI355X (complex128 unless
 // noted): 28-qubit layered circuit of 315 gates 40.1 -> 27.8 ms (16 passes of
 // 1.64 ms; a read and write of the 4 GiB state takes 1.28 ms), 24-qubit
-// ansatz forward 8.2 -> 3.7 ms, 29-qubit QFT in complex64 25.8 -> 9.0 ms, 200
-// gates on one 12-qubit tile 194 -> 118 us.  A real gate on a resident tile
+// ansatz forward 8.2 -> 3.7 ms, 29-qubit QFT in complex64 25.8 -> 9.3 ms, 200
+// gates on one 12-qubit tile 194 -> 120 us.  A real gate on a resident tile
 // costs about 375 cycles per tile and CU (256 of them FP64 instructions), a
 // general one 630 (512), X 296; complex64 tiles 615, 1140 and 370 for twice
 // the amplitudes.  Tiles of 2^13 complex128 amplitudes (512 lanes) save one
